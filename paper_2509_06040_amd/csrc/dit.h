@@ -84,6 +84,10 @@ br_status launch_attention(int dtype, const void* qkv, void* out, int B, int L, 
                            hipStream_t st);
 br_status launch_gemm_bf16(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
                            const EpiArgs& ea, int variant, hipStream_t st);
+br_status launch_gemm_ksplit(int dtype, int mode, const void* A, int lda, const void* W, int ldw, int M, int N, int K,
+                             const EpiArgs& ea, int tile, hipStream_t st);
+br_status launch_gemm_f32(int mode, const float* A, int lda, const float* W, int ldw, int M, int N, int K,
+                          const EpiArgs& ea, int variant, hipStream_t st);
 bool gemm_stream_supported(int M, int N, int K, size_t bytes_a, size_t bytes_w);
 br_status launch_gemm_bf16_stream(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
                                   const EpiArgs& ea, int group_n, int row_block, int stagger_slack, int stagger_crit,
@@ -205,19 +209,27 @@ struct Epilogue {
       scatter_unpatch(r, n, v0, v1, v2, v3);
     }
   }
-  // EPI_UNPATCH: token (tt, th, tw) raster, element (c, dt, dh, dw)
+  // EPI_UNPATCH: token (tt, th, tw) raster, element (c, dt, dh, dw).  The place in the latent is a sum of
+  // a part of the column and a part of the token, so a caller that walks rows at fixed columns keeps
+  // the former.  Elements of one patch row are neighbours: with an even patch width they leave in pairs.
   __device__ inline void scatter_unpatch(const Row& r, int n, float v0, float v1, float v2, float v3) const {
-    float* v = reinterpret_cast<float*>(a.out) + r.o;
     const int tw = r.tok % a.gw, th = (r.tok / a.gw) % a.gh, tt = r.tok / (a.gw * a.gh);
+    float* v = reinterpret_cast<float*>(a.out) + r.o + ((long long)tt * a.pt * a.lh + th * a.ph) * a.lw + tw * a.pw;
     const float vals[4] = {v0, v1, v2, v3};
+    long long at[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int el = n + e;
       const int dw = el % a.pw, dh = (el / a.pw) % a.ph, dt = (el / (a.pw * a.ph)) % a.pt,
                 c = el / (a.pw * a.ph * a.pt);
-      const long long idx =
-          (((long long)c * a.lt + tt * a.pt + dt) * a.lh + th * a.ph + dh) * a.lw + tw * a.pw + dw;
-      v[idx] = vals[e];
+      at[e] = (((long long)c * a.lt + dt) * a.lh + dh) * a.lw + dw;
+    }
+    if (a.pw % 2 == 0 && (reinterpret_cast<uintptr_t>(a.out) & 7) == 0) {
+      *reinterpret_cast<float2*>(v + at[0]) = make_float2(vals[0], vals[1]);
+      *reinterpret_cast<float2*>(v + at[2]) = make_float2(vals[2], vals[3]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[at[e]] = vals[e];
     }
   }
   // four consecutive output columns n..n+3 (n % 4 == 0)

@@ -342,78 +342,13 @@ br_status launch_ln_modulate(int dtype, const float* x, void* out, int n_rows, i
   return BR_OK;
 }
 
-// --------------------------------------------------------------- fp32 GEMM
-// C[m, n] = sum_k A[m, k] W[n, k]; 64x64 tile, 16-deep, 4x4 outputs per thread.
-template <int MODE>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W,
-                                                       int ldw, int M, int N, int K, Epilogue<MODE, float> epi) {
-  __shared__ float sA[16][64 + 4], sW[16][64 + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + i * 256, row = e >> 4, kk = e & 15;
-      const int gm = m0 + row, gn = n0 + row, gk = k0 + kk;
-      sA[kk][row] = (gm < M && gk < K) ? A[(size_t)gm * lda + gk] : 0.f;
-      sW[kk][row] = (gn < N && gk < K) ? W[(size_t)gn * ldw + gk] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], w[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = sA[kk][ty * 4 + i];
-        w[i] = sW[kk][tx * 4 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  const int n = n0 + tx * 4;
-  if (n >= N) return;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m < M) {
-      const auto r = epi.row(m);
-      epi.store(r, n, acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-    }
-  }
-}
-
-template <int MODE>
-static br_status gemm_f32_mode(const float* A, int lda, const float* W, int ldw, int M, int N, int K, const EpiArgs& ea,
-                               hipStream_t st) {
-  Epilogue<MODE, float> epi{ea};
-  hipLaunchKernelGGL((gemm_f32_kernel<MODE>), dim3(cdiv(N, 64), cdiv(M, 64)), dim3(256), 0, st, A, lda, W, ldw, M, N, K,
-                     epi);
-  BR_LAUNCH_CHECK();
-  return BR_OK;
-}
-
 br_status launch_gemm(int dtype, int mode, const void* A, int lda, const void* W, int ldw, int M, int N, int K,
                       const EpiArgs& ea, hipStream_t st) {
   if (M == 0) return BR_OK;
   BR_REQUIRE(N % 4 == 0, BR_ESHAPE, "gemm: N must be a multiple of 4");
   if (dtype == BR_BF16)
     return launch_gemm_bf16(mode, (const bf16*)A, lda, (const bf16*)W, ldw, M, N, K, ea, -1, st);
-  const float* a = (const float*)A;
-  const float* w = (const float*)W;
-  switch (mode) {
-    case EPI_BIAS: return gemm_f32_mode<EPI_BIAS>(a, lda, w, ldw, M, N, K, ea, st);
-    case EPI_BIAS_GELU: return gemm_f32_mode<EPI_BIAS_GELU>(a, lda, w, ldw, M, N, K, ea, st);
-    case EPI_BIAS_GATE_RES: return gemm_f32_mode<EPI_BIAS_GATE_RES>(a, lda, w, ldw, M, N, K, ea, st);
-    case EPI_PATCH_EMBED: return gemm_f32_mode<EPI_PATCH_EMBED>(a, lda, w, ldw, M, N, K, ea, st);
-    case EPI_BIAS_F32: return gemm_f32_mode<EPI_BIAS_F32>(a, lda, w, ldw, M, N, K, ea, st);
-    case EPI_UNPATCH: return gemm_f32_mode<EPI_UNPATCH>(a, lda, w, ldw, M, N, K, ea, st);
-  }
-  return fail(BR_EINVAL, "gemm: unknown epilogue");
+  return launch_gemm_f32(mode, (const float*)A, lda, (const float*)W, ldw, M, N, K, ea, -1, st);
 }
 
 // ---------------------------------------------------------- fp32 attention

@@ -31,7 +31,7 @@ extern "C" br_status br_op_gemm(int32_t dtype, int32_t epilogue, const void* A, 
   if (dtype == BR_BF16)
     return launch_gemm_bf16(epilogue, (const bf16*)A, lda, (const bf16*)W, ldw, M, N, K, ea, variant,
                             (hipStream_t)stream);
-  return launch_gemm(dtype, epilogue, A, lda, W, ldw, M, N, K, ea, (hipStream_t)stream);
+  return launch_gemm_f32(epilogue, (const float*)A, lda, (const float*)W, ldw, M, N, K, ea, variant, (hipStream_t)stream);
 }
 
 extern "C" br_status br_op_attention(int32_t dtype, const void* qkv, void* out, int32_t B, int32_t L, int32_t NH,

@@ -263,3 +263,46 @@ def test_velocity_chunked_batches_agree(lib):
     with pytest.raises(br.BranchRolloutError) as e:
         br.velocity(model, dev(z), 0.5, cond_dev(cfg, cond), cidx, v2, bytes_buffer(256))
     assert e.value.code == -4
+
+
+# every form of the fp32 GEMM (128x128 and 64x128 tiles, 32x32 tiles with the waves splitting K) at tile
+# edges, with K of less than one stage, whole stages and a stage that ends inside a 16-byte chunk pair
+@pytest.mark.parametrize("variant", [-1, 4, 5, 8])
+@pytest.mark.parametrize("M,N,K", [(1, 4, 4), (31, 36, 12), (33, 132, 16), (64, 128, 20), (65, 124, 32), (129, 260, 144),
+                                   (257, 128, 1040), (1000, 516, 96)])
+def test_gemm_fp32_every_form(lib, variant, M, N, K):
+    rng = np.random.default_rng(M * 7 + K)
+    A, W, b = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (N, K), (N,)))
+    ref = A.astype(np.float64) @ W.astype(np.float64).T + b
+    out = torch.full((M + 1, N), -9.0, device=DEV)
+    br.op_gemm(br.F32, 0, dev(A), dev(W), dev(b), out[:M], variant=variant)
+    # fp32 sums of K products: rounding errors of 2^-24 each add up to about sqrt(K) 2^-24 < 2e-6 of the norm
+    assert rel_l2(host(out)[:M], ref) < 2e-6
+    assert (host(out)[M] == -9.0).all()
+    L = 1 if M % 5 else 5
+    x0, mods = rng.standard_normal((M, N)).astype(np.float32), rng.standard_normal((3, N)).astype(np.float32)
+    cond = (np.arange(M // L) % 3).astype(np.int32)
+    x = dev(x0.copy())
+    br.op_gemm(br.F32, 2, dev(A), dev(W), dev(b), x, mods=dev(mods), gate_off=0, cond=dev(cond), L=L, variant=variant)
+    assert rel_l2(host(x), x0 + np.repeat(mods[cond], L, axis=0) * ref) < 2e-6
+
+
+@pytest.mark.parametrize("off,K", [(1, 64), (0, 30), (2, 33)])
+def test_gemm_fp32_operands_that_are_not_16_byte_aligned(lib, off, K):
+    rng = np.random.default_rng(K)
+    M, N = 70, 72
+    A, W, b = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (N, K), (N,)))
+    buf = torch.zeros(M * K + off, device=DEV)
+    buf[off:] = dev(A).reshape(-1)
+    out = torch.empty((M, N), device=DEV)
+    br.op_gemm(br.F32, 0, buf[off:].view(M, K), dev(W), dev(b), out)
+    assert rel_l2(host(out), A.astype(np.float64) @ W.astype(np.float64).T + b) < 1e-6
+
+
+@pytest.mark.parametrize("patch,latent", [((1, 1, 1), (4, 1, 5, 7)), ((1, 3, 3), (4, 2, 6, 9)), ((2, 1, 4), (2, 4, 3, 8))])
+def test_velocity_fp32_patch_widths(lib, patch, latent):
+    """Odd and even patch widths: the unpatchify epilogue stores single elements or pairs."""
+    cfg = synth.model_cfg(1, 32, 2, latent, patch, 3, synth.F32)
+    got, ref, _ = _velocity_case(cfg, 2, 2, 0.4, 5, 0.1)
+    for b in range(2):
+        assert_velocity(cfg, got[b], ref[b], 1e-4, "patch %s b=%d" % (patch, b))
