@@ -93,6 +93,7 @@ br_status launch_gemm_bf16_stream(int mode, const bf16* A, int lda, const bf16* 
                                   const EpiArgs& ea, int group_n, int row_block, int stagger_slack, int stagger_crit,
                                   hipStream_t st);
 br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH, int DH, int q_prescaled, hipStream_t st);
+br_status launch_attention_f32(const float* qkv, float* out, int B, int L, int NH, int DH, hipStream_t st);
 br_status launch_ln_modulate(int dtype, const float* x, void* out, int n_rows, int rows_per_sample, int L_in, int H,
                              const float* mods, int A, int shift_off, int scale_off, const int* condmap,
                              hipStream_t st);

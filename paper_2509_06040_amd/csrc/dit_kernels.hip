@@ -351,62 +351,12 @@ br_status launch_gemm(int dtype, int mode, const void* A, int lda, const void* W
   return launch_gemm_f32(mode, (const float*)A, lda, (const float*)W, ldw, M, N, K, ea, -1, st);
 }
 
-// ---------------------------------------------------------- fp32 attention
-// One thread per query, streaming over all keys with an online softmax.
-template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ qkv, float* __restrict__ out, int L,
-                                                      int H, float scale) {
-  const int b = blockIdx.z, h = blockIdx.y, qi = blockIdx.x * 64 + threadIdx.x;
-  const float* base = qkv + (size_t)b * L * 3 * H + h * DH;
-  const bool live = qi < L;
-  float q[DH], o[DH];
-#pragma unroll
-  for (int d = 0; d < DH; ++d) {
-    q[d] = live ? base[(size_t)qi * 3 * H + d] * scale : 0.f;
-    o[d] = 0.f;
-  }
-  float mx = -INFINITY, den = 0.f;
-  for (int j = 0; j < L; ++j) {
-    const float* kr = base + (size_t)j * 3 * H + H;
-    const float* vr = kr + H;
-    float s = 0.f;
-#pragma unroll
-    for (int d = 0; d < DH; ++d) s = fmaf(q[d], kr[d], s);
-    const float mn = fmaxf(mx, s);
-    const float alpha = __expf(mx - mn), p = __expf(s - mn);
-    den = den * alpha + p;
-#pragma unroll
-    for (int d = 0; d < DH; ++d) o[d] = fmaf(p, vr[d], o[d] * alpha);
-    mx = mn;
-  }
-  if (live) {
-    float* orow = out + ((size_t)b * L + qi) * H + h * DH;
-    const float inv = 1.f / den;
-#pragma unroll
-    for (int d = 0; d < DH; ++d) orow[d] = o[d] * inv;
-  }
-}
-
 br_status launch_attention(int dtype, const void* qkv, void* out, int B, int L, int NH, int DH, int q_prescaled,
                            hipStream_t st) {
   if (B == 0) return BR_OK;
   if (dtype == BR_BF16) return launch_attention_bf16((const bf16*)qkv, (bf16*)out, B, L, NH, DH, q_prescaled, st);
   BR_REQUIRE(!q_prescaled, BR_EINVAL, "attention: prescaled queries are a bf16 layout");
-  BR_REQUIRE(NH <= 65535 && B <= 65535, BR_ESHAPE, "attention: too many heads or samples for one launch");
-  dim3 g(cdiv(L, 64), NH, B), blk(64);
-  const float scale = 1.0f / sqrtf((float)DH);
-  const int H = NH * DH;
-#define BR_AT(D_) hipLaunchKernelGGL((attn_f32_kernel<D_>), g, blk, 0, st, (const float*)qkv, (float*)out, L, H, scale)
-  switch (DH) {
-    case 16: BR_AT(16); break;
-    case 32: BR_AT(32); break;
-    case 64: BR_AT(64); break;
-    case 128: BR_AT(128); break;
-    default: return fail(BR_ESHAPE, "attention: head dim must be 16, 32, 64 or 128");
-  }
-#undef BR_AT
-  BR_LAUNCH_CHECK();
-  return BR_OK;
+  return launch_attention_f32((const float*)qkv, (float*)out, B, L, NH, DH, st);
 }
 
 // -------------------------------------------------------------- launchers

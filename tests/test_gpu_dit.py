@@ -306,3 +306,36 @@ def test_velocity_fp32_patch_widths(lib, patch, latent):
     got, ref, _ = _velocity_case(cfg, 2, 2, 0.4, 5, 0.1)
     for b in range(2):
         assert_velocity(cfg, got[b], ref[b], 1e-4, "patch %s b=%d" % (patch, b))
+
+
+# one key, one tile of 32 keys and its neighbours, fewer tiles than waves, every wave with a different
+# number of tiles; the last two have enough (sample, head) pairs for the grouped order
+@pytest.mark.parametrize("dh,nh,L,B", [(16, 1, 1, 1), (32, 2, 31, 1), (64, 1, 32, 2), (128, 2, 33, 1), (16, 3, 97, 2),
+                                       (64, 2, 161, 1), (128, 1, 290, 1), (32, 8, 70, 4), (16, 11, 40, 3)])
+def test_attention_fp32_tile_edges(lib, dh, nh, L, B):
+    rng = np.random.default_rng(dh + L)
+    qkv = (rng.standard_normal((B, L, 3 * nh * dh)) * 1.5).astype(np.float32)
+    out = torch.full((B, L, nh * dh), 3.0, device=DEV)
+    br.op_attention(br.F32, dev(qkv), out, nh)
+    assert rel_l2(host(out), _attention_ref(qkv.astype(np.float64), nh)) < 2e-6
+
+
+def test_attention_fp32_reference_moves_and_unaligned_buffers(lib):
+    """Scores that jump by hundreds between key tiles, in either direction; and the same call on buffers
+    that are only 4-byte aligned."""
+    rng = np.random.default_rng(2)
+    nh, dh, L = 2, 32, 200
+    qkv = rng.standard_normal((1, L, 3 * nh * dh)).astype(np.float32)
+    H = nh * dh
+    qkv[0, :, :H] += 3.0
+    qkv[0, 64:96, H:2 * H] += 20.0
+    qkv[0, 96:128, H:2 * H] -= 20.0
+    ref = _attention_ref(qkv.astype(np.float64), nh)
+    out = torch.empty((1, L, H), device=DEV)
+    br.op_attention(br.F32, dev(qkv), out, nh)
+    # exponents reach 340: a relative rounding of 2^-24 of the score is 4e-5 of the probability
+    assert rel_l2(host(out), ref) < 1e-4
+    buf, obuf = torch.zeros(qkv.size + 1, device=DEV), torch.zeros(L * H + 1, device=DEV)
+    buf[1:] = dev(qkv).reshape(-1)
+    br.op_attention(br.F32, buf[1:].view(1, L, 3 * H), obuf[1:].view(1, L, H), nh)
+    assert rel_l2(host(obuf)[1:].reshape(1, L, H), ref) < 1e-4
