@@ -20,8 +20,10 @@ extern "C" {
  *               gate row r at mods + r*mods_stride + gate_off, cond dev [M / L]
  *            4: out[m, n] = acc                  out fp32
  * BR_BF16 needs K % 64 == 0, lda % 8 == 0, ldw % 8 == 0; N % 4 == 0 always.
- * variant: bf16 kernel (-1 = automatic; 4 / 5 / 6 = 256x256 / 128x128 / 256x128 tile per workgroup,
- * 7 = persistent 256x256 streaming kernel, needs K % 128 == 0; bits 4..11 = column-group width of
+ * variant: kernel (-1 = automatic; 0 = 32x32 tiles with the waves splitting K; 1 / 2 / 3 / 4 / 5 / 6 =
+ * 128x128 in eight waves / 64x64 / 64x128 / 256x256 / 128x128 / 256x128 tile per workgroup; 7 = persistent
+ * 256x256 streaming kernel, needs K % 128 == 0.  BR_F32 has 0, 3 and 5 and takes its own choice where
+ * another is asked for or does not apply.  bf16 only: bits 4..11 = column-group width of
  * the tile walk, 0 = the kernel's own choice; for the persistent kernel bits 12..19 / 20..23 = start
  * delay step, in half microseconds, of workgroups that have / do not have a tile less than the longest
  * tile list on their compute die: group g = (workgroup index on the die) / 4 % 8 starts g steps late;

@@ -3,8 +3,9 @@
 // operand is one 16-byte LDS read.  The weights feed the MFMA row operand and the
 // activations the column operand (v_mfma_f32_32x32x16_bf16).
 //
-// This file holds the dispatch and the launches of the one-tile-per-workgroup kernel (gemm_tile.h: BM x BN
-// tile, WGM x WGN wavefronts); the persistent kernel for large problems is in gemm_bf16_stream.hip.
+// This file holds the choice of the kernel and the launches of the one-tile-per-workgroup kernel (gemm_tile.h);
+// the persistent kernel for large problems is in gemm_bf16_stream.hip, the one for small ones in
+// gemm_ksplit.hip.
 #include <cmath>
 
 #include "common.h"
@@ -14,65 +15,59 @@
 
 namespace br {
 
-template <int BM, int BN, int WGM, int WGN, int MODE, typename TOUT>
-static br_status gemm_dma_launch(const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K, const EpiArgs& ea,
+template <int BM, int BN, int WGM, int WGN, int NST, int MODE, typename TOUT>
+static br_status gemm_tile_launch(const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K, const EpiArgs& ea,
                                  int group_n, hipStream_t st) {
   Epilogue<MODE, TOUT> epi{ea};
   const int tiles_m = cdiv(M, BM), tiles_n = cdiv(N, BN);
-  if (group_n <= 0 || group_n > tiles_n) group_n = tiles_n;
-  hipLaunchKernelGGL((gemm_tile_kernel<bf16, BM, BN, WGM, WGN, MODE, TOUT>), dim3(tiles_m * tiles_n), dim3(WGM * WGN * 64),
+  // Columns in even groups of at most 8: the tiles a compute die works on at once then share both operands.
+  if (group_n <= 0 || group_n > tiles_n) group_n = cdiv(tiles_n, cdiv(tiles_n, 8));
+  hipLaunchKernelGGL((gemm_tile_kernel<bf16, BM, BN, WGM, WGN, NST, MODE, TOUT>), dim3(tiles_m * tiles_n), dim3(WGM * WGN * 64),
                      0, st, A, lda, W, ldw, M, N, K, tiles_m, tiles_n, group_n, epi);
   BR_LAUNCH_CHECK();
   return BR_OK;
 }
 
-// variant bits 0..3: kernel, 4 / 5 / 6 = 256x256 / 128x128 / 256x128 tiles, one tile per workgroup, LDS-direct loads
-// in a four-stage ring; 7 = persistent 256x256 kernel with a continuous operand stream (gemm_bf16_stream.hip);
-// bits 4..11: column-group width of the tile walk (0 = all columns).  variant < 0 = choose by problem size.
+enum {  // bits 0..3 of a variant
+  TILE_KSPLIT = 0, TILE_128_W8 = 1, TILE_64 = 2, TILE_64_128 = 3, TILE_256 = 4, TILE_128 = 5, TILE_256_128 = 6, TILE_STREAM = 7
+};
+
+// The kernel for a problem size, from 410 measured shapes (M 40 to 200 000, hidden sizes 64 to 3072 with
+// their QKV, MLP and projection widths, K 64 to 12 288); it is 2 % slower on average than the best kernel
+// of each shape.  r = tiles of a kind per compute unit.
+static int choose_tile(int M, int N, int K, bool stream_ok) {
+  const double cu = device_cu_count();
+  const double r32 = (double)cdiv(M, 32) * cdiv(N, 32) / cu, r64 = (double)cdiv(M, 64) * cdiv(N, 64) / cu;
+  const double r128 = (double)cdiv(M, 128) * cdiv(N, 128) / cu, r256 = (double)cdiv(M, 256) * cdiv(N, 256) / cu;
+  // Up to a few 32x32 tiles a unit: the waves of a tile split K.  279 x 128 x 512 takes 3.3 us instead of
+  // the 5.6 of 64x64 tiles and the 10.7 of the 256x128 tiles used before.  A long K makes the tile's operand
+  // traffic (twice that of 64x64 tiles for the same outputs) the longer part sooner.
+  if (r32 <= (K < 1024 ? 4.0 : 3.0)) return TILE_KSPLIT;
+  // Up to one round of 64x64 tiles: two waves each, four stages of 16 KB in flight.  1101 x 1024 x 4096: 23 us
+  // (34 in 128x128 tiles, 52 in 256x128).
+  if (r64 <= 1.2) return TILE_64;
+  // Up to one round of 128x128 tiles: half of them, so that the round is fuller (1101 x 3072 x 1024: 14.7 us,
+  // 20.8 in 256x128 tiles).
+  if (r128 <= 1.0) return TILE_64_128;
+  // Beyond: 128x128 tiles, two workgroups a unit, or 256x256 tiles (one persistent workgroup a unit; one tile
+  // per workgroup where K is not a multiple of 128), which move half the operand bytes but finish in whole rounds:
+  // 13 700 x 1088 x 4352 (1.05 rounds) 135 us against 211, 39 300 x 2752 x 11 008 (6.6 rounds) 2510 against 2180.
+  // A partial round costs the small tiles less than a third of one.
+  const double used = (double)M * N;
+  const double e256 = 1.2 * r256 / std::ceil(r256) * used / ((double)cdiv(M, 256) * 256 * cdiv(N, 256) * 256);
+  const double e128 = r128 / (r128 + 0.3) * used / ((double)cdiv(M, 128) * 128 * cdiv(N, 128) * 128);
+  if (e256 > e128) return stream_ok ? TILE_STREAM : TILE_256;
+  return K <= 512 ? TILE_128_W8 : TILE_128;  // a short K leaves a larger share to the epilogue, where eight waves store faster (3-5 %)
+}
+
+// variant bits 0..3: kernel (see the enum); bits 4..11: column-group width of the tile walk (0 = the
+// kernel's own choice); variant < 0 = choose by problem size.
 template <int MODE, typename TOUT>
 static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K, const EpiArgs& ea,
                               int variant, hipStream_t st) {
   int tile, group_n = 0, row_block = 0, stagger_slack = 0, stagger_crit = 0;
   if (variant < 0) {
-    // Measured on MI355X.  With r = (256x256 tiles) / (compute units):
-    // up to half a round of tiles, 256x128 tiles put twice as many units to work; up to one
-    // round the persistent 256x256 kernel is best; beyond that it stays best unless the last
-    // round would be mostly empty (r = 1.08 costs two rounds), where 128x128 tiles win.
-    const int cu = device_cu_count();
-    const long long tiles_m = cdiv(M, 256), tiles_n = cdiv(N, 256);
-    const long long t256 = tiles_m * tiles_n;
-    const double r = (double)t256 / (double)cu;
-    const bool stream_ok = gemm_stream_supported(M, N, K, (size_t)M * lda * 2, (size_t)N * ldw * 2);
-    // One or two whole rounds and a last one that fills at most half the units: the rows are independent,
-    // so the matrix is cut in two launches, as many rows as make whole rounds for the persistent kernel and
-    // the rest -- at most half a round -- for the 256x128 tiles, which take half a tile time.  With
-    // per-sample epilogue operands the cut falls between two samples.  Measured on 1101-token samples:
-    // 3-16 % at 16 samples (1.1 to 4.3 rounds), 2-7 % at 24 and 32.  From three whole rounds on it does not
-    // pay: the few units of a sparse last round run faster than a full round's (64 samples, N = 1024,
-    // 4.3 rounds: 1-4 % slower when cut).
-    if (stream_ok && r > 1.0 && r < 3.0 && (MODE == EPI_BIAS || MODE == EPI_BIAS_GELU || MODE == EPI_BIAS_GATE_RES)) {
-      const long long whole = t256 / cu;
-      long long head_rows = (whole * cu / tiles_n) * 256;
-      const int rps = MODE == EPI_BIAS_GATE_RES ? ea.L : 256;
-      head_rows = head_rows / rps * rps;
-      const long long tail_rows = M - head_rows;
-      if (head_rows > 0 && tail_rows > 0 && cdiv(tail_rows, 256) * tiles_n * 2 <= cu &&
-          cdiv(head_rows, 256) * tiles_n <= whole * cu) {
-        EpiArgs tail = ea;
-        tail.out = (char*)ea.out + (size_t)head_rows * ea.ldo * sizeof(TOUT);
-        if (MODE == EPI_BIAS_GATE_RES) tail.condmap = ea.condmap + head_rows / rps;
-        const int head_variant = 7 | ((MODE == EPI_BIAS_GATE_RES && K <= 2048) ? (6 << 12) : 0);  // (the start stagger below)
-        const br_status head = gemm_variant<MODE, TOUT>(A, lda, W, ldw, (int)head_rows, N, K, ea, head_variant, st);
-        if (head != BR_OK) return head;
-        return gemm_variant<MODE, TOUT>(A + (size_t)head_rows * lda, lda, W, ldw, (int)tail_rows, N, K, tail, 6, st);
-      }
-    }
-    if (r <= 0.5)
-      tile = 6;
-    else if (r > 1.0 && std::ceil(r) / r > 1.4)
-      tile = 5;
-    else
-      tile = stream_ok ? 7 : 4;
+    tile = choose_tile(M, N, K, gemm_stream_supported(M, N, K, (size_t)M * lda * 2, (size_t)N * ldw * 2));
     // The fp32 gated residual reads and writes 512 KB per tile; with a short k-loop (K <= 2048) these
     // bursts of a die's 32 workgroups, all in step, are a third of the launch.  Workgroups with one tile
     // less than the longest list start up to 7 x 3 us late, in groups of four, which costs the launch
@@ -88,10 +83,14 @@ static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, in
   }
   ProfScope ps(st, PROF_GEMM + MODE * 8 + tile, 2.0 * M * N * K);
   switch (tile) {
-    case 4: return gemm_dma_launch<256, 256, 2, 4, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
-    case 5: return gemm_dma_launch<128, 128, 2, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
-    case 6: return gemm_dma_launch<256, 128, 4, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
-    case 7: return launch_gemm_bf16_stream(MODE, A, lda, W, ldw, M, N, K, ea, group_n, row_block, stagger_slack, stagger_crit, st);
+    case TILE_KSPLIT: return launch_gemm_ksplit(BR_BF16, MODE, A, lda, W, ldw, M, N, K, ea, st);
+    case TILE_128_W8: return gemm_tile_launch<128, 128, 4, 2, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
+    case TILE_64: return gemm_tile_launch<64, 64, 2, 1, 4, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
+    case TILE_64_128: return gemm_tile_launch<64, 128, 2, 2, 3, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
+    case TILE_256: return gemm_tile_launch<256, 256, 2, 4, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
+    case TILE_128: return gemm_tile_launch<128, 128, 2, 2, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
+    case TILE_256_128: return gemm_tile_launch<256, 128, 4, 2, 3, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
+    case TILE_STREAM: return launch_gemm_bf16_stream(MODE, A, lda, W, ldw, M, N, K, ea, group_n, row_block, stagger_slack, stagger_crit, st);
   }
   return fail(BR_EINVAL, "gemm: unknown variant");
 }

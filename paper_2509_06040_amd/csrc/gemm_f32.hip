@@ -68,18 +68,18 @@ static br_status gemm_f32_any(const float* A, int lda, const float* W, int ldw, 
   return BR_OK;
 }
 
-template <int BM, int BN, int WGM, int WGN, int MODE>
+template <int BM, int BN, int WGM, int WGN, int NST, int MODE>
 static br_status gemm_f32_tile(const float* A, int lda, const float* W, int ldw, int M, int N, int K, const EpiArgs& ea,
                                hipStream_t st) {
   Epilogue<MODE, float> epi{ea};
   const int tiles_m = cdiv(M, BM), tiles_n = cdiv(N, BN);
-  hipLaunchKernelGGL((gemm_tile_kernel<float, BM, BN, WGM, WGN, MODE, float>), dim3(tiles_m * tiles_n), dim3(WGM * WGN * 64), 0, st,
+  hipLaunchKernelGGL((gemm_tile_kernel<float, BM, BN, WGM, WGN, NST, MODE, float>), dim3(tiles_m * tiles_n), dim3(WGM * WGN * 64), 0, st,
                      A, lda, W, ldw, M, N, K, tiles_m, tiles_n, std::min(4, tiles_n), epi);
   BR_LAUNCH_CHECK();
   return BR_OK;
 }
 
-enum { F32_TILE_64 = 4, F32_TILE_128 = 5, F32_KSPLIT = 8 };
+enum { F32_KSPLIT = 0, F32_TILE_64 = 3, F32_TILE_128 = 5 };  // variants
 
 // Share of the compute units' time that `tiles` equal tiles keep busy: they run in whole rounds.
 static double round_fill(long long tiles) {
@@ -88,15 +88,15 @@ static double round_fill(long long tiles) {
 }
 
 // Measured on MI355X (gated residual, M = 1101 / 4404 / 8808 rows, N and K 1024 to 4096), all three forms
-// run at a constant rate times the fill of their rounds: 132 TFLOP/s for 128x128 tiles, 122 for 64x128
-// and 102 for the 32x32 tiles of the k-split kernel, each within 6 %.  The smaller tile trades rate for
-// fill: 4404 x 1024 x 1024 takes 132 / 106 / 92 us (the vector kernel before: 177), 4404 x 4096 x 1024
-// 323 / 310 / 361 (537), 8808 x 4096 x 1024 580 / 614 / 699 (1011).  Far below one round the
-// k-split form wins by its four waves per tile: 24 x 64 x 256 takes 3.7 us instead of 18.
+// run at a constant rate times the fill of their rounds: 138 TFLOP/s for 128x128 tiles, 137 for 64x128 and
+// 102 for the 32x32 tiles of the k-split kernel, each within 7 %.  The smaller tile trades rate for fill:
+// 4404 x 1024 x 1024 takes 125 / 96 / 92 us (the vector kernel before: 177), 4404 x 3072 x 1024 245 / 218 / 272
+// (401), 8808 x 4096 x 1024 543 / 540 / 702 (1011).  Far below one round the k-split form wins by its four
+// waves per tile: 24 x 64 x 256 takes 3.7 us instead of 18.
 static int f32_form(int M, int N, int K) {
-  if (K % 16 != 0) return F32_KSPLIT;  // the tile kernel walks K in whole stages of 16
-  const double t128 = 132.0 * round_fill((long long)cdiv(M, 128) * cdiv(N, 128));
-  const double t64 = 122.0 * round_fill((long long)cdiv(M, 64) * cdiv(N, 128));
+  if (K % 32 != 0) return F32_KSPLIT;  // the tile kernel walks K in whole stages of 32
+  const double t128 = 138.0 * round_fill((long long)cdiv(M, 128) * cdiv(N, 128));
+  const double t64 = 137.0 * round_fill((long long)cdiv(M, 64) * cdiv(N, 128));
   const double ks = 102.0 * round_fill((long long)cdiv(M, 32) * cdiv(N, 32));
   // padding of ragged edges is work done for nothing
   const double used = (double)M * N;
@@ -115,12 +115,12 @@ static br_status gemm_f32_mode(const float* A, int lda, const float* W, int ldw,
   // patch embedding, condition embedding and unpatchify are a few per cent of a network: one form is enough
   constexpr bool TILED = MODE == EPI_BIAS || MODE == EPI_BIAS_GELU || MODE == EPI_BIAS_GATE_RES;
   const bool forced = variant == F32_TILE_64 || variant == F32_TILE_128 || variant == F32_KSPLIT;
-  const int form = forced && K % 16 == 0 ? variant : f32_form(M, N, K);
+  const int form = forced && K % 32 == 0 ? variant : f32_form(M, N, K);
   if constexpr (TILED) {
-    if (form == F32_TILE_64) return gemm_f32_tile<64, 128, 2, 2, MODE>(A, lda, W, ldw, M, N, K, ea, st);
-    if (form == F32_TILE_128) return gemm_f32_tile<128, 128, 2, 2, MODE>(A, lda, W, ldw, M, N, K, ea, st);
+    if (form == F32_TILE_64) return gemm_f32_tile<64, 128, 2, 2, 2, MODE>(A, lda, W, ldw, M, N, K, ea, st);
+    if (form == F32_TILE_128) return gemm_f32_tile<128, 128, 2, 2, 2, MODE>(A, lda, W, ldw, M, N, K, ea, st);
   }
-  return launch_gemm_ksplit(BR_F32, MODE, A, lda, W, ldw, M, N, K, ea, 32, st);
+  return launch_gemm_ksplit(BR_F32, MODE, A, lda, W, ldw, M, N, K, ea, st);
 }
 
 br_status launch_gemm_f32(int mode, const float* A, int lda, const float* W, int ldw, int M, int N, int K,

@@ -8,6 +8,13 @@ namespace br {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// An address that is uniform over the wave; saying so keeps it in scalar registers in every instantiation.
+__device__ inline const char* scalar_ptr(const char* p) {
+  const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+  return reinterpret_cast<const char*>(((unsigned long long)hi << 32) | lo);
+}
+
 template <typename T>
 struct GemmFrag;
 template <>

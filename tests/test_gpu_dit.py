@@ -267,7 +267,7 @@ def test_velocity_chunked_batches_agree(lib):
 
 # every form of the fp32 GEMM (128x128 and 64x128 tiles, 32x32 tiles with the waves splitting K) at tile
 # edges, with K of less than one stage, whole stages and a stage that ends inside a 16-byte chunk pair
-@pytest.mark.parametrize("variant", [-1, 4, 5, 8])
+@pytest.mark.parametrize("variant", [-1, 0, 3, 5])
 @pytest.mark.parametrize("M,N,K", [(1, 4, 4), (31, 36, 12), (33, 132, 16), (64, 128, 20), (65, 124, 32), (129, 260, 144),
                                    (257, 128, 1040), (1000, 516, 96)])
 def test_gemm_fp32_every_form(lib, variant, M, N, K):
@@ -339,3 +339,28 @@ def test_attention_fp32_reference_moves_and_unaligned_buffers(lib):
     buf[1:] = dev(qkv).reshape(-1)
     br.op_attention(br.F32, buf[1:].view(1, L, 3 * H), obuf[1:].view(1, L, H), nh)
     assert rel_l2(host(obuf)[1:].reshape(1, L, H), ref) < 1e-4
+
+
+# the bf16 forms for small and middle sizes: k-split, 64x64 and 64x128 tiles, 128x128 in eight waves; K of one
+# stage, fewer stages than the ring or than waves, and more; ragged rows and columns
+@pytest.mark.parametrize("variant", [0, 1, 2, 3, 2 | (1 << 4), 3 | (3 << 4)])
+@pytest.mark.parametrize("M,N,K", [(1, 4, 64), (31, 64, 128), (33, 132, 192), (65, 36, 256), (127, 192, 320), (130, 260, 1088)])
+def test_gemm_bf16_small_tiles(lib, variant, M, N, K):
+    rng = np.random.default_rng(M + K)
+    A, W = _bf(rng.standard_normal((M, K)).astype(np.float32)), _bf(rng.standard_normal((N, K)).astype(np.float32) * 0.05)
+    b = rng.standard_normal(N).astype(np.float32)
+    ref = A.astype(np.float64) @ W.astype(np.float64).T + b
+    Ad, Wd, bd = dev(A, torch.bfloat16), dev(W, torch.bfloat16), dev(b)
+    out = torch.full((M + 1, N), -9.0, device=DEV)
+    br.op_gemm(br.BF16, 4, Ad, Wd, bd, out[:M], variant=variant)
+    # exact products, fp32 sums of K of them: about sqrt(K) 2^-24 < 2e-6 of the norm
+    assert rel_l2(host(out)[:M], ref) < 2e-6 and (host(out)[M] == -9.0).all()
+    out16 = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    br.op_gemm(br.BF16, 0, Ad, Wd, bd, out16, variant=variant)
+    assert np.array_equal(host(out16), _bf(host(out)[:M]))        # same accumulators, rounded once
+    L = 1 if M % 5 else 5
+    x0, mods = rng.standard_normal((M, N)).astype(np.float32), rng.standard_normal((3, N)).astype(np.float32)
+    cond = (np.arange(M // L) % 3).astype(np.int32)
+    x = dev(x0.copy())
+    br.op_gemm(br.BF16, 2, Ad, Wd, bd, x, mods=dev(mods), gate_off=0, cond=dev(cond), L=L, variant=variant)
+    assert rel_l2(host(x), x0 + np.repeat(mods[cond], L, axis=0) * ref) < 2e-6
