@@ -32,13 +32,13 @@ enum {  // bits 0..3 of a variant
   TILE_KSPLIT = 0, TILE_128_W8 = 1, TILE_64 = 2, TILE_64_128 = 3, TILE_256 = 4, TILE_128 = 5, TILE_256_128 = 6, TILE_STREAM = 7
 };
 
-// The kernel for a problem size, from 410 measured shapes (M 40 to 200 000, hidden sizes 64 to 3072 with
-// their QKV, MLP and projection widths, K 64 to 12 288); it is 2 % slower on average than the best kernel
-// of each shape.  r = tiles of a kind per compute unit.
-static int choose_tile(int M, int N, int K, bool stream_ok) {
+// The kernel for a problem size.  r = tiles of a kind per compute unit.  (The part for small problems is from 410
+// measured shapes: M 40 to 200 000, hidden sizes 64 to 3072 with their QKV, MLP and projection widths.)
+// *height: rows of a tile of the persistent kernel, in units of 32.
+static int choose_tile(int M, int N, int K, bool stream_ok, int* height) {
   const double cu = device_cu_count();
   const double r32 = (double)cdiv(M, 32) * cdiv(N, 32) / cu, r64 = (double)cdiv(M, 64) * cdiv(N, 64) / cu;
-  const double r128 = (double)cdiv(M, 128) * cdiv(N, 128) / cu, r256 = (double)cdiv(M, 256) * cdiv(N, 256) / cu;
+  const double r128 = (double)cdiv(M, 128) * cdiv(N, 128) / cu;
   // Up to a few 32x32 tiles a unit: the waves of a tile split K.  279 x 128 x 512 takes 3.3 us instead of
   // the 5.6 of 64x64 tiles and the 10.7 of the 256x128 tiles used before.  A long K makes the tile's operand
   // traffic (twice that of 64x64 tiles for the same outputs) the longer part sooner.
@@ -49,36 +49,41 @@ static int choose_tile(int M, int N, int K, bool stream_ok) {
   // Up to one round of 128x128 tiles: half of them, so that the round is fuller (1101 x 3072 x 1024: 14.7 us,
   // 20.8 in 256x128 tiles).
   if (r128 <= 1.0) return TILE_64_128;
-  // Beyond: 128x128 tiles, two workgroups a unit, or 256x256 tiles (one persistent workgroup a unit; one tile
-  // per workgroup where K is not a multiple of 128), which move half the operand bytes but finish in whole rounds:
-  // 13 700 x 1088 x 4352 (1.05 rounds) 135 us against 211, 39 300 x 2752 x 11 008 (6.6 rounds) 2510 against 2180.
-  // A partial round costs the small tiles less than a third of one.
-  const double used = (double)M * N;
-  const double e256 = 1.2 * r256 / std::ceil(r256) * used / ((double)cdiv(M, 256) * 256 * cdiv(N, 256) * 256);
-  const double e128 = r128 / (r128 + 0.3) * used / ((double)cdiv(M, 128) * 128 * cdiv(N, 128) * 128);
-  if (e256 > e128) return stream_ok ? TILE_STREAM : TILE_256;
-  return K <= 512 ? TILE_128_W8 : TILE_128;  // a short K leaves a larger share to the epilogue, where eight waves store faster (3-5 %)
+  // Beyond: the persistent kernel, whose tiles are 128 to 256 rows high so that the last round of tiles is full
+  // (9216 x 3072 x 12 288: 545 us in 432 tiles of 256 rows, 1.7 rounds, 490 in 504 of 224; 17 616 x 1024 x 1024: 67 us
+  // in 256 rows, 50 in 160), or 128x128 tiles with two workgroups a unit where those fit better.  The costs are in
+  // 32 x 256 x K blocks a unit: a tile costs three quarters of a block beyond its rows (epilogue, operands of W), a
+  // part of a round 0.6 of what it leaves idle (the units that work run faster at the chip's power limit); 128x128
+  // tiles move twice the operand bytes.  Fitted to 124 shapes (M 500 to 100 000, N 256 to 12 288, K 256 to 12 288):
+  // 0.5 % slower on average than the best kernel of each shape.
+  double best = 1.4 * 2.0 * (r128 + 0.4);
+  int tile = K <= 512 ? TILE_128_W8 : TILE_128;  // a short K leaves a larger share to the epilogue, where eight waves store faster (3-5 %)
+  for (int h = 8; h >= 4; --h) {
+    if (!stream_ok && h < 8) break;
+    const double r = (double)cdiv(M, 32 * h) * cdiv(N, 256) / cu;
+    const double cost = (0.4 * r + 0.6 * std::ceil(r)) * (h + 0.75);
+    if (cost < best) {
+      best = cost;
+      tile = stream_ok ? TILE_STREAM : TILE_256;
+      *height = h;
+    }
+  }
+  return tile;
 }
 
-// variant bits 0..3: kernel (see the enum); bits 4..11: column-group width of the tile walk (0 = the
-// kernel's own choice); variant < 0 = choose by problem size.
+// variant bits 0..3: kernel (see the enum); bits 4..11: column-group width of the tile walk (0 = the kernel's own
+// choice); for the persistent kernel bits 12..15: rows of a tile in units of 32 (4 to 8, else 8), bits 24..30: row block
+// of the walk in units of 8 tile rows.  variant < 0 = choose by problem size.
 template <int MODE, typename TOUT>
 static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K, const EpiArgs& ea,
                               int variant, hipStream_t st) {
-  int tile, group_n = 0, row_block = 0, stagger_slack = 0, stagger_crit = 0;
+  int tile, group_n = 0, row_block = 0, height = 0;
   if (variant < 0) {
-    tile = choose_tile(M, N, K, gemm_stream_supported(M, N, K, (size_t)M * lda * 2, (size_t)N * ldw * 2));
-    // The fp32 gated residual reads and writes 512 KB per tile; with a short k-loop (K <= 2048) these
-    // bursts of a die's 32 workgroups, all in step, are a third of the launch.  Workgroups with one tile
-    // less than the longest list start up to 7 x 3 us late, in groups of four, which costs the launch
-    // nothing and spreads the bursts: measured 6 % (64 samples) to 14 % (32 samples) on the image
-    // network's projection GEMM (1101-token samples, N = K = 1024), nothing on deeper k-loops.
-    if (MODE == EPI_BIAS_GATE_RES && K <= 2048) stagger_slack = 300;
+    tile = choose_tile(M, N, K, gemm_stream_supported(MODE, K, (size_t)M * lda * 2, (size_t)N * ldw * 2), &height);
   } else {
     tile = variant & 15;
     group_n = (variant >> 4) & 255;
-    stagger_slack = ((variant >> 12) & 255) * 50;  // half microseconds -> 10 ns ticks
-    stagger_crit = ((variant >> 20) & 15) * 50;
+    height = (variant >> 12) & 15;
     row_block = ((variant >> 24) & 127) * 8;
   }
   ProfScope ps(st, PROF_GEMM + MODE * 8 + tile, 2.0 * M * N * K);
@@ -90,7 +95,7 @@ static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, in
     case TILE_256: return gemm_tile_launch<256, 256, 2, 4, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
     case TILE_128: return gemm_tile_launch<128, 128, 2, 2, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
     case TILE_256_128: return gemm_tile_launch<256, 128, 4, 2, 3, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
-    case TILE_STREAM: return launch_gemm_bf16_stream(MODE, A, lda, W, ldw, M, N, K, ea, group_n, row_block, stagger_slack, stagger_crit, st);
+    case TILE_STREAM: return launch_gemm_bf16_stream(MODE, A, lda, W, ldw, M, N, K, ea, height, group_n, row_block, st);
   }
   return fail(BR_EINVAL, "gemm: unknown variant");
 }

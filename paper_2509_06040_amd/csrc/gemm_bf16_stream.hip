@@ -1,56 +1,66 @@
-// Persistent bf16 GEMM for gfx950: C[m, n] = sum_k A[m, k] W[n, k], fp32 accumulate,
-// fused epilogue.  One workgroup per compute unit walks a list of 256x256 output
-// tiles; the operand stream (global memory -> LDS directly) never stops at a tile
-// boundary: while the last k-steps of a tile are multiplied the first stage of the
-// next tile is already being fetched, and it keeps landing while the finished tile
-// goes through its epilogue.
+// Persistent bf16 GEMM for gfx950: C[m, n] = sum_k A[m, k] W[n, k], fp32 accumulate, fused epilogue.  One
+// workgroup per compute unit, four waves (one per SIMD, all 512 registers each), walks a list of BM x 256 output
+// tiles, BM = 32 RB; a wave owns 16 RB x 128 outputs.  The operand stream (global memory -> LDS directly) never
+// stops at a tile boundary: while the last k-steps of a tile are multiplied the first stages of the next tile are
+// already being fetched, and they keep landing while the finished tile goes through its epilogue.
 //
-// Stages are 64 deep (128-byte row segments: measured 1.6x the L2->LDS throughput of
-// 64-byte segments on MI355X) and there are two of them; the refill of a stage is
-// issued three quarters of the way through the other one, right after the only
-// barrier of the stage.  Measured with the math in the loop, one 64 KB stage in
-// flight beats three 32 KB stages in flight.
-//
-// Operand loads of a tile wholly inside the matrix take a scalar block address and one of two
-// constant per-lane offsets, so the k-loop issues no vector arithmetic beside the MFMAs (the
-// two do not overlap on this hardware).
-//
-// Epilogue (gemm_epilogue.h): the MFMA accumulator layout gives a lane 4 consecutive columns
-// of ONE row, which would make every store instruction touch 32 different rows.  Each wave
-// therefore passes its tile through a private 4 KB LDS buffer and writes whole row segments.
+// What bounds it: the matrix pipe at the clock that the chip sustains on the data.  The earlier form (eight waves of
+// 128 x 64, 32x32x16 instructions, a stage's refill issued in one burst) ran 147 456 x 9216 x 3072 at 1240 TFLOP/s
+// with random operands and 1650 with zeros, this one at 1500 and 1990; four things make the difference:
+//  - Four waves of 128 x 128 read a third less of the operands from LDS than eight of 128 x 64.
+//  - Sixteen LDS-direct loads a wave and stage, spread evenly over its 128 matrix instructions.  The vector memory
+//    path takes 64 bytes a clock: a burst stands in front of the wave's next matrix instructions (it is issued in
+//    order), and costs a quarter of the launch.
+//  - To have time for that, the two halves of a ring slot are refilled at different times.  The W fragments of a
+//    stage are all read half a stage ahead, so that W's half of the slot is free early: W of stage q + 2 is fetched
+//    during the first half of stage q, A of stage q + 2 during the second, and each has at least half a stage to land.
+//  - 16x16x32 matrix instructions in an order in which neighbours share an operand draw less power than 32x32x16
+//    ones: the clock is higher on random operands (7 to 14 % of the launch), the same on zeros.
 //
 // Requirements: K % 128 == 0 (every tile starts on ring slot 0), K >= 128, operands below 4 GiB.
+#include <cmath>
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "dit.h"
-#include "gemm_epilogue.h"
+#include "gemm_epilogue_wide.h"
+#include "gemm_frag.h"
 
 namespace br {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 #define BR_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
 namespace {
-constexpr int BM = 256, BN = 256, WGM = 2, WGN = 4, NW = 8;
-constexpr int WTM = 128, WTN = 64, TM = 4, TN = 2;
-constexpr int BK = 64;                                              // k-depth of a stage
-constexpr int IA = BM / 8 / NW, IW = BN / 8 / NW, LPT = IA + IW;    // LDS-direct loads per wave and stage (8 rows each)
-constexpr int SA = BM * 128, STAGE = (BM + BN) * 128;               // bytes
-constexpr int EPILOGUE_STORES = TM * 2 * 4;                         // store instructions of a full wave tile
+constexpr int BN = 256, NW = 4;
+constexpr int BK = 64;            // k-depth of a stage: 128-byte row segments (64-byte ones pull a third less through the L2)
+constexpr int IW = BN / 8 / NW;   // LDS-direct loads of W per wave and stage (8 rows each)
 }  // namespace
 
-template <int S>
-__shared__ __attribute__((aligned(1024))) char g_ring[STAGE];
-__shared__ __attribute__((aligned(1024))) char g_epi[NW * 4096];
+template <int BYTES, int S>
+__shared__ __attribute__((aligned(1024))) char g_ring[BYTES];
+__shared__ __attribute__((aligned(1024))) char g_epi[NW * WIDE_EPI_BYTES];
 
-__device__ inline const char* uniform_ptr(const char* p) {
-  const unsigned long long v = reinterpret_cast<unsigned long long>(p);
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-  return reinterpret_cast<const char*>(((unsigned long long)hi << 32) | lo);
+// f(integral_constant 0) ... f(integral_constant N - 1)
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// Matrix instructions on accumulators that stay in the accumulation registers.  (From the builtin the compiler keeps
+// some of the 64 blocks in vector registers and moves them back and forth.)  The first of a tile starts from zero.
+__device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& w, const bf16x8& a) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(a));
+}
+__device__ __forceinline__ void mfma16_first(f32x4& c, const bf16x8& w, const bf16x8& a) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(w), "v"(a));
 }
 
 // Maps the j-th tile of workgroup `wg` to (tile_m, tile_n); false when the list is exhausted.
@@ -84,213 +94,196 @@ __device__ inline bool stream_tile(int wg, int nwg, int j, int tiles_m, int tile
   return true;
 }
 
-template <int MODE, typename TOUT>
-__global__ __launch_bounds__(512) void gemm_bf16_stream_kernel(const bf16* __restrict__ A, int lda,
-                                                               const bf16* __restrict__ W, int ldw, int M, int N, int K,
-                                                               int tiles_m, int tiles_n, int group_n, int row_block, int stagger_slack, int stagger_crit,
-                                                               Epilogue<MODE, TOUT> epi) {
+template <int RB, int MODE, typename TOUT>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, 1))) void gemm_bf16_stream_kernel(
+    const bf16* __restrict__ A, int lda, const bf16* __restrict__ W, int ldw, int M, int N, int K, int tiles_m, int tiles_n,
+    int group_n, int row_block, Epilogue<MODE, TOUT> epi) {
+  constexpr int BM = 32 * RB, IA = BM / 8 / NW, LPT = IA + IW;
+  constexpr int SA = BM * 128, STAGE = (BM + BN) * 128;  // bytes
+  constexpr int NM = 8 * RB;                             // matrix instructions of a k32-step
   const int tid = threadIdx.x, lane = tid & 63;
-  // Workgroups that start together stay in step tile after tile, so the epilogues of the 32
-  // workgroups of a compute die hit that die's memory port in one burst per round, with the port
-  // idle in between.  Shifting groups of workgroups against each other spreads that traffic.
-  // The four workgroups that share a row panel of A (consecutive ids on a die) keep one phase,
-  // so they still fetch the panel together.  A workgroup whose tile list is one shorter than
-  // the longest on its die starts up to 7 * stagger_slack ticks late (10 ns units) at no cost
-  // to the launch; the others start up to 7 * stagger_crit ticks late.
-  if (stagger_slack > 0 || stagger_crit > 0) {
-    const int nt = tiles_m * tiles_n, x = blockIdx.x & 7, i = blockIdx.x >> 3, per_x = ((int)gridDim.x - x + 7) >> 3;
-    const int cnt = nt / 8 + (x < nt % 8 ? 1 : 0);
-    const int n_mine = i < cnt ? (cnt - i + per_x - 1) / per_x : 0, n_max = (cnt + per_x - 1) / per_x;
-    const unsigned long long wait = (unsigned long long)((i >> 2) & 7) * (unsigned)(n_mine < n_max ? stagger_slack : stagger_crit);
-    const unsigned long long t0 = wall_clock64();
-    while (wall_clock64() - t0 < wait) __builtin_amdgcn_s_sleep(16);
-  }
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wv % WGM) * WTM, wn0 = (wv / WGM) * WTN;
-  const int l32 = lane & 31, lh = lane >> 5;
+  const int wm0 = (wv & 1) * 16 * RB, wn0 = (wv >> 1) * 128;
   const int nst = K / BK;  // stages per tile (even)
 
-  // A stage row is 128 bytes = eight 16-byte chunks; chunk c of row r sits in slot
-  // c ^ ((r >> 1) & 7): sixteen consecutive rows at one chunk index then cover all 64 LDS
-  // banks.  An LDS-direct load fills 8 consecutive rows (lane = 8 * row + slot), so the
-  // swizzle is applied to the global address the lane fetches from.
-  const int ld_row = lane >> 3;                                        // row inside an 8-row block
-  // all rows this lane ever loads have (row >> 1) & 7 == (ld_row >> 1) & 3 + 4 * (block & 1)
-  auto src_off = [&](int tile_row0, int blk, int limit, int ld) {
-    const int row = blk * 8 + ld_row;
-    const int c = (lane & 7) ^ ((row >> 1) & 7);
-    return (unsigned)(((size_t)min(tile_row0 + row, limit - 1) * ld + c * 8) * 2);
+  // A stage row is 128 bytes = eight 16-byte chunks; chunk c of row r sits in slot c ^ ((r >> 1) & 7): sixteen
+  // consecutive rows at one chunk index then cover all 64 LDS banks.  An LDS-direct load fills 8 consecutive rows
+  // (lane = 8 * row + slot), so the swizzle is applied to the global address that the lane fetches from.
+  // Byte offset inside a stage of this lane's fragment of 16-row block 0 for k32-step 0 (row lane & 15, chunk
+  // lane >> 4); block b is 2048 bytes further, step 1 is the same ^ 64.
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int fa_off = (wm0 + l16) * 128 + ((lq ^ ((l16 >> 1) & 7)) << 4);
+  const int fw_off = SA + (wn0 + l16) * 128 + ((lq ^ ((l16 >> 1) & 7)) << 4);
+
+  // ---- load cursor: tile and stage of the operand stream that the next refill fetches; rows past the end of the
+  // matrix read its last row
+  int ld_j = 0, ld_q = 0;
+  unsigned off_a[IA], off_w[IW];
+  const char *ld_a, *ld_w;
+  auto ld_tile = [&](int tm, int tn) {
+    const int m0 = tm * BM, n0 = tn * BN;
+#pragma unroll
+    for (int j = 0; j < IA; ++j) {
+      const int row = (wv * IA + j) * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+      off_a[j] = (unsigned)min(row, M - 1 - m0) * (unsigned)lda * 2u + c * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < IW; ++j) {
+      const int row = (wv * IW + j) * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+      off_w[j] = (unsigned)min(row, N - 1 - n0) * (unsigned)ldw * 2u + c * 16;
+    }
+    ld_a = reinterpret_cast<const char*>(A + (size_t)m0 * lda);
+    ld_w = reinterpret_cast<const char*>(W + (size_t)n0 * ldw);
   };
-  // fragment byte offsets inside a stage for k16-step 0; step ks is the same offset ^ (ks << 5)
-  int fa_off[TM], fw_off[TN];
-#pragma unroll
-  for (int j = 0; j < TM; ++j) {
-    const int row = wm0 + j * 32 + l32;
-    fa_off[j] = row * 128 + ((lh ^ ((row >> 1) & 7)) << 4);
-  }
-#pragma unroll
-  for (int i = 0; i < TN; ++i) {
-    const int row = wn0 + i * 32 + l32;
-    fw_off[i] = SA + row * 128 + ((lh ^ ((row >> 1) & 7)) << 4);
-  }
-
-  int tile_j = 0, tm = 0, tn = 0, tmn = 0, tnn = 0;
-  stream_tile(blockIdx.x, gridDim.x, 0, tiles_m, tiles_n, group_n, row_block, &tm, &tn);
-  bool has_next = stream_tile(blockIdx.x, gridDim.x, 1, tiles_m, tiles_n, group_n, row_block, &tmn, &tnn);
-
-  // Per-lane byte offsets of an LDS-direct load from the first row of its 8-row block, for
-  // even and odd blocks (the swizzle of a row depends on the block only through its parity);
-  // the block's base address is uniform and is carried in scalar registers, so a load of a
-  // tile wholly inside the matrix costs no vector arithmetic at all.  Vector instructions
-  // and MFMAs do not overlap on this hardware: every one saved here is matrix time gained.
-  static_assert(IA % 2 == 0 && IW % 2 == 0, "block parity must follow the load index");
-  unsigned voff_a[2], voff_w[2];
-#pragma unroll
-  for (int par = 0; par < 2; ++par) {
-    const unsigned c = (lane & 7) ^ ((ld_row >> 1) | (4 * par));
-    voff_a[par] = (unsigned)ld_row * (unsigned)lda * 2 + c * 16;
-    voff_w[par] = (unsigned)ld_row * (unsigned)ldw * 2 + c * 16;
-  }
-
-  // Stream element q of the current tile: stage q if q < nst, stage q - nst of the next tile
-  // otherwise (the last stage again when there is no next tile: a fetch nobody reads).
-  auto issue = [&](auto S, int q) {
-    char* ring = g_ring<decltype(S)::value>;
-    const unsigned base = (unsigned)(uintptr_t)BR_LPTR(ring);
-    const bool wrap = q >= nst && has_next;
-    const unsigned kb = (unsigned)(wrap ? q - nst : min(q, nst - 1)) * (BK * 2);
-    const int rm = (wrap ? tmn : tm) * BM, rn = (wrap ? tnn : tn) * BN;
-    if (rm + BM <= M && rn + BN <= N) {
-      // (the addresses are uniform; saying so keeps them in scalar registers in every instantiation)
-      const char* a_blk = uniform_ptr(reinterpret_cast<const char*>(A) + ((size_t)(rm + wv * IA * 8) * lda) * 2 + kb);
-      const char* w_blk = uniform_ptr(reinterpret_cast<const char*>(W) + ((size_t)(rn + wv * IW * 8) * ldw) * 2 + kb);
-#pragma unroll
-      for (int j = 0; j < IA; ++j) {
-        const unsigned dst = base + (wv * IA + j) * 1024;
-        const char* blk = a_blk + (size_t)j * 8 * lda * 2;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff_a[j & 1]), "s"(blk) : "memory", "m0");
-      }
-#pragma unroll
-      for (int j = 0; j < IW; ++j) {
-        const unsigned dst = base + SA + (wv * IW + j) * 1024;
-        const char* blk = w_blk + (size_t)j * 8 * ldw * 2;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff_w[j & 1]), "s"(blk) : "memory", "m0");
-      }
-    } else {  // ragged tile: rows past the end read the last row
-      const bf16* a_base = A;
-      const bf16* w_base = W;
-#pragma unroll
-      for (int j = 0; j < IA; ++j) {
-        const unsigned src = src_off(rm, wv * IA + j, M, lda) + kb;
-        const unsigned dst = base + (wv * IA + j) * 1024;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(src), "s"(a_base) : "memory", "m0");
-      }
-#pragma unroll
-      for (int j = 0; j < IW; ++j) {
-        const unsigned src = src_off(rn, wv * IW + j, N, ldw) + kb;
-        const unsigned dst = base + SA + (wv * IW + j) * 1024;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(src), "s"(w_base) : "memory", "m0");
+  auto ld_advance = [&]() {  // to the next stage; at the end of the list the last stage stays: fetches nobody reads
+    ++ld_q;
+    ld_a += BK * 2;
+    ld_w += BK * 2;
+    if (ld_q == nst) {
+      int tm, tn;
+      if (stream_tile(blockIdx.x, gridDim.x, ld_j + 1, tiles_m, tiles_n, group_n, row_block, &tm, &tn)) {
+        ++ld_j;
+        ld_q = 0;
+        ld_tile(tm, tn);
+      } else {
+        --ld_q;
+        ld_a -= BK * 2;
+        ld_w -= BK * 2;
       }
     }
   };
+  auto load_a = [&](auto S, int n) {
+    char* ring = g_ring<STAGE, decltype(S)::value>;
+    const unsigned dst = (unsigned)(uintptr_t)BR_LPTR(ring) + (wv * IA + n) * 1024, src = off_a[n];
+    const char* p = scalar_ptr(ld_a);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(src), "s"(p) : "memory", "m0");
+  };
+  auto load_w = [&](auto S, int n) {
+    char* ring = g_ring<STAGE, decltype(S)::value>;
+    const unsigned dst = (unsigned)(uintptr_t)BR_LPTR(ring) + SA + (wv * IW + n) * 1024, src = off_w[n];
+    const char* p = scalar_ptr(ld_w);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(src), "s"(p) : "memory", "m0");
+  };
 
-  f32x16 acc[TN][TM];
-  auto zero_acc = [&]() {
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  f32x4 acc[8][RB];           // 16x16 blocks: columns, rows
+  bf16x8 fa[2][RB], fw[2][8];  // fragments of the two k32-steps of a stage
+  auto read_a = [&](const char* stage, int h, int n) {
+    fa[h][n] = *reinterpret_cast<const bf16x8*>(stage + (fa_off ^ (h << 6)) + n * 2048);
   };
-  zero_acc();
-
-  // two fragment sets: set (ks & 1) holds k16-step ks
-  bf16x8 fa[2][TM], fw[2][TN];
-  auto read_frags = [&](const char* stage, int ks, int set) {
-#pragma unroll
-    for (int j = 0; j < TM; ++j) fa[set][j] = *reinterpret_cast<const bf16x8*>(stage + (fa_off[j] ^ (ks << 5)));
-#pragma unroll
-    for (int i = 0; i < TN; ++i) fw[set][i] = *reinterpret_cast<const bf16x8*>(stage + (fw_off[i] ^ (ks << 5)));
-  };
-  auto mma = [&](int set) {
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[set][i], fa[set][j], acc[i][j], 0, 0, 0);
-  };
-  // One stage = four k16-steps; the fragments of step ks+1 are read while step ks is multiplied.
-  // After the reads of the last step have been issued and have arrived, the other stage must
-  // have landed too (nothing younger is in flight); one barrier then makes both true for every
-  // wave, the freed stage is refilled, and the first fragments of the other stage are read.
-  // `stores_behind`: the wave has issued at least that many stores since the fetch of the
-  // other stage (the epilogue of a tile wholly inside the matrix).  Memory operations retire in
-  // issue order, so the other stage has landed once no more than that many are outstanding,
-  // and the stores' write acknowledgements need not be waited for yet.
-  auto stage_step = [&](auto S, int q, int stores_behind) {
-    constexpr int CUR = decltype(S)::value, NXT = CUR ^ 1;
-    const char* cur = g_ring<CUR>;
-#pragma unroll
-    for (int ks = 0; ks < 3; ++ks) {
-      read_frags(cur, ks + 1, (ks + 1) & 1);
-      __builtin_amdgcn_sched_barrier(0);
-      mma(ks & 1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (stores_behind >= EPILOGUE_STORES)
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(EPILOGUE_STORES) : "memory");
-    else if (stores_behind >= EPILOGUE_STORES / 2)
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(EPILOGUE_STORES / 2) : "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    issue(std::integral_constant<int, CUR>{}, q + 2);
-    read_frags(g_ring<NXT>, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    mma(1);
-    __builtin_amdgcn_sched_barrier(0);
+  auto read_w = [&](const char* stage, int h, int n) {
+    fw[h][n] = *reinterpret_cast<const bf16x8*>(stage + (fw_off ^ (h << 6)) + n * 2048);
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
+  // matrix instruction t of a k32-step: W block t / RB, the A blocks forwards and back
+  auto mma_one = [&](auto H, auto FIRST, auto TT) {
+    constexpr int h = decltype(H)::value, t = decltype(TT)::value, i = t / RB, j = (i & 1) ? RB - 1 - t % RB : t % RB;
+    if constexpr (decltype(FIRST)::value && h == 0)
+      mfma16_first(acc[i][j], fw[h][i], fa[h][j]);
+    else
+      mfma16(acc[i][j], fw[h][i], fa[h][j]);
+  };
+  // One stage.  It finds in registers the A and W fragments of its step 0 and all but the last W fragment of its step
+  // 1, and leaves the same of the next stage.  First barrier: every wave has read its W fragments, W's half of the slot
+  // is refilled behind it (stage + 2).  Second barrier: every wave has read its A fragments, and the other slot has
+  // landed (only the refill of W just issued is younger); A's half is refilled behind it.
+  // `stores_behind`: the wave has issued at least that many stores since the last loads of the other slot (a tile's
+  // epilogue).  Memory operations retire in issue order, so their write acknowledgements need not be waited for.
+  auto stage_step = [&](auto S, auto FIRST, int stores_behind) {
+    constexpr int CUR = decltype(S)::value, NXT = CUR ^ 1;
+    constexpr int W_STEP = (7 * RB - 2) / 8;
+    using C = std::integral_constant<int, CUR>;
+    const char* cur = g_ring<STAGE, CUR>;
+    const char* nxt = g_ring<STAGE, NXT>;
+    static_for<NM>([&](auto TT) {
+      constexpr int t = decltype(TT)::value;
+      if (t == 0) read_w(cur, 1, 7);
+      if (t == RB) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        ld_advance();
+      }
+      if (t >= RB && (t - RB) % 4 == 0 && (t - RB) / 4 < RB) read_a(cur, 1, (t - RB) / 4);
+      if (t >= RB + 2 && (t - RB - 2) % W_STEP == 0 && (t - RB - 2) / W_STEP < IW) load_w(C{}, (t - RB - 2) / W_STEP);
+      __builtin_amdgcn_sched_barrier(0);
+      mma_one(I0{}, FIRST, TT);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if (stores_behind >= 8 * RB)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(8 * RB + IW < 63 ? 8 * RB + IW : 63) : "memory");
+    else if (stores_behind >= 4 * RB)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(4 * RB + IW) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(IW) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    static_for<NM>([&](auto TT) {
+      constexpr int t = decltype(TT)::value;
+      if (t % 2 == 0 && t / 2 < RB)
+        read_a(nxt, 0, t / 2);
+      else if (t % 2 == 0 && t / 2 < RB + 8)
+        read_w(nxt, 0, t / 2 - RB);
+      if (t % RB == 1 && t > RB) read_w(nxt, 1, t / RB - 1);  // (block t / RB - 1 of this step is done)
+      if (t % 8 == 4) load_a(C{}, t / 8);
+      __builtin_amdgcn_sched_barrier(0);
+      mma_one(I1{}, FIRST, TT);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto read_first = [&]() {  // what the first stage of a tile finds in registers
+#pragma unroll
+    for (int n = 0; n < RB; ++n) read_a(g_ring<STAGE, 0>, 0, n);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) read_w(g_ring<STAGE, 0>, 0, n);
+#pragma unroll
+    for (int n = 0; n < 7; ++n) read_w(g_ring<STAGE, 0>, 1, n);
+  };
 
-  issue(I0{}, 0);
-  issue(I1{}, 1);
+  int tm, tn;
+  stream_tile(blockIdx.x, gridDim.x, 0, tiles_m, tiles_n, group_n, row_block, &tm, &tn);
+  ld_tile(tm, tn);
+#pragma unroll
+  for (int n = 0; n < IA; ++n) load_a(I0{}, n);
+#pragma unroll
+  for (int n = 0; n < IW; ++n) load_w(I0{}, n);
+  ld_advance();
+#pragma unroll
+  for (int n = 0; n < IA; ++n) load_a(I1{}, n);
+#pragma unroll
+  for (int n = 0; n < IW; ++n) load_w(I1{}, n);
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  read_frags(g_ring<0>, 0, 0);
+  read_first();
 
-  char* ebuf = g_epi + wv * 4096;
-  int stores_behind = 0;
+  char* ebuf = g_epi + wv * WIDE_EPI_BYTES;
+  int stores_behind = 0, tile_j = 0;
   for (;;) {
-    stage_step(I0{}, 0, stores_behind);
-    stage_step(I1{}, 1, 0);
+    stage_step(I0{}, std::true_type{}, stores_behind);
+    stage_step(I1{}, std::false_type{}, 0);
     for (int q = 2; q < nst; q += 2) {
-      stage_step(I0{}, q, 0);
-      stage_step(I1{}, q + 1, 0);
+      stage_step(I0{}, std::false_type{}, 0);
+      stage_step(I1{}, std::false_type{}, 0);
     }
-    // ---- epilogue of tile (tm, tn); the next tile's first stages keep landing meanwhile
-    stores_behind = wave_epilogue<TM, TN, MODE, TOUT>(acc, ebuf, tm * BM + wm0, tn * BN + wn0, M, N, epi, lane);
-    zero_acc();
-    if (!has_next) break;
-    // read the next tile's first fragments again rather than keep them alive across the
-    // epilogue, which needs the registers for the rows it fetches ahead
-    read_frags(g_ring<0>, 0, 0);
-    tm = tmn;
-    tn = tnn;
+    // ---- epilogue of tile (tm, tn); the next tile's first stages keep landing meanwhile.  (The compiler does not see
+    // that the accumulators come from matrix instructions: the wait for the last of them is written here.)
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    stores_behind = wide_epilogue<RB, MODE, TOUT>(acc, ebuf, tm * BM + wm0, tn * BN + wn0, M, N, epi, lane);
     ++tile_j;
-    has_next = stream_tile(blockIdx.x, gridDim.x, tile_j + 1, tiles_m, tiles_n, group_n, row_block, &tmn, &tnn);
+    if (!stream_tile(blockIdx.x, gridDim.x, tile_j, tiles_m, tiles_n, group_n, row_block, &tm, &tn)) break;
+    // read the next tile's first fragments again rather than keep them alive across the epilogue, which needs the
+    // registers for the rows it fetches ahead
+    read_first();
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the fetches past the end of the stream
 }
 
-template <int MODE, typename TOUT>
+template <int RB, int MODE, typename TOUT>
 static br_status stream_launch(const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K, const EpiArgs& ea,
-                               int group_n, int row_block, int stagger_slack, int stagger_crit, hipStream_t st) {
+                               int group_n, int row_block, hipStream_t st) {
   Epilogue<MODE, TOUT> epi{ea};
-  const int tiles_m = cdiv(M, BM), tiles_n = cdiv(N, BN);
+  const int tiles_m = cdiv(M, 32 * RB), tiles_n = cdiv(N, BN);
   // Default walk: column groups of 4.  The 32 tiles an XCD works on at once then span 8 row
   // panels x 4 column panels, the squarest footprint, i.e. the fewest operand panels to pull
   // into its L2 per round (a third fewer fetched bytes than whole rows of 12 or 16 tiles).
@@ -305,31 +298,39 @@ static br_status stream_launch(const bf16* A, int lda, const bf16* W, int ldw, i
   const int n_cu = device_cu_count();
   const int nt = tiles_m * tiles_n;
   const int grid = nt < n_cu ? nt : n_cu;
-  hipLaunchKernelGGL((gemm_bf16_stream_kernel<MODE, TOUT>), dim3(grid), dim3(512), 0, st, A, lda, W, ldw, M, N, K,
-                     tiles_m, tiles_n, group_n, row_block, stagger_slack, stagger_crit, epi);
+  hipLaunchKernelGGL((gemm_bf16_stream_kernel<RB, MODE, TOUT>), dim3(grid), dim3(256), 0, st, A, lda, W, ldw, M, N, K,
+                     tiles_m, tiles_n, group_n, row_block, epi);
   BR_LAUNCH_CHECK();
   return BR_OK;
 }
 
-bool gemm_stream_supported(int M, int N, int K, size_t bytes_a, size_t bytes_w) {
-  // 32-bit byte offsets from the operand bases
-  return K >= 128 && K % 128 == 0 && bytes_a < (1ull << 32) && bytes_w < (1ull << 32);
+template <int MODE, typename TOUT>
+static br_status stream_height(const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K, const EpiArgs& ea,
+                               int height, int group_n, int row_block, hipStream_t st) {
+  switch (height) {
+    case 4: return stream_launch<4, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, st);
+    case 5: return stream_launch<5, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, st);
+    case 6: return stream_launch<6, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, st);
+    case 7: return stream_launch<7, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, st);
+  }
+  return stream_launch<8, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, st);
+}
+
+bool gemm_stream_supported(int mode, int K, size_t bytes_a, size_t bytes_w) {
+  return (mode == EPI_BIAS || mode == EPI_BIAS_GELU || mode == EPI_BIAS_GATE_RES || mode == EPI_BIAS_F32) && K >= 128 &&
+         K % 128 == 0 && bytes_a < (1ull << 32) && bytes_w < (1ull << 32);
 }
 
 br_status launch_gemm_bf16_stream(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
-                                  const EpiArgs& ea, int group_n, int row_block, int stagger_slack, int stagger_crit,
-                                  hipStream_t st) {
-  BR_REQUIRE(stagger_slack >= 0 && stagger_slack <= 20000 && stagger_crit >= 0 && stagger_crit <= 20000, BR_EINVAL,
-             "streaming gemm: stagger out of range");
-  BR_REQUIRE(gemm_stream_supported(M, N, K, (size_t)M * lda * 2, (size_t)N * ldw * 2), BR_ESHAPE,
+                                  const EpiArgs& ea, int height, int group_n, int row_block, hipStream_t st) {
+  BR_REQUIRE(gemm_stream_supported(mode, K, (size_t)M * lda * 2, (size_t)N * ldw * 2), BR_ESHAPE,
              "streaming gemm: needs K % 128 == 0 and operands below 4 GiB");
+  if (height < 4 || height > 8) height = 8;
   switch (mode) {
-    case EPI_BIAS: return stream_launch<EPI_BIAS, bf16>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, stagger_slack, stagger_crit, st);
-    case EPI_BIAS_GELU: return stream_launch<EPI_BIAS_GELU, bf16>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, stagger_slack, stagger_crit, st);
-    case EPI_BIAS_GATE_RES: return stream_launch<EPI_BIAS_GATE_RES, float>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, stagger_slack, stagger_crit, st);
-    case EPI_PATCH_EMBED: return stream_launch<EPI_PATCH_EMBED, float>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, stagger_slack, stagger_crit, st);
-    case EPI_BIAS_F32: return stream_launch<EPI_BIAS_F32, float>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, stagger_slack, stagger_crit, st);
-    case EPI_UNPATCH: return stream_launch<EPI_UNPATCH, float>(A, lda, W, ldw, M, N, K, ea, group_n, row_block, stagger_slack, stagger_crit, st);
+    case EPI_BIAS: return stream_height<EPI_BIAS, bf16>(A, lda, W, ldw, M, N, K, ea, height, group_n, row_block, st);
+    case EPI_BIAS_GELU: return stream_height<EPI_BIAS_GELU, bf16>(A, lda, W, ldw, M, N, K, ea, height, group_n, row_block, st);
+    case EPI_BIAS_GATE_RES: return stream_height<EPI_BIAS_GATE_RES, float>(A, lda, W, ldw, M, N, K, ea, height, group_n, row_block, st);
+    case EPI_BIAS_F32: return stream_height<EPI_BIAS_F32, float>(A, lda, W, ldw, M, N, K, ea, height, group_n, row_block, st);
   }
   return fail(BR_EINVAL, "gemm: unknown epilogue");
 }

@@ -106,6 +106,32 @@ def test_gemm_two_launch_cut_matches_one_launch_and_fp64(lib, mode):
     assert rel_l2(host(outs[0].float())[rows], ref) < tol
 
 
+@pytest.mark.parametrize("height", [4, 5, 6, 7, 8])
+@pytest.mark.parametrize("M,N,K,L", [(32, 256, 128, 32), (255, 260, 256, 255), (1290, 772, 384, 129), (2 * 1101, 1024, 256, 1101), (640, 128, 128, 20)])
+def test_gemm_persistent_tile_heights(lib, height, M, N, K, L):
+    """Every tile height: one stage pair and more, ragged rows and columns, samples that end inside a wave's
+    rows (L 129, 1101) and more than two of them (L 20), nothing written past the last row."""
+    rng = np.random.default_rng(M + N + height)
+    A, W = _bf(rng.standard_normal((M, K)).astype(np.float32)), _bf(rng.standard_normal((N, K)).astype(np.float32) * 0.05)
+    b, x0 = rng.standard_normal(N).astype(np.float32), rng.standard_normal((M, N)).astype(np.float32)
+    mods = rng.standard_normal((M // L, N)).astype(np.float32)
+    Ad, Wd, bd = dev(A, torch.bfloat16), dev(W, torch.bfloat16), dev(b)
+    lin = A.astype(np.float64) @ W.astype(np.float64).T + b
+    variant = 7 | (height << 12)
+    out = torch.full((M + 8, N), -9.0, device=DEV)
+    br.op_gemm(br.BF16, 4, Ad, Wd, bd, out[:M], variant=variant)
+    assert rel_l2(host(out[:M]), lin) < 1e-5 and bool((out[M:] == -9.0).all())
+    for mode, ref in ((0, lin), (1, dit.gelu_tanh(lin))):
+        o16 = torch.full((M + 8, N), -9.0, dtype=torch.bfloat16, device=DEV)
+        br.op_gemm(br.BF16, mode, Ad, Wd, bd, o16[:M], variant=variant)
+        assert rel_l2(host(o16[:M].float()), ref) < 4e-3 and bool((o16[M:] == -9.0).all())
+    x = torch.full((M + 8, N), -9.0, device=DEV)
+    x[:M] = dev(x0)
+    cond = np.arange(M // L, dtype=np.int32)[::-1].copy()
+    br.op_gemm(br.BF16, 2, Ad, Wd, bd, x[:M], mods=dev(mods), gate_off=0, cond=dev(cond), L=L, variant=variant)
+    assert rel_l2(host(x[:M]), x0 + np.repeat(mods[cond], L, axis=0) * lin) < 1e-5 and bool((x[M:] == -9.0).all())
+
+
 def _attention_ref(qkv, nh):
     B, L, H3 = qkv.shape
     H = H3 // 3
