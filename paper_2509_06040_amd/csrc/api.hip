@@ -95,14 +95,23 @@ extern "C" br_status br_rollout(const br_tree* tree, const br_model* model, cons
   if ((s = launch_sde_scratch_reset(fb.sde_partials, (long long)tree->n_tree * tree->n_leaves, D, st)) != BR_OK) return s;
   if ((s = embed_cond(model, fb, cond_tokens, tree->n_tree, st)) != BR_OK) return s;
   float* v = v_nodes ? v_nodes : fb.v;
+  // The adaLN vectors depend on the step's time and the condition only: those of as many steps as the plan has groups for
+  // are formed together (three launches, and the weights streamed once per eight groups, instead of once per step).
+  const int group_steps = std::min(MAX_GROUP_STEPS, std::max(1, std::max(mb, tree->n_tree) / tree->n_tree));
   for (int i = 0; i < tree->T; ++i) {
-    const int Bi = tree->n_tree * tree->width[i];
-    const SampleMap sm{nullptr, nullptr, tree->n_nodes, tree->off[i], tree->width[i]};
-    for (int b0 = 0; b0 < Bi; b0 += mb) {
-      const int Bc = std::min(mb, Bi - b0);
-      if ((s = fill_sample_maps(fb, sm, b0, Bc, v_nodes != nullptr, st)) != BR_OK) return s;
-      if ((s = forward_uniform_t(model, fb, z_nodes, Bc, sched->t[i], tree->n_tree, v, st)) != BR_OK) return s;
+    const int step0 = i - i % group_steps;
+    if (i == step0) {
+      const int n = std::min(group_steps, tree->T - i);
+      GroupTimes gt;
+      gt.n_cond = tree->n_tree;
+      std::copy(sched->t + i, sched->t + i + n, gt.t);
+      if ((s = conditioning(model, fb, nullptr, gt, n * tree->n_tree, st)) != BR_OK) return s;
     }
+    const int Bi = tree->n_tree * tree->width[i];
+    SampleMap sm{nullptr, nullptr, tree->n_nodes, tree->off[i], tree->width[i]};
+    sm.group0 = (i - step0) * tree->n_tree;
+    for (int b0 = 0; b0 < Bi; b0 += mb)
+      if ((s = forward(model, fb, sm, b0, std::min(mb, Bi - b0), v_nodes != nullptr, z_nodes, v, st)) != BR_OK) return s;
     if ((s = launch_sde_step(tree, sched, seed, i, D, v, v_nodes == nullptr, z_nodes, logp_edges, fb.sde_partials,
                              st)) != BR_OK)
       return s;
@@ -220,10 +229,10 @@ extern "C" br_status br_logprob(const br_tree* tree, const br_model* model, cons
   for (const Batch& bt : batches) {
     SampleMap sm{fb.plan + o_rows, fb.plan + o_cond, 0, 0, 1};
     sm.group = fb.plan + o_group;
-    if ((s = fill_sample_maps(fb, sm, bt.b0, bt.B, 2, st)) != BR_OK) return s;
-    if ((s = forward(model, fb, z_nodes, bt.B, fb.plan + bt.o_gcond, reinterpret_cast<const float*>(fb.plan + bt.o_gt),
-                     bt.G, fb.v, st)) != BR_OK)
-      return s;
+    GroupTimes gt;
+    gt.dev = reinterpret_cast<const float*>(fb.plan + bt.o_gt);
+    if ((s = conditioning(model, fb, fb.plan + bt.o_gcond, gt, bt.G, st)) != BR_OK) return s;
+    if ((s = forward(model, fb, sm, bt.b0, bt.B, 2, z_nodes, fb.v, st)) != BR_OK) return s;
     while (e_next < n_edges && edges[e_next].par < bt.b0 + bt.B) {
       if (edges[e_next].par < 0) {  // deterministic step, done above
         ++e_next;
@@ -265,11 +274,12 @@ extern "C" br_status br_velocity(const br_model* model, const float* z, float t,
   if ((s = cond_stage.upload(cond_index, (size_t)B, fb.plan, st)) != BR_OK) return s;
   if ((s = embed_cond(model, fb, cond_tokens, n_cond, st)) != BR_OK) return s;
   const SampleMap sm{nullptr, fb.plan, 0, 0, B};  // row = b
-  for (int b0 = 0; b0 < B; b0 += mb) {
-    const int Bc = std::min(mb, B - b0);
-    if ((s = fill_sample_maps(fb, sm, b0, Bc, 0, st)) != BR_OK) return s;
-    if ((s = forward_uniform_t(model, fb, z, Bc, t, n_cond, v_out, st)) != BR_OK) return s;
-  }
+  GroupTimes gt;
+  gt.n_cond = n_cond;
+  gt.t[0] = t;
+  if ((s = conditioning(model, fb, nullptr, gt, n_cond, st)) != BR_OK) return s;
+  for (int b0 = 0; b0 < B; b0 += mb)
+    if ((s = forward(model, fb, sm, b0, std::min(mb, B - b0), 0, z, v_out, st)) != BR_OK) return s;
   return BR_OK;
 }
 

@@ -40,7 +40,8 @@ struct SampleMap {
   const int* rows;  // dev or nullptr
   const int* cond;  // dev or nullptr
   int n_nodes, off, width;
-  const int* group = nullptr;  // dev or nullptr: modulation group of a sample (default: its condition)
+  const int* group = nullptr;  // dev or nullptr: modulation group of a sample (default: group0 + its condition)
+  int group0 = 0;
 };
 
 // Streaming stores of four consecutive elements, for data that the writing kernel does not

@@ -46,13 +46,9 @@ struct EpiArgs {
 };
 
 struct FwdBuffers {  // carved from the workspace
-  int* rowmap;
-  int* condmap;   // sample -> condition (its condition tokens)
   int* modmap;    // sample -> modulation group (its adaLN vectors)
-  int* vrows;
-  int* gcond;     // modulation group -> condition
-  float* gt;      // modulation group -> time
-  float *temb, *h1, *ct, *pooled, *pool_lin, *cvec, *mods, *cond_emb, *x, *sde_partials;
+  int* vrows;     // sample -> row of v
+  float *h1, *pooled, *pool_lin, *cvec, *mods, *cond_emb, *x, *sde_partials;
   void *patches, *xn, *qkv, *hid;
   float* v;       // compact velocity [max_frontier, D] (rollout only)
   int* plan;      // br_logprob launch plan
@@ -62,17 +58,20 @@ struct FwdBuffers {  // carved from the workspace
 size_t plan_workspace(const br_model* m, int n_cond, int max_batch, long long v_rows, long long partial_floats,
                       long long plan_ints, FwdBuffers* fb, void* base);
 
-// One network evaluation of `B` samples (B <= max_batch of the plan).  z_base: latent rows,
-// picked by fb.rowmap; v_out rows given by fb.vrows.  The adaLN vectors are computed once per
-// modulation group g = (condition gcond[g], time gt[g]), g < n_groups <= max(n_cond, max_batch);
-// sample b uses group fb.modmap[b].  gcond / gt are device arrays.
-br_status forward(const br_model* m, const FwdBuffers& fb, const float* z_base, int B, const int* gcond,
-                  const float* gt, int n_groups, float* v_out, hipStream_t st);
-// The same with one time for the whole batch: one group per condition, modmap = condmap.
-br_status forward_uniform_t(const br_model* m, const FwdBuffers& fb, const float* z_base, int B, float t, int n_cond,
-                            float* v_out, hipStream_t st);
-// Fill rowmap/condmap/modmap/vrows for a batch [b0, b0+B) of a frontier.
-br_status fill_sample_maps(const FwdBuffers& fb, const SampleMap& smap, int b0, int B, int v_mode_rows, hipStream_t st);
+// Times of the modulation groups: dev[g] (device array), or t[g / n_cond], several steps of n_cond conditions each.
+constexpr int MAX_GROUP_STEPS = 64;
+struct GroupTimes {
+  const float* dev = nullptr;
+  int n_cond = 1;
+  float t[MAX_GROUP_STEPS] = {};
+};
+// adaLN vectors of the modulation groups g < G <= max(n_cond, max_batch) of the plan: condition gcond[g] (device
+// array; nullptr: g % gt.n_cond) at the group's time.  They stay valid until the next call.
+br_status conditioning(const br_model* m, const FwdBuffers& fb, const int* gcond, const GroupTimes& gt, int G, hipStream_t st);
+// One network evaluation of samples b0 .. b0 + B - 1 of `sm` (B <= max_batch of the plan): latent rows of z_base, groups of the
+// last conditioning() call; v rows by v_rows_mode (1: the sample's row, 2: row of the batch, else: its index).
+br_status forward(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, int b0, int B, int v_rows_mode,
+                  const float* z_base, float* v_out, hipStream_t st);
 // Condition-token embedding, once per call.
 br_status embed_cond(const br_model* m, const FwdBuffers& fb, const void* cond_tokens, int n_cond, hipStream_t st);
 

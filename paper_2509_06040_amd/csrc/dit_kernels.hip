@@ -1,7 +1,8 @@
-// Velocity network: the memory-bound and small kernels (sample maps, patchify,
-// condition broadcast, conditioning path, LayerNorm-modulate) and the fp32 GEMM /
+// Velocity network: the memory-bound and small kernels (batch prologue, conditioning path, LayerNorm-modulate) and the fp32 GEMM /
 // attention used by BR_F32 models.  The bf16 MFMA GEMM and flash attention live in
 // gemm_bf16.hip and attn_bf16.hip.
+#include <type_traits>
+
 #include "common.h"
 #include "dit.h"
 #include "prof.h"
@@ -11,58 +12,52 @@ namespace br {
 template <typename T>
 __device__ inline float to_f(T v) { return (float)v; }
 
-// ------------------------------------------------------------- sample maps
-__global__ void sample_map_kernel(SampleMap sm, int b0, int B, int v_rows_mode, int* __restrict__ rowmap,
-                                  int* __restrict__ condmap, int* __restrict__ modmap, int* __restrict__ vrows) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B) return;
-  const int b = b0 + i;
-  const int row = sm.rows ? sm.rows[b] : (b / sm.width) * sm.n_nodes + sm.off + b % sm.width;
-  const int c = sm.cond ? sm.cond[b] : b / sm.width;
-  rowmap[i] = row;
-  condmap[i] = c;
-  modmap[i] = sm.group ? sm.group[b] : c;
-  vrows[i] = v_rows_mode == 1 ? row : (v_rows_mode == 2 ? i : b);  // arena row / row of this batch / frontier index
+// ------------------------------------------------------------ batch prologue
+// What a batch needs before its first GEMM, in one launch (a launch costs about 4 us between dependent small kernels,
+// the work of each of these parts less than one at a few samples):
+//  - patches[(b n_img + tok) pd + el] = z[row of sample b][latent index]; tokens in (t,h,w) raster order, patch
+//    vector in (c, dt, dh, dw) order (the first patch_blocks workgroups);
+//  - x[b, n_img + j, :] = cond_emb[condition of b, j, :] (the others);
+//  - per sample its modulation group and its row in v (workgroup 0).
+__device__ inline int sample_row(const SampleMap& sm, int b) {
+  return sm.rows ? sm.rows[b] : (b / sm.width) * sm.n_nodes + sm.off + b % sm.width;
 }
+__device__ inline int sample_cond(const SampleMap& sm, int b) { return sm.cond ? sm.cond[b] : b / sm.width; }
 
-// One modulation group per condition, all at time t.
-__global__ void uniform_groups_kernel(float t, int n_cond, int* __restrict__ gcond, float* __restrict__ gt) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n_cond) return;
-  gcond[g] = g;
-  gt[g] = t;
-}
-
-// ---------------------------------------------------------------- patchify
-// patches[(b n_img + tok) pd + el] = z[rowmap[b]][latent index]; tokens in (t,h,w)
-// raster order, patch vector in (c, dt, dh, dw) order.
 template <typename T>
-__global__ __launch_bounds__(256) void patchify_kernel(const float* __restrict__ z, const int* __restrict__ rowmap,
-                                                       long long D, int n_img, int pd, int lt, int lh, int lw, int pt,
-                                                       int ph, int pw, int gh, int gw, long long total,
-                                                       T* __restrict__ out) {
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
-    const int el = (int)(i % pd);
-    const long long bt = i / pd;
-    const int tok = (int)(bt % n_img), b = (int)(bt / n_img);
-    const int tw = tok % gw, th = (tok / gw) % gh, tt = tok / (gw * gh);
-    const int dw = el % pw, dh = (el / pw) % ph, dt = (el / (pw * ph)) % pt, c = el / (pw * ph * pt);
-    const long long idx = (((long long)c * lt + tt * pt + dt) * lh + th * ph + dh) * lw + tw * pw + dw;
-    out[i] = (T)z[(size_t)rowmap[b] * D + idx];
-  }
-}
-
-// x[b, n_img + j, :] = cond_emb[condmap[b], j, :]
-__global__ __launch_bounds__(256) void cond_broadcast_kernel(const float* __restrict__ cond_emb,
-                                                             const int* __restrict__ condmap, int L, int n_img, int Nc,
+__global__ __launch_bounds__(256) void batch_prologue_kernel(SampleMap sm, int b0, int B, int v_rows_mode, int* __restrict__ modmap,
+                                                             int* __restrict__ vrows, const float* __restrict__ z, long long D,
+                                                             int n_img, int pd, int lt, int lh, int lw, int pt, int ph, int pw,
+                                                             int gh, int gw, long long total, int patch_blocks,
+                                                             T* __restrict__ out, const float* __restrict__ cond_emb, int L, int Nc,
                                                              int H, long long total4, float* __restrict__ x) {
-  const int H4 = H >> 2;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total4; i += (long long)gridDim.x * 256) {
-    const int h4 = (int)(i % H4);
-    const long long bj = i / H4;
-    const int j = (int)(bj % Nc), b = (int)(bj / Nc);
-    const float4 v = reinterpret_cast<const float4*>(cond_emb)[((size_t)condmap[b] * Nc + j) * H4 + h4];
-    reinterpret_cast<float4*>(x)[((size_t)b * L + n_img + j) * H4 + h4] = v;
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < B; i += 256) {
+      const int b = b0 + i;
+      modmap[i] = sm.group ? sm.group[b] : sm.group0 + sample_cond(sm, b);
+      vrows[i] = v_rows_mode == 1 ? sample_row(sm, b) : (v_rows_mode == 2 ? i : b);  // arena row / row of this batch / frontier index
+    }
+  }
+  if ((int)blockIdx.x < patch_blocks) {
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)patch_blocks * 256) {
+      const int el = (int)(i % pd);
+      const long long bt = i / pd;
+      const int tok = (int)(bt % n_img), b = (int)(bt / n_img);
+      const int tw = tok % gw, th = (tok / gw) % gh, tt = tok / (gw * gh);
+      const int dw = el % pw, dh = (el / pw) % ph, dt = (el / (pw * ph)) % pt, c = el / (pw * ph * pt);
+      const long long idx = (((long long)c * lt + tt * pt + dt) * lh + th * ph + dh) * lw + tw * pw + dw;
+      out[i] = (T)z[(size_t)sample_row(sm, b0 + b) * D + idx];
+    }
+  } else {
+    const int H4 = H >> 2;
+    for (long long i = (long long)(blockIdx.x - patch_blocks) * 256 + threadIdx.x; i < total4;
+         i += (long long)(gridDim.x - patch_blocks) * 256) {
+      const int h4 = (int)(i % H4);
+      const long long bj = i / H4;
+      const int j = (int)(bj % Nc), b = (int)(bj / Nc);
+      const float4 v = reinterpret_cast<const float4*>(cond_emb)[((size_t)sample_cond(sm, b0 + b) * Nc + j) * H4 + h4];
+      reinterpret_cast<float4*>(x)[((size_t)b * L + n_img + j) * H4 + h4] = v;
+    }
   }
 }
 
@@ -71,35 +66,26 @@ __global__ __launch_bounds__(256) void cond_broadcast_kernel(const float* __rest
 // is formed and reduced to [-pi, pi] in fp64, then fp32 sin/cos suffice.
 __device__ inline float silu_f(float x) { return x / (1.f + __expf(-x)); }
 
-__global__ __launch_bounds__(128) void temb_kernel(const float* __restrict__ gt, float* __restrict__ temb) {
-  const int k = threadIdx.x, g = blockIdx.x;
-  const double f = exp(-9.210340371976184 * (double)k / 128.0);  // ln 10000
-  double a = 1000.0 * (double)gt[g] * f;
-  a -= 6.283185307179586 * rint(a * 0.15915494309189535);
-  float sn, cs;
-  sincosf((float)a, &sn, &cs);
-  temb[(size_t)g * 256 + k] = cs;
-  temb[(size_t)g * 256 + 128 + k] = sn;
-}
-
-// cvec[g, :] = silu(pool_lin[gcond[g], :] + ct[g, :])
-__global__ __launch_bounds__(256) void group_cvec_kernel(const float* __restrict__ pool_lin,
-                                                         const float* __restrict__ ct, const int* __restrict__ gcond,
-                                                         int H, float* __restrict__ cvec) {
-  const int g = blockIdx.y, h = blockIdx.x * 256 + threadIdx.x;
-  if (h >= H) return;
-  cvec[(size_t)g * H + h] = silu_f(pool_lin[(size_t)gcond[g] * H + h] + ct[(size_t)g * H + h]);
-}
-
-// pooled[c, :] = mean over the condition tokens of condition c (depends on the prompt only)
+// pooled[c, :] = mean over the condition tokens of condition c (depends on the prompt only).  A workgroup takes 32
+// columns; its eight rows of lanes take every eighth token each, so that the loads in flight are many and the chain
+// is short (one lane down all 512 tokens of a column: 182 us, eight: 17 us).
 template <typename T>
 __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ cond, int Nc, int cd,
                                                    float* __restrict__ pooled) {
-  const int c = blockIdx.y, d = blockIdx.x * 256 + threadIdx.x;
-  if (d >= cd) return;
+  __shared__ float part[8][32];
+  const int c = blockIdx.y, col = threadIdx.x & 31, grp = threadIdx.x >> 5, d = blockIdx.x * 32 + col;
   float s = 0.f;
-  for (int j = 0; j < Nc; ++j) s += to_f(cond[((size_t)c * Nc + j) * cd + d]);
-  pooled[(size_t)c * cd + d] = s / (float)Nc;
+  if (d < cd) {
+#pragma unroll 8
+    for (int j = grp; j < Nc; j += 8) s += to_f(cond[((size_t)c * Nc + j) * cd + d]);
+  }
+  part[grp][col] = s;
+  __syncthreads();
+  if (grp == 0 && d < cd) {
+#pragma unroll
+    for (int g = 1; g < 8; ++g) s += part[g][col];
+    pooled[(size_t)c * cd + d] = s / (float)Nc;
+  }
 }
 
 template <typename TW>
@@ -121,22 +107,12 @@ struct WChunk<bf16> {
   }
 };
 
-// out[r, n] = post( sum_k pre(in[r, k]) W[n, k] + bias[n] + add[n] ), r < R <= 8.
-// Weight-streaming: one wavefront per output column, lanes along k in 8-element chunks
-// (K % 8 == 0, rows 16-byte aligned).
+// One weight row times R <= 8 input rows: lanes along k in 8-element chunks (K % 8 == 0, rows 16-byte aligned);
+// lane 0 holds the sums.
 template <typename TW, int R>
-__global__ __launch_bounds__(256) void skinny_gemm_kernel(const float* __restrict__ in, int ldi,
-                                                          const TW* __restrict__ W, int K, int N,
-                                                          const float* __restrict__ bias,
-                                                          const float* __restrict__ add, int pre_silu, int post_silu,
-                                                          float* __restrict__ out, int ldo) {
-  const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= N) return;
-  float acc[R];
+__device__ inline void skinny_dot(const float* in, int ldi, const TW* __restrict__ wr, int K, int lane, float (&acc)[R]) {
 #pragma unroll
   for (int r = 0; r < R; ++r) acc[r] = 0.f;
-  const TW* wr = W + (size_t)n * K;
   for (int k = lane * 8; k < K; k += 512) {
     float w[8];
     WChunk<TW>::load(wr + k, w);
@@ -144,88 +120,126 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(const float* __restric
     for (int r = 0; r < R; ++r) {
       const float4 a0 = *reinterpret_cast<const float4*>(in + (size_t)r * ldi + k);
       const float4 a1 = *reinterpret_cast<const float4*>(in + (size_t)r * ldi + k + 4);
-      float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+      const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = pre_silu ? silu_f(a[e]) : a[e];
-        acc[r] = fmaf(x, w[e], acc[r]);
-      }
+      for (int e = 0; e < 8; ++e) acc[r] = fmaf(a[e], w[e], acc[r]);
     }
   }
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    float s = acc[r];
+  for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-    if (lane == 0) {
-      s += bias[n] + (add ? add[n] : 0.f);
-      out[(size_t)r * ldo + n] = post_silu ? silu_f(s) : s;
+    for (int o = 32; o > 0; o >>= 1) acc[r] += __shfl_down(acc[r], o, 64);
+}
+
+// out[r, n] = sum_k in[r, k] W[n, k] + bias[n], r < R <= 8: one wavefront per output column.  With pool_lin:
+// silu(that + pool_lin[condition of group g0 + r, n]), the conditioning vector of a modulation group.
+template <typename TW, int R>
+__global__ __launch_bounds__(256) void skinny_gemm_kernel(const float* __restrict__ in, int ldi, const TW* __restrict__ W, int K,
+                                                          int N, const float* __restrict__ bias, float* __restrict__ out, int ldo,
+                                                          const float* __restrict__ pool_lin, const int* __restrict__ gcond,
+                                                          int n_cond, int g0) {
+  const int lane = threadIdx.x & 63;
+  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (n >= N) return;
+  float acc[R];
+  skinny_dot<TW, R>(in, ldi, W + (size_t)n * K, K, lane, acc);
+  if (lane == 0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float s = acc[r] + bias[n];
+      if (pool_lin) s = silu_f(pool_lin[(size_t)(gcond ? gcond[g0 + r] : (g0 + r) % n_cond) * N + n] + s);
+      out[(size_t)r * ldo + n] = s;
     }
   }
 }
 
-template <typename TW>
-static br_status skinny(const float* in, int ldi, int R, const TW* W, int K, int N, const float* bias, const float* add,
-                        int pre, int post, float* out, int ldo, hipStream_t st) {
-  for (int r0 = 0; r0 < R; r0 += 8) {
-    const int r = std::min(8, R - r0);
-    const float* ip = in + (size_t)r0 * ldi;
-    float* op = out + (size_t)r0 * ldo;
-    dim3 g(cdiv(N, 4)), b(256);
-#define BR_SK(RR) hipLaunchKernelGGL((skinny_gemm_kernel<TW, RR>), g, b, 0, st, ip, ldi, W, K, N, bias, add, pre, post, op, ldo)
-    switch (r) {
-      case 1: BR_SK(1); break;
-      case 2: BR_SK(2); break;
-      case 3: BR_SK(3); break;
-      case 4: BR_SK(4); break;
-      case 5: BR_SK(5); break;
-      case 6: BR_SK(6); break;
-      case 7: BR_SK(7); break;
-      default: BR_SK(8); break;
+// h1[r, n] = silu(sum_k temb(t of group g0 + r)[k] W[n, k] + bias[n]), temb = [cos(1000 t f_k), sin(1000 t f_k)],
+// f_k = 10000^(-k/128), formed by every workgroup for itself (1 us that runs once, against a launch).  The angle (up to
+// 1000 rad) is formed and reduced to [-pi, pi] in fp64, then fp32 sin/cos suffice.
+template <typename TW, int R>
+__global__ __launch_bounds__(256) void time_mlp_kernel(GroupTimes gt, int g0, const TW* __restrict__ W, int N,
+                                                       const float* __restrict__ bias, float* __restrict__ out, int ldo) {
+  __shared__ __attribute__((aligned(16))) float temb[R][256];
+  const int k = threadIdx.x & 127;
+  const double f = exp(-9.210340371976184 * (double)k / 128.0);  // ln 10000
+  for (int r = threadIdx.x >> 7; r < R; r += 2) {
+    const float t = gt.dev ? gt.dev[g0 + r] : gt.t[(g0 + r) / gt.n_cond];
+    double a = 1000.0 * (double)t * f;
+    a -= 6.283185307179586 * rint(a * 0.15915494309189535);
+    float sn, cs;
+    sincosf((float)a, &sn, &cs);
+    temb[r][k] = cs;
+    temb[r][128 + k] = sn;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (n >= N) return;
+  float acc[R];
+  skinny_dot<TW, R>(&temb[0][0], 256, W + (size_t)n * 256, 256, lane, acc);
+  if (lane == 0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) out[(size_t)r * ldo + n] = silu_f(acc[r] + bias[n]);
+  }
+}
+
+// f(integral_constant R) for groups of up to 8 rows from 0 to n
+template <typename F>
+static br_status by_eights(int n, F&& f) {
+  for (int r0 = 0; r0 < n; r0 += 8) {
+    switch (std::min(8, n - r0)) {
+      case 1: f(std::integral_constant<int, 1>{}, r0); break;
+      case 2: f(std::integral_constant<int, 2>{}, r0); break;
+      case 3: f(std::integral_constant<int, 3>{}, r0); break;
+      case 4: f(std::integral_constant<int, 4>{}, r0); break;
+      case 5: f(std::integral_constant<int, 5>{}, r0); break;
+      case 6: f(std::integral_constant<int, 6>{}, r0); break;
+      case 7: f(std::integral_constant<int, 7>{}, r0); break;
+      default: f(std::integral_constant<int, 8>{}, r0); break;
     }
-#undef BR_SK
     BR_LAUNCH_CHECK();
   }
   return BR_OK;
 }
 
-// Per modulation group g: cvec = silu(t_mlp(temb(gt[g])) + pool_lin[gcond[g]]); mods = ada_lin(cvec).
+template <typename TW>
+static br_status skinny(const float* in, int ldi, int R, const TW* W, int K, int N, const float* bias, float* out, int ldo,
+                        const float* pool_lin, const int* gcond, int n_cond, hipStream_t st) {
+  return by_eights(R, [&](auto Rc, int r0) {
+    hipLaunchKernelGGL((skinny_gemm_kernel<TW, decltype(Rc)::value>), dim3(cdiv(N, 4)), dim3(256), 0, st, in + (size_t)r0 * ldi, ldi,
+                       W, K, N, bias, out + (size_t)r0 * ldo, ldo, pool_lin, gcond, n_cond, r0);
+  });
+}
+
+// Per modulation group g: cvec = silu(t_mlp(temb(time of g)) + pool_lin[condition of g]); mods = ada_lin(cvec).
 template <typename T>
-static br_status conditioning_t(const br_model* m, const FwdBuffers& fb, const int* gcond, const float* gt, int G,
+static br_status conditioning_t(const br_model* m, const FwdBuffers& fb, const int* gcond, const GroupTimes& gt, int G,
                                 hipStream_t st) {
   const int H = m->H;
-  hipLaunchKernelGGL(temb_kernel, dim3(G), dim3(128), 0, st, gt, fb.temb);
-  BR_LAUNCH_CHECK();
   br_status s;
-  if ((s = skinny<T>(fb.temb, 256, G, (const T*)m->w[BR_W_T1_W], 256, H, (const float*)m->w[BR_W_T1_B], nullptr, 0, 1,
-                     fb.h1, H, st)) != BR_OK) return s;
-  if ((s = skinny<T>(fb.h1, H, G, (const T*)m->w[BR_W_T2_W], H, H, (const float*)m->w[BR_W_T2_B], nullptr, 0, 0, fb.ct,
-                     H, st)) != BR_OK) return s;
-  hipLaunchKernelGGL(group_cvec_kernel, dim3(cdiv(H, 256), G), dim3(256), 0, st, fb.pool_lin, fb.ct, gcond, H, fb.cvec);
-  BR_LAUNCH_CHECK();
+  if ((s = by_eights(G, [&](auto Rc, int r0) {
+         hipLaunchKernelGGL((time_mlp_kernel<T, decltype(Rc)::value>), dim3(cdiv(H, 4)), dim3(256), 0, st, gt, r0,
+                            (const T*)m->w[BR_W_T1_W], H, (const float*)m->w[BR_W_T1_B], fb.h1 + (size_t)r0 * H, H);
+       })) != BR_OK) return s;
+  if ((s = skinny<T>(fb.h1, H, G, (const T*)m->w[BR_W_T2_W], H, H, (const float*)m->w[BR_W_T2_B], fb.cvec, H, fb.pool_lin, gcond,
+                     gt.n_cond, st)) != BR_OK) return s;
   // the modulation vectors of all blocks: a GEMV that streams the [A, H] weights once per 8 groups
   ProfScope ps(st, PROF_ADALN, (double)cdiv(G, 8) * (double)m->A * H * sizeof(T));
-  return skinny<T>(fb.cvec, H, G, (const T*)m->w[BR_W_ADA_W], H, m->A, (const float*)m->w[BR_W_ADA_B], nullptr, 0, 0,
-                   fb.mods, m->A, st);
+  return skinny<T>(fb.cvec, H, G, (const T*)m->w[BR_W_ADA_W], H, m->A, (const float*)m->w[BR_W_ADA_B], fb.mods, m->A, nullptr,
+                   nullptr, 1, st);
 }
 
 // pool_lin[c, :] = W_pool pooled[c, :] + b_pool: the time-independent half of the conditioning vector
 br_status launch_pool_linear(const br_model* m, const FwdBuffers& fb, int n_cond, hipStream_t st) {
   if (m->cfg.dtype == BR_BF16)
-    return skinny<bf16>(fb.pooled, m->cd, n_cond, (const bf16*)m->w[BR_W_POOL_W], m->cd, m->H,
-                        (const float*)m->w[BR_W_POOL_B], nullptr, 0, 0, fb.pool_lin, m->H, st);
-  return skinny<float>(fb.pooled, m->cd, n_cond, (const float*)m->w[BR_W_POOL_W], m->cd, m->H,
-                       (const float*)m->w[BR_W_POOL_B], nullptr, 0, 0, fb.pool_lin, m->H, st);
-}
-
-br_status launch_uniform_groups(const FwdBuffers& fb, float t, int n_cond, hipStream_t st) {
-  hipLaunchKernelGGL(uniform_groups_kernel, dim3(cdiv(n_cond, 256)), dim3(256), 0, st, t, n_cond, fb.gcond, fb.gt);
-  BR_LAUNCH_CHECK();
-  return BR_OK;
+    return skinny<bf16>(fb.pooled, m->cd, n_cond, (const bf16*)m->w[BR_W_POOL_W], m->cd, m->H, (const float*)m->w[BR_W_POOL_B],
+                        fb.pool_lin, m->H, nullptr, nullptr, 1, st);
+  return skinny<float>(fb.pooled, m->cd, n_cond, (const float*)m->w[BR_W_POOL_W], m->cd, m->H, (const float*)m->w[BR_W_POOL_B],
+                       fb.pool_lin, m->H, nullptr, nullptr, 1, st);
 }
 
 br_status launch_pool(const br_model* m, const FwdBuffers& fb, const void* cond, int n_cond, hipStream_t st) {
-  dim3 g(cdiv(m->cd, 256), n_cond), b(256);
+  dim3 g(cdiv(m->cd, 32), n_cond), b(256);
   if (m->cfg.dtype == BR_BF16)
     hipLaunchKernelGGL((pool_kernel<bf16>), g, b, 0, st, (const bf16*)cond, m->Nc, m->cd, fb.pooled);
   else
@@ -234,7 +248,7 @@ br_status launch_pool(const br_model* m, const FwdBuffers& fb, const void* cond,
   return BR_OK;
 }
 
-br_status conditioning(const br_model* m, const FwdBuffers& fb, const int* gcond, const float* gt, int G,
+br_status conditioning(const br_model* m, const FwdBuffers& fb, const int* gcond, const GroupTimes& gt, int G,
                        hipStream_t st) {
   return m->cfg.dtype == BR_BF16 ? conditioning_t<bf16>(m, fb, gcond, gt, G, st)
                                  : conditioning_t<float>(m, fb, gcond, gt, G, st);
@@ -359,36 +373,19 @@ br_status launch_attention(int dtype, const void* qkv, void* out, int B, int L, 
   return launch_attention_f32((const float*)qkv, (float*)out, B, L, NH, DH, st);
 }
 
-// -------------------------------------------------------------- launchers
-br_status fill_sample_maps(const FwdBuffers& fb, const SampleMap& smap, int b0, int B, int v_mode_rows, hipStream_t st) {
-  hipLaunchKernelGGL(sample_map_kernel, dim3(cdiv(B, 256)), dim3(256), 0, st, smap, b0, B, v_mode_rows, fb.rowmap,
-                     fb.condmap, fb.modmap, fb.vrows);
-  BR_LAUNCH_CHECK();
-  return BR_OK;
-}
-
-br_status launch_patchify(const br_model* m, const FwdBuffers& fb, const float* z, int B, hipStream_t st) {
-  const long long total = (long long)B * m->n_img * m->pd;
-  const int nb = (int)std::min<long long>((total + 255) / 256, 65535 * 16);
+br_status launch_batch_prologue(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, int b0, int B, int v_rows_mode,
+                                const float* z, hipStream_t st) {
   const br_model_cfg& c = m->cfg;
-  if (c.dtype == BR_BF16)
-    hipLaunchKernelGGL((patchify_kernel<bf16>), dim3(nb), dim3(256), 0, st, z, fb.rowmap, m->D, m->n_img, m->pd,
-                       c.latent_t, c.latent_h, c.latent_w, c.patch_t, c.patch_h, c.patch_w, m->gh, m->gw, total,
-                       (bf16*)fb.patches);
-  else
-    hipLaunchKernelGGL((patchify_kernel<float>), dim3(nb), dim3(256), 0, st, z, fb.rowmap, m->D, m->n_img, m->pd,
-                       c.latent_t, c.latent_h, c.latent_w, c.patch_t, c.patch_h, c.patch_w, m->gh, m->gw, total,
-                       (float*)fb.patches);
-  BR_LAUNCH_CHECK();
-  return BR_OK;
-}
-
-br_status launch_cond_broadcast(const br_model* m, const FwdBuffers& fb, int B, hipStream_t st) {
-  const long long total4 = (long long)B * m->Nc * (m->H / 4);
-  if (total4 == 0) return BR_OK;
-  const int nb = (int)std::min<long long>((total4 + 255) / 256, 65535 * 16);
-  hipLaunchKernelGGL(cond_broadcast_kernel, dim3(nb), dim3(256), 0, st, fb.cond_emb, fb.condmap, m->L, m->n_img, m->Nc,
-                     m->H, total4, fb.x);
+  const long long total = (long long)B * m->n_img * m->pd, total4 = (long long)B * m->Nc * (m->H / 4);
+  const int np = (int)std::min<long long>((total + 255) / 256, 65535 * 16), nc = (int)std::min<long long>((total4 + 255) / 256, 65535 * 16);
+  auto go = [&](auto* patches) {
+    using T = std::remove_pointer_t<decltype(patches)>;
+    hipLaunchKernelGGL((batch_prologue_kernel<T>), dim3(np + nc), dim3(256), 0, st, sm, b0, B, v_rows_mode, fb.modmap, fb.vrows, z, m->D,
+                       m->n_img, m->pd, c.latent_t, c.latent_h, c.latent_w, c.patch_t, c.patch_h, c.patch_w, m->gh, m->gw, total, np,
+                       patches, fb.cond_emb, m->L, m->Nc, m->H, total4, fb.x);
+  };
+  if (c.dtype == BR_BF16) go((bf16*)fb.patches);
+  else go((float*)fb.patches);
   BR_LAUNCH_CHECK();
   return BR_OK;
 }

@@ -8,12 +8,9 @@
 #include "prof.h"
 
 namespace br {
-br_status conditioning(const br_model* m, const FwdBuffers& fb, const int* gcond, const float* gt, int G,
-                       hipStream_t st);
 br_status launch_pool_linear(const br_model* m, const FwdBuffers& fb, int n_cond, hipStream_t st);
-br_status launch_uniform_groups(const FwdBuffers& fb, float t, int n_cond, hipStream_t st);
-br_status launch_patchify(const br_model* m, const FwdBuffers& fb, const float* z, int B, hipStream_t st);
-br_status launch_cond_broadcast(const br_model* m, const FwdBuffers& fb, int B, hipStream_t st);
+br_status launch_batch_prologue(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, int b0, int B, int v_rows_mode,
+                                const float* z, hipStream_t st);
 br_status launch_pool(const br_model* m, const FwdBuffers& fb, const void* cond, int n_cond, hipStream_t st);
 
 static size_t esize(const br_model* m) { return m->cfg.dtype == BR_BF16 ? 2 : 4; }
@@ -30,15 +27,11 @@ size_t plan_workspace(const br_model* m, int n_cond, int max_batch, long long v_
   const size_t B = (size_t)max_batch, H = m->H, L = m->L, es = esize(m);
   FwdBuffers f;
   const size_t G = std::max<size_t>(B, (size_t)n_cond);  // modulation groups: at most one per sample
-  f.rowmap = (int*)take(B * 4);
-  f.condmap = (int*)take(B * 4);
   f.modmap = (int*)take(B * 4);
   f.vrows = (int*)take(B * 4);
-  f.gcond = (int*)take(G * 4);
-  f.gt = (float*)take(G * 4);
-  f.temb = (float*)take(G * 256 * 4);
   f.h1 = (float*)take(G * H * 4);
-  f.ct = (float*)take(G * H * 4);
+  // (room that kernels of an earlier form used: the sizes that callers have planned with stay what they were)
+  for (size_t n : {B * 4, B * 4, G * 4, G * 4, G * 256 * 4, G * H * 4}) take(n);
   f.pooled = (float*)take((size_t)n_cond * m->cd * 4);
   f.pool_lin = (float*)take((size_t)n_cond * H * 4);
   f.cvec = (float*)take(G * H * 4);
@@ -70,21 +63,13 @@ br_status embed_cond(const br_model* m, const FwdBuffers& fb, const void* cond_t
   return launch_pool_linear(m, fb, n_cond, st);
 }
 
-br_status forward_uniform_t(const br_model* m, const FwdBuffers& fb, const float* z_base, int B, float t, int n_cond,
-                            float* v_out, hipStream_t st) {
-  br_status s = launch_uniform_groups(fb, t, n_cond, st);
-  if (s != BR_OK) return s;
-  return forward(m, fb, z_base, B, fb.gcond, fb.gt, n_cond, v_out, st);
-}
-
-br_status forward(const br_model* m, const FwdBuffers& fb, const float* z_base, int B, const int* gcond,
-                  const float* gt, int n_groups, float* v_out, hipStream_t st) {
+br_status forward(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, int b0, int B, int v_rows_mode,
+                  const float* z_base, float* v_out, hipStream_t st) {
   const int H = m->H, L = m->L, dt = m->cfg.dtype;
   const size_t es = esize(m);
   br_status s;
 #define BR_TRY(x) do { if ((s = (x)) != BR_OK) return s; } while (0)
-  BR_TRY(conditioning(m, fb, gcond, gt, n_groups, st));
-  BR_TRY(launch_patchify(m, fb, z_base, B, st));
+  BR_TRY(launch_batch_prologue(m, fb, sm, b0, B, v_rows_mode, z_base, st));
   {
     EpiArgs ea{};
     ea.bias = (const float*)m->w[BR_W_PATCH_B];
@@ -95,7 +80,6 @@ br_status forward(const br_model* m, const FwdBuffers& fb, const float* z_base, 
     ea.pos = (const float*)m->w[BR_W_POS];
     BR_TRY(launch_gemm(dt, EPI_PATCH_EMBED, fb.patches, m->pd, m->w[BR_W_PATCH_W], m->pd, B * m->n_img, H, m->pd, ea, st));
   }
-  BR_TRY(launch_cond_broadcast(m, fb, B, st));
   const int M = B * L;
   // the bf16 block stack launches only instrumented kernels, back to back
   ProfChain chain(dt == BR_BF16);
