@@ -170,3 +170,49 @@ def test_tree_kernels_at_and_beyond_their_largest_trees(lib):
         with pytest.raises(br.BranchRolloutError) as e:
             call()
         assert e.value.code == -3
+
+
+@pytest.mark.parametrize("kind,latent,shift", [(br.REWARD_LINEAR, (4, 1, 1, 1), 0), (br.REWARD_TANH, (1, 1, 64, 512), 0),      # one element a thread; whole rounds of eight
+                                               (br.REWARD_LINEAR, (4, 1, 128, 256), 0), (br.REWARD_LINEAR, (4, 1, 127, 259), 0),  # 131 072: last of one launch; beyond it
+                                               (br.REWARD_VIDEO, (4, 3, 6, 7), 0), (br.REWARD_VIDEO, (2, 3, 64, 130), 0),        # planes of odd and of 16-byte multiples
+                                               (br.REWARD_VIDEO, (2, 3, 8, 10), 1)])                                           # latents that are not 16-byte aligned
+def test_leaf_rewards_at_the_edges_of_their_kernels(lib, kind, latent, shift):
+    D = int(np.prod(latent))
+    t = br.Tree(3, (0, 1), 2, n_tree=2)
+    rng = np.random.default_rng(D)
+    n = 2 * t.n_nodes
+    z = rng.standard_normal((n, D)).astype(np.float32)
+    w = rng.standard_normal(latent[1] * latent[0] if kind == br.REWARD_VIDEO else D).astype(np.float32)
+    buf = torch.zeros(n * D + shift, device=DEV)
+    zd = buf[shift:].view(n, D)
+    zd.copy_(dev(z))
+    out = torch.empty(2 * t.n_leaves, device=DEV)
+    br.leaf_reward(t, zd, kind, dev(w), 0.7, latent, out, bytes_buffer(max(256, br.reward_scratch_bytes(t, kind, latent))))
+    leaves = np.concatenate([z[c * t.n_nodes + t.off[3]: (c + 1) * t.n_nodes] for c in range(2)])
+    if kind == br.REWARD_VIDEO:
+        ref = rewards.reward_video(leaves, w.reshape(latent[1], latent[0]), *latent, lam=0.7)
+    else:
+        ref = rewards.reward_linear(leaves, w, kind == br.REWARD_TANH)
+    # fp32 products summed pairwise: below 1e-6 of the largest
+    assert np.abs(host(out) - ref).max() < 2e-6 * max(1.0, np.abs(ref).max())
+
+
+@pytest.mark.parametrize("T,splits,C", [(8, (0, 1, 2, 3, 4, 5), 16), (8, (0, 1, 2, 3, 4, 5), 17), (7, (0, 1, 2, 3, 4, 5, 6), 2), (40, (1,), 110), (40, (1,), 60)])
+def test_fusion_and_pruning_at_the_edges_of_their_kernels(lib, T, splits, C):
+    """Forests of 1024 leaves (the most of one pruning workgroup) and more, 8192 edges and more; nodes with 64 and
+    128 leaves in a tree whose pairs fit in LDS."""
+    t = br.Tree(T, splits, 2, n_tree=C)
+    o = tree.tree_build(T, splits, 2)
+    rng = np.random.default_rng(T + C)
+    r = np.tanh(rng.standard_normal(C * t.n_leaves)).astype(np.float32)
+    lp = (rng.standard_normal(C * t.n_nodes) * 0.3).astype(np.float32)
+    rb, adv = _fuse(t, r, lp, 1.0)
+    rb_ref = fusion.fuse_rewards(o, r, lp, 1.0, C)
+    assert np.abs(rb - rb_ref).max() < 1e-6
+    assert np.abs(adv - fusion.depth_advantages(o, rb_ref, C, eps=1e-8, ddof=0, a_max=5.0)).max() <= 1e-5
+    kept, nk = torch.empty(C * t.n_edges, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    mask = prune.depth_mask_seeded(T, 2, 42)
+    for mode, b in ((1, 0), (2, 1)):
+        br.prune(t, dev(r), mode, b, mask, kept, nk)
+        ref = prune.kept_edges(o, r, C, mode, b, mask)
+        assert int(host(nk)[0]) == len(ref) and np.array_equal(host(kept)[:len(ref)], ref)
