@@ -87,6 +87,17 @@ br_status launch_gemm_ksplit(int dtype, int mode, const void* A, int lda, const 
                              const EpiArgs& ea, hipStream_t st);
 br_status launch_gemm_f32(int mode, const float* A, int lda, const float* W, int ldw, int M, int N, int K,
                           const EpiArgs& ea, int variant, hipStream_t st);
+// GEMM whose A operand is LayerNorm(x[src(r), :]) (1 + scale) + shift (rows as in launch_ln_modulate), for small problems.
+struct LnArgs {
+  const float* x;
+  int rows_per_sample, L_in;
+  const float* mods;
+  int A, shift_off, scale_off;
+  const int* condmap;
+};
+bool ln_gemm_fits(int dtype, int M, int N, int K, const void* x, const void* mods, int A, int shift_off, int scale_off);
+br_status launch_ln_gemm(int dtype, int mode, const LnArgs& ln, const void* W, int M, int N, int K, const EpiArgs& ea,
+                         hipStream_t st);
 bool gemm_stream_supported(int mode, int K, size_t bytes_a, size_t bytes_w);
 br_status launch_gemm_bf16_stream(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
                                   const EpiArgs& ea, int height, int group_n, int row_block, hipStream_t st);

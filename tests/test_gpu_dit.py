@@ -279,6 +279,17 @@ def test_velocity_small_bf16_matches_oracle(lib):
             assert_velocity(cfg, got[b], ref[b], 2e-2, "small bf16 b=%d" % b)                   # stated bf16 tolerance
 
 
+@pytest.mark.parametrize("hidden,heads,dtype,B", [(48, 3, synth.F32, 1), (32, 2, synth.F32, 9), (256, 8, synth.F32, 2), (272, 17, synth.F32, 1),
+                                                  (64, 1, synth.BF16, 2), (192, 3, synth.BF16, 3), (512, 4, synth.BF16, 1), (576, 9, synth.BF16, 1)])
+def test_velocity_normalisation_inside_the_gemm(lib, hidden, heads, dtype, B):
+    """Hidden sizes of a part of a stage, of whole stages, the largest whose rows fit beside the operands (256 in fp32,
+    512 in bf16) and the next; rows that end inside a tile."""
+    cfg = synth.model_cfg(2, hidden, heads, (16, 1, 6, 10), (1, 2, 2), 5, dtype)
+    got, ref, _ = _velocity_case(cfg, min(2, B), B, 0.4, 2, 0.05)
+    for b in range(B):
+        assert_velocity(cfg, got[b], ref[b], 1e-4 if dtype == synth.F32 else 2e-2, "hidden %d b=%d" % (hidden, b))
+
+
 def test_velocity_chunked_batches_agree(lib):
     cfg = synth.WORKLOADS["tiny"]["model"]
     got, ref, (model, W, z, cond, cidx) = _velocity_case(cfg, 2, 5, 0.5, 4)
