@@ -83,7 +83,7 @@ br_status launch_attention(int dtype, const void* qkv, void* out, int B, int L, 
                            hipStream_t st);
 br_status launch_gemm_bf16(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
                            const EpiArgs& ea, int variant, hipStream_t st);
-br_status launch_gemm_ksplit(int dtype, int mode, const void* A, int lda, const void* W, int ldw, int M, int N, int K,
+br_status launch_gemm_small(int dtype, int mode, const void* A, int lda, const void* W, int ldw, int M, int N, int K,
                              const EpiArgs& ea, hipStream_t st);
 br_status launch_gemm_f32(int mode, const float* A, int lda, const float* W, int ldw, int M, int N, int K,
                           const EpiArgs& ea, int variant, hipStream_t st);

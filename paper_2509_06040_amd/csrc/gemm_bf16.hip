@@ -5,7 +5,7 @@
 //
 // This file holds the choice of the kernel and the launches of the one-tile-per-workgroup kernel (gemm_tile.h);
 // the persistent kernel for large problems is in gemm_bf16_stream.hip, the one for small ones in
-// gemm_ksplit.hip.
+// gemm_small.hip.
 #include <cmath>
 
 #include "common.h"
@@ -29,7 +29,7 @@ static br_status gemm_tile_launch(const bf16* A, int lda, const bf16* W, int ldw
 }
 
 enum {  // bits 0..3 of a variant
-  TILE_KSPLIT = 0, TILE_128_W8 = 1, TILE_64 = 2, TILE_64_128 = 3, TILE_256 = 4, TILE_128 = 5, TILE_256_128 = 6, TILE_STREAM = 7
+  TILE_32 = 0, TILE_128_W8 = 1, TILE_64 = 2, TILE_64_128 = 3, TILE_256 = 4, TILE_128 = 5, TILE_256_128 = 6, TILE_STREAM = 7
 };
 
 // The kernel for a problem size.  r = tiles of a kind per compute unit.  (The part for small problems is from 410
@@ -39,10 +39,10 @@ static int choose_tile(int M, int N, int K, bool stream_ok, int* height) {
   const double cu = device_cu_count();
   const double r32 = (double)cdiv(M, 32) * cdiv(N, 32) / cu, r64 = (double)cdiv(M, 64) * cdiv(N, 64) / cu;
   const double r128 = (double)cdiv(M, 128) * cdiv(N, 128) / cu;
-  // Up to a few 32x32 tiles a unit: the waves of a tile split K.  279 x 128 x 512 takes 3.3 us instead of
-  // the 5.6 of 64x64 tiles and the 10.7 of the 256x128 tiles used before.  A long K makes the tile's operand
-  // traffic (twice that of 64x64 tiles for the same outputs) the longer part sooner.
-  if (r32 <= (K < 1024 ? 4.0 : 3.0)) return TILE_KSPLIT;
+  // Up to a few 32x32 tiles a unit: four waves a tile.  279 x 128 x 512 takes 3.2 us instead of the 5.3 of 64x64
+  // tiles, 300 x 1024 x 4096 10.4 instead of 23.  A long K makes the tile's operand traffic (twice that of 64x64 tiles
+  // for the same outputs) the longer part sooner.
+  if (r32 <= (K < 1024 ? 4.0 : 3.0)) return TILE_32;
   // Up to one round of 64x64 tiles: two waves each, four stages of 16 KB in flight.  1101 x 1024 x 4096: 23 us
   // (34 in 128x128 tiles, 52 in 256x128).
   if (r64 <= 1.2) return TILE_64;
@@ -88,7 +88,7 @@ static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, in
   }
   ProfScope ps(st, PROF_GEMM + MODE * 8 + tile, 2.0 * M * N * K);
   switch (tile) {
-    case TILE_KSPLIT: return launch_gemm_ksplit(BR_BF16, MODE, A, lda, W, ldw, M, N, K, ea, st);
+    case TILE_32: return launch_gemm_small(BR_BF16, MODE, A, lda, W, ldw, M, N, K, ea, st);
     case TILE_128_W8: return gemm_tile_launch<128, 128, 4, 2, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
     case TILE_64: return gemm_tile_launch<64, 64, 2, 1, 4, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
     case TILE_64_128: return gemm_tile_launch<64, 128, 2, 2, 3, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);

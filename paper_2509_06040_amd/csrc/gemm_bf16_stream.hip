@@ -30,7 +30,6 @@
 namespace br {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 #define BR_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 

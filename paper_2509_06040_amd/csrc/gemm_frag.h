@@ -1,12 +1,16 @@
-// Operand fragments of the 32x32 matrix instructions: 16 bytes of k per lane.  The contraction order inside
-// a pair of 16-byte chunks (lanes 0..31 hold the first, lanes 32..63 the second) is free as long as both
-// operands use the same one, so fp32 takes its four elements one instruction at a time (k = e and 4 + e).
+// Operand fragments of the matrix instructions, read from a stage: 128 bytes of k of every row, 16-byte chunk c of row r
+// in slot c ^ ((r >> 1) & 7) of the row.
+//
+// Every kernel adds the products of an output in ascending k, so a result does not depend on the kernel that a problem size
+// selects: fp32 instructions are chains of fused multiply-adds over their k, lane group after lane group, and bf16
+// instructions of 16 and of 32 k round alike (both checked bit for bit).
 #pragma once
 #include <hip/hip_runtime.h>
 
 namespace br {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // An address that is uniform over the wave; saying so keeps it in scalar registers in every instantiation.
 __device__ inline const char* scalar_ptr(const char* p) {
@@ -15,12 +19,16 @@ __device__ inline const char* scalar_ptr(const char* p) {
   return reinterpret_cast<const char*>(((unsigned long long)hi << 32) | lo);
 }
 
+// 32x32 instructions: lanes 0..31 hold the first half of an instruction's k, lanes 32..63 the second.  The fragments of chunk
+// pair p (chunks 2p and 2p + 1) are at offset(row, lane / 32) ^ (p << 5).
 template <typename T>
 struct GemmFrag;
 template <>
 struct GemmFrag<__bf16> {
   typedef __bf16 type __attribute__((ext_vector_type(8)));
   static constexpr int STEPS = 1;  // matrix instructions per chunk pair
+  static __device__ inline int offset(int row, int lh) { return row * 128 + ((lh ^ ((row >> 1) & 7)) << 4); }
+  static __device__ inline type load(const char* p, int off) { return *reinterpret_cast<const type*>(p + off); }
   static __device__ inline f32x16 mma(const type& w, const type& a, const f32x16& c, int) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a, c, 0, 0, 0);
   }
@@ -28,10 +36,39 @@ struct GemmFrag<__bf16> {
 template <>
 struct GemmFrag<float> {
   typedef float type __attribute__((ext_vector_type(4)));
-  static constexpr int STEPS = 4;
+  static constexpr int STEPS = 4;  // k = 2 e and 2 e + 1 of the pair's eight
+  static __device__ inline int offset(int row, int lh) { return row * 128 + (((row >> 1) & 7) << 4) + lh * 4; }
+  // (two reads of two words each, 3 % of a launch more than one of a chunk, which would interleave the chunks of a pair: 0 4 1 5
+  // 2 6 3 7; exchanging those between the halves of the wave costs 8 %, four reads of one word 5)
+  static __device__ inline type load(const char* p, int off) {
+    const float* c0 = reinterpret_cast<const float*>(p + off);
+    const float* c1 = reinterpret_cast<const float*>(p + (off ^ 16));
+    return type{c0[0], c0[2], c1[0], c1[2]};
+  }
   static __device__ inline f32x16 mma(const type& w, const type& a, const f32x16& c, int e) {
     return __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], a[e], c, 0, 0, 0);
   }
+};
+
+// 16x16 instructions: fragment i of a stage for lane group g = lane / 16, at offset(row, g) ^ (i * FLIP), is chunk 4 i + g (bf16,
+// 32 k an instruction) or word g of chunk i (fp32, 4 k).
+template <typename T>
+struct GemmFrag16;
+template <>
+struct GemmFrag16<__bf16> {
+  typedef __bf16 type __attribute__((ext_vector_type(8)));
+  static constexpr int COUNT = 2, FLIP = 64;  // fragments of a stage
+  static __device__ inline int offset(int row, int g) { return row * 128 + ((g ^ ((row >> 1) & 7)) << 4); }
+  static __device__ inline f32x4 mma(const type& w, const type& a, const f32x4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, c, 0, 0, 0);
+  }
+};
+template <>
+struct GemmFrag16<float> {
+  typedef float type;
+  static constexpr int COUNT = 8, FLIP = 16;
+  static __device__ inline int offset(int row, int g) { return row * 128 + (((row >> 1) & 7) << 4) + g * 4; }
+  static __device__ inline f32x4 mma(float w, float a, const f32x4& c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(w, a, c, 0, 0, 0); }
 };
 
 }  // namespace br

@@ -78,18 +78,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_kernel(const T* __res
   }
   const char* a_tile = reinterpret_cast<const char*>(A + (size_t)m0 * lda);
   const char* w_tile = reinterpret_cast<const char*>(W + (size_t)n0 * ldw);
-  // byte offsets of this lane's operand fragments inside a stage for chunk pair 0; pair p is the same ^ (p << 5)
-  int fa_off[TM], fw_off[TN];
-#pragma unroll
-  for (int j = 0; j < TM; ++j) {
-    const int row = wm0 + j * 32 + l32;
-    fa_off[j] = row * 128 + ((lh ^ ((row >> 1) & 7)) << 4);
-  }
-#pragma unroll
-  for (int i = 0; i < TN; ++i) {
-    const int row = wn0 + i * 32 + l32;
-    fw_off[i] = SA + row * 128 + ((lh ^ ((row >> 1) & 7)) << 4);
-  }
+  // byte offsets of this lane's first operand fragments inside a stage for chunk pair 0; pair p is the same ^ (p << 5), the
+  // fragments of the other 32-row blocks are 4 KB apart
+  const int fa_off = GemmFrag<T>::offset(wm0 + l32, lh), fw_off = SA + GemmFrag<T>::offset(wn0 + l32, lh);
 
   f32x16 acc[TN][TM];
 #pragma unroll
@@ -136,9 +127,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_kernel(const T* __res
   frag fa[2][TM], fw[2][TN];
   auto read_pair = [&](const char* stage, int p, int set) {
 #pragma unroll
-    for (int j = 0; j < TM; ++j) fa[set][j] = *reinterpret_cast<const frag*>(stage + (fa_off[j] ^ (p << 5)));
+    for (int j = 0; j < TM; ++j) fa[set][j] = GemmFrag<T>::load(stage + j * 4096, fa_off ^ (p << 5));
 #pragma unroll
-    for (int i = 0; i < TN; ++i) fw[set][i] = *reinterpret_cast<const frag*>(stage + (fw_off[i] ^ (p << 5)));
+    for (int i = 0; i < TN; ++i) fw[set][i] = GemmFrag<T>::load(stage + i * 4096, fw_off ^ (p << 5));
   };
   auto mma_pair = [&](int set) {
 #pragma unroll

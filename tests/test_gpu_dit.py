@@ -302,7 +302,7 @@ def test_velocity_chunked_batches_agree(lib):
     assert e.value.code == -4
 
 
-# every form of the fp32 GEMM (128x128 and 64x128 tiles, 32x32 tiles with the waves splitting K) at tile
+# every form of the fp32 GEMM (128x128, 64x128 and 32x32 tiles) at tile
 # edges, with K of less than one stage, whole stages and a stage that ends inside a 16-byte chunk pair
 @pytest.mark.parametrize("variant", [-1, 0, 3, 5])
 @pytest.mark.parametrize("M,N,K", [(1, 4, 4), (31, 36, 12), (33, 132, 16), (64, 128, 20), (65, 124, 32), (129, 260, 144),
@@ -378,7 +378,7 @@ def test_attention_fp32_reference_moves_and_unaligned_buffers(lib):
     assert rel_l2(host(obuf)[1:].reshape(1, L, H), ref) < 1e-4
 
 
-# the bf16 forms for small and middle sizes: k-split, 64x64 and 64x128 tiles, 128x128 in eight waves; K of one
+# the bf16 forms for small and middle sizes: 32x32, 64x64 and 64x128 tiles, 128x128 in eight waves; K of one
 # stage, fewer stages than the ring or than waves, and more; ragged rows and columns
 @pytest.mark.parametrize("variant", [0, 1, 2, 3, 2 | (1 << 4), 3 | (3 << 4)])
 @pytest.mark.parametrize("M,N,K", [(1, 4, 64), (31, 64, 128), (33, 132, 192), (65, 36, 256), (127, 192, 320), (130, 260, 1088)])
@@ -401,3 +401,55 @@ def test_gemm_bf16_small_tiles(lib, variant, M, N, K):
     x = dev(x0.copy())
     br.op_gemm(br.BF16, 2, Ad, Wd, bd, x, mods=dev(mods), gate_off=0, cond=dev(cond), L=L, variant=variant)
     assert rel_l2(host(x), x0 + np.repeat(mods[cond], L, axis=0) * ref) < 2e-6
+
+
+# Every kernel of either dtype adds k in ascending order, so a result has the same bits whichever a problem size selects.
+# K of one stage, of less or more whole stages than a ring holds, and (fp32) ends inside a stage; ragged rows and columns.
+@pytest.mark.parametrize("dt,M,N,K", [(br.BF16, 93, 128, 256), (br.BF16, 1101, 260, 1024), (br.BF16, 40, 64, 3072), (br.BF16, 300, 132, 64),
+                                      (br.BF16, 70, 512, 1088), (br.F32, 33, 36, 20), (br.F32, 65, 132, 32), (br.F32, 70, 64, 144),
+                                      (br.F32, 300, 260, 256), (br.F32, 1101, 132, 1024), (br.F32, 40, 64, 1056)])
+def test_gemm_bits_do_not_depend_on_the_kernel(lib, dt, M, N, K):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K)
+    tdt = torch.bfloat16 if dt == br.BF16 else torch.float32
+    A, W = (torch.randn(s, generator=g, device=DEV).to(tdt) for s in ((M, K), (N, K)))
+    b = torch.randn(N, generator=g, device=DEV)
+    mode = 4 if dt == br.BF16 else 0          # fp32 outputs; (fp32 operands: bias, which has every tile form)
+
+    def run(A, variant):
+        out = torch.full((A.shape[0], N), -9.0, device=DEV)
+        br.op_gemm(dt, mode, A, W, b, out, variant=variant)
+        return out
+    ref = run(A, 0)
+    variants = [-1, 1, 2, 3, 4, 5, 6] + ([7] if K % 128 == 0 else []) if dt == br.BF16 else [-1, 3, 5]
+    for v in variants:
+        assert torch.equal(run(A, v), ref), v
+    # the automatic choice for a few rows alone, and for the same rows at the end of a large problem
+    lone = run(A[:31], -1)
+    assert torch.equal(lone, ref[:31])
+    large = torch.cat([A.repeat(12000 // M, 1), A[:31]])
+    assert torch.equal(run(large, -1)[-31:], lone)
+    if dt == br.F32:  # operands that only the vector kernel takes
+        buf = torch.empty(M * K + 1, device=DEV)
+        buf[1:] = A.reshape(-1)
+        assert torch.equal(run(buf[1:].view(M, K), -1), ref)
+
+
+@pytest.mark.parametrize("hidden,heads,lat,cond,dtype,B", [(1024, 16, (16, 1, 64, 64), 77, synth.BF16, 13), (1536, 12, (16, 3, 20, 24), 512, synth.BF16, 36),
+                                                           (1024, 16, (16, 1, 32, 32), 77, synth.F32, 5)])
+def test_velocity_does_not_depend_on_the_batch(lib, hidden, heads, lat, cond, dtype, B):
+    """A sample alone, in a whole batch and in chunks of one and two (small workspaces): the same bits."""
+    cfg = synth.model_cfg(2, hidden, heads, lat, (1, 2, 2), cond, dtype)
+    model = make_model(cfg, synth.make_weights(cfg, 3, 0.03))
+    D = synth.model_sizes(cfg)["D"]
+    z, c = dev(synth.random_latents(B, D, 4)), cond_dev(cfg, synth.cond_tokens(cfg, 2, 5))
+    idx = np.arange(B) % 2
+
+    def run(z, idx, ws_batch):
+        v = torch.empty_like(z)
+        br.velocity(model, z, 0.4, c, idx, v, bytes_buffer(br.workspace_bytes(None, model, ws_batch)))
+        return v
+    whole = run(z, idx, B)
+    assert torch.equal(run(z, idx, 2), whole)
+    alone = torch.cat([run(z[b:b + 1].clone(), idx[b:b + 1], 2) for b in range(B)])
+    assert torch.equal(alone, whole)
