@@ -107,6 +107,12 @@ br_status launch_ln_modulate(int dtype, const float* x, void* out, int n_rows, i
                              const float* mods, int A, int shift_off, int scale_off, const int* condmap,
                              hipStream_t st);
 
+// Sum of the squares of four deviations from a row's mean, rounded in the same places wherever a row is normalised.
+__device__ inline float sum_sq4(const float4& v, float mean) {
+  const float a = v.x - mean, b = v.y - mean, c = v.z - mean, d = v.w - mean;
+  return fmaf(a, a, b * b) + fmaf(c, c, d * d);
+}
+
 // ---- epilogue device code, shared by the fp32 and the MFMA GEMM
 __device__ inline float gelu_tanh_f(float x) {
   // 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)), u = sqrt(2/pi) (x + 0.044715 x^3);

@@ -289,16 +289,9 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
   float q = 0.f;
   if (VPL > 0) {
 #pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-      const float a = v[i].x - mean, bq = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
-      q += (a * a + bq * bq) + (c * c + d * d);
-    }
+    for (int i = 0; i < VPL; ++i) q += sum_sq4(v[i], mean);
   } else {
-    for (int i = lane; i < H4; i += 64) {
-      const float4 u = xr[i];
-      const float a = u.x - mean, bq = u.y - mean, c = u.z - mean, d = u.w - mean;
-      q += (a * a + bq * bq) + (c * c + d * d);
-    }
+    for (int i = lane; i < H4; i += 64) q += sum_sq4(xr[i], mean);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);

@@ -27,7 +27,8 @@ extern __shared__ __attribute__((aligned(1024))) char g_krows[];  // LN: the til
 // LN-modulated rows of the residual stream as the A operand: eight lanes of the workgroup take a row of the tile each,
 // keep it in registers (K <= 1024 / sizeof(T)) and leave it in LDS in the layout of the stages.  Every column tile does it
 // again for its rows (from cache).  Sums over eight lanes cost three exchanges; a wave per row, as in ln_modulate_kernel,
-// would pass eight rows through six, which takes longer than the launch that is saved.
+// would pass eight rows through six, which takes longer than the launch that is saved.  The sums are those of that
+// kernel all the same: a lane holds what eight of its lanes do (sub, sub + 8, ...), and adds them up in its exchanges' order.
 template <typename T>
 __device__ inline void ln_rows(const LnArgs& ln, int m0, int M, int K, int tid) {
   constexpr int V = 32 / (int)sizeof(T);  // float4 of a lane
@@ -47,19 +48,22 @@ __device__ inline void ln_rows(const LnArgs& ln, int m0, int M, int K, int tid) 
       sc[i] = reinterpret_cast<const float4*>(mrow + ln.scale_off)[c4];
     }
   }
-  float s = 0.f, q = 0.f;
+  // p[j] = sum of lane sub + 8 j there
+  auto row_sum = [](const float (&p)[8]) {
+    float s = ((p[0] + p[4]) + (p[2] + p[6])) + ((p[1] + p[5]) + (p[3] + p[7]));  // (distances 32, 16, 8)
 #pragma unroll
-  for (int i = 0; i < V; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    return s;
+  };
+  float p[8] = {};
 #pragma unroll
-  for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  const float mean = s / (float)K;
+  for (int i = 0; i < V; ++i) p[i & 7] += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+  const float mean = row_sum(p) / (float)K;
+  float p2[8] = {};
 #pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const float a = v[i].x - mean, bq = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
-    if (sub + 8 * i < H4) q += (a * a + bq * bq) + (c * c + d * d);
-  }
-#pragma unroll
-  for (int o = 4; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+  for (int i = 0; i < V; ++i)
+    if (sub + 8 * i < H4) p2[i & 7] += sum_sq4(v[i], mean);
+  const float q = row_sum(p2);
   const float rstd = 1.0f / __builtin_sqrtf(q / (float)K + 1e-6f);
 #pragma unroll
   for (int i = 0; i < V; ++i) {

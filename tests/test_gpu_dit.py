@@ -453,3 +453,21 @@ def test_velocity_does_not_depend_on_the_batch(lib, hidden, heads, lat, cond, dt
     assert torch.equal(run(z, idx, 2), whole)
     alone = torch.cat([run(z[b:b + 1].clone(), idx[b:b + 1], 2) for b in range(B)])
     assert torch.equal(alone, whole)
+
+
+@pytest.mark.parametrize("hidden,heads,dtype", [(48, 3, synth.F32), (64, 4, synth.F32), (256, 8, synth.F32), (64, 1, synth.BF16), (128, 2, synth.BF16),
+                                                (192, 3, synth.BF16), (512, 4, synth.BF16)])
+def test_velocity_bits_where_the_normalisation_moves_into_the_gemm(lib, hidden, heads, dtype):
+    """A sample alone (its rows normalised by the GEMM that reads them) and among enough others that every GEMM has more
+    tiles than compute units (normalised by a launch of its own): the same bits."""
+    cfg = synth.model_cfg(2, hidden, heads, (16, 1, 14, 18), (1, 2, 2), 6, dtype)
+    model = make_model(cfg, synth.make_weights(cfg, 3, 0.05))
+    sizes = synth.model_sizes(cfg)
+    B = 256 * 32 // sizes["n_img"] + 2                    # rows of the narrowest call: the final projection, 64 columns
+    z, c = dev(synth.random_latents(1, sizes["D"], 4)), cond_dev(cfg, synth.cond_tokens(cfg, 1, 5))
+    out = []
+    for n in (1, B):
+        v = torch.empty((n, sizes["D"]), device=DEV)
+        br.velocity(model, z.repeat(n, 1), 0.4, c, np.zeros(n, np.int32), v, bytes_buffer(br.workspace_bytes(None, model, n)))
+        out.append(v)
+    assert torch.equal(out[1], out[0].expand(B, -1))
