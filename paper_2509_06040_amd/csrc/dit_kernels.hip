@@ -66,26 +66,32 @@ __global__ __launch_bounds__(256) void batch_prologue_kernel(SampleMap sm, int b
 // is formed and reduced to [-pi, pi] in fp64, then fp32 sin/cos suffice.
 __device__ inline float silu_f(float x) { return x / (1.f + __expf(-x)); }
 
-// pooled[c, :] = mean over the condition tokens of condition c (depends on the prompt only).  A workgroup takes 32
-// columns; its eight rows of lanes take every eighth token each, so that the loads in flight are many and the chain
-// is short (one lane down all 512 tokens of a column of 3072: 182 us, eight: 7).
+// pooled[c, :] = mean over the condition tokens of condition c (depends on the prompt only), added in token order.  A
+// workgroup takes 64 columns: its four waves fetch POOL_CHUNK tokens at a time, a quarter of them in flight per lane, and one
+// wave adds them up from LDS (one lane down all 512 tokens of a column of 3072 by itself: 182 us, so: 8).
+constexpr int POOL_CHUNK = 128;
 template <typename T>
 __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ cond, int Nc, int cd,
                                                    float* __restrict__ pooled) {
-  __shared__ float part[8][32];
-  const int c = blockIdx.y, col = threadIdx.x & 31, grp = threadIdx.x >> 5, d = blockIdx.x * 32 + col;
+  __shared__ float tok[POOL_CHUNK][64];
+  const int c = blockIdx.y, col = threadIdx.x & 63, grp = threadIdx.x >> 6, d = blockIdx.x * 64 + col;
+  const T* p = cond + (size_t)c * Nc * cd + min(d, cd - 1);
   float s = 0.f;
-  if (d < cd) {
-#pragma unroll 8
-    for (int j = grp; j < Nc; j += 8) s += to_f(cond[((size_t)c * Nc + j) * cd + d]);
-  }
-  part[grp][col] = s;
-  __syncthreads();
-  if (grp == 0 && d < cd) {
+  for (int j0 = 0; j0 < Nc; j0 += POOL_CHUNK) {
+    T v[POOL_CHUNK / 4];
 #pragma unroll
-    for (int g = 1; g < 8; ++g) s += part[g][col];
-    pooled[(size_t)c * cd + d] = s / (float)Nc;
+    for (int k = 0; k < POOL_CHUNK / 4; ++k) v[k] = p[(size_t)min(j0 + 4 * k + grp, Nc - 1) * cd];
+#pragma unroll
+    for (int k = 0; k < POOL_CHUNK / 4; ++k) tok[4 * k + grp][col] = to_f(v[k]);
+    __syncthreads();
+    if (grp == 0) {
+      const int n = min(POOL_CHUNK, Nc - j0);
+#pragma unroll 16
+      for (int j = 0; j < n; ++j) s += tok[j][col];
+    }
+    __syncthreads();
   }
+  if (grp == 0 && d < cd) pooled[(size_t)c * cd + d] = s / (float)Nc;
 }
 
 template <typename TW>
@@ -239,7 +245,7 @@ br_status launch_pool_linear(const br_model* m, const FwdBuffers& fb, int n_cond
 }
 
 br_status launch_pool(const br_model* m, const FwdBuffers& fb, const void* cond, int n_cond, hipStream_t st) {
-  dim3 g(cdiv(m->cd, 32), n_cond), b(256);
+  dim3 g(cdiv(m->cd, 64), n_cond), b(256);
   if (m->cfg.dtype == BR_BF16)
     hipLaunchKernelGGL((pool_kernel<bf16>), g, b, 0, st, (const bf16*)cond, m->Nc, m->cd, fb.pooled);
   else

@@ -471,3 +471,20 @@ def test_velocity_bits_where_the_normalisation_moves_into_the_gemm(lib, hidden, 
         br.velocity(model, z.repeat(n, 1), 0.4, c, np.zeros(n, np.int32), v, bytes_buffer(br.workspace_bytes(None, model, n)))
         out.append(v)
     assert torch.equal(out[1], out[0].expand(B, -1))
+
+
+@pytest.mark.parametrize("n_tok", [64, 300])
+def test_condition_mean_adds_the_tokens_in_order(lib, n_tok):
+    """1 + 2^-24 rounds to 1 in fp32, so in token order the small tokens behind the first one leave no trace; added among
+    themselves first, they would.  The tokens' own embeddings are switched off (zero weights)."""
+    cfg = synth.model_cfg(1, 64, 4, (4, 1, 8, 8), (1, 2, 2), n_tok, synth.F32)
+    W = synth.make_weights(cfg, 1, 0.1)
+    W["cond_w"][:] = 0.0
+    cond = np.zeros((2, n_tok, cfg["cond_dim"]), np.float32)
+    cond[:, 0] = 1.0
+    cond[1, 1:] = 2.0 ** -24
+    model = make_model(cfg, W)
+    z = dev(np.repeat(synth.random_latents(1, synth.model_sizes(cfg)["D"], 2), 2, axis=0))
+    v = torch.empty_like(z)
+    br.velocity(model, z, 0.6, dev(cond), np.array([0, 1], np.int32), v, bytes_buffer(br.workspace_bytes(None, model, 2)))
+    assert torch.equal(v[0], v[1])
