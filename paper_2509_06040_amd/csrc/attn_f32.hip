@@ -86,7 +86,7 @@ __global__ __launch_bounds__(NW * 64, DH == 128 ? 1 : 2) void attn_f32_kernel(co
     const char* kp = reinterpret_cast<const char*>(base + (size_t)kt * KT * ld + H);
     const char* vp = kp + (size_t)H * 4;
     const unsigned dst = (unsigned)(uintptr_t)BR_LPTR(mine);
-    const int last = L - 1 - kt * KT;  // rows past the end read the last key (their scores are masked)
+    const int last = L - 1 - kt * KT;  // rows past the end read the last key (their scores and values are masked)
 #pragma unroll
     for (int t = 0; t < NI; ++t) {
       const int row = t * RPI + lrow;
@@ -128,19 +128,24 @@ __global__ __launch_bounds__(NW * 64, DH == 128 ? 1 : 2) void attn_f32_kernel(co
     if (kt == nkt - 1) {
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        if (kt * KT + 8 * (r >> 2) + 4 * lh + (r & 3) >= L) s[r] = -INFINITY;
+        if (kt * KT + 8 * (r >> 2) + 4 * lh + (r & 3) >= L) {
+          s[r] = -INFINITY;
+#pragma unroll
+          for (int d = 0; d < DB; ++d) vf[d][r] = 0.f;  // (0 times an infinite value would be a NaN)
+        }
     }
     float mx = s[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m_run, mx);  // finite: a tile has at least one key
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    // the reference: the largest score so far, 0 while all of them are -inf (the wave holds only a part of the keys)
+    const float m_new = fmaxf(m_run, mx), m_ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
     m_run = m_new;
     float sum = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[r] = __builtin_amdgcn_exp2f(s[r] - m_new);
+      s[r] = __builtin_amdgcn_exp2f(s[r] - m_ref);
       sum += s[r];
     }
     l_run = l_run * alpha + sum;
@@ -161,7 +166,7 @@ __global__ __launch_bounds__(NW * 64, DH == 128 ? 1 : 2) void attn_f32_kernel(co
   float m_all = part_m[0][l32];
 #pragma unroll
   for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, part_m[w][l32]);
-  const float f = __builtin_amdgcn_exp2f(m_run - m_all);  // 0 for a wave without keys
+  const float f = __builtin_amdgcn_exp2f(m_run - m_all);  // 0 for a wave without keys; (NaN if every score is -inf)
   if (lh == 0) part_l[wv][l32] = l_run * f;
   static_assert(32 * RB <= 2 * TILE_B, "a partial output reuses the wave's slot");
 #pragma unroll

@@ -488,3 +488,33 @@ def test_condition_mean_adds_the_tokens_in_order(lib, n_tok):
     v = torch.empty_like(z)
     br.velocity(model, z, 0.6, dev(cond), np.array([0, 1], np.int32), v, bytes_buffer(br.workspace_bytes(None, model, 2)))
     assert torch.equal(v[0], v[1])
+
+
+@pytest.mark.parametrize("dh,L", [(16, 33), (64, 45), (128, 70), (32, 131)])
+def test_attention_fp32_infinite_values_and_scores(lib, dh, L):
+    """An infinite value is an infinite output where its key is not masked, the last key of a ragged tile among them; keys that
+    score -inf throughout the first tile of a wave (or of all but one) have no weight; only where all keys do there is no result."""
+    rng = np.random.default_rng(L)
+    qkv = rng.standard_normal((1, L, 3 * dh)).astype(np.float32)
+    qkv[0, :, 0] = 1.0                                     # every query scores key j with k[j, 0] + finite
+    def run(qkv):
+        out = torch.empty((1, L, dh), device=DEV)
+        br.op_attention(br.F32, dev(qkv), out, 1)
+        return host(out)[0]
+    a = qkv.copy()
+    a[0, L - 1, 2 * dh + 3] = np.inf
+    got, plain = run(a), run(qkv)
+    assert np.isposinf(got[:, 3]).all()
+    rest = np.arange(dh) != 3
+    assert np.array_equal(got[:, rest], plain[:, rest])
+    for masked in (np.arange(0, 32), np.arange(0, L - 2), np.arange(L - 3, L)):
+        b = qkv.copy()
+        b[0, masked, dh] = -np.inf
+        keep = np.setdiff1d(np.arange(L), masked)
+        c = qkv.astype(np.float64)
+        s = (c[0, :, :dh] @ c[0, keep, dh:2 * dh].T) / np.sqrt(dh)
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        assert rel_l2(run(b), (p / p.sum(axis=1, keepdims=True)) @ c[0, keep, 2 * dh:]) < 2e-6, masked
+    b = qkv.copy()
+    b[0, :, dh] = -np.inf
+    assert np.isnan(run(b)).all()
