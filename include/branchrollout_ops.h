@@ -20,13 +20,13 @@ extern "C" {
  *               gate row r at mods + r*mods_stride + gate_off, cond dev [M / L]
  *            4: out[m, n] = acc                  out fp32
  * BR_BF16 needs K % 64 == 0, lda % 8 == 0, ldw % 8 == 0; N % 4 == 0 always.
- * variant: kernel (-1 = automatic; 0 = 32x32 tiles; 1 / 2 / 3 / 4 / 5 / 6 =
- * 128x128 in eight waves / 64x64 / 64x128 / 256x256 / 128x128 / 256x128 tile per workgroup; 7 = persistent
- * streaming kernel, tiles of 128 to 256 rows x 256 columns, needs K % 128 == 0.  BR_F32 has 0, 3 and 5 and takes its own choice where
- * another is asked for or does not apply.  bf16 only: bits 4..11 = column-group width of
- * the tile walk, 0 = the kernel's own choice; for the persistent kernel bits 12..15 = rows of a tile in units
- * of 32 (4 to 8; any other value: 8), bits 24..30 = rows of a row block of the tile walk in units of 8 tile
- * rows, 0 = the kernel's own choice.  All of them give the same
+ * variant: bits 0..3 = kernel (-1 = automatic; 0 = 32x32 tiles; 1 / 2 / 3 / 4 / 5 / 6 = 128x128 in eight waves /
+ * 64x64 / 64x128 / 256x256 / 128x128 / 256x128 tile per workgroup; 7 = persistent streaming kernel with tiles of
+ * 256 rows x 256 columns, 8 / 9 / 10 / 11 = the same with 128 / 160 / 192 / 224 rows, need K % 128 == 0.  BR_F32
+ * has 0, 3 and 5 and takes its own choice where another is asked for or does not apply.  bf16 only: bits 4..11 =
+ * column-group width of the tile walk, 0 = the kernel's own choice; for the persistent kernel bits 24..30 = rows of a
+ * row block of the tile walk in units of 8 tile rows, 0 = the kernel's own choice; bits 12..23, start delays of
+ * workgroups in earlier versions, are accepted and have no effect.  All of them give the same
  * results, bit for bit: every output is the sum over k in ascending order. */
 br_status br_op_gemm(int32_t dtype, int32_t epilogue, const void* A, int32_t lda, const void* W,
                      int32_t ldw, int32_t M, int32_t N, int32_t K, const float* bias, void* out,

@@ -28,7 +28,7 @@ static br_status gemm_tile_launch(const bf16* A, int lda, const bf16* W, int ldw
   return BR_OK;
 }
 
-enum {  // bits 0..3 of a variant
+enum {  // bits 0..3 of a variant; TILE_STREAM + 1 .. + 4: the persistent kernel with 4 .. 7 times 32 rows a tile
   TILE_32 = 0, TILE_128_W8 = 1, TILE_64 = 2, TILE_64_128 = 3, TILE_256 = 4, TILE_128 = 5, TILE_256_128 = 6, TILE_STREAM = 7
 };
 
@@ -72,8 +72,8 @@ static int choose_tile(int M, int N, int K, bool stream_ok, int* height) {
 }
 
 // variant bits 0..3: kernel (see the enum); bits 4..11: column-group width of the tile walk (0 = the kernel's own
-// choice); for the persistent kernel bits 12..15: rows of a tile in units of 32 (4 to 8, else 8), bits 24..30: row block
-// of the walk in units of 8 tile rows.  variant < 0 = choose by problem size.
+// choice); for the persistent kernel bits 24..30: row block of the walk in units of 8 tile rows (bits 12..23 were start
+// delays of an earlier form and are ignored).  variant < 0 = choose by problem size.
 template <int MODE, typename TOUT>
 static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K, const EpiArgs& ea,
                               int variant, hipStream_t st) {
@@ -83,7 +83,11 @@ static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, in
   } else {
     tile = variant & 15;
     group_n = (variant >> 4) & 255;
-    height = (variant >> 12) & 15;
+    height = 8;
+    if (tile > TILE_STREAM && tile <= TILE_STREAM + 4) {
+      height = tile - TILE_STREAM + 3;
+      tile = TILE_STREAM;
+    }
     row_block = ((variant >> 24) & 127) * 8;
   }
   ProfScope ps(st, PROF_GEMM + MODE * 8 + tile, 2.0 * M * N * K);

@@ -324,7 +324,6 @@ br_status launch_gemm_bf16_stream(int mode, const bf16* A, int lda, const bf16* 
                                   const EpiArgs& ea, int height, int group_n, int row_block, hipStream_t st) {
   BR_REQUIRE(gemm_stream_supported(mode, K, (size_t)M * lda * 2, (size_t)N * ldw * 2), BR_ESHAPE,
              "streaming gemm: needs K % 128 == 0 and operands below 4 GiB");
-  if (height < 4 || height > 8) height = 8;
   switch (mode) {
     case EPI_BIAS: return stream_height<EPI_BIAS, bf16>(A, lda, W, ldw, M, N, K, ea, height, group_n, row_block, st);
     case EPI_BIAS_GELU: return stream_height<EPI_BIAS_GELU, bf16>(A, lda, W, ldw, M, N, K, ea, height, group_n, row_block, st);

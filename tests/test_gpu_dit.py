@@ -106,6 +106,9 @@ def test_gemm_two_launch_cut_matches_one_launch_and_fp64(lib, mode):
     assert rel_l2(host(outs[0].float())[rows], ref) < tol
 
 
+STREAM = {4: 8, 5: 9, 6: 10, 7: 11, 8: 7}  # variant of the persistent kernel by rows of a tile in units of 32
+
+
 @pytest.mark.parametrize("height", [4, 5, 6, 7, 8])
 @pytest.mark.parametrize("M,N,K,L", [(32, 256, 128, 32), (255, 260, 256, 255), (1290, 772, 384, 129), (2 * 1101, 1024, 256, 1101), (640, 128, 128, 20)])
 def test_gemm_persistent_tile_heights(lib, height, M, N, K, L):
@@ -117,7 +120,7 @@ def test_gemm_persistent_tile_heights(lib, height, M, N, K, L):
     mods = rng.standard_normal((M // L, N)).astype(np.float32)
     Ad, Wd, bd = dev(A, torch.bfloat16), dev(W, torch.bfloat16), dev(b)
     lin = A.astype(np.float64) @ W.astype(np.float64).T + b
-    variant = 7 | (height << 12)
+    variant = STREAM[height]
     out = torch.full((M + 8, N), -9.0, device=DEV)
     br.op_gemm(br.BF16, 4, Ad, Wd, bd, out[:M], variant=variant)
     assert rel_l2(host(out[:M]), lin) < 1e-5 and bool((out[M:] == -9.0).all())
@@ -518,3 +521,23 @@ def test_attention_fp32_infinite_values_and_scores(lib, dh, L):
     b = qkv.copy()
     b[0, :, dh] = -np.inf
     assert np.isnan(run(b)).all()
+
+
+def test_gemm_variant_word(lib):
+    """Heights of the persistent kernel are kernel numbers of their own; what callers pass as start delays (bits 12..23) stays
+    accepted and changes nothing; numbers beyond are refused."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    M, N, K = 700, 512, 256
+    A, W = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((M, K), (N, K)))
+    b = torch.randn(N, generator=g, device=DEV)
+    ref = torch.empty((M, N), device=DEV)
+    br.op_gemm(br.BF16, 4, A, W, b, ref, variant=5)
+    for variant in [7, 8, 9, 10, 11] + [v | (d << 12) for v in (7, 9) for d in (4, 6, 255, 4095)]:
+        out = torch.empty((M, N), device=DEV)
+        br.op_gemm(br.BF16, 4, A, W, b, out, variant=variant)
+        assert torch.equal(out, ref), variant
+    for variant in (12, 13, 14, 15):
+        with pytest.raises(br.BranchRolloutError) as e:
+            br.op_gemm(br.BF16, 4, A, W, b, ref, variant=variant)
+        assert e.value.code == -1
