@@ -626,9 +626,10 @@ br_status launch_leaf_reward(const br_tree* t, const float* z, int kind, const f
                        t->n_leaves, lh * lw, scratch);
     BR_LAUNCH_CHECK();
     hipLaunchKernelGGL(reward_video_finish_kernel, dim3(nl), dim3(256), 0, st, scratch, w, lc, lt, lam, rewards);
-  } else if (D <= 131072) {
-    // Up to this leaf one workgroup reads it in the time of a launch: 64 leaves of 65 536 elements 4.2 + 2.6 us and a
-    // gap in two launches.
+  } else if (D <= 65536) {
+    // Up to this leaf one workgroup reads it in less than the launch that is saved: a call that is waited for takes
+    // 20-21 us instead of 21-22 at 65 536 elements and 1 to 64 leaves (18-19 at 16 384), in a run of calls 8.4 instead of 12.8;
+    // at 131 072 it would take 23-27.
     hipLaunchKernelGGL(reward_dot_leaf_kernel, dim3(nl), dim3(1024), 0, st, z, w, D, t->n_nodes, t->off[t->T], t->n_leaves,
                        1.0 / sqrt((double)D), kind == BR_REWARD_TANH ? 1 : 0, rewards);
   } else {

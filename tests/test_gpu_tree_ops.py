@@ -173,7 +173,8 @@ def test_tree_kernels_at_and_beyond_their_largest_trees(lib):
 
 
 @pytest.mark.parametrize("kind,latent,shift", [(br.REWARD_LINEAR, (4, 1, 1, 1), 0), (br.REWARD_TANH, (1, 1, 64, 512), 0),      # one element a thread; whole rounds of eight
-                                               (br.REWARD_LINEAR, (4, 1, 128, 256), 0), (br.REWARD_LINEAR, (4, 1, 127, 259), 0),  # 131 072: last of one launch; beyond it
+                                               (br.REWARD_LINEAR, (4, 1, 128, 128), 0), (br.REWARD_LINEAR, (4, 1, 127, 131), 0),  # 65 536: last of one launch; beyond it
+                                               (br.REWARD_LINEAR, (4, 1, 128, 256), 0), (br.REWARD_LINEAR, (4, 1, 127, 259), 0),
                                                (br.REWARD_VIDEO, (4, 3, 6, 7), 0), (br.REWARD_VIDEO, (2, 3, 64, 130), 0),        # planes of odd and of 16-byte multiples
                                                (br.REWARD_VIDEO, (2, 3, 8, 10), 1)])                                           # latents that are not 16-byte aligned
 def test_leaf_rewards_at_the_edges_of_their_kernels(lib, kind, latent, shift):
@@ -216,3 +217,18 @@ def test_fusion_and_pruning_at_the_edges_of_their_kernels(lib, T, splits, C):
         br.prune(t, dev(r), mode, b, mask, kept, nk)
         ref = prune.kept_edges(o, r, C, mode, b, mask)
         assert int(host(nk)[0]) == len(ref) and np.array_equal(host(kept)[:len(ref)], ref)
+
+
+@pytest.mark.parametrize("latent,one_launch", [((4, 1, 128, 128), True), ((4, 1, 127, 131), False), ((4, 1, 128, 256), False)])
+def test_large_leaves_are_split_over_workgroups(lib, latent, one_launch):
+    """Leaves beyond 65 536 elements go through partial sums in the scratch (one workgroup would take longer than two launches);
+    smaller ones leave the scratch as it is."""
+    D = int(np.prod(latent))
+    t = br.Tree(3, (0,), 2)
+    rng = np.random.default_rng(D)
+    z, w = rng.standard_normal((t.n_nodes, D)).astype(np.float32), rng.standard_normal(D).astype(np.float32)
+    out = torch.empty(t.n_leaves, device=DEV)
+    scratch = torch.full((max(256, br.reward_scratch_bytes(t, br.REWARD_LINEAR, latent)),), 171, dtype=torch.uint8, device=DEV)
+    br.leaf_reward(t, dev(z), br.REWARD_LINEAR, dev(w), 0.0, latent, out, scratch)
+    assert bool((scratch == 171).all()) == one_launch
+    assert np.abs(host(out) - rewards.reward_linear(z[t.off[3]:], w)).max() < 2e-6 * np.abs(host(out)).max() + 2e-6
