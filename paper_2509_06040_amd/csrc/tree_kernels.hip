@@ -96,7 +96,12 @@ __global__ __launch_bounds__(1024) void reward_dot_leaf_kernel(const float* __re
   }
 }
 
-// Stage 1 (video): mean of one (channel, frame) plane; grid (C*F, n_leaves_total).
+// Stage 1 (video): mean of one (channel, frame) plane; grid (C*F, n_leaves_total).  VEC: planes of a multiple of four elements
+// at 16-byte aligned addresses (leaves are then multiples of four elements too), eight pieces in flight a thread: 67 MB in
+// 13 us; one element at a time 20.  Planes below 2048 elements have too few pieces for it (256 leaves of 16 planes of 1024: 7.6 us,
+// 7.3 by elements).  A kernel of its own: the registers of the pieces would cost the other form workgroups (256 leaves of
+// 48 planes of 63 elements 8.9 us, 10.1 with both in one).
+template <bool VEC>
 __global__ __launch_bounds__(256) void reward_plane_mean_kernel(const float* __restrict__ z, long long D, int n_nodes,
                                                                 int leaf_off, int n_leaves, int plane,
                                                                 float* __restrict__ means) {
@@ -104,8 +109,7 @@ __global__ __launch_bounds__(256) void reward_plane_mean_kernel(const float* __r
   const int g = blockIdx.y, c = g / n_leaves, l = g - c * n_leaves;
   const float* p = z + ((size_t)c * n_nodes + leaf_off + l) * D + (size_t)blockIdx.x * plane;
   float acc = 0.f;
-  if ((plane & 3) == 0 && (reinterpret_cast<uintptr_t>(z) & 15) == 0) {  // (leaves are multiples of four elements)
-    // eight pieces in flight a thread: 67 MB in 13 us; one element at a time 20
+  if constexpr (VEC) {
     const float4* p4 = reinterpret_cast<const float4*>(p);
     const int n4 = plane >> 2;
     for (int i = threadIdx.x; i < n4; i += 8 * 256) {
@@ -121,18 +125,19 @@ __global__ __launch_bounds__(256) void reward_plane_mean_kernel(const float* __r
   acc = wsum_f(acc);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0)
-    means[(size_t)g * gridDim.x + blockIdx.x] = ((red[0] + red[1]) + (red[2] + red[3])) / (float)plane;
+  if (threadIdx.x == 0) means[(size_t)g * gridDim.x + blockIdx.x] = ((red[0] + red[1]) + (red[2] + red[3])) / (float)plane;
 }
 
-// Stage 2 (video): m is stored [C, F] per leaf; w is [F, C].
-__global__ __launch_bounds__(256) void reward_video_finish_kernel(const float* __restrict__ means,
+// Stage 2 (video): m is stored [C, F] per leaf; w is [F, C].  One wavefront where it has few means to add (the exchange
+// through LDS costs 0.3 us), four for more.
+template <int NT>
+__global__ __launch_bounds__(NT) void reward_video_finish_kernel(const float* __restrict__ means,
                                                                  const float* __restrict__ w, int C, int F, float lam,
                                                                  float* __restrict__ out) {
   const int g = blockIdx.x;
   const float* m = means + (size_t)g * C * F;
   double lin = 0.0, pen = 0.0;
-  for (int i = threadIdx.x; i < C * F; i += 256) {
+  for (int i = threadIdx.x; i < C * F; i += NT) {
     const int c = i / F, f = i - c * F;
     lin += (double)w[f * C + c] * (double)m[i];
     if (f + 1 < F) {
@@ -140,17 +145,21 @@ __global__ __launch_bounds__(256) void reward_video_finish_kernel(const float* _
       pen += d * d;
     }
   }
-  __shared__ double red[2][4];
   lin = wsum_d(lin);
   pen = wsum_d(pen);
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = lin;
-    red[1][threadIdx.x >> 6] = pen;
+  if constexpr (NT > 64) {
+    __shared__ double red[2][NT / 64];
+    if ((threadIdx.x & 63) == 0) {
+      red[0][threadIdx.x >> 6] = lin;
+      red[1][threadIdx.x >> 6] = pen;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      lin = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+      pen = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+    }
   }
-  __syncthreads();
   if (threadIdx.x == 0) {
-    lin = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-    pen = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
     double r = lin / sqrt((double)F * C);
     if (F > 1) r -= (double)lam * pen / (double)(F - 1);
     out[g] = (float)r;
@@ -622,10 +631,13 @@ br_status launch_leaf_reward(const br_tree* t, const float* z, int kind, const f
   BR_REQUIRE(nl <= 65535, BR_ESHAPE, "leaf reward: more than 65535 leaves are not supported");
   if (kind == BR_REWARD_VIDEO) {
     BR_REQUIRE(lc * lt <= 65535 * 32, BR_ESHAPE, "leaf reward: too many planes");
-    hipLaunchKernelGGL(reward_plane_mean_kernel, dim3(lc * lt, nl), dim3(256), 0, st, z, D, t->n_nodes, t->off[t->T],
-                       t->n_leaves, lh * lw, scratch);
+    const bool vec = lh * lw % 4 == 0 && lh * lw >= 2048 && (reinterpret_cast<uintptr_t>(z) & 15) == 0;
+    hipLaunchKernelGGL(vec ? reward_plane_mean_kernel<true> : reward_plane_mean_kernel<false>, dim3(lc * lt, nl), dim3(256), 0, st, z, D,
+                       t->n_nodes, t->off[t->T], t->n_leaves, lh * lw, scratch);
     BR_LAUNCH_CHECK();
-    hipLaunchKernelGGL(reward_video_finish_kernel, dim3(nl), dim3(256), 0, st, scratch, w, lc, lt, lam, rewards);
+    const bool few = lc * lt <= 128;
+    hipLaunchKernelGGL(few ? reward_video_finish_kernel<64> : reward_video_finish_kernel<256>, dim3(nl), dim3(few ? 64 : 256), 0, st,
+                       scratch, w, lc, lt, lam, rewards);
   } else if (D <= 65536) {
     // Up to this leaf one workgroup reads it in less than the launch that is saved: a call that is waited for takes
     // 20-21 us instead of 21-22 at 65 536 elements and 1 to 64 leaves (18-19 at 16 384), in a run of calls 8.4 instead of 12.8;

@@ -176,6 +176,7 @@ def test_tree_kernels_at_and_beyond_their_largest_trees(lib):
                                                (br.REWARD_LINEAR, (4, 1, 128, 128), 0), (br.REWARD_LINEAR, (4, 1, 127, 131), 0),  # 65 536: last of one launch; beyond it
                                                (br.REWARD_LINEAR, (4, 1, 128, 256), 0), (br.REWARD_LINEAR, (4, 1, 127, 259), 0),
                                                (br.REWARD_VIDEO, (4, 3, 6, 7), 0), (br.REWARD_VIDEO, (2, 3, 64, 130), 0),        # planes of odd and of 16-byte multiples
+                                               (br.REWARD_VIDEO, (2, 3, 32, 64), 0), (br.REWARD_VIDEO, (2, 3, 32, 64), 1),      # 2048: first plane by pieces of four
                                                (br.REWARD_VIDEO, (2, 3, 8, 10), 1)])                                           # latents that are not 16-byte aligned
 def test_leaf_rewards_at_the_edges_of_their_kernels(lib, kind, latent, shift):
     D = int(np.prod(latent))
