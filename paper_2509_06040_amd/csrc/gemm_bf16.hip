@@ -34,8 +34,9 @@ enum {  // bits 0..3 of a variant; TILE_STREAM + 1 .. + 4: the persistent kernel
 
 // The kernel for a problem size.  r = tiles of a kind per compute unit.  (The part for small problems is from 410
 // measured shapes: M 40 to 200 000, hidden sizes 64 to 3072 with their QKV, MLP and projection widths.)
-// *height: rows of a tile of the persistent kernel, in units of 32.
-static int choose_tile(int M, int N, int K, bool stream_ok, int* height) {
+// rps: rows of a sample where the epilogue looks something up per sample, else 0.  *height: rows of a tile of the
+// persistent kernel, in units of 32.
+static int choose_tile(int M, int N, int K, int rps, bool stream_ok, int* height) {
   const double cu = device_cu_count();
   const double r32 = (double)cdiv(M, 32) * cdiv(N, 32) / cu, r64 = (double)cdiv(M, 64) * cdiv(N, 64) / cu;
   const double r128 = (double)cdiv(M, 128) * cdiv(N, 128) / cu;
@@ -56,12 +57,20 @@ static int choose_tile(int M, int N, int K, bool stream_ok, int* height) {
   // part of a round 0.6 of what it leaves idle (the units that work run faster at the chip's power limit); 128x128
   // tiles move twice the operand bytes.  Fitted to 124 shapes (M 500 to 100 000, N 256 to 12 288, K 256 to 12 288):
   // 0.5 % slower on average than the best kernel of each shape.
+  //
+  // A wave of the persistent kernel owns 16 rows per unit of height.  Where those span more than two samples, every
+  // row looks its sample up by itself, with nothing fetched ahead: 4 us a block, as much as the products of K = 900
+  // (59 613 rows of 93 a sample, 1536 x 1536: 324 us in 160 rows, 505 in 192; 10 960 rows of 20, 512 x 512: 24.5 us in the
+  // persistent kernel, 17.1 in 128x128 tiles of eight waves, whose waves own 32 rows).  83 shapes with samples of 20 to
+  // 4608 rows: 1.2 % slower on average than the best kernel of each; without this term 5.8 % on the short ones.
   double best = 1.4 * 2.0 * (r128 + 0.4);
-  int tile = K <= 512 ? TILE_128_W8 : TILE_128;  // a short K leaves a larger share to the epilogue, where eight waves store faster (3-5 %)
+  // eight waves store faster (3-5 %), which a short K leaves a larger share to, and own half the rows each
+  int tile = K <= 512 || (rps > 0 && rps < 64) ? TILE_128_W8 : TILE_128;
   for (int h = 8; h >= 4; --h) {
     if (!stream_ok && h < 8) break;
     const double r = (double)cdiv(M, 32 * h) * cdiv(N, 256) / cu;
-    const double cost = (0.4 * r + 0.6 * std::ceil(r)) * (h + 0.75);
+    const double lookups = rps > 0 && rps < 16 * h ? 900.0 / K * h : 0.0;
+    const double cost = (0.4 * r + 0.6 * std::ceil(r)) * (h + 0.75 + lookups);
     if (cost < best) {
       best = cost;
       tile = stream_ok ? TILE_STREAM : TILE_256;
@@ -79,7 +88,7 @@ static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, in
                               int variant, hipStream_t st) {
   int tile, group_n = 0, row_block = 0, height = 0;
   if (variant < 0) {
-    tile = choose_tile(M, N, K, gemm_stream_supported(MODE, K, (size_t)M * lda * 2, (size_t)N * ldw * 2), &height);
+    tile = choose_tile(M, N, K, MODE == EPI_BIAS_GATE_RES ? ea.L : 0, gemm_stream_supported(MODE, K, (size_t)M * lda * 2, (size_t)N * ldw * 2), &height);
   } else {
     tile = variant & 15;
     group_n = (variant >> 4) & 255;
