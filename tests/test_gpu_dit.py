@@ -70,11 +70,10 @@ def test_gemm_gated_residual_epilogue(lib):
 
 
 @pytest.mark.parametrize("mode", [0, 1, 2])
-def test_gemm_two_launch_cut_matches_one_launch_and_fp64(lib, mode):
-    """16 samples of 1101 tokens and 1024 output columns are 1.08 rounds of 256x256 tiles on 256
-    compute units: the library cuts the rows between two samples into a launch of the persistent
-    kernel and one of 256x128 tiles.  Same bits as the persistent kernel alone, and right against
-    fp64 on sampled rows on both sides of the cut (each sample with its own gate)."""
+def test_gemm_tile_height_of_a_sparse_last_round_matches_full_height_and_fp64(lib, mode):
+    """16 samples of 1101 tokens and 1024 output columns are 1.08 rounds of 256x256 tiles on 256 compute units: the library takes
+    tiles of 160 rows.  Same bits as tiles of 256 rows, and right against fp64 on sampled rows around tile and sample
+    boundaries (each sample with its own gate)."""
     rng = np.random.default_rng(mode)
     L, B, N, K, C = 1101, 16, 1024, 256, 5
     M = L * B
@@ -306,10 +305,11 @@ def test_velocity_chunked_batches_agree(lib):
 
 
 # every form of the fp32 GEMM (128x128, 64x128 and 32x32 tiles) at tile
-# edges, with K of less than one stage, whole stages and a stage that ends inside a 16-byte chunk pair
+# edges, with K of less than one stage, one to 32 whole stages of 32 (the tile kernels' ring has two slots; where K is not
+# a multiple of 32 the 32x32 tiles take over) and a stage that ends inside a 16-byte chunk pair
 @pytest.mark.parametrize("variant", [-1, 0, 3, 5])
 @pytest.mark.parametrize("M,N,K", [(1, 4, 4), (31, 36, 12), (33, 132, 16), (64, 128, 20), (65, 124, 32), (129, 260, 144),
-                                   (257, 128, 1040), (1000, 516, 96)])
+                                   (257, 128, 1040), (1000, 516, 96), (129, 132, 64), (65, 260, 128), (257, 124, 160), (130, 388, 1024)])
 def test_gemm_fp32_every_form(lib, variant, M, N, K):
     rng = np.random.default_rng(M * 7 + K)
     A, W, b = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (N, K), (N,)))
@@ -541,3 +541,40 @@ def test_gemm_variant_word(lib):
         with pytest.raises(br.BranchRolloutError) as e:
             br.op_gemm(br.BF16, 4, A, W, b, ref, variant=variant)
         assert e.value.code == -1
+
+
+@pytest.mark.parametrize("M,N,K,form", [(4404, 1024, 1024, 3), (1101, 3072, 1024, 5), (1101, 1024, 1024, 0)])
+def test_gemm_fp32_automatic_choice_of_every_form(lib, M, N, K, form):
+    """Shapes that the size rule gives to 64x128, 128x128 and 32x32 tiles: as the form by itself, and right against fp64."""
+    rng = np.random.default_rng(N + M)
+    A, W, b = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (N, K), (N,)))
+    outs = []
+    for variant in (-1, form):
+        out = torch.empty((M, N), device=DEV)
+        br.op_gemm(br.F32, 1, dev(A), dev(W), dev(b), out, variant=variant)
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])
+    rows = np.r_[0:3, 63:66, 127:130, M - 130:M - 126, M - 3:M]
+    # fp32 sums of K products: about sqrt(K) 2^-24 of the norm
+    assert rel_l2(host(outs[0])[rows], dit.gelu_tanh(A[rows].astype(np.float64) @ W.astype(np.float64).T + b)) < 3e-6
+
+
+@pytest.mark.parametrize("height", [4, 5, 6, 7, 8])
+@pytest.mark.parametrize("M,N,K,L", [(37 * 1101, 1024, 128, 1101), (438 * 93, 1020, 384, 93), (2037 * 20, 1024, 256, 20)])
+def test_gemm_persistent_tiles_after_the_first(lib, height, M, N, K, L):
+    """Every workgroup takes two to five tiles: the operand stream crosses tile boundaries, the next tile's first stages are
+    waited for with the epilogue's stores in flight.  Every element of every output form against the 128x128 kernel, which has one
+    tile per workgroup, bit for bit; samples longer and shorter than a wave's rows."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(height + K)
+    A, W = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((M, K), (N, K)))
+    b, x0 = torch.randn(N, generator=g, device=DEV), torch.randn((M, N), generator=g, device=DEV)
+    mods = torch.randn((7, N), generator=g, device=DEV)
+    cond = (torch.arange(M // L, device=DEV) % 7).int()
+    for mode, dt in ((4, torch.float32), (0, torch.bfloat16), (1, torch.bfloat16), (2, torch.float32)):
+        outs = []
+        for variant in (STREAM[height], 5):
+            out = x0.clone() if mode == 2 else torch.full((M, N), -9.0, dtype=dt, device=DEV)
+            br.op_gemm(br.BF16, mode, A, W, b, out, mods=mods if mode == 2 else None, cond=cond if mode == 2 else None, L=L, variant=variant)
+            outs.append(out)
+        assert torch.equal(outs[0], outs[1]), (mode, height)
