@@ -55,6 +55,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // Matrix instructions on accumulators that stay in the accumulation registers.  (From the builtin the compiler keeps
 // some of the 64 blocks in vector registers and moves them back and forth.)  The first of a tile starts from zero.
+// The compiler does not know that these are matrix instructions and adds no wait states: two between a vector instruction that
+// writes an operand and the instruction, nineteen before a result is read.  The operands therefore come straight from LDS reads
+// (for which it does wait) and the accumulators are touched by nothing else until the s_nop behind the loop;
+// tests/test_matrix_instructions.py checks the built code for it.
 __device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& w, const bf16x8& a) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(a));
 }
