@@ -267,8 +267,10 @@ static br_status ln_mode(int mode, const LnArgs& ln, const T* W, int M, int N, i
 
 br_status launch_ln_gemm(int dtype, int mode, const LnArgs& ln, const void* W, int M, int N, int K, const EpiArgs& ea,
                          hipStream_t st) {
-  ProfScope ps(st, PROF_GEMM + mode * 8, 2.0 * M * N * K);
-  if (dtype == BR_BF16) return ln_mode<bf16, bf16>(mode, ln, (const bf16*)W, M, N, K, ea, st);
+  if (dtype == BR_BF16) {  // (only bf16 GEMMs are instrumented)
+    ProfScope ps(st, PROF_GEMM + mode * 8, 2.0 * M * N * K);
+    return ln_mode<bf16, bf16>(mode, ln, (const bf16*)W, M, N, K, ea, st);
+  }
   return ln_mode<float, float>(mode, ln, (const float*)W, M, N, K, ea, st);
 }
 

@@ -578,3 +578,18 @@ def test_gemm_persistent_tiles_after_the_first(lib, height, M, N, K, L):
             br.op_gemm(br.BF16, mode, A, W, b, out, mods=mods if mode == 2 else None, cond=cond if mode == 2 else None, L=L, variant=variant)
             outs.append(out)
         assert torch.equal(outs[0], outs[1]), (mode, height)
+
+
+def test_profile_lists_gemms_of_bf16_networks_only(lib):
+    """Ids 0..47 are bf16 GEMMs (epilogue * 8 + kernel); an fp32 network has none, whether or not its small GEMMs normalise
+    their rows themselves."""
+    for dtype, expect in ((synth.F32, False), (synth.BF16, True)):
+        cfg = synth.model_cfg(1, 64, 1, (16, 1, 8, 8), (1, 2, 2), 5, dtype)
+        br.profile_enable(True)
+        try:
+            _velocity_case(cfg, 1, 2, 0.5, 1)
+            torch.cuda.synchronize()
+            ids = br.profile_read()
+        finally:
+            br.profile_enable(False)
+        assert any(i < 48 for i in ids) == expect, ids
