@@ -30,8 +30,6 @@ size_t plan_workspace(const br_model* m, int n_cond, int max_batch, long long v_
   f.modmap = (int*)take(B * 4);
   f.vrows = (int*)take(B * 4);
   f.h1 = (float*)take(G * H * 4);
-  // (room that kernels of an earlier form used: the sizes that callers have planned with stay what they were)
-  for (size_t n : {B * 4, B * 4, G * 4, G * 4, G * 256 * 4, G * H * 4}) take(n);
   f.pooled = (float*)take((size_t)n_cond * m->cd * 4);
   f.pool_lin = (float*)take((size_t)n_cond * H * 4);
   f.cvec = (float*)take(G * H * 4);

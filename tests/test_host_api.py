@@ -96,3 +96,22 @@ def test_model_create_validates_shapes():
     fake[3] = 0x1004                                                       # misaligned
     assert lib.br_model_create(C.byref(cfg), fake, br.W_COUNT, C.byref(h)) == -1
     assert lib.br_workspace_bytes(None, None, 4) == 0
+
+
+@pytest.mark.parametrize("dtype,hidden,heads", [(br.F32, 64, 4), (br.BF16, 128, 2)])
+def test_workspace_is_what_the_network_uses(dtype, hidden, heads):
+    """Bytes per sample of br_velocity's workspace (as many conditions as samples): the buffers of one network evaluation and
+    nothing else.  256 samples at a time, so that the alignment of the buffers drops out."""
+    lib = br.load()
+    blocks, ratio, cond, cd, es = 2, 4, 8, 64, 4 if dtype == br.F32 else 2
+    cfg = br.ModelCfg(blocks, hidden, heads, ratio, 4, 1, 8, 8, 1, 2, 2, cond, cd, dtype)
+    fake = (C.c_void_p * br.W_COUNT)(*[0x1000] * br.W_COUNT)
+    h = C.c_void_p()
+    assert lib.br_model_create(C.byref(cfg), fake, br.W_COUNT, C.byref(h)) == 0
+    n_img, patch = 16, 16
+    L, A = n_img + cond, blocks * 6 * hidden + 2 * hidden
+    floats = 3 * hidden + cd + A + cond * hidden + L * hidden     # time MLP, pooled rows, adaLN vectors, tokens, stream
+    ints = 3                                                      # group, velocity row and condition of a sample
+    acts = n_img * patch + L * hidden * (1 + 3 + ratio)           # patches; normalised rows, QKV, hidden layer
+    assert lib.br_workspace_bytes(None, h, 512) - lib.br_workspace_bytes(None, h, 256) == 256 * (4 * (floats + ints) + es * acts)
+    lib.br_model_free(h)
