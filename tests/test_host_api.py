@@ -104,11 +104,11 @@ def test_workspace_is_what_the_network_uses(dtype, hidden, heads):
     nothing else.  256 samples at a time, so that the alignment of the buffers drops out."""
     lib = br.load()
     blocks, ratio, cond, cd, es = 2, 4, 8, 64, 4 if dtype == br.F32 else 2
-    cfg = br.ModelCfg(blocks, hidden, heads, ratio, 4, 1, 8, 8, 1, 2, 2, cond, cd, dtype)
+    cfg = br.ModelCfg(blocks, hidden, heads, ratio, 16, 1, 8, 8, 1, 2, 2, cond, cd, dtype)
     fake = (C.c_void_p * br.W_COUNT)(*[0x1000] * br.W_COUNT)
     h = C.c_void_p()
     assert lib.br_model_create(C.byref(cfg), fake, br.W_COUNT, C.byref(h)) == 0
-    n_img, patch = 16, 16
+    n_img, patch = 16, 64
     L, A = n_img + cond, blocks * 6 * hidden + 2 * hidden
     floats = 3 * hidden + cd + A + cond * hidden + L * hidden     # time MLP, pooled rows, adaLN vectors, tokens, stream
     ints = 3                                                      # group, velocity row and condition of a sample
