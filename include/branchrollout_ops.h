@@ -20,8 +20,8 @@ extern "C" {
  *               gate row r at mods + r*mods_stride + gate_off, cond dev [M / L]
  *            4: out[m, n] = acc                  out fp32
  * BR_BF16 needs K % 64 == 0, lda % 8 == 0, ldw % 8 == 0; N % 4 == 0 always.
- * variant: bits 0..3 = kernel (-1 = automatic; 0 = 32x32 tiles; 1 / 2 / 3 / 4 / 5 / 6 = 128x128 in eight waves /
- * 64x64 / 64x128 / 256x256 / 128x128 / 256x128 tile per workgroup; 7 = persistent streaming kernel with tiles of
+ * variant: bits 0..3 = kernel (-1 = automatic; 0 = 32x32 tiles; 1 / 2 / 3 / 4 / 5 = 128x128 in eight waves /
+ * 64x64 / 64x128 / 256x256 / 128x128 tile per workgroup, 6 = as 5; 7 = persistent streaming kernel with tiles of
  * 256 rows x 256 columns, 8 / 9 / 10 / 11 = the same with 128 / 160 / 192 / 224 rows, need K % 128 == 0.  BR_F32
  * has 0, 3 and 5 and takes its own choice where another is asked for or does not apply.  bf16 only: bits 4..11 =
  * column-group width of the tile walk, 0 = the kernel's own choice; for the persistent kernel bits 24..30 = rows of a

@@ -29,7 +29,7 @@ static br_status gemm_tile_launch(const bf16* A, int lda, const bf16* W, int ldw
 }
 
 enum {  // bits 0..3 of a variant; TILE_STREAM + 1 .. + 4: the persistent kernel with 4 .. 7 times 32 rows a tile
-  TILE_32 = 0, TILE_128_W8 = 1, TILE_64 = 2, TILE_64_128 = 3, TILE_256 = 4, TILE_128 = 5, TILE_256_128 = 6, TILE_STREAM = 7
+  TILE_32 = 0, TILE_128_W8 = 1, TILE_64 = 2, TILE_64_128 = 3, TILE_256 = 4, TILE_128 = 5, TILE_STREAM = 7
 };
 
 // The kernel for a problem size.  r = tiles of a kind per compute unit.  (The part for small problems is from 410
@@ -93,6 +93,7 @@ static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, in
     tile = variant & 15;
     group_n = (variant >> 4) & 255;
     height = 8;
+    if (tile == 6) tile = TILE_128;  // (256x128 tiles in earlier versions)
     if (tile > TILE_STREAM && tile <= TILE_STREAM + 4) {
       height = tile - TILE_STREAM + 3;
       tile = TILE_STREAM;
@@ -107,7 +108,6 @@ static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, in
     case TILE_64_128: return gemm_tile_launch<64, 128, 2, 2, 3, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
     case TILE_256: return gemm_tile_launch<256, 256, 2, 4, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
     case TILE_128: return gemm_tile_launch<128, 128, 2, 2, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
-    case TILE_256_128: return gemm_tile_launch<256, 128, 4, 2, 3, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
     case TILE_STREAM: return launch_gemm_bf16_stream(MODE, A, lda, W, ldw, M, N, K, ea, height, group_n, row_block, st);
   }
   return fail(BR_EINVAL, "gemm: unknown variant");

@@ -186,10 +186,8 @@ __device__ inline void wave_epilogue_bf16_full(const f32x16_e (&acc)[TN][TM], ch
   }
 }
 
-// Returns a lower bound on the number of store instructions the wave has issued (every lane
-// active): 4 per 16-row pass on the branch-free path, unknown (0) on the guarded ones.
 template <int TM, int TN, int MODE, typename TOUT>
-__device__ inline int wave_epilogue(const f32x16_e (&acc)[TN][TM], char* ebuf, int m_base, int n_base, int M, int N,
+__device__ inline void wave_epilogue(const f32x16_e (&acc)[TN][TM], char* ebuf, int m_base, int n_base, int M, int N,
                                     const Epilogue<MODE, TOUT>& epi, int lane) {
   static_assert(TN == 2, "waves own 64 output columns");
   const int rps = epi.rows_per_sample();
@@ -198,15 +196,12 @@ __device__ inline int wave_epilogue(const f32x16_e (&acc)[TN][TM], char* ebuf, i
   } else if (m_base + TM * 32 <= M && n_base + TN * 32 <= N) {
     if constexpr ((MODE == EPI_BIAS || MODE == EPI_BIAS_GELU) && std::is_same<TOUT, bf16>::value) {
       wave_epilogue_bf16_full<TM, TN, MODE>(acc, ebuf, m_base, n_base, epi, lane);
-      return TM * 4;
     } else {
       wave_epilogue_pair<true, TM, TN, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
-      return TM * 2 * 4;
     }
   } else {
     wave_epilogue_pair<false, TM, TN, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
   }
-  return 0;
 }
 
 }  // namespace br
