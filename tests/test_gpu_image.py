@@ -150,3 +150,24 @@ def test_reevaluated_logprob_on_an_edge_of_every_retained_step(image_run, part):
         _, std = sde.step_coefficients(sched["t"][i], sched["t"][i + 1], sched["sigma"][i])
         ref = sde.transition_logp(host(r["z"][g]).astype(np.float64), mu, std, True)
         assert abs(got[e] - ref) <= 1e-3 * abs(ref), (i, g, got[e], ref)
+
+
+def test_logprob_under_the_same_policy_and_in_other_batches(image_run):
+    """Velocities have the same bits in whatever batch a parent is evaluated.  Re-evaluations in frontiers of mixed parents and in
+    batches of three then differ only by how many workgroups share an edge's elements: each adds its sum rounded to 2^-12,
+    up to 128 of them in a total of about 65 536, 3e-7.  The rollout's own log-probs differ by the rounding of the stored
+    latents as well: 2^-24 of about 1 over a noise scale of 0.07 is 1e-6 of a normal deviate, in both directions."""
+    r = image_run
+    ids = r.get("ids")
+    if ids is None:
+        pytest.skip("needs the kept-edge set of the pruning test")
+    outs = []
+    for ws in (r["ws"], bytes_buffer(br.workspace_bytes(r["t"], r["model"], 3))):
+        out = torch.empty(len(ids), device=DEV)
+        br.logprob(r["t"], r["model"], r["sched"], cond_dev(r["cfg"], r["cond"]), r["z"], ids, out, ws)
+        outs.append(host(out))
+    lp = host(r["logp"])[ids]
+    between, same = (np.abs(outs[0] - outs[1]) / np.abs(lp)).max(), (np.abs(outs[0] - lp) / np.abs(lp)).max()
+    print("same-policy log-probs: %.2e between batches, %.2e from the rollout" % (between, same), flush=True)
+    assert between < 1e-6
+    assert same < 2e-6

@@ -66,6 +66,7 @@ def test_large_image_shape_full_frontier_agrees_with_the_checked_batch(large_cas
     # grouped launch order): far inside the bf16 tolerance of the oracle check above
     for b in range(3):
         assert_velocity(cfg, got[b], r["v3"][b], 2e-3, "large image, sample %d in the batch of 32" % b)
+        assert np.array_equal(got[b], r["v3"][b])      # every kernel adds in the same order
     # and no sample of the batch is a copy of another or left unwritten
     n = np.linalg.norm(got, axis=1)
     assert np.all(n > 0.5 * n[0]) and np.all(n < 2 * n[0])
@@ -109,6 +110,7 @@ def test_video_shape_batch_of_eight_agrees_with_single_samples(video_case):
         v1 = torch.empty((1, sz["D"]), device=DEV)
         br.velocity(r["model"], dev(r["z"][b:b + 1]), 0.3, cond_dev(cfg, r["cond"]), r["cidx"][b:b + 1], v1, ws)
         assert_velocity(cfg, r["v"][b], host(v1)[0], 2e-3, "video, sample %d alone against the batch of 8" % b)
+        assert np.array_equal(r["v"][b], host(v1)[0])
     assert len({r["v"][b].tobytes() for b in range(8)}) == 8
 
 
