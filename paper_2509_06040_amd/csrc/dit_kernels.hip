@@ -1,6 +1,5 @@
-// Velocity network: the memory-bound and small kernels (batch prologue, conditioning path, LayerNorm-modulate) and the fp32 GEMM /
-// attention used by BR_F32 models.  The bf16 MFMA GEMM and flash attention live in
-// gemm_bf16.hip and attn_bf16.hip.
+// Velocity network: the memory-bound and small kernels (batch prologue, conditioning path, LayerNorm-modulate) and the
+// dispatch by type to the GEMMs (gemm_bf16.hip, gemm_f32.hip) and the attention (attn_bf16.hip, attn_f32.hip).
 #include <type_traits>
 
 #include "common.h"

@@ -1,5 +1,5 @@
 // fp32 GEMM: C[m, n] = sum_k A[m, k] W[n, k] with the fused epilogues, on the matrix cores
-// (v_mfma_f32_32x32x2_f32, full fp32; 157 TFLOP/s nominal, twice the vector rate).  This file holds the
+// (v_mfma_f32_32x32x2_f32 and 16x16x4, full fp32; 157 TFLOP/s nominal, twice the vector rate).  This file holds the
 // choice between the tile kernel (gemm_tile.h) and the kernel for small problems (gemm_small.hip), and a vector
 // kernel for operands that cannot be fetched in 16-byte pieces.
 #include <algorithm>

@@ -246,8 +246,9 @@ br_status launch_gemm_small(int dtype, int mode, const void* A, int lda, const v
   return small_mode<float, float>(mode, (const float*)A, lda, (const float*)W, ldw, M, N, K, ea, st);
 }
 
-// The normalised rows share the 64 KB of LDS with the slots: 32 KB of them, i.e. K <= 256 in fp32 and 512 in bf16.  Up
-// to one workgroup a compute unit: beyond, what every column tile does again for itself takes longer than the launch.
+// The normalised rows take at most 32 KB of LDS beside 16 or 24 KB of slots, i.e. K <= 256 in fp32 and 512 in bf16: three
+// workgroups fit a compute unit, and a lane holds a row's eighth in registers.  Up to one workgroup a unit: beyond, what
+// every column tile does again for itself takes longer than the launch.
 bool ln_gemm_fits(int dtype, int M, int N, int K, const void* x, const void* mods, int A, int shift_off, int scale_off) {
   const size_t es = dtype == BR_BF16 ? 2 : 4;
   return (size_t)K * es <= 1024 && (K * es) % 16 == 0 && (long long)cdiv(M, BM) * cdiv(N, BN) <= device_cu_count() &&
