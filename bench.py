@@ -50,16 +50,16 @@ ORDER = ("image", "video", "image_large")
 # same counter reads for a plain 1 GiB device copy; see profiles/hot_kernels_hbm_traffic.md.  Keyed
 # by (workload, kernel label); valid only for the kernel sources hashed beside the figures.
 TRAFFIC = {
-    'image_large|gemm_bf16[bias_gate_residual,256x256 persistent stream]': dict(bytes_per_launch=6612766740, sources=('gemm_bf16_stream.hip', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='d08d8047b1b8c4977796a3d75174dee298cd7cee'),
-    'image_large|gemm_bf16[bias_gelu,256x256 persistent stream]': dict(bytes_per_launch=9183573064, sources=('gemm_bf16_stream.hip', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='d08d8047b1b8c4977796a3d75174dee298cd7cee'),
-    'image_large|gemm_bf16[bias,256x256 persistent stream]': dict(bytes_per_launch=7166651914, sources=('gemm_bf16_stream.hip', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='d08d8047b1b8c4977796a3d75174dee298cd7cee'),
-    'image_large|attn_bf16[d128]': dict(bytes_per_launch=2340423731, sources=('attn_bf16.hip',), sha1='deb7cb68be1bb871d37e9d8f4121d812368a0ff2'),
-    'image_large|ln_modulate': dict(bytes_per_launch=1213816248, sources=('dit_kernels.hip', 'common.h'), sha1='123bdb315659e2bc89a1f7bd3071b9530aa623d9'),
-    'image|gemm_bf16[bias_gate_residual,256x256 persistent stream]': dict(bytes_per_launch=636361196, sources=('gemm_bf16_stream.hip', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='d08d8047b1b8c4977796a3d75174dee298cd7cee'),
-    'image|gemm_bf16[bias_gelu,256x256 persistent stream]': dict(bytes_per_launch=654394143, sources=('gemm_bf16_stream.hip', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='d08d8047b1b8c4977796a3d75174dee298cd7cee'),
-    'image|gemm_bf16[bias,256x256 persistent stream]': dict(bytes_per_launch=502440038, sources=('gemm_bf16_stream.hip', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='d08d8047b1b8c4977796a3d75174dee298cd7cee'),
-    'image|attn_bf16[d64]': dict(bytes_per_launch=258966323, sources=('attn_bf16.hip',), sha1='deb7cb68be1bb871d37e9d8f4121d812368a0ff2'),
-    'image|ln_modulate': dict(bytes_per_launch=193824737, sources=('dit_kernels.hip', 'common.h'), sha1='123bdb315659e2bc89a1f7bd3071b9530aa623d9'),
+    'image_large|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=6952045158, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
+    'image_large|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=9131821466, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
+    'image_large|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=7260456594, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
+    'image_large|attn_bf16[d128]': dict(bytes_per_launch=2336352973, sources=('attn_bf16.hip',), sha1='deb7cb68be1bb871d37e9d8f4121d812368a0ff2'),
+    'image_large|ln_modulate': dict(bytes_per_launch=1213816320, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='4f9257b4d8c9ab0f648887a8347f2979685e772d'),
+    'image|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=546744704, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
+    'image|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=679507439, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
+    'image|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=508911121, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
+    'image|attn_bf16[d64]': dict(bytes_per_launch=258962227, sources=('attn_bf16.hip',), sha1='deb7cb68be1bb871d37e9d8f4121d812368a0ff2'),
+    'image|ln_modulate': dict(bytes_per_launch=193815347, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='4f9257b4d8c9ab0f648887a8347f2979685e772d'),
 }
 
 
