@@ -26,14 +26,24 @@ __host__ __device__ inline PhiloxKey philox_key(uint64_t seed) {
   return k;
 }
 
+// a ^ b ^ c: one instruction on gfx950 (truth table 0x96), which the compiler does not form by itself.  A round is two
+// 32x32 -> 64 bit products and two of these; as pairs of exclusive-ors they are a third of a block's vector instructions.
+__host__ __device__ inline uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+  return a ^ b ^ c;
+#endif
+}
+
 __host__ __device__ inline void philox4x32_10(const PhiloxKey& key, uint32_t c0, uint32_t c1,
                                               uint32_t c2, uint32_t c3, uint32_t out[4]) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ key.k0[r];
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ key.k1[r];
+    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, key.k0[r]);
+    const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, key.k1[r]);
     c1 = (uint32_t)p1;
     c3 = (uint32_t)p0;
     c0 = n0;

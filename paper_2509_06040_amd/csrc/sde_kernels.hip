@@ -77,50 +77,67 @@ __device__ inline bool accumulate_share(unsigned long long* word, float s, int n
   return true;
 }
 
-// One grid row per parent (blockIdx.y); KC = children per parent handled in registers; a thread
-// has UNR quads of z and of v in flight and walks the row with the grid's stride.  The last
-// block of a row writes logp of the parent's KC children: (c0 - sum xi^2 / 2) * inv_div, 0 on
-// a deterministic step.  words: one per child, index b*KC + k.
-template <int KC, int UNR, int NT>
+// One grid row per parent (blockIdx.y); KC = children per parent handled in registers (KC > 1: a split, whose children share
+// xi_0); a thread has UNR quads of z and of v in flight and walks the row with the grid's stride.  The last block of a row
+// writes logp of the parent's KC children: (c0 - sum xi^2 / 2) * inv_div, 0 on a deterministic step.  words: one per child,
+// index b*KC + k.
+//
+// What bounds it: HBM on plain steps (8 rows of 2.1 million elements: 32.5 us, 6.2 TB/s).  A split (4 rows into 8 children of
+// that size, 134 MB) took 30.5 us and takes 25.3, 5.3 TB/s: the noise of a quad costs about 1500 cycles of a SIMD, so
+//  - the next quads are fetched before the noise of the current ones is formed, and there is one branch-free body, in which
+//    the generator blocks of parent and children interleave (29.2 us);
+//  - the atomics of a block's children leave one wave together instead of one round trip after the other (25.3 us).
+// 1024 threads a block, two blocks a unit and two quads in flight are within 4 % or slower.
+template <int KC, bool NOISE, int UNR, int NT>
 __global__ __launch_bounds__(NT) void sde_step_kernel(float* __restrict__ z, const float* __restrict__ v, int v_compact,
                                                        long long D, int n_nodes, int off_p, int off_c, int width_p,
-                                                       int is_split, StepCoef cf, PhiloxKey key, int step,
+                                                       StepCoef cf, PhiloxKey key, int step,
                                                        unsigned long long* __restrict__ words, float* __restrict__ logp) {
-  __shared__ float red[NT / 64];
+  __shared__ float red[KC][NT / 64];
   const int b = blockIdx.y;
   const int c = b / width_p, j = b - c * width_p;
   const int prow = c * n_nodes + off_p + j;
-  const int crow0 = c * n_nodes + off_c + (is_split ? j * KC : j);
+  const int crow0 = c * n_nodes + off_c + j * KC;
   const float4* zp = reinterpret_cast<const float4*>(z + (size_t)prow * D);
   const float4* vp = reinterpret_cast<const float4*>(v + (size_t)(v_compact ? b : prow) * D);
   const long long nq = D >> 2;
   float acc[KC];
 #pragma unroll
   for (int k = 0; k < KC; ++k) acc[k] = 0.f;
-  for (long long q0 = (long long)blockIdx.x * (NT * UNR) + threadIdx.x; q0 < nq; q0 += (long long)gridDim.x * (NT * UNR)) {
+  const long long stride = (long long)gridDim.x * (NT * UNR);
+  long long q0 = (long long)blockIdx.x * (NT * UNR) + threadIdx.x;
+  float4 zn[UNR], vn[UNR];  // the next quads: in flight while the noise of the current ones is formed
+  auto fetch = [&](long long at) {
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const long long q = min(at + u * NT, nq - 1);
+      zn[u] = zp[q];
+      vn[u] = vp[q];
+    }
+  };
+  fetch(q0);
+  for (; q0 < nq; q0 += stride) {
     float4 zz[UNR], vv[UNR];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      const long long q = q0 + u * NT;
-      if (q < nq) {
-        zz[u] = zp[q];
-        vv[u] = vp[q];
-      }
+      zz[u] = zn[u];
+      vv[u] = vn[u];
     }
+    fetch(q0 + stride);
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       const long long q = q0 + u * NT;
       if (q >= nq) break;
       float mu[4] = {fmaf(cf.a_z, zz[u].x, cf.a_v * vv[u].x), fmaf(cf.a_z, zz[u].y, cf.a_v * vv[u].y),
                      fmaf(cf.a_z, zz[u].z, cf.a_v * vv[u].z), fmaf(cf.a_z, zz[u].w, cf.a_v * vv[u].w)};
-      float x0[4] = {0.f, 0.f, 0.f, 0.f};
-      if (cf.noise && is_split) philox_normal4(key, (uint32_t)q, (uint32_t)prow, (uint32_t)step, TAG_XI0, x0);
+      float x0[4];
+      if (NOISE && KC > 1) philox_normal4(key, (uint32_t)q, (uint32_t)prow, (uint32_t)step, TAG_XI0, x0);
 #pragma unroll
       for (int k = 0; k < KC; ++k) {
         float xi[4] = {0.f, 0.f, 0.f, 0.f};
-        if (cf.noise) {
+        if (NOISE) {
           philox_normal4(key, (uint32_t)q, (uint32_t)(crow0 + k), (uint32_t)step, TAG_ETA, xi);
-          if (is_split) {
+          if (KC > 1) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) xi[e] = cf.ca * x0[e] + cf.cb * xi[e];
           }
@@ -135,16 +152,21 @@ __global__ __launch_bounds__(NT) void sde_step_kernel(float* __restrict__ z, con
       }
     }
   }
-  float s[KC];
 #pragma unroll
-  for (int k = 0; k < KC; ++k) s[k] = block_sum<NT>(acc[k], red);
-  if (threadIdx.x == 0) {
+  for (int k = 0; k < KC; ++k) {
+    const float w = wave_sum(acc[k]);
+    if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = w;
+  }
+  __syncthreads();
+  // a lane per child: the atomics' round trips (1-2 us across the compute dies) run side by side
+  if (threadIdx.x < KC) {
+    const int k = threadIdx.x;
+    float s = 0.f;
 #pragma unroll
-    for (int k = 0; k < KC; ++k) {
-      double tot;
-      if (accumulate_share(words + (size_t)b * KC + k, s[k], gridDim.x, &tot))
-        logp[crow0 + k] = cf.noise ? (float)((cf.c0 - 0.5 * tot) * cf.inv_div) : 0.f;
-    }
+    for (int w = 0; w < NT / 64; w += 2) s += red[k][w] + red[k][w + 1];
+    double tot;
+    if (accumulate_share(words + (size_t)b * KC + k, s, gridDim.x, &tot))
+      logp[crow0 + k] = NOISE ? (float)((cf.c0 - 0.5 * tot) * cf.inv_div) : 0.f;
   }
 }
 
@@ -326,9 +348,12 @@ br_status launch_sde_step(const br_tree* t, const br_sched* s, uint64_t seed, in
   dim3 grid(sde_grid_x(D, n_par), n_par);
   // algorithmic bytes: z and v of every parent read once, every child written once
   ProfScope ps(st, PROF_SDE_STEP, (double)n_par * (2.0 + K) * 4.0 * (double)D);
-#define BR_SDE_ARGS z, v, v_compact, (long long)D, t->n_nodes, off_p, off_c, t->width[i], split, cf, key, i, words, logp
+#define BR_SDE_ARGS z, v, v_compact, (long long)D, t->n_nodes, off_p, off_c, t->width[i], cf, key, i, words, logp
 #define BR_SDE_LAUNCH(KC) \
-  hipLaunchKernelGGL((sde_step_kernel<KC, BR_SDE_UNROLL, BR_SDE_THREADS>), grid, dim3(BR_SDE_THREADS), 0, st, BR_SDE_ARGS)
+  do { \
+    if (cf.noise) hipLaunchKernelGGL((sde_step_kernel<KC, true, BR_SDE_UNROLL, BR_SDE_THREADS>), grid, dim3(BR_SDE_THREADS), 0, st, BR_SDE_ARGS); \
+    else hipLaunchKernelGGL((sde_step_kernel<KC, false, BR_SDE_UNROLL, BR_SDE_THREADS>), grid, dim3(BR_SDE_THREADS), 0, st, BR_SDE_ARGS); \
+  } while (0)
   if (K == 1) BR_SDE_LAUNCH(1);
   else if (K == 2) BR_SDE_LAUNCH(2);
   else if (K == 3) BR_SDE_LAUNCH(3);
