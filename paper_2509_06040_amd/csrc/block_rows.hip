@@ -1,0 +1,514 @@
+// The row-local part of a network block in one launch, for narrow networks: everything between two attentions works on
+// each row by itself, so a workgroup takes 16 RT rows of the residual stream through
+//   output projection -> gated residual -> LayerNorm-modulate -> MLP (GELU) -> gated residual -> LayerNorm-modulate
+//   -> QKV projection of the next block, or final linear and unpatchify behind the last one,
+// and, as the head of the network, through patch gathering -> patch embedding -> LayerNorm-modulate -> QKV projection of
+// the first block.  A block is then two launches (attention, this) instead of five to seven, and nothing but the residual
+// rows and the QKV rows passes through memory.
+//
+// What bounds it: latency with few rows, then the weights, 12 H^2 of them, that every workgroup streams through its compute
+// unit.  The activations stay in LDS.  Every wave fetches the weights of its own columns, 16 rows of 128 bytes a step, in whole
+// lines into a ring of its own (global -> LDS directly), 8 KB ahead and across the ends of the phases: the next phase's
+// weights are under way while a phase's last products, its barrier and the LayerNorm run, and no barrier waits for weights.
+// (Fetched straight into registers, in the layout of the matrix instruction, four lanes of a load touch four lines: 14
+// bytes a clock of a compute unit, a quarter of this.)  One loop serves all phases: most of the code runs for the first time in
+// each launch, and 20 KB more of it, with a phase each, cost 2 us.
+//
+// Every output is one chain over k in ascending order (gemm_frag.h), every rounding and every LayerNorm sum is where
+// the separate kernels have it: the results are theirs bit for bit, whatever the number of rows selects.
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+#include <utility>
+
+#include "common.h"
+#include "dit.h"
+#include "gemm_frag.h"
+#include "prof.h"
+
+namespace br {
+
+#define BR_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
+
+namespace {
+constexpr int NW = 8, NT = NW * 64;  // waves, threads
+constexpr int RING_B = 8192;         // LDS of a wave's weights in flight
+constexpr int LDS_LIMIT = 160 * 1024;
+
+}  // namespace
+
+// n / d for n d < 2^32 by a multiplication (a division is 35 instructions, one after the other)
+struct FastDiv {
+  unsigned m;
+  FastDiv() = default;
+  explicit FastDiv(int d) : m(d > 1 ? (unsigned)(((1ull << 32) + d - 1) / d) : 0u) {}
+  __device__ __forceinline__ int div(int n) const { return m ? (int)__umulhi((unsigned)n, m) : n; }
+};
+
+struct RowsArgs {
+  FastDiv by_L, by_H4, by_mq, by_pd, by_pw, by_ph, by_pt, by_gw, by_gh;
+  int M, L, n_img;                  // rows; rows and image rows of a sample
+  int H, RH, NTAIL;                 // hidden size, MLP width, columns of the tail (3 H or the patch vector)
+  float* x;                         // [M, H] residual stream
+  const float* mods;                // modulation vectors: per group, consecutive from mods_off (see the kernel)
+  int A, mods_off, mods_n;          // row length; offset and number of floats taken
+  const int* modmap;                // [samples] group (body)
+  const void* attn;                 // [M, H] (body)
+  const void *w0, *fc1_w, *fc2_w, *tail_w;  // w0: output projection, or patch embedding (head)
+  const float *b0, *fc1_b, *fc2_b, *tail_b;
+  void* qkv;                        // [M, 3 H]
+  int qcols;
+  float qscale;
+  Epilogue<EPI_UNPATCH, float> fin;
+  // head
+  SampleMap sm;
+  int s0, B, v_rows_mode;
+  int *modmap_out, *vrows;
+  const float *z, *pos, *cond_emb;
+  long long D;
+  int pd, lt, lh, lw, pt, ph, pw, gh, gw, Nc;
+  // LDS: byte offsets of the regions behind the residual rows
+  int o_act, o_hid, o_mods, o_bias, o_ring;
+};
+
+// Sum over groups of N consecutive lanes, at distances N / 2 ... 1 in turn (the order of __shfl_xor, without its trips to the LDS
+// unit).  Rotations by 8, 4 of 16 lanes reach the lane that the exclusive-or reaches, or one that holds the same sum.
+template <int N>
+__device__ __forceinline__ float lanes_sum(float x) {
+  static_assert(N >= 16, "whole rows of 16 lanes");
+  if constexpr (N == 64) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    x = __builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]);
+  }
+  if constexpr (N >= 32) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    x = __builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]);
+  }
+  auto add = [&](auto CTRL) { x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(CTRL)::value, 0xf, 0xf, true)); };
+  add(std::integral_constant<int, 0x128>{});  // row_ror:8
+  add(std::integral_constant<int, 0x124>{});  // row_ror:4
+  add(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+  add(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+  return x;
+}
+
+enum { ROWS_HEAD = 0, ROWS_BODY = 1, ROWS_LAST = 2 };
+
+template <typename T, int RT, int SPS, int KIND>
+__global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
+  constexpr int ES = (int)sizeof(T), BMR = 16 * RT, LPR = NT / BMR, V = 64 / LPR;
+  constexpr bool BF = ES == 2;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  char* const xs = lds;                 // residual rows, 16-byte chunk c of row r in slot c ^ (r & xm)
+  char* const act = lds + a.o_act;      // operand rows in stages of 128 bytes a row (gemm_frag.h)
+  char* const hid = lds + a.o_hid;      // MLP rows (head: patch rows), likewise
+  float* const smods = reinterpret_cast<float*>(lds + a.o_mods);
+  float* const sbias = reinterpret_cast<float*>(lds + a.o_bias);
+
+  const int H = a.H, H4 = H >> 2, M = a.M, L = a.L;
+  const int m0 = blockIdx.x * BMR;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int xm = (H & 63) == 0 ? 15 : (H & 31) == 0 ? 7 : 3;
+  const int b_first = a.by_L.div(m0);
+
+  if (KIND == ROWS_HEAD && blockIdx.x == 0) {  // per-sample maps of the batch
+    for (int i = tid; i < a.B; i += NT) {
+      const int b = a.s0 + i;
+      a.modmap_out[i] = a.sm.group ? a.sm.group[b] : a.sm.group0 + sample_cond(a.sm, b);
+      a.vrows[i] = a.v_rows_mode == 1 ? sample_row(a.sm, b) : (a.v_rows_mode == 2 ? i : b);
+    }
+  }
+  // behind the last block only image rows have an output
+  if (KIND == ROWS_LAST && m0 - b_first * L >= a.n_img && a.by_L.div(min(m0 + BMR, M) - 1) == b_first) return;
+
+  // ---- rows, modulation vectors and biases to LDS (global -> LDS directly, 1 KB per wave and instruction)
+  auto fill = [&](char* dst, const void* src) {
+    const unsigned d = (unsigned)(uintptr_t)BR_LPTR(dst);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(d), "v"(src) : "memory", "m0");
+  };
+  if (KIND != ROWS_HEAD) {
+    const int n_act = BMR * (((H * ES + 127) >> 7) * 8), kc = H * ES / 16;
+    for (int p = wv; p * 64 < n_act; p += NW) {
+      const int i = p * 64 + lane, row = (i >> 3) & (BMR - 1), c = (i / (8 * BMR)) * 8 + ((i & 7) ^ ((row >> 1) & 7));
+      fill(act + p * 1024, reinterpret_cast<const char*>(a.attn) + (size_t)min(m0 + row, M - 1) * H * ES + min(c, kc - 1) * 16);
+    }
+  }
+  for (int p = wv; p * 64 < BMR * H4; p += NW) {
+    const int i = p * 64 + lane, row = a.by_H4.div(i), c = (i - row * H4) ^ (row & xm), m = min(m0 + row, M - 1);
+    const float* src = a.x + (size_t)m * H;
+    if (KIND == ROWS_HEAD) {  // what the patch embedding is added to, or the embedded condition token
+      const int b = a.by_L.div(m), tok = m - b * L;
+      src = tok < a.n_img ? a.pos + (size_t)tok * H : a.cond_emb + ((size_t)sample_cond(a.sm, a.s0 + b) * a.Nc + (tok - a.n_img)) * H;
+    }
+    fill(xs + p * 1024, src + c * 4);
+  }
+  const int b_last = a.by_L.div(min(m0 + BMR, M) - 1), mq = a.mods_n >> 2, n_mods = (b_last - b_first + 1) * mq;
+  for (int p = wv; p * 64 < n_mods; p += NW) {
+    const int i = min(p * 64 + lane, n_mods - 1), s = a.by_mq.div(i), b = b_first + s;
+    const int g = KIND != ROWS_HEAD ? a.modmap[b] : a.sm.group ? a.sm.group[a.s0 + b] : a.sm.group0 + sample_cond(a.sm, a.s0 + b);
+    fill(reinterpret_cast<char*>(smods) + p * 1024, a.mods + (size_t)g * a.A + a.mods_off + (i - s * mq) * 4);
+  }
+  // biases: first product | FC1 | FC2 | tail
+  const int nb1 = H4, nb2 = KIND == ROWS_HEAD ? nb1 : nb1 + (a.RH >> 2), nb3 = KIND == ROWS_HEAD ? nb2 : nb2 + H4,
+            nb4 = nb3 + (a.NTAIL >> 2);
+  for (int p = wv; p * 64 < nb4; p += NW) {
+    const int i = min(p * 64 + lane, nb4 - 1);
+    const float* src = i < nb1 ? a.b0 + i * 4 : i < nb2 ? a.fc1_b + (i - nb1) * 4 : i < nb3 ? a.fc2_b + (i - nb2) * 4 : a.tail_b + (i - nb3) * 4;
+    fill(reinterpret_cast<char*>(sbias) + p * 1024, src);
+  }
+  if (KIND == ROWS_HEAD) {  // patch vectors (c, dt, dh, dw) of the image rows
+    for (int e = tid; e < BMR * a.pd; e += NT) {
+      const int row = a.by_pd.div(e), el = e - row * a.pd, m = min(m0 + row, M - 1), b = a.by_L.div(m), tok = min(m - b * L, a.n_img - 1);
+      const int t1 = a.by_gw.div(tok), tt = a.by_gh.div(t1), tw = tok - t1 * a.gw, th = t1 - tt * a.gh;
+      const int e1 = a.by_pw.div(el), e2 = a.by_ph.div(e1), c = a.by_pt.div(e2);
+      const int dw = el - e1 * a.pw, dh = e1 - e2 * a.ph, dt = e2 - c * a.pt;
+      const long long idx = (((long long)c * a.lt + tt * a.pt + dt) * a.lh + th * a.ph + dh) * a.lw + tw * a.pw + dw;
+      const int byte = el * ES;
+      *reinterpret_cast<T*>(hid + (byte >> 7) * (BMR * 128) + row * 128 + ((((byte >> 4) & 7) ^ ((row >> 1) & 7)) << 4) + (byte & 15)) =
+          (T)a.z[(size_t)sample_row(a.sm, a.s0 + b) * a.D + idx];
+    }
+    // zeros to the end of the last step, whose weights are the row's first ones once more
+    const int end = (a.pd * ES + SPS * 128 - 1) / (SPS * 128) * (SPS * 8);
+    for (int row = tid; row < BMR; row += NT)
+      for (int c = a.pd * ES / 16; c < end; ++c)
+        *reinterpret_cast<float4*>(hid + (c >> 3) * (BMR * 128) + row * 128 + (((c & 7) ^ ((row >> 1) & 7)) << 4)) = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+
+  // ---- phases: 0 the first product, 1 FC1, 2 FC2, 3 the tail (head: 0 and 3).  One has N columns, 16 a block, dealt out to the
+  // waves; a row of its weights is kb bytes, in steps of SPS times 128.
+  constexpr int STEP_B = SPS * 2048, PD = RING_B / STEP_B;
+  struct Phase {
+    const char* w;
+    int N, kb, steps;
+  };
+  auto phase = [&](int ph) {
+    Phase p;
+    p.w = reinterpret_cast<const char*>(ph == 0 ? a.w0 : ph == 1 ? a.fc1_w : ph == 2 ? a.fc2_w : a.tail_w);
+    p.N = ph == 1 ? a.RH : ph == 3 ? a.NTAIL : H;
+    p.kb = (ph == 2 ? a.RH : KIND == ROWS_HEAD && ph == 0 ? a.pd : H) * ES;
+    p.steps = (p.kb + SPS * 128 - 1) / (SPS * 128);
+    return p;
+  };
+  // The fetch cursor: place in the wave's list of column blocks of all phases.  A load fills eight rows (lane = 8 row + slot), slot
+  // s of row r from chunk s ^ ((r >> 1) & 7).  Only a patch vector may end inside a step: what lies past its end is fetched from
+  // the start of the row.
+  char* const my_ring = lds + a.o_ring + wv * RING_B;
+  const unsigned ring = (unsigned)(uintptr_t)BR_LPTR(my_ring);
+  const int lrow = lane >> 3, chunk0 = ((lane & 7) ^ ((lrow >> 1) & 7)) * 16, chunk1 = chunk0 ^ 64;
+  int f_ph = 0, f_cb = wv, f_left, f_off, f_slot = 0;
+  unsigned f_row0, f_row1;
+  Phase fp = phase(0);
+  auto f_block = [&]() __attribute__((always_inline)) {  // to a block that exists; at the end of the list a last one stays
+    while (f_cb * 16 >= fp.N && f_ph < 3) {
+      f_ph = KIND == ROWS_HEAD ? 3 : f_ph + 1;
+      fp = phase(f_ph);
+      f_cb = wv;
+    }
+    f_row0 = (unsigned)min(f_cb * 16 + lrow, fp.N - 1) * (unsigned)fp.kb;
+    f_row1 = (unsigned)min(f_cb * 16 + 8 + lrow, fp.N - 1) * (unsigned)fp.kb;
+    f_off = 0;
+    f_left = fp.steps;
+  };
+  auto fetch = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < SPS; ++u) {
+      const unsigned dst = ring + f_slot + u * 2048;
+      const int at0 = f_off + u * 128 + chunk0, at1 = f_off + u * 128 + chunk1;
+      const unsigned o0 = f_row0 + (KIND != ROWS_HEAD || at0 < fp.kb ? at0 : 0), o1 = f_row1 + (KIND != ROWS_HEAD || at1 < fp.kb ? at1 : 0);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(o0), "s"(fp.w) : "memory", "m0");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst + 1024), "v"(o1), "s"(fp.w) : "memory", "m0");
+    }
+    f_slot = (f_slot + STEP_B) & (RING_B - 1);
+    f_off += SPS * 128;
+    if (--f_left == 0) {
+      f_cb += NW;
+      f_block();
+    }
+  };
+  // this lane's fragments of a step (of its row of the weights, and of its operand row of row tile 0): GemmFrag16
+  typedef typename GemmFrag16<T>::type frag;
+  constexpr int NF = GemmFrag16<T>::COUNT, FLIP = GemmFrag16<T>::FLIP;
+  const int fo = GemmFrag16<T>::offset(l16, lq);
+  int slot = 0;
+  // four columns of operand row `row` as T
+  auto put = [&](char* op, int row, int n, float v0, float v1, float v2, float v3) {
+    const int byte = n * ES;
+    store4<T>(reinterpret_cast<T*>(op + (byte >> 7) * (BMR * 128) + row * 128 + ((((byte >> 4) & 7) ^ ((row >> 1) & 7)) << 4) + (byte & 15)), v0, v1, v2, v3);
+  };
+  auto x_at = [&](int row, int c4) { return reinterpret_cast<float4*>(xs + row * H * 4 + ((c4 ^ (row & xm)) << 4)); };
+  int srow[RT];  // modulation vectors of this lane's row of each row tile (floats)
+#pragma unroll
+  for (int r = 0; r < RT; ++r) srow[r] = (a.by_L.div(min(m0 + r * 16 + l16, M - 1)) - b_first) * a.mods_n;
+
+  // LayerNorm of the rows in xs, modulated with the vectors at `shift` and `shift` + H, to `act`; LPR lanes a row, whose sums are
+  // those of ln_modulate_kernel's 64 (this lane holds what its lanes sub, sub + LPR, ... do).  The rows go to memory as well.
+  auto layer_norm = [&](int shift, bool store) {
+    const int row = tid / LPR, sub = tid % LPR, m = m0 + row;
+    const float* mr = smods + (a.by_L.div(min(m, M - 1)) - b_first) * a.mods_n + shift;
+    float4 v[V];
+    float p[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const int c4 = sub + LPR * i;
+      v[i] = c4 < H4 ? *x_at(row, c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+      p[i] = (v[i].x + v[i].y) + (v[i].z + v[i].w);
+      if (store && c4 < H4 && m < M) *reinterpret_cast<float4*>(a.x + (size_t)m * H + c4 * 4) = v[i];
+    }
+    auto row_sum = [&]() {
+#pragma unroll
+      for (int d = V / 2; d > 0; d >>= 1)
+#pragma unroll
+        for (int j = 0; j < d; ++j) p[j] += p[j + d];
+      return lanes_sum<LPR>(p[0]);
+    };
+    const float mean = row_sum() / (float)H;
+#pragma unroll
+    for (int i = 0; i < V; ++i) p[i] = sub + LPR * i < H4 ? sum_sq4(v[i], mean) : 0.f;
+    const float rstd = 1.0f / __builtin_sqrtf(row_sum() / (float)H + 1e-6f);
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const int c4 = sub + LPR * i;
+      if (c4 < H4) {
+        const float4 sh = reinterpret_cast<const float4*>(mr)[c4], sc = reinterpret_cast<const float4*>(mr + H)[c4];
+        put(act, row, c4 * 4, fmaf((v[i].x - mean) * rstd, 1.f + sc.x, sh.x), fmaf((v[i].y - mean) * rstd, 1.f + sc.y, sh.y),
+            fmaf((v[i].z - mean) * rstd, 1.f + sc.z, sh.z), fmaf((v[i].w - mean) * rstd, 1.f + sc.w, sh.w));
+      }
+    }
+  };
+  auto bias4 = [&](int at) { return *reinterpret_cast<const float4*>(sbias + at); };
+
+  long long vo[RT];  // last: where the sample of this lane's rows starts in v
+  int vtok[RT];
+  if constexpr (KIND == ROWS_LAST) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const int m = m0 + r * 16 + l16, b = a.by_L.div(min(m, M - 1));
+      vtok[r] = m < M ? m - b * L : a.n_img;
+      vo[r] = (long long)a.fin.a.vrows[b] * a.D;
+    }
+  }
+  f_block();
+#pragma unroll 1
+  for (int i = 0; i < PD; ++i) fetch();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+
+#pragma unroll 1
+  for (int ph = 0; ph < 4; ph = KIND == ROWS_HEAD ? ph + 3 : ph + 1) {
+    const Phase p = phase(ph);
+    const char* const op = ph == 2 || (KIND == ROWS_HEAD && ph == 0) ? hid : act;
+    frag o[SPS][RT][NF];
+    const int bias_at = ph == 0 ? 0 : KIND == ROWS_HEAD || ph == 1 ? H : ph == 2 ? H + a.RH : 2 * H + a.RH;
+#pragma unroll 1
+    for (int cb = wv; cb * 16 < p.N; cb += NW) {
+      f32x4 acc[RT];
+#pragma unroll
+      for (int r = 0; r < RT; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const char* os = op;
+#pragma unroll 1
+      for (int k = 0; k < p.steps; ++k) {
+        // the step has landed (PD - 1 younger ones may be under way), its fragments are read, its slot is refilled
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * SPS * (PD - 1)) : "memory");
+        frag w[SPS][NF];
+#pragma unroll
+        for (int u = 0; u < SPS; ++u)
+#pragma unroll
+          for (int i = 0; i < NF; ++i) w[u][i] = *reinterpret_cast<const frag*>(my_ring + slot + u * 2048 + (fo ^ (i * FLIP)));
+        if (p.steps > 1 || cb == wv) {  // (rows of one step stay in registers: what binds the loop is the LDS)
+#pragma unroll
+          for (int u = 0; u < SPS; ++u)
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+              for (int i = 0; i < NF; ++i) o[u][r][i] = *reinterpret_cast<const frag*>(os + (u * RT + r) * 2048 + (fo ^ (i * FLIP)));
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < SPS; ++u)
+#pragma unroll
+          for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) acc[r] = GemmFrag16<T>::mma(w[u][i], o[u][r][i], acc[r]);
+        fetch();
+        slot = (slot + STEP_B) & (RING_B - 1);
+        os += SPS * BMR * 128;
+      }
+      const int n = cb * 16 + lq * 4;
+      if (n < p.N) {
+        const float4 bb = bias4(bias_at + n);
+        if (ph == 1) {  // hidden row = GELU(product + bias)
+#pragma unroll
+          for (int r = 0; r < RT; ++r)
+            put(hid, r * 16 + l16, n, gelu_tanh_f(acc[r][0] + bb.x), gelu_tanh_f(acc[r][1] + bb.y), gelu_tanh_f(acc[r][2] + bb.z),
+                gelu_tanh_f(acc[r][3] + bb.w));
+        } else if (ph == 3) {
+          const float cs = n < a.qcols ? a.qscale : 1.f;
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            const int m = m0 + r * 16 + l16;
+            const float v0 = acc[r][0] + bb.x, v1 = acc[r][1] + bb.y, v2 = acc[r][2] + bb.z, v3 = acc[r][3] + bb.w;
+            if constexpr (KIND == ROWS_LAST) {
+              if (vtok[r] < a.n_img) a.fin.scatter_unpatch({vo[r], nullptr, vtok[r]}, n, v0, v1, v2, v3);
+            } else {
+              if (m < M) store4<T>(reinterpret_cast<T*>(a.qkv) + (size_t)m * a.NTAIL + n, v0 * cs, v1 * cs, v2 * cs, v3 * cs);
+            }
+          }
+        } else if (KIND == ROWS_HEAD) {  // image rows: position + (product + bias)
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            const int m = min(m0 + r * 16 + l16, M - 1);
+            if (m - a.by_L.div(m) * L < a.n_img) {
+              float4* x = x_at(r * 16 + l16, n >> 2);
+              float4 v = *x;
+              v.x = (acc[r][0] + bb.x) + v.x;
+              v.y = (acc[r][1] + bb.y) + v.y;
+              v.z = (acc[r][2] + bb.z) + v.z;
+              v.w = (acc[r][3] + bb.w) + v.w;
+              *x = v;
+            }
+          }
+        } else {  // rows += gate * (product + bias); a sample's vectors: gate, shift, scale, gate of the MLP, shift, scale of the tail
+          const int gate = ph == 0 ? 0 : 3 * H;
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            const float4 g = *reinterpret_cast<const float4*>(smods + srow[r] + gate + n);
+            float4* x = x_at(r * 16 + l16, n >> 2);
+            float4 v = *x;
+            v.x = fmaf(g.x, acc[r][0] + bb.x, v.x);
+            v.y = fmaf(g.y, acc[r][1] + bb.y, v.y);
+            v.z = fmaf(g.z, acc[r][2] + bb.z, v.z);
+            v.w = fmaf(g.w, acc[r][3] + bb.w, v.w);
+            *x = v;
+          }
+        }
+      }
+    }
+    if (ph == 3) break;
+    __syncthreads();
+    if (ph == 1) continue;
+    layer_norm(KIND == ROWS_HEAD ? 0 : ph == 0 ? H : 4 * H, KIND == ROWS_HEAD || (KIND == ROWS_BODY && ph == 2));
+    __syncthreads();
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the fetches past the end of the list
+}
+
+namespace {
+struct RowsLds {
+  int act, hid, mods, bias, ring, total;
+};
+// KIND's vectors of a sample: 2 H floats (head) or 6 H; samples that 16 rt rows can touch: at most (16 rt - 2) / L + 2
+RowsLds rows_lds(const br_model* m, int rt, bool head, int ntail) {
+  const int es = m->cfg.dtype == BR_BF16 ? 2 : 4, rows = 16 * rt, samples = std::min(rows, (rows - 2) / m->L + 2);
+  const size_t op = (size_t)rows * align_up((size_t)m->H * es, 128);
+  const size_t hid = (size_t)rows * align_up((size_t)(head ? m->pd : m->R * m->H) * es, 256);
+  const size_t mods = align_up((size_t)samples * (head ? 2 : 6) * m->H * 4, 1024);
+  const size_t bias = align_up((size_t)(head ? m->H + ntail : 2 * m->H + m->R * m->H + ntail) * 4, 1024);
+  RowsLds l;
+  size_t o = (size_t)rows * m->H * 4;
+  l.act = (int)o;
+  l.hid = (int)(o += op);
+  l.mods = (int)(o += hid);
+  l.bias = (int)(o += mods);
+  l.ring = (int)(o += bias);
+  l.total = (int)std::min<size_t>(o + NW * RING_B, 1 << 30);
+  return l;
+}
+}  // namespace
+
+// Row tiles of 16 per workgroup for M rows, 0: the separate kernels.  One tile while that gives every compute unit at most one
+// workgroup, two beyond (the weights are then streamed half as often), as far as the rows fit the LDS.  Whole velocity calls in us,
+// separate kernels -> fused:  bf16 hidden 64: 55 rows 105 -> 73, 2940 190 -> 117, 49 000 531 -> 400;  128: 279 rows 91 -> 68,
+// 13 500 300 -> 190, 55 700 550 -> 442;  192: 55 rows 122 -> 101;  256 (one tile only): 248 rows 169 -> 158, 3968 237 -> 172.
+// fp32 64: 24 rows 81 -> 64, 26 400 410 -> 358;  128 (one tile only): 762 rows 670 -> 655, 1905 177 -> 161.  Wider rows stream
+// more weights than the launches cost.
+int rows_fused_tiles(const br_model* m, const FwdBuffers& fb, int M) {
+  const bool bf = m->cfg.dtype == BR_BF16;
+  const uintptr_t p = (uintptr_t)fb.x | (uintptr_t)fb.mods | (uintptr_t)fb.xn | (uintptr_t)fb.qkv | (uintptr_t)fb.cond_emb;
+  if ((p & 15) != 0 || m->H * (bf ? 2 : 4) % 128 != 0 || m->H > (bf ? 256 : 128) || M > 65535) return 0;  // (FastDiv: M L < 2^32)
+  const int rt = cdiv(M, 16) <= device_cu_count() ? 1 : 2;
+  for (int head = 0; head < 2; ++head)
+    if (rows_lds(m, rt, head, std::max(3 * m->H, m->pd)).total > LDS_LIMIT) return 0;
+  return rt;
+}
+
+// block < 0: the head of the network; else the rows of block `block` and the tail behind it.
+br_status launch_block_rows(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, int b0, int B, int v_rows_mode,
+                            const float* z, float* v_out, int block, int rt, hipStream_t st) {
+  const br_model_cfg& c = m->cfg;
+  const size_t es = c.dtype == BR_BF16 ? 2 : 4;
+  const int H = m->H, RH = m->R * H, k = std::max(block, 0);
+  const bool head = block < 0, last = block == m->NB - 1;
+  auto w = [&](int id, size_t per_block, int i) { return (const char*)m->w[id] + (size_t)i * per_block * es; };
+  auto bias = [&](int id, size_t per_block, int i) { return (const float*)m->w[id] + (size_t)i * per_block; };
+  RowsArgs a{};
+  a.M = B * m->L; a.L = m->L; a.n_img = m->n_img;
+  a.H = H; a.RH = RH;
+  a.by_L = FastDiv(m->L); a.by_H4 = FastDiv(H / 4);
+  a.x = fb.x;
+  a.mods = fb.mods; a.A = m->A;
+  a.mods_off = head ? 0 : k * 6 * H + 2 * H;
+  a.mods_n = head ? 2 * H : 6 * H;
+  a.by_mq = FastDiv(a.mods_n / 4);
+  a.modmap = fb.modmap;
+  a.attn = fb.xn;
+  a.D = m->D;
+  if (head) {
+    a.w0 = m->w[BR_W_PATCH_W]; a.b0 = (const float*)m->w[BR_W_PATCH_B];
+    a.sm = sm; a.s0 = b0; a.B = B; a.v_rows_mode = v_rows_mode;
+    a.modmap_out = fb.modmap; a.vrows = fb.vrows;
+    a.z = z; a.pos = (const float*)m->w[BR_W_POS]; a.cond_emb = fb.cond_emb;
+    a.pd = m->pd; a.lt = c.latent_t; a.lh = c.latent_h; a.lw = c.latent_w;
+    a.pt = c.patch_t; a.ph = c.patch_h; a.pw = c.patch_w; a.gh = m->gh; a.gw = m->gw; a.Nc = m->Nc;
+    a.by_pd = FastDiv(m->pd); a.by_pw = FastDiv(c.patch_w); a.by_ph = FastDiv(c.patch_h); a.by_pt = FastDiv(c.patch_t);
+    a.by_gw = FastDiv(m->gw); a.by_gh = FastDiv(m->gh);
+  } else {
+    a.w0 = w(BR_W_PROJ_W, (size_t)H * H, k); a.b0 = bias(BR_W_PROJ_B, H, k);
+    a.fc1_w = w(BR_W_FC1_W, (size_t)RH * H, k); a.fc1_b = bias(BR_W_FC1_B, RH, k);
+    a.fc2_w = w(BR_W_FC2_W, (size_t)RH * H, k); a.fc2_b = bias(BR_W_FC2_B, H, k);
+  }
+  if (last) {
+    a.NTAIL = m->pd;
+    a.tail_w = m->w[BR_W_FINAL_W]; a.tail_b = (const float*)m->w[BR_W_FINAL_B];
+    EpiArgs& e = a.fin.a;
+    e.out = v_out; e.vrows = fb.vrows;
+    e.lt = c.latent_t; e.lh = c.latent_h; e.lw = c.latent_w;
+    e.pt = c.patch_t; e.ph = c.patch_h; e.pw = c.patch_w; e.gh = m->gh; e.gw = m->gw;
+  } else {
+    a.NTAIL = 3 * H;
+    a.tail_w = w(BR_W_QKV_W, (size_t)3 * H * H, block + 1); a.tail_b = bias(BR_W_QKV_B, (size_t)3 * H, block + 1);
+    a.qkv = fb.qkv;
+    if (c.dtype == BR_BF16) {  // (as in forward())
+      a.qcols = H;
+      a.qscale = (float)(1.4426950408889634 / sqrt((double)m->DH));
+    }
+  }
+  const RowsLds l = rows_lds(m, rt, head, a.NTAIL);
+  a.o_act = l.act; a.o_hid = l.hid; a.o_mods = l.mods; a.o_bias = l.bias; a.o_ring = l.ring;
+  const double flops = 2.0 * a.M * H * ((head ? m->pd : H + 2.0 * RH) + a.NTAIL);
+  ProfScope ps(st, PROF_BLOCK_ROWS + (head ? 0 : last ? 2 : 1), flops, c.dtype == BR_BF16);  // (only bf16 networks are instrumented)
+  // steps of 256 bytes where the rows of all weights are whole numbers of them (the patch vector is padded)
+  const bool wide = H * es % 256 == 0;
+  auto go = [&](auto Tc, auto RTc, auto SPSc) {
+    constexpr int R_ = decltype(RTc)::value, S_ = decltype(SPSc)::value;
+    using T = decltype(Tc);
+    const dim3 g(cdiv(a.M, 16 * R_)), b(NT);
+    if (head) hipLaunchKernelGGL((block_rows_kernel<T, R_, S_, ROWS_HEAD>), g, b, l.total, st, a);
+    else if (last) hipLaunchKernelGGL((block_rows_kernel<T, R_, S_, ROWS_LAST>), g, b, l.total, st, a);
+    else hipLaunchKernelGGL((block_rows_kernel<T, R_, S_, ROWS_BODY>), g, b, l.total, st, a);
+  };
+  auto shape = [&](auto Tc) {
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    if (rt == 1) wide ? go(Tc, I1{}, I2{}) : go(Tc, I1{}, I1{});
+    else wide ? go(Tc, I2{}, I2{}) : go(Tc, I2{}, I1{});
+  };
+  if (c.dtype == BR_BF16) shape(bf16{});
+  else shape(float{});
+  BR_LAUNCH_CHECK();
+  return BR_OK;
+}
+
+}  // namespace br

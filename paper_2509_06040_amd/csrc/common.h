@@ -43,6 +43,10 @@ struct SampleMap {
   const int* group = nullptr;  // dev or nullptr: modulation group of a sample (default: group0 + its condition)
   int group0 = 0;
 };
+__device__ inline int sample_row(const SampleMap& sm, int b) {
+  return sm.rows ? sm.rows[b] : (b / sm.width) * sm.n_nodes + sm.off + b % sm.width;
+}
+__device__ inline int sample_cond(const SampleMap& sm, int b) { return sm.cond ? sm.cond[b] : b / sm.width; }
 
 // Streaming stores of four consecutive elements, for data that the writing kernel does not
 // read again: the lines are not kept in the cache of the compute die that wrote them, which

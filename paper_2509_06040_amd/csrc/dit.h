@@ -98,6 +98,10 @@ struct LnArgs {
 bool ln_gemm_fits(int dtype, int M, int N, int K, const void* x, const void* mods, int A, int shift_off, int scale_off);
 br_status launch_ln_gemm(int dtype, int mode, const LnArgs& ln, const void* W, int M, int N, int K, const EpiArgs& ea,
                          hipStream_t st);
+// The row-local part of a block (block_rows.hip): row tiles per workgroup for M rows (0: use the separate kernels), and the launch.
+int rows_fused_tiles(const br_model* m, const FwdBuffers& fb, int M);
+br_status launch_block_rows(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, int b0, int B, int v_rows_mode,
+                            const float* z, float* v_out, int block, int rt, hipStream_t st);
 bool gemm_stream_supported(int mode, int K, size_t bytes_a, size_t bytes_w);
 br_status launch_gemm_bf16_stream(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
                                   const EpiArgs& ea, int height, int group_n, int row_block, hipStream_t st);

@@ -18,11 +18,6 @@ __device__ inline float to_f(T v) { return (float)v; }
 //    vector in (c, dt, dh, dw) order (the first patch_blocks workgroups);
 //  - x[b, n_img + j, :] = cond_emb[condition of b, j, :] (the others);
 //  - per sample its modulation group and its row in v (workgroup 0).
-__device__ inline int sample_row(const SampleMap& sm, int b) {
-  return sm.rows ? sm.rows[b] : (b / sm.width) * sm.n_nodes + sm.off + b % sm.width;
-}
-__device__ inline int sample_cond(const SampleMap& sm, int b) { return sm.cond ? sm.cond[b] : b / sm.width; }
-
 template <typename T>
 __global__ __launch_bounds__(256) void batch_prologue_kernel(SampleMap sm, int b0, int B, int v_rows_mode, int* __restrict__ modmap,
                                                              int* __restrict__ vrows, const float* __restrict__ z, long long D,

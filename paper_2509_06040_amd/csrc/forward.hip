@@ -67,6 +67,14 @@ br_status forward(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, 
   const size_t es = esize(m);
   br_status s;
 #define BR_TRY(x) do { if ((s = (x)) != BR_OK) return s; } while (0)
+  if (const int rt = rows_fused_tiles(m, fb, B * L)) {
+    ProfChain chain(dt == BR_BF16);
+    for (int k = -1; k < m->NB; ++k) {
+      if (k >= 0) BR_TRY(launch_attention(dt, fb.qkv, fb.xn, B, L, m->NH, m->DH, dt == BR_BF16 ? 1 : 0, st));
+      BR_TRY(launch_block_rows(m, fb, sm, b0, B, v_rows_mode, z_base, v_out, k, rt, st));
+    }
+    return BR_OK;
+  }
   BR_TRY(launch_batch_prologue(m, fb, sm, b0, B, v_rows_mode, z_base, st));
   {
     EpiArgs ea{};

@@ -10,6 +10,7 @@ enum ProfId {
   PROF_LOGP_EVAL = 201,
   PROF_LN_MOD = 300,
   PROF_ADALN = 301,     // the adaLN modulation GEMV (weight streaming)
+  PROF_BLOCK_ROWS = 400,  // + head 0 / body 1 / last 2: the fused row kernel of narrow networks
 };
 bool prof_on();
 void prof_begin(hipStream_t st, int id, double work);  // work: flops or bytes of this launch
@@ -29,7 +30,7 @@ struct ProfChain {
 struct ProfScope {
   hipStream_t st;
   bool on;
-  ProfScope(hipStream_t s, int id, double work) : st(s), on(prof_on()) {
+  ProfScope(hipStream_t s, int id, double work, bool enable = true) : st(s), on(enable && prof_on()) {
     if (on) prof_begin(st, id, work);
   }
   ~ProfScope() {

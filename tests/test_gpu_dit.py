@@ -476,6 +476,34 @@ def test_velocity_bits_where_the_normalisation_moves_into_the_gemm(lib, hidden, 
     assert torch.equal(out[1], out[0].expand(B, -1))
 
 
+@pytest.mark.parametrize("hidden,heads,lat,pt,cond,dtype,Bs", [
+    (64, 1, (16, 1, 14, 18), 1, 6, synth.BF16, (1, 70, 950)), (128, 1, (16, 2, 14, 18), 2, 7, synth.BF16, (3, 200, 940)),
+    (192, 3, (16, 1, 8, 6), 1, 3, synth.BF16, (1, 280)), (256, 2, (16, 1, 14, 18), 1, 6, synth.BF16, (2, 61)),
+    (32, 2, (4, 1, 6, 10), 1, 2, synth.F32, (1, 300)), (64, 4, (4, 1, 8, 8), 1, 8, synth.F32, (1, 171, 2740)),
+    (96, 3, (4, 2, 10, 6), 2, 5, synth.F32, (5, 250)), (128, 2, (4, 1, 14, 18), 1, 6, synth.F32, (1, 61))])
+def test_velocity_of_narrow_networks_with_fused_rows(lib, hidden, heads, lat, pt, cond, dtype, Bs):
+    """Narrow networks run the row-local part of a block in one launch, with one or two tiles of 16 rows a workgroup (the last one
+    ragged, tiles across samples), in steps of 128 or 256 bytes, patch vectors shorter than a step; from the last batch size on
+    some fall back on the separate kernels.  A sample has the same bits in every batch, and is right against the oracle."""
+    cfg = synth.model_cfg(2, hidden, heads, lat, (pt, 2, 2), cond, dtype)
+    W = synth.make_weights(cfg, 3, 0.05)
+    model = make_model(cfg, W)
+    D = synth.model_sizes(cfg)["D"]
+    n = max(Bs)
+    z, tok = synth.random_latents(5, D, 4), synth.cond_tokens(cfg, 2, 5)
+    zd, c = dev(z)[torch.arange(n, device=DEV) % 5], cond_dev(cfg, tok)
+    outs = []
+    for B in Bs:
+        v = torch.empty((B, D), device=DEV)
+        br.velocity(model, zd[:B].contiguous(), 0.4, c, np.arange(B) % 5 % 2, v, bytes_buffer(br.workspace_bytes(None, model, max(B, 2))))
+        outs.append(v)
+    assert_velocity(cfg, host(outs[0])[0], dit.forward(cfg, W, z[:1], 0.4, tok, np.zeros(1, np.int32))[0], 2e-2 if dtype == synth.BF16 else 1e-4)
+    for v in outs[1:]:
+        first = v[:min(5, len(v))]
+        assert torch.equal(first[:len(outs[0])], outs[0][:len(first)])
+        assert torch.equal(v, first[torch.arange(len(v), device=DEV) % 5])
+
+
 @pytest.mark.parametrize("n_tok", [64, 300])
 def test_condition_mean_adds_the_tokens_in_order(lib, n_tok):
     """1 + 2^-24 rounds to 1 in fp32, so in token order the small tokens behind the first one leave no trace; added among
