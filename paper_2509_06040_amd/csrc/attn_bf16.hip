@@ -26,9 +26,9 @@ namespace br {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 #define BR_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
@@ -120,14 +120,20 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
   float m_run = 0.f, l_run = 0.f;  // reference (a bf16 value) and row sum of the probabilities taken against it
-  const bf16x2 one2 = {(bf16)1.0f, (bf16)1.0f};
-  // the k-step that subtracts the reference: key side 1 in k-slot 0, query side -m_run there
-  bf16x8 onef, mf;
+  // Row sums on the matrix pipe: v_mfma_f32_16x16x32 takes the registers of a probability step (lanes 0..15 / 16..31: keys 0..7 of
+  // queries 0..15 / 16..31, lanes 32..63 their keys 8..15) as sixteen columns of four k-groups, so the even groups belong to
+  // one half of the queries, the odd ones to the other; the row side is 1 where a row's result lands in that half's lanes.  Sixteen
+  // cycles of the matrix pipe a step instead of four v_dot2c_f32_bf16: head dim 64 2-3 % of the launch, 128 nothing by itself.
+  bf16x8 ones;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    onef[e] = (bf16)((e == 0 && lh == 0) ? 1.f : 0.f);
-    mf[e] = (bf16)0.f;
-  }
+  for (int e = 0; e < 8; ++e) ones[e] = (bf16)((((lane >> 4) ^ (lane >> 2)) & 1) == 0 ? 1.f : 0.f);
+  asm volatile("" : "+v"(ones));
+  // the k-step that subtracts the reference: key side 1 in k-slot 0, query side -m_run there
+  // -m_run, sixteen times: what a score block starts from.  (One more k-step with the constant 1 on the key side needs no registers, but
+  // is 2 of 34 matrix instructions of a tile at head dim 128, 2 of 18 at 64: 1-2 % of the launch.)
+  f32x16 cm;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) cm[r] = 0.f;
 
   // Key and value tiles go from global memory straight into LDS, 1 KB (RPI rows) per
   // instruction: lane i fills bytes 16 i .. 16 i + 15 of the instruction's span, so the chunk
@@ -209,16 +215,13 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
     issue(min(it + 1, nkv - 1) * KV_TILE, buf ^ 1);
 
     // S^T tile minus the reference: s[kb][r] = score of key k0 + 32 kb + 8 (r/4) + 4 lh + r%4 for query
-    // l32, less m_run of that query.  The subtraction rides on the matrix pipe: one more k-step whose
-    // key side is the constant 1 and whose query side is -m_run (exact in bf16).
+    // l32, less m_run of that query, from which the accumulators start.
     f32x16 s[2];
     auto scores = [&]() __attribute__((always_inline)) {
       if constexpr (RA == 0) {
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-          s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(onef, mf, s[kb], 0, 0, 0);
+          s[kb] = cm;
           const int row = kb * 32 + l32;
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks) {
@@ -236,17 +239,11 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
         bf16x8 kf[RA + 1];
 #pragma unroll
         for (int i = 0; i < RA && i < N; ++i) kf[i] = read_k(i);
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-          s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(onef, mf, s[kb], 0, 0, 0);
-        }
         static_for<N>([&](auto Ic) __attribute__((always_inline)) {
           constexpr int i = decltype(Ic)::value;
           if (i + RA < N) kf[(i + RA) % (RA + 1)] = read_k(i + RA);
           __builtin_amdgcn_sched_barrier(0);
-          s[i / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i % (RA + 1)], qf[i % KS], s[i / KS], 0, 0, 0);
+          s[i / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i % (RA + 1)], qf[i % KS], i % KS == 0 ? cm : s[i / KS], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
         });
       }
@@ -261,12 +258,12 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
       }
     };
     // p = 2^(s) (scores already in units of log2 e / sqrt(d)) or 2^(s scale): rounded to bf16 as the
-    // column operand of the second product, step 2 kb + j; l_tile = this lane's sum of the rounded
-    // values (what that product sums), two per instruction.
+    // column operand of the second product, step 2 kb + j; l_tile = the query's sum of the rounded values
+    // (what that product sums), in both of its lanes.
     bf16x8 pf[2 * NKB];
     float l_tile;
     auto probabilities = [&]() __attribute__((always_inline)) {
-      l_tile = 0.f;
+      f32x4 lt = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int st = 0; st < 2 * NKB; ++st) {
 #pragma unroll
@@ -274,18 +271,15 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
           const float x = s[st >> 1][8 * (st & 1) + e];
           pf[st][e] = (bf16)__builtin_amdgcn_exp2f(PRE ? x : x * scale_log2);
         }
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          const bf16x2 pr = {pf[st][e], pf[st][e + 1]};
-          l_tile = __builtin_amdgcn_fdot2_f32_bf16(pr, one2, l_tile, false);
-        }
+        lt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[st], lt, 0, 0, 0);
       }
+      l_tile = lt[0];
     };
     // Softmax does not care which reference m is subtracted as long as numerator and denominator use
     // the same one; here it is whatever the query's running maximum was when it last had to move.
     // It has to move only when a probability would leave the comfortable range, and since
     // probabilities are positive that shows in the row sum the kernel forms anyway: no maximum is
-    // taken on the way.  When some lane's sum of 32 probabilities passes 2^10 (or is not a number:
+    // taken on the way.  When some query's sum of 64 probabilities passes 2^11 (or is not a number:
     // overflow), and on a wave's first tile, the scores are formed once more, the reference follows
     // the maximum (rounded to bf16; the accumulators are rescaled, 1 + DH/2 multiplications per lane)
     // and the probabilities are taken again.  With an exact running maximum nearly every tile of a
@@ -293,7 +287,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
     // instructions -- which on this chip are not hidden behind the matrix instructions.
     scores();
     probabilities();
-    if (it == 0 || __builtin_amdgcn_ballot_w64(!(l_tile <= 1024.f)) != 0) {
+    if (it == 0 || __builtin_amdgcn_ballot_w64(!(l_tile <= 2048.f)) != 0) {
       scores();
       float mx = -INFINITY;
 #pragma unroll
@@ -316,7 +310,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[kb][r] -= delta;
       m_run = m_new;
-      mf[0] = lh == 0 ? (bf16)(-m_new) : (bf16)0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) cm[r] = -m_new;
+      asm volatile("" : "+v"(cm));
       probabilities();
     }
     l_run += l_tile;
@@ -394,8 +390,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
       __syncthreads();
     }
   }
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  const float inv = 1.f / l_tot;
+  const float inv = 1.f / l_run;
   if (qi < L) {
     bf16* orow = out + ((size_t)b * L + qi) * H + (size_t)h * DH;
 #pragma unroll
