@@ -105,7 +105,7 @@ extern "C" br_status br_rollout(const br_tree* tree, const br_model* model, cons
       GroupTimes gt;
       gt.n_cond = tree->n_tree;
       std::copy(sched->t + i, sched->t + i + n, gt.t);
-      if ((s = conditioning(model, fb, nullptr, gt, n * tree->n_tree, st)) != BR_OK) return s;
+      if ((s = conditioning(model, fb, i == 0 ? cond_tokens : nullptr, tree->n_tree, nullptr, gt, n * tree->n_tree, st)) != BR_OK) return s;
     }
     const int Bi = tree->n_tree * tree->width[i];
     SampleMap sm{nullptr, nullptr, tree->n_nodes, tree->off[i], tree->width[i]};
@@ -231,7 +231,7 @@ extern "C" br_status br_logprob(const br_tree* tree, const br_model* model, cons
     sm.group = fb.plan + o_group;
     GroupTimes gt;
     gt.dev = reinterpret_cast<const float*>(fb.plan + bt.o_gt);
-    if ((s = conditioning(model, fb, fb.plan + bt.o_gcond, gt, bt.G, st)) != BR_OK) return s;
+    if ((s = conditioning(model, fb, bt.b0 == 0 ? cond_tokens : nullptr, tree->n_tree, fb.plan + bt.o_gcond, gt, bt.G, st)) != BR_OK) return s;
     if ((s = forward(model, fb, sm, bt.b0, bt.B, 2, z_nodes, fb.v, st)) != BR_OK) return s;
     while (e_next < n_edges && edges[e_next].par < bt.b0 + bt.B) {
       if (edges[e_next].par < 0) {  // deterministic step, done above
@@ -269,15 +269,21 @@ extern "C" br_status br_velocity(const br_model* model, const float* z, float t,
   BR_REQUIRE(mb >= 1, BR_EWORKSPACE, "br_velocity: workspace too small");
   FwdBuffers fb;
   plan_workspace(model, n_cond, mb, 0, 0, B, &fb, workspace);
-  static PinnedStage cond_stage;  // (shared by all callers of br_velocity; uploads are serialised)
   br_status s;
-  if ((s = cond_stage.upload(cond_index, (size_t)B, fb.plan, st)) != BR_OK) return s;
+  SampleMap sm{nullptr, nullptr, 0, 0, B};  // row = b
+  if (B <= SampleMap::MAX_INLINE && n_cond <= 65536) {
+    sm.n_inline = B;
+    std::copy(cond_index, cond_index + B, sm.inl);
+  } else {
+    static PinnedStage cond_stage;  // (shared by all callers of br_velocity; uploads are serialised)
+    if ((s = cond_stage.upload(cond_index, (size_t)B, fb.plan, st)) != BR_OK) return s;
+    sm.cond = fb.plan;
+  }
   if ((s = embed_cond(model, fb, cond_tokens, n_cond, st)) != BR_OK) return s;
-  const SampleMap sm{nullptr, fb.plan, 0, 0, B};  // row = b
   GroupTimes gt;
   gt.n_cond = n_cond;
   gt.t[0] = t;
-  if ((s = conditioning(model, fb, nullptr, gt, n_cond, st)) != BR_OK) return s;
+  if ((s = conditioning(model, fb, cond_tokens, n_cond, nullptr, gt, n_cond, st)) != BR_OK) return s;
   for (int b0 = 0; b0 < B; b0 += mb)
     if ((s = forward(model, fb, sm, b0, std::min(mb, B - b0), 0, z, v_out, st)) != BR_OK) return s;
   return BR_OK;

@@ -42,11 +42,17 @@ struct SampleMap {
   int n_nodes, off, width;
   const int* group = nullptr;  // dev or nullptr: modulation group of a sample (default: group0 + its condition)
   int group0 = 0;
+  // conditions of up to MAX_INLINE samples, passed with the launch (a transfer of a few integers and the event behind it cost 10 us)
+  static constexpr int MAX_INLINE = 64;
+  int n_inline = 0;
+  uint16_t inl[MAX_INLINE] = {};
 };
 __device__ inline int sample_row(const SampleMap& sm, int b) {
   return sm.rows ? sm.rows[b] : (b / sm.width) * sm.n_nodes + sm.off + b % sm.width;
 }
-__device__ inline int sample_cond(const SampleMap& sm, int b) { return sm.cond ? sm.cond[b] : b / sm.width; }
+__device__ inline int sample_cond(const SampleMap& sm, int b) {
+  return sm.cond ? sm.cond[b] : sm.n_inline ? sm.inl[b] : b / sm.width;
+}
 
 // Streaming stores of four consecutive elements, for data that the writing kernel does not
 // read again: the lines are not kept in the cache of the compute die that wrote them, which

@@ -48,7 +48,7 @@ struct EpiArgs {
 struct FwdBuffers {  // carved from the workspace
   int* modmap;    // sample -> modulation group (its adaLN vectors)
   int* vrows;     // sample -> row of v
-  float *h1, *pooled, *pool_lin, *cvec, *mods, *cond_emb, *x, *sde_partials;
+  float *h1, *pooled, *cvec, *mods, *cond_emb, *x, *sde_partials;
   void *patches, *xn, *qkv, *hid;
   float* v;       // compact velocity [max_frontier, D] (rollout only)
   int* plan;      // br_logprob launch plan
@@ -66,8 +66,10 @@ struct GroupTimes {
   float t[MAX_GROUP_STEPS] = {};
 };
 // adaLN vectors of the modulation groups g < G <= max(n_cond, max_batch) of the plan: condition gcond[g] (device
-// array; nullptr: g % gt.n_cond) at the group's time.  They stay valid until the next call.
-br_status conditioning(const br_model* m, const FwdBuffers& fb, const int* gcond, const GroupTimes& gt, int G, hipStream_t st);
+// array; nullptr: g % gt.n_cond) at the group's time.  They stay valid until the next call.  cond_tokens (the first call of an
+// entry point; else nullptr): the tokens of all n_cond conditions, whose means every later call uses.
+br_status conditioning(const br_model* m, const FwdBuffers& fb, const void* cond_tokens, int n_cond, const int* gcond, const GroupTimes& gt,
+                       int G, hipStream_t st);
 // One network evaluation of samples b0 .. b0 + B - 1 of `sm` (B <= max_batch of the plan): latent rows of z_base, groups of the
 // last conditioning() call; v rows by v_rows_mode (1: the sample's row, 2: row of the batch, else: its index).
 br_status forward(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, int b0, int B, int v_rows_mode,

@@ -56,8 +56,6 @@ __global__ __launch_bounds__(256) void batch_prologue_kernel(SampleMap sm, int b
 }
 
 // ------------------------------------------------------- conditioning path
-// temb = [cos(1000 t f_k), sin(1000 t f_k)], f_k = 10000^(-k/128).  The angle (up to 1000 rad)
-// is formed and reduced to [-pi, pi] in fp64, then fp32 sin/cos suffice.
 __device__ inline float silu_f(float x) { return x / (1.f + __expf(-x)); }
 
 // pooled[c, :] = mean over the condition tokens of condition c (depends on the prompt only), added in token order.  A
@@ -65,10 +63,9 @@ __device__ inline float silu_f(float x) { return x / (1.f + __expf(-x)); }
 // wave adds them up from LDS (one lane down all 512 tokens of a column of 3072 by itself: 182 us, so: 8).
 constexpr int POOL_CHUNK = 128;
 template <typename T>
-__global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ cond, int Nc, int cd,
-                                                   float* __restrict__ pooled) {
-  __shared__ float tok[POOL_CHUNK][64];
-  const int c = blockIdx.y, col = threadIdx.x & 63, grp = threadIdx.x >> 6, d = blockIdx.x * 64 + col;
+__device__ inline void pool_columns(const T* __restrict__ cond, int Nc, int cd, float* __restrict__ pooled, int c, int col_block,
+                                    float (*tok)[64]) {
+  const int col = threadIdx.x & 63, grp = threadIdx.x >> 6, d = col_block * 64 + col;
   const T* p = cond + (size_t)c * Nc * cd + min(d, cd - 1);
   float s = 0.f;
   for (int j0 = 0; j0 < Nc; j0 += POOL_CHUNK) {
@@ -107,19 +104,23 @@ struct WChunk<bf16> {
   }
 };
 
-// One weight row times R <= 8 input rows: lanes along k in 8-element chunks (K % 8 == 0, rows 16-byte aligned);
+// One weight row times R <= 8 input rows (row r at row(r)): lanes along k in 8-element chunks (K % 8 == 0, rows 16-byte aligned);
 // lane 0 holds the sums.
-template <typename TW, int R>
-__device__ inline void skinny_dot(const float* in, int ldi, const TW* __restrict__ wr, int K, int lane, float (&acc)[R]) {
+template <typename TW, int R, typename ROW>
+__device__ inline void skinny_dot(ROW&& row, const TW* __restrict__ wr, int K, int lane, float (&acc)[R]) {
+  const float* in[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) acc[r] = 0.f;
+  for (int r = 0; r < R; ++r) {
+    acc[r] = 0.f;
+    in[r] = row(r);
+  }
   for (int k = lane * 8; k < K; k += 512) {
     float w[8];
     WChunk<TW>::load(wr + k, w);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const float4 a0 = *reinterpret_cast<const float4*>(in + (size_t)r * ldi + k);
-      const float4 a1 = *reinterpret_cast<const float4*>(in + (size_t)r * ldi + k + 4);
+      const float4 a0 = *reinterpret_cast<const float4*>(in[r] + k);
+      const float4 a1 = *reinterpret_cast<const float4*>(in[r] + k + 4);
       const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[r] = fmaf(a[e], w[e], acc[r]);
@@ -131,39 +132,31 @@ __device__ inline void skinny_dot(const float* in, int ldi, const TW* __restrict
     for (int o = 32; o > 0; o >>= 1) acc[r] += __shfl_down(acc[r], o, 64);
 }
 
-// out[r, n] = sum_k in[r, k] W[n, k] + bias[n], r < R <= 8: one wavefront per output column.  With pool_lin:
-// silu(that + pool_lin[condition of group g0 + r, n]), the conditioning vector of a modulation group.
-template <typename TW, int R>
-__global__ __launch_bounds__(256) void skinny_gemm_kernel(const float* __restrict__ in, int ldi, const TW* __restrict__ W, int K,
-                                                          int N, const float* __restrict__ bias, float* __restrict__ out, int ldo,
-                                                          const float* __restrict__ pool_lin, const int* __restrict__ gcond,
-                                                          int n_cond, int g0) {
-  const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= N) return;
-  float acc[R];
-  skinny_dot<TW, R>(in, ldi, W + (size_t)n * K, K, lane, acc);
-  if (lane == 0) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      float s = acc[r] + bias[n];
-      if (pool_lin) s = silu_f(pool_lin[(size_t)(gcond ? gcond[g0 + r] : (g0 + r) % n_cond) * N + n] + s);
-      out[(size_t)r * ldo + n] = s;
-    }
-  }
-}
+// The conditioning path is three dependent launches, each over groups of R <= 8 rows (modulation groups): the time MLP's first layer
+// and, where asked for, the pooled conditions; its second layer with the pooled half of the vector; the modulation vectors.
+// (Launches of their own for the pooled mean and its linear layer cost a small network 4 us each, and so did every eight rows.)
 
-// h1[r, n] = silu(sum_k temb(t of group g0 + r)[k] W[n, k] + bias[n]), temb = [cos(1000 t f_k), sin(1000 t f_k)],
+// h1[g, n] = silu(sum_k temb(t of group g)[k] W[n, k] + bias[n]), temb = [cos(1000 t f_k), sin(1000 t f_k)],
 // f_k = 10000^(-k/128), formed by every workgroup for itself (1 us that runs once, against a launch).  The angle (up to
-// 1000 rad) is formed and reduced to [-pi, pi] in fp64, then fp32 sin/cos suffice.
-template <typename TW, int R>
-__global__ __launch_bounds__(256) void time_mlp_kernel(GroupTimes gt, int g0, const TW* __restrict__ W, int N,
-                                                       const float* __restrict__ bias, float* __restrict__ out, int ldo) {
-  __shared__ __attribute__((aligned(16))) float temb[R][256];
+// 1000 rad) is formed and reduced to [-pi, pi] in fp64, then fp32 sin/cos suffice.  The workgroups behind these pool.
+template <typename T, int R>
+__global__ __launch_bounds__(256) void cond_first_kernel(GroupTimes gt, int G, const T* __restrict__ W, int N, const float* __restrict__ bias,
+                                                         float* __restrict__ h1, int time_blocks, const T* __restrict__ cond, int Nc, int cd,
+                                                         int col_blocks, float* __restrict__ pooled) {
+  __shared__ __attribute__((aligned(16))) float lds[POOL_CHUNK * 64];
+  static_assert(R * 256 <= POOL_CHUNK * 64, "embeddings fit");
+  if ((int)blockIdx.x >= time_blocks) {
+    const int i = blockIdx.x - time_blocks, c = i / col_blocks;
+    pool_columns<T>(cond, Nc, cd, pooled, c, i - c * col_blocks, reinterpret_cast<float(*)[64]>(lds));
+    return;
+  }
+  float(*temb)[256] = reinterpret_cast<float(*)[256]>(lds);
+  const int per = (N + 3) / 4, ch = blockIdx.x / per, g0 = ch * R;
   const int k = threadIdx.x & 127;
   const double f = exp(-9.210340371976184 * (double)k / 128.0);  // ln 10000
   for (int r = threadIdx.x >> 7; r < R; r += 2) {
-    const float t = gt.dev ? gt.dev[g0 + r] : gt.t[(g0 + r) / gt.n_cond];
+    const int g = min(g0 + r, G - 1);
+    const float t = gt.dev ? gt.dev[g] : gt.t[g / gt.n_cond];
     double a = 1000.0 * (double)t * f;
     a -= 6.283185307179586 * rint(a * 0.15915494309189535);
     float sn, cs;
@@ -173,85 +166,109 @@ __global__ __launch_bounds__(256) void time_mlp_kernel(GroupTimes gt, int g0, co
   }
   __syncthreads();
   const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int n = (blockIdx.x - ch * per) * 4 + (threadIdx.x >> 6);
   if (n >= N) return;
   float acc[R];
-  skinny_dot<TW, R>(&temb[0][0], 256, W + (size_t)n * 256, 256, lane, acc);
+  skinny_dot<T, R>([&](int r) { return &temb[r][0]; }, W + (size_t)n * 256, 256, lane, acc);
   if (lane == 0) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) out[(size_t)r * ldo + n] = silu_f(acc[r] + bias[n]);
+    for (int r = 0; r < R; ++r)
+      if (g0 + r < G) h1[(size_t)(g0 + r) * N + n] = silu_f(acc[r] + bias[n]);
   }
 }
 
-// f(integral_constant R) for groups of up to 8 rows from 0 to n
-template <typename F>
-static br_status by_eights(int n, F&& f) {
-  for (int r0 = 0; r0 < n; r0 += 8) {
-    switch (std::min(8, n - r0)) {
-      case 1: f(std::integral_constant<int, 1>{}, r0); break;
-      case 2: f(std::integral_constant<int, 2>{}, r0); break;
-      case 3: f(std::integral_constant<int, 3>{}, r0); break;
-      case 4: f(std::integral_constant<int, 4>{}, r0); break;
-      case 5: f(std::integral_constant<int, 5>{}, r0); break;
-      case 6: f(std::integral_constant<int, 6>{}, r0); break;
-      case 7: f(std::integral_constant<int, 7>{}, r0); break;
-      default: f(std::integral_constant<int, 8>{}, r0); break;
+// cvec[g, n] = silu((sum_k pooled[condition of g, k] Wp[n, k] + bp[n]) + (sum_k h1[g, k] W[n, k] + bias[n])): the conditioning
+// vector of a modulation group.
+template <typename TW, int R>
+__global__ __launch_bounds__(256) void cond_vector_kernel(const float* __restrict__ h1, const TW* __restrict__ W, const float* __restrict__ bias,
+                                                          const float* __restrict__ pooled, const TW* __restrict__ Wp,
+                                                          const float* __restrict__ bp, int cd, const int* __restrict__ gcond, int n_cond,
+                                                          int G, int N, float* __restrict__ cvec) {
+  const int lane = threadIdx.x & 63;
+  const int n = blockIdx.x * 4 + (threadIdx.x >> 6), g0 = blockIdx.y * R;
+  if (n >= N) return;
+  float acc[R], pool[R];
+  skinny_dot<TW, R>([&](int r) { return h1 + (size_t)min(g0 + r, G - 1) * N; }, W + (size_t)n * N, N, lane, acc);
+  skinny_dot<TW, R>([&](int r) {
+    const int g = min(g0 + r, G - 1);
+    return pooled + (size_t)(gcond ? gcond[g] : g % n_cond) * cd;
+  }, Wp + (size_t)n * cd, cd, lane, pool);
+  if (lane == 0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (g0 + r < G) cvec[(size_t)(g0 + r) * N + n] = silu_f((pool[r] + bp[n]) + (acc[r] + bias[n]));
+  }
+}
+
+// out[g, n] = sum_k in[g, k] W[n, k] + bias[n]: one wavefront per column, which keeps to its weight row for all groups (the second
+// eight find it in cache: 448 000 columns of 3072 for 64 groups stream 2.7 GB once).
+template <typename TW, int R>
+__global__ __launch_bounds__(256) void skinny_gemm_kernel(const float* __restrict__ in, int G, const TW* __restrict__ W, int K, int N,
+                                                          const float* __restrict__ bias, float* __restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (n >= N) return;
+  for (int g0 = 0; g0 < G; g0 += R) {
+    float acc[R];
+    skinny_dot<TW, R>([&](int r) { return in + (size_t)min(g0 + r, G - 1) * K; }, W + (size_t)n * K, K, lane, acc);
+    if (lane == 0) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (g0 + r < G) out[(size_t)(g0 + r) * N + n] = acc[r] + bias[n];
     }
-    BR_LAUNCH_CHECK();
   }
-  return BR_OK;
 }
 
-template <typename TW>
-static br_status skinny(const float* in, int ldi, int R, const TW* W, int K, int N, const float* bias, float* out, int ldo,
-                        const float* pool_lin, const int* gcond, int n_cond, hipStream_t st) {
-  return by_eights(R, [&](auto Rc, int r0) {
-    hipLaunchKernelGGL((skinny_gemm_kernel<TW, decltype(Rc)::value>), dim3(cdiv(N, 4)), dim3(256), 0, st, in + (size_t)r0 * ldi, ldi,
-                       W, K, N, bias, out + (size_t)r0 * ldo, ldo, pool_lin, gcond, n_cond, r0);
-  });
+// f(integral_constant R): the rows that a wavefront takes together, all of up to eight
+template <typename F>
+static void with_rows(int n, F&& f) {
+  switch (std::min(8, n)) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 7: f(std::integral_constant<int, 7>{}); break;
+    default: f(std::integral_constant<int, 8>{}); break;
+  }
 }
 
-// Per modulation group g: cvec = silu(t_mlp(temb(time of g)) + pool_lin[condition of g]); mods = ada_lin(cvec).
+// Per modulation group g: cvec = silu(t_mlp(temb(time of g)) + pool_lin(mean token of its condition)); mods = ada_lin(cvec).
 template <typename T>
-static br_status conditioning_t(const br_model* m, const FwdBuffers& fb, const int* gcond, const GroupTimes& gt, int G,
-                                hipStream_t st) {
+static br_status conditioning_t(const br_model* m, const FwdBuffers& fb, const T* cond_tokens, int n_cond, const int* gcond,
+                                const GroupTimes& gt, int G, hipStream_t st) {
   const int H = m->H;
-  br_status s;
-  if ((s = by_eights(G, [&](auto Rc, int r0) {
-         hipLaunchKernelGGL((time_mlp_kernel<T, decltype(Rc)::value>), dim3(cdiv(H, 4)), dim3(256), 0, st, gt, r0,
-                            (const T*)m->w[BR_W_T1_W], H, (const float*)m->w[BR_W_T1_B], fb.h1 + (size_t)r0 * H, H);
-       })) != BR_OK) return s;
-  if ((s = skinny<T>(fb.h1, H, G, (const T*)m->w[BR_W_T2_W], H, H, (const float*)m->w[BR_W_T2_B], fb.cvec, H, fb.pool_lin, gcond,
-                     gt.n_cond, st)) != BR_OK) return s;
-  // the modulation vectors of all blocks: a GEMV that streams the [A, H] weights once per 8 groups
-  ProfScope ps(st, PROF_ADALN, (double)cdiv(G, 8) * (double)m->A * H * sizeof(T));
-  return skinny<T>(fb.cvec, H, G, (const T*)m->w[BR_W_ADA_W], H, m->A, (const float*)m->w[BR_W_ADA_B], fb.mods, m->A, nullptr,
-                   nullptr, 1, st);
-}
-
-// pool_lin[c, :] = W_pool pooled[c, :] + b_pool: the time-independent half of the conditioning vector
-br_status launch_pool_linear(const br_model* m, const FwdBuffers& fb, int n_cond, hipStream_t st) {
-  if (m->cfg.dtype == BR_BF16)
-    return skinny<bf16>(fb.pooled, m->cd, n_cond, (const bf16*)m->w[BR_W_POOL_W], m->cd, m->H, (const float*)m->w[BR_W_POOL_B],
-                        fb.pool_lin, m->H, nullptr, nullptr, 1, st);
-  return skinny<float>(fb.pooled, m->cd, n_cond, (const float*)m->w[BR_W_POOL_W], m->cd, m->H, (const float*)m->w[BR_W_POOL_B],
-                       fb.pool_lin, m->H, nullptr, nullptr, 1, st);
-}
-
-br_status launch_pool(const br_model* m, const FwdBuffers& fb, const void* cond, int n_cond, hipStream_t st) {
-  dim3 g(cdiv(m->cd, 64), n_cond), b(256);
-  if (m->cfg.dtype == BR_BF16)
-    hipLaunchKernelGGL((pool_kernel<bf16>), g, b, 0, st, (const bf16*)cond, m->Nc, m->cd, fb.pooled);
-  else
-    hipLaunchKernelGGL((pool_kernel<float>), g, b, 0, st, (const float*)cond, m->Nc, m->cd, fb.pooled);
+  auto w = [&](int id) { return (const T*)m->w[id]; };
+  auto b = [&](int id) { return (const float*)m->w[id]; };
+  with_rows(G, [&](auto Rc) {
+    constexpr int R = decltype(Rc)::value;
+    const int chunks = cdiv(G, R), time_blocks = chunks * cdiv(H, 4), col_blocks = cdiv(m->cd, 64);
+    hipLaunchKernelGGL((cond_first_kernel<T, R>), dim3(time_blocks + (cond_tokens ? n_cond * col_blocks : 0)), dim3(256), 0, st, gt, G,
+                       w(BR_W_T1_W), H, b(BR_W_T1_B), fb.h1, time_blocks, cond_tokens, m->Nc, m->cd, col_blocks, fb.pooled);
+  });
+  BR_LAUNCH_CHECK();
+  with_rows(G, [&](auto Rc) {
+    constexpr int R = decltype(Rc)::value;
+    hipLaunchKernelGGL((cond_vector_kernel<T, R>), dim3(cdiv(H, 4), cdiv(G, R)), dim3(256), 0, st, fb.h1, w(BR_W_T2_W), b(BR_W_T2_B),
+                       fb.pooled, w(BR_W_POOL_W), b(BR_W_POOL_B), m->cd, gcond, gt.n_cond, G, H, fb.cvec);
+  });
+  BR_LAUNCH_CHECK();
+  // the modulation vectors of all blocks: a GEMV that streams the [A, H] weights
+  ProfScope ps(st, PROF_ADALN, (double)m->A * H * sizeof(T));
+  with_rows(G, [&](auto Rc) {
+    constexpr int R = decltype(Rc)::value;
+    hipLaunchKernelGGL((skinny_gemm_kernel<T, R>), dim3(cdiv(m->A, 4)), dim3(256), 0, st, fb.cvec, G, w(BR_W_ADA_W), H, m->A, b(BR_W_ADA_B),
+                       fb.mods);
+  });
   BR_LAUNCH_CHECK();
   return BR_OK;
 }
 
-br_status conditioning(const br_model* m, const FwdBuffers& fb, const int* gcond, const GroupTimes& gt, int G,
-                       hipStream_t st) {
-  return m->cfg.dtype == BR_BF16 ? conditioning_t<bf16>(m, fb, gcond, gt, G, st)
-                                 : conditioning_t<float>(m, fb, gcond, gt, G, st);
+br_status conditioning(const br_model* m, const FwdBuffers& fb, const void* cond_tokens, int n_cond, const int* gcond,
+                       const GroupTimes& gt, int G, hipStream_t st) {
+  return m->cfg.dtype == BR_BF16 ? conditioning_t<bf16>(m, fb, (const bf16*)cond_tokens, n_cond, gcond, gt, G, st)
+                                 : conditioning_t<float>(m, fb, (const float*)cond_tokens, n_cond, gcond, gt, G, st);
 }
 
 // ------------------------------------------------------- LayerNorm-modulate

@@ -8,10 +8,8 @@
 #include "prof.h"
 
 namespace br {
-br_status launch_pool_linear(const br_model* m, const FwdBuffers& fb, int n_cond, hipStream_t st);
 br_status launch_batch_prologue(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, int b0, int B, int v_rows_mode,
                                 const float* z, hipStream_t st);
-br_status launch_pool(const br_model* m, const FwdBuffers& fb, const void* cond, int n_cond, hipStream_t st);
 
 static size_t esize(const br_model* m) { return m->cfg.dtype == BR_BF16 ? 2 : 4; }
 
@@ -31,7 +29,6 @@ size_t plan_workspace(const br_model* m, int n_cond, int max_batch, long long v_
   f.vrows = (int*)take(B * 4);
   f.h1 = (float*)take(G * H * 4);
   f.pooled = (float*)take((size_t)n_cond * m->cd * 4);
-  f.pool_lin = (float*)take((size_t)n_cond * H * 4);
   f.cvec = (float*)take(G * H * 4);
   f.mods = (float*)take(G * m->A * 4);
   f.cond_emb = (float*)take((size_t)n_cond * m->Nc * H * 4);
@@ -49,16 +46,11 @@ size_t plan_workspace(const br_model* m, int n_cond, int max_batch, long long v_
 }
 
 br_status embed_cond(const br_model* m, const FwdBuffers& fb, const void* cond_tokens, int n_cond, hipStream_t st) {
-  br_status sp = launch_pool(m, fb, cond_tokens, n_cond, st);
-  if (sp != BR_OK) return sp;
   EpiArgs ea{};
   ea.bias = (const float*)m->w[BR_W_COND_B];
   ea.out = fb.cond_emb;
   ea.ldo = m->H;
-  if ((sp = launch_gemm(m->cfg.dtype, EPI_BIAS_F32, cond_tokens, m->cd, m->w[BR_W_COND_W], m->cd, n_cond * m->Nc,
-                        m->H, m->cd, ea, st)) != BR_OK)
-    return sp;
-  return launch_pool_linear(m, fb, n_cond, st);
+  return launch_gemm(m->cfg.dtype, EPI_BIAS_F32, cond_tokens, m->cd, m->w[BR_W_COND_W], m->cd, n_cond * m->Nc, m->H, m->cd, ea, st);
 }
 
 br_status forward(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, int b0, int B, int v_rows_mode,

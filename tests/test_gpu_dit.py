@@ -504,6 +504,27 @@ def test_velocity_of_narrow_networks_with_fused_rows(lib, hidden, heads, lat, pt
         assert torch.equal(v, first[torch.arange(len(v), device=DEV) % 5])
 
 
+@pytest.mark.parametrize("n_cond", [1, 8, 11])
+def test_velocity_conditions_passed_with_the_launch_or_transferred(lib, n_cond):
+    """Up to 64 samples carry their conditions in the launch, more in a buffer; up to eight conditions share a pass over the
+    weights of the conditioning path.  Each sample as it is by itself under its condition, and one right against the oracle."""
+    cfg = synth.model_cfg(1, 64, 4, (4, 1, 8, 8), (1, 2, 2), 8, synth.F32)
+    W = synth.make_weights(cfg, 1, 0.1)
+    model, D = make_model(cfg, W), synth.model_sizes(cfg)["D"]
+    z, tok = synth.random_latents(65, D, 2), synth.cond_tokens(cfg, n_cond, 3)
+    idx = ((np.arange(65) * 7 + 3) % n_cond).astype(np.int32)
+    out = {}
+    for B in (64, 65):
+        out[B] = torch.empty((B, D), device=DEV)
+        br.velocity(model, dev(z[:B]), 0.6, dev(tok), idx[:B], out[B], bytes_buffer(br.workspace_bytes(None, model, B)))
+    assert torch.equal(out[64], out[65][:64])
+    for b in (0, 37, 64):
+        one = torch.empty((1, D), device=DEV)
+        br.velocity(model, dev(z[b:b + 1]), 0.6, dev(tok[idx[b]:idx[b] + 1]), np.zeros(1, np.int32), one, bytes_buffer(br.workspace_bytes(None, model, 1)))
+        assert torch.equal(one[0], out[65][b])
+    assert_velocity(cfg, host(out[65])[64], dit.forward(cfg, W, z[64:], 0.6, tok, idx[64:])[0], 1e-4)
+
+
 @pytest.mark.parametrize("n_tok", [64, 300])
 def test_condition_mean_adds_the_tokens_in_order(lib, n_tok):
     """1 + 2^-24 rounds to 1 in fp32, so in token order the small tokens behind the first one leave no trace; added among
