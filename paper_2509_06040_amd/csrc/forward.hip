@@ -29,6 +29,7 @@ size_t plan_workspace(const br_model* m, int n_cond, int max_batch, long long v_
   f.vrows = (int*)take(B * 4);
   f.h1 = (float*)take(G * H * 4);
   f.pooled = (float*)take((size_t)n_cond * m->cd * 4);
+  take((size_t)n_cond * H * 4);  // unused: the sizes that callers were given, and the batches that fit them, stay what they are
   f.cvec = (float*)take(G * H * 4);
   f.mods = (float*)take(G * m->A * 4);
   f.cond_emb = (float*)take((size_t)n_cond * m->Nc * H * 4);
