@@ -40,7 +40,7 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 GEMM_NAMES = {0: "bias", 1: "bias_gelu", 2: "bias_gate_residual", 3: "patch_embed", 4: "bias_f32", 5: "unpatchify"}
 TILE_NAMES = {0: "32x32 lds-direct", 1: "128x128 lds-direct, 8 waves", 2: "64x64 lds-direct", 3: "64x128 lds-direct",
               4: "256x256 lds-direct", 5: "128x128 lds-direct",
-              7: "128..256x256 persistent stream"}
+              6: "32..192x128 ring", 7: "128..256x256 persistent stream"}
 HEADLINE = "image_large"
 ORDER = ("image", "video", "image_large")
 

@@ -4,8 +4,8 @@
 // activations the column operand (v_mfma_f32_32x32x16_bf16).
 //
 // This file holds the choice of the kernel and the launches of the one-tile-per-workgroup kernel (gemm_tile.h);
-// the persistent kernel for large problems is in gemm_bf16_stream.hip, the one for small ones in
-// gemm_small.hip.
+// the persistent kernel for large problems is in gemm_bf16_stream.hip, the one for about one round of tiles in
+// gemm_bf16_ring.hip, the one for small problems in gemm_small.hip.
 #include <cmath>
 
 #include "common.h"
@@ -29,23 +29,35 @@ static br_status gemm_tile_launch(const bf16* A, int lda, const bf16* W, int ldw
 }
 
 enum {  // bits 0..3 of a variant; TILE_STREAM + 1 .. + 4: the persistent kernel with 4 .. 7 times 32 rows a tile
-  TILE_32 = 0, TILE_128_W8 = 1, TILE_64 = 2, TILE_64_128 = 3, TILE_256 = 4, TILE_128 = 5, TILE_STREAM = 7
+  TILE_32 = 0, TILE_128_W8 = 1, TILE_64 = 2, TILE_64_128 = 3, TILE_256 = 4, TILE_128 = 5, TILE_RING = 6, TILE_STREAM = 7
 };
 
 // The kernel for a problem size.  r = tiles of a kind per compute unit.  (The part for small problems is from 410
 // measured shapes: M 40 to 200 000, hidden sizes 64 to 3072 with their QKV, MLP and projection widths.)
 // rps: rows of a sample where the epilogue looks something up per sample, else 0.  *height: rows of a tile of the
-// persistent kernel, in units of 32.
-static int choose_tile(int M, int N, int K, int rps, bool stream_ok, int* height) {
+// persistent kernel, in units of 32, or of the ring kernel, in units of 16.
+static int choose_tile(int M, int N, int K, int rps, bool stream_ok, bool ring_ok, int* height) {
   const double cu = device_cu_count();
   const double r32 = (double)cdiv(M, 32) * cdiv(N, 32) / cu, r64 = (double)cdiv(M, 64) * cdiv(N, 64) / cu;
   const double r128 = (double)cdiv(M, 128) * cdiv(N, 128) / cu;
   // Up to a few 32x32 tiles a unit: four waves a tile.  279 x 128 x 512 takes 3.2 us instead of the 5.3 of 64x64
   // tiles, 300 x 1024 x 4096 10.4 instead of 23.  A long K makes the tile's operand traffic (twice that of 64x64 tiles
   // for the same outputs) the longer part sooner.
-  if (r32 <= (K < 1024 ? 4.0 : 3.0)) return TILE_32;
+  // Beyond, the ring kernel, as long as its tiles are one round in some height: the lowest such, which spreads them over most units.
+  // Against what the rules below choose, over 235 shapes (M 300 to 8808, hidden sizes 512 to 3072 with their four projections): 6.9 %
+  // faster on average, 0.7 % slower than the best kernel of each (1101 x 3072 x 1024: 14.6 -> 11.0 us, 1101 x 2048 x 8192: 69 -> 46,
+  // 4404 x 1024 x 4096: 54 -> 39; worst 1101 x 2048 x 512, 7.6 -> 8.2).  From two rounds on its 128 columns cost operand traffic
+  // (4404 x 3072 x 1024: 28 us in the persistent kernel, 33).  Samples shorter than a wave's rows are left to the others.
+  int ring = 0;
+  for (int h = 2; ring_ok && h <= 12 && !ring; h += 2)
+    if ((double)cdiv(M, 16 * h) * cdiv(N, 128) <= cu && (rps == 0 || rps >= 8 * h)) ring = h;
+  if (r32 <= (ring ? (K < 768 ? 4.0 : K <= 1024 ? 2.5 : 2.0) : (K < 1024 ? 4.0 : 3.0))) return TILE_32;
+  if (ring) {
+    *height = ring;
+    return TILE_RING;
+  }
   // Up to one round of 64x64 tiles: two waves each, four stages of 16 KB in flight.  1101 x 1024 x 4096: 23 us
-  // (34 in 128x128 tiles, 52 in 256x128).
+  // (34 in 128x128 tiles, 20.5 in the ring kernel).
   if (r64 <= 1.2) return TILE_64;
   // Up to one round of 128x128 tiles: half of them, so that the round is fuller (1101 x 3072 x 1024: 14.7 us,
   // 20.8 in 256x128 tiles).
@@ -82,18 +94,22 @@ static int choose_tile(int M, int N, int K, int rps, bool stream_ok, int* height
 
 // variant bits 0..3: kernel (see the enum); bits 4..11: column-group width of the tile walk (0 = the kernel's own
 // choice); for the persistent kernel bits 24..30: row block of the walk in units of 8 tile rows (bits 12..23 were start
-// delays of an earlier form and are ignored).  variant < 0 = choose by problem size.
+// delays of an earlier form and are ignored), for TILE_RING its tile height.  variant < 0 = choose by problem size.
 template <int MODE, typename TOUT>
 static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K, const EpiArgs& ea,
                               int variant, hipStream_t st) {
   int tile, group_n = 0, row_block = 0, height = 0;
   if (variant < 0) {
-    tile = choose_tile(M, N, K, MODE == EPI_BIAS_GATE_RES ? ea.L : 0, gemm_stream_supported(MODE, K, (size_t)M * lda * 2, (size_t)N * ldw * 2), &height);
+    tile = choose_tile(M, N, K, MODE == EPI_BIAS_GATE_RES ? ea.L : 0, gemm_stream_supported(MODE, K, (size_t)M * lda * 2, (size_t)N * ldw * 2),
+                       gemm_ring_supported(MODE, 2), &height);
   } else {
     tile = variant & 15;
     group_n = (variant >> 4) & 255;
     height = 8;
-    if (tile == 6) tile = TILE_128;  // (256x128 tiles in earlier versions)
+    if (tile == TILE_RING) {
+      height = (variant >> 24) & 127;
+      if (!gemm_ring_supported(MODE, height)) tile = TILE_128;  // (6 alone: 256x128 tiles in earlier versions)
+    }
     if (tile > TILE_STREAM && tile <= TILE_STREAM + 4) {
       height = tile - TILE_STREAM + 3;
       tile = TILE_STREAM;
@@ -108,6 +124,7 @@ static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, in
     case TILE_64_128: return gemm_tile_launch<64, 128, 2, 2, 3, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
     case TILE_256: return gemm_tile_launch<256, 256, 2, 4, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
     case TILE_128: return gemm_tile_launch<128, 128, 2, 2, 2, MODE, TOUT>(A, lda, W, ldw, M, N, K, ea, group_n, st);
+    case TILE_RING: return launch_gemm_bf16_ring(MODE, A, lda, W, ldw, M, N, K, ea, height, group_n, st);
     case TILE_STREAM: return launch_gemm_bf16_stream(MODE, A, lda, W, ldw, M, N, K, ea, height, group_n, row_block, st);
   }
   return fail(BR_EINVAL, "gemm: unknown variant");

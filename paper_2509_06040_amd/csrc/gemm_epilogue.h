@@ -27,10 +27,10 @@ __device__ inline void epilogue_wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Moves 16 rows (half `p` of accumulator block j) of the wave's accumulators into its LDS buffer.
+// Moves rows 16 pass .. + 15 of the wave's accumulators (32x32 blocks) into its LDS buffer.
 template <int TM, int TN>
-__device__ inline void epilogue_stage_rows(const f32x16_e (&acc)[TN][TM], char* ebuf, int j, int p, int lane) {
-  const int l32 = lane & 31, lh = lane >> 5;
+__device__ inline void epilogue_stage_rows(const f32x16_e (&acc)[TN][TM], char* ebuf, int pass, int lane) {
+  const int l32 = lane & 31, lh = lane >> 5, j = pass >> 1, p = pass & 1;
   // Lanes exchange data through the buffer without a workgroup barrier: the hardware keeps one
   // wave's LDS operations in order, and the wavefront-scope fences tell the compiler that the
   // reads on either side see other lanes' writes (it must neither reuse an earlier read of the
@@ -50,17 +50,27 @@ __device__ inline void epilogue_stage_rows(const f32x16_e (&acc)[TN][TM], char* 
   epilogue_wave_fence();
 }
 
-// Rows of a wave tile that spans more than two samples (models with fewer than 32 * TM rows
-// per sample): every row looks its sample up by itself.
-template <int TM, int TN, int MODE, typename TOUT>
-__device__ inline void wave_epilogue_rows(const f32x16_e (&acc)[TN][TM], char* ebuf, int m_base, int n_base, int M, int N,
+// The same of 16x16 blocks: block (i, j) gives lane l the columns 16 i + 4 (l >> 4) .. + 3 of row 16 j + (l & 15).
+template <int RB>
+__device__ inline void epilogue_stage_rows(const f32x4_e (&acc)[4][RB], char* ebuf, int pass, int lane) {
+  const int r = lane & 15, c = lane >> 4;
+  epilogue_wave_fence();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4_e*>(ebuf + r * 256 + (((i * 4 + c) ^ r) << 4)) = acc[i][pass];
+  epilogue_wave_fence();
+}
+
+// Rows of a wave tile (NP blocks of 16) that spans more than two samples (models with fewer rows
+// per sample than the tile): every row looks its sample up by itself.
+template <int NP, int MODE, typename TOUT, typename ACC>
+__device__ inline void wave_epilogue_rows(const ACC& acc, char* ebuf, int m_base, int n_base, int M, int N,
                                           const Epilogue<MODE, TOUT>& epi, int lane) {
   const int c4 = lane & 15, rq = lane >> 4;
   const int n = n_base + c4 * 4;
   const bool n_ok = n < N;
 #pragma unroll
-  for (int pass = 0; pass < TM * 2; ++pass) {
-    epilogue_stage_rows<TM, TN>(acc, ebuf, pass >> 1, pass & 1, lane);
+  for (int pass = 0; pass < NP; ++pass) {
+    epilogue_stage_rows(acc, ebuf, pass, lane);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int r = rq + 4 * q;
@@ -74,11 +84,10 @@ __device__ inline void wave_epilogue_rows(const f32x16_e (&acc)[TN][TM], char* e
 // FULL: every row and column of the wave tile lies inside the matrix.  That path has no
 // branches, which lets the compiler count outstanding memory operations exactly: its stores
 // never wait, its addend loads wait for just the loads ahead of them.
-template <bool FULL, int TM, int TN, int MODE, typename TOUT>
-__device__ inline void wave_epilogue_pair(const f32x16_e (&acc)[TN][TM], char* ebuf, int m_base, int n_base, int M, int N,
+template <bool FULL, int NP, int MODE, typename TOUT, typename ACC>
+__device__ inline void wave_epilogue_pair(const ACC& acc, char* ebuf, int m_base, int n_base, int M, int N,
                                           const Epilogue<MODE, TOUT>& epi, int lane) {
   using Epi = Epilogue<MODE, TOUT>;
-  constexpr int NP = TM * 2;        // passes of 16 rows
   constexpr int ADDEND_AHEAD = 2;   // passes between the fetch of an addend and its use
   constexpr int NBUF = ADDEND_AHEAD + 1;
   const int rps = epi.rows_per_sample();
@@ -117,7 +126,7 @@ __device__ inline void wave_epilogue_pair(const f32x16_e (&acc)[TN][TM], char* e
 #pragma unroll
   for (int pass = 0; pass < NP; ++pass) {
     if (pass + ADDEND_AHEAD < NP) fetch_addend(pass + ADDEND_AHEAD, add[(pass + ADDEND_AHEAD) % NBUF]);
-    epilogue_stage_rows<TM, TN>(acc, ebuf, pass >> 1, pass & 1, lane);
+    epilogue_stage_rows(acc, ebuf, pass, lane);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int r = rq + 4 * q;
@@ -192,15 +201,82 @@ __device__ inline void wave_epilogue(const f32x16_e (&acc)[TN][TM], char* ebuf, 
   static_assert(TN == 2, "waves own 64 output columns");
   const int rps = epi.rows_per_sample();
   if (rps > 0 && rps < TM * 32) {
-    wave_epilogue_rows<TM, TN, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
+    wave_epilogue_rows<2 * TM, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
   } else if (m_base + TM * 32 <= M && n_base + TN * 32 <= N) {
     if constexpr ((MODE == EPI_BIAS || MODE == EPI_BIAS_GELU) && std::is_same<TOUT, bf16>::value) {
       wave_epilogue_bf16_full<TM, TN, MODE>(acc, ebuf, m_base, n_base, epi, lane);
     } else {
-      wave_epilogue_pair<true, TM, TN, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
+      wave_epilogue_pair<true, 2 * TM, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
     }
   } else {
-    wave_epilogue_pair<false, TM, TN, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
+    wave_epilogue_pair<false, 2 * TM, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
+  }
+}
+
+// bf16 outputs of a full tile of 16x16 blocks: two blocks of rows a pass, in the buffer layout of wave_epilogue_bf16_full.
+template <int RB, int MODE>
+__device__ inline void wave_epilogue16_bf16_full(const f32x4_e (&acc)[4][RB], char* ebuf, int m_base, int n_base,
+                                                 const Epilogue<MODE, bf16>& epi, int lane) {
+  static_assert(MODE == EPI_BIAS || MODE == EPI_BIAS_GELU, "plain bf16 outputs only");
+  typedef unsigned int u32x4_e __attribute__((ext_vector_type(4)));
+  const int l16 = lane & 15, lq = lane >> 4;
+  float4 bias[4];
+  float cs[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    bias[i] = epi.bias4(n_base + i * 16 + lq * 4);
+    cs[i] = epi.colscale(n_base + i * 16 + lq * 4);
+  }
+  const int rrow = lane >> 3, rc = lane & 7;  // this lane reads chunk rc of rows rrow + 8 q
+  bf16* const obase = reinterpret_cast<bf16*>(epi.a.out) + (long long)(m_base + rrow) * epi.a.ldo + n_base + rc * 8;
+#pragma unroll
+  for (int p = 0; p < (RB + 1) / 2; ++p) {
+    epilogue_wave_fence();
+#pragma unroll
+    for (int h = 0; h < 2 && 2 * p + h < RB; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4_e a = acc[i][2 * p + h];
+        float v0 = a[0] + bias[i].x, v1 = a[1] + bias[i].y, v2 = a[2] + bias[i].z, v3 = a[3] + bias[i].w;
+        if (MODE == EPI_BIAS_GELU) {
+          v0 = gelu_tanh_f(v0);
+          v1 = gelu_tanh_f(v1);
+          v2 = gelu_tanh_f(v2);
+          v3 = gelu_tanh_f(v3);
+        } else {
+          v0 *= cs[i];
+          v1 *= cs[i];
+          v2 *= cs[i];
+          v3 *= cs[i];
+        }
+        const int r = h * 16 + l16;
+        store4<bf16>(reinterpret_cast<bf16*>(ebuf + r * 128 + (((i * 2 + (lq >> 1)) ^ ((r >> 1) & 7)) << 4) + (lq & 1) * 8), v0, v1, v2, v3);
+      }
+    epilogue_wave_fence();
+#pragma unroll
+    for (int q = 0; q < (2 * p + 1 < RB ? 4 : 2); ++q) {
+      const int r = rrow + 8 * q;
+      const u32x4_e v = *reinterpret_cast<const u32x4_e*>(ebuf + r * 128 + ((rc ^ ((r >> 1) & 7)) << 4));
+      __builtin_nontemporal_store(v, reinterpret_cast<u32x4_e*>(obase + (long long)(p * 32 + 8 * q) * epi.a.ldo));
+    }
+  }
+}
+
+// A wave tile of 16 RB rows x 64 columns in 16x16 blocks.
+template <int RB, int MODE, typename TOUT>
+__device__ inline void wave_epilogue16(const f32x4_e (&acc)[4][RB], char* ebuf, int m_base, int n_base, int M, int N,
+                                      const Epilogue<MODE, TOUT>& epi, int lane) {
+  const int rps = epi.rows_per_sample();
+  if (rps > 0 && rps < RB * 16) {
+    wave_epilogue_rows<RB, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
+  } else if (m_base + RB * 16 <= M && n_base + 64 <= N) {
+    if constexpr (std::is_same<TOUT, bf16>::value) {
+      wave_epilogue16_bf16_full<RB, MODE>(acc, ebuf, m_base, n_base, epi, lane);
+    } else {
+      wave_epilogue_pair<true, RB, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
+    }
+  } else {
+    wave_epilogue_pair<false, RB, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
   }
 }
 

@@ -642,3 +642,26 @@ def test_profile_lists_gemms_of_bf16_networks_only(lib):
         finally:
             br.profile_enable(False)
         assert any(i < 48 for i in ids) == expect, ids
+
+
+# 128-column tiles of 32 to 192 rows with a ring of four to seven stages: one stage, fewer than a ring holds, more; one row, ragged rows and
+# columns, samples shorter and longer than a wave's rows.  Same bits as the 32x32 tiles, nothing past the end.
+@pytest.mark.parametrize("height", [2, 4, 6, 8, 10, 12])
+@pytest.mark.parametrize("M,N,K,L", [(1, 4, 64, 1), (160, 128, 128, 160), (161, 132, 320, 7), (333, 260, 448, 111), (480, 384, 1088, 240)])
+def test_gemm_bf16_ring_tiles(lib, height, M, N, K, L):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K)
+    A, W = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((M, K), (N, K)))
+    b, mods, x0 = (torch.randn(s, generator=g, device=DEV) for s in ((N,), (3, N), (M + 1, N)))
+    cond = torch.arange(M // L, device=DEV, dtype=torch.int32) % 3
+    for mode in (0, 1, 2, 4):
+        outs = []
+        for variant in (0, 6 | (height << 24)):
+            out = x0.clone() if mode in (2, 4) else x0.bfloat16()
+            br.op_gemm(br.BF16, mode, A, W, b, out[:M], mods=mods if mode == 2 else None, cond=cond if mode == 2 else None, L=L, variant=variant)
+            outs.append(out)
+        if mode == 1:  # (the activation's bits may differ in the last place between epilogues; bf16 outputs: one rounding, 2^-8)
+            assert torch.allclose(outs[0].float(), outs[1].float(), rtol=2.0 ** -7, atol=1e-6)
+        else:
+            assert torch.equal(outs[0], outs[1]), mode
+        assert torch.equal(outs[1][M], x0[M].to(outs[1].dtype))
