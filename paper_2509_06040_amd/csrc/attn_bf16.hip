@@ -128,7 +128,6 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (bf16)((((lane >> 4) ^ (lane >> 2)) & 1) == 0 ? 1.f : 0.f);
   asm volatile("" : "+v"(ones));
-  // the k-step that subtracts the reference: key side 1 in k-slot 0, query side -m_run there
   // -m_run, sixteen times: what a score block starts from.  (One more k-step with the constant 1 on the key side needs no registers, but
   // is 2 of 34 matrix instructions of a tile at head dim 128, 2 of 18 at 64: 1-2 % of the launch.)
   f32x16 cm;
@@ -293,10 +292,21 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = (float)(bf16)(m_run + (it == 0 ? mx : fmaxf(mx, 0.f)));
-      const float delta = m_new - m_run;
+        for (int r = 0; r < 16; ++r) mx = __builtin_elementwise_maximum(mx, s[kb][r]);
+      mx = __builtin_elementwise_maximum(mx, __shfl_xor(mx, 32, 64));
+      float m_new = (float)(bf16)(m_run + (it == 0 ? mx : fmaxf(mx, 0.f)));
+      float delta = m_new - m_run;
+      // A query with a probability that is not finite (itself or a key it meets is not, or no key of a first tile scores above -inf) has
+      // no result.  Zero times that is not zero, so its probabilities stay out of the sums it shares an instruction for.
+      const bool lost = !((PRE ? mx - delta : (mx - delta) * scale_log2) <= 127.f);
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(lost) != 0, 0)) {
+        m_new = lost ? m_run : m_new;
+        delta = lost ? 0.f : delta;
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[kb][r] = lost ? -INFINITY : s[kb][r];
+      }
       if (it != 0) {
         const float alpha = __builtin_amdgcn_exp2f(PRE ? -delta : -delta * scale_log2);
         l_run *= alpha;
@@ -314,6 +324,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
       for (int r = 0; r < 16; ++r) cm[r] = -m_new;
       asm volatile("" : "+v"(cm));
       probabilities();
+      l_tile = lost ? __builtin_nanf("") : l_tile;
     }
     l_run += l_tile;
 

@@ -572,6 +572,46 @@ def test_attention_fp32_infinite_values_and_scores(lib, dh, L):
     assert np.isnan(run(b)).all()
 
 
+@pytest.mark.parametrize("prescaled", [0, 1])
+@pytest.mark.parametrize("dh,L", [(64, 100), (64, 300), (128, 100), (128, 257)])
+def test_attention_bf16_queries_without_a_result(lib, dh, L, prescaled):
+    """A query that is not finite, or that a key scores +inf, has no result in its head; every other query keeps its own, also one
+    whose row sums come out of the same matrix instruction, and the queries next to the last one, which fills the rows past the end."""
+    rng = np.random.default_rng(dh + L)
+    H, c = 2 * dh, np.log2(np.e) / np.sqrt(dh)
+    qkv = rng.standard_normal((1, L, 3 * H)).astype(np.float32)
+    if prescaled:
+        qkv[..., :H] *= c
+    qkv = _bf(qkv)
+
+    def check(a, lost):
+        out = torch.full((1, L, H), 3.0, dtype=torch.bfloat16, device=DEV)
+        br.op_attention(br.BF16, dev(a, torch.bfloat16), out, 2, q_prescaled=prescaled)
+        got = host(out)[0]
+        x = a.astype(np.float64)
+        x[0, lost, :dh] = 0.0                                        # (their own rows are not compared)
+        if prescaled:
+            x[..., :H] /= c
+        s = x[0].reshape(L, 3, 2, dh).transpose(1, 2, 0, 3)
+        with np.errstate(invalid="ignore"):
+            sc = np.nan_to_num(s[0] @ s[1].transpose(0, 2, 1) / np.sqrt(dh), nan=0.0, neginf=-np.inf)
+        p = np.exp(sc - sc.max(axis=2, keepdims=True))
+        ref = (p / p.sum(axis=2, keepdims=True) @ s[2]).transpose(1, 0, 2).reshape(L, H)
+        kept = np.setdiff1d(np.arange(L), lost)
+        assert np.isnan(got[lost, :dh]).all(), lost
+        assert rel_l2(got[kept, :dh], ref[kept, :dh]) < 3e-3, lost   # as in test_attention_bf16
+        assert rel_l2(got[:, dh:], ref[:, dh:]) < 3e-3, lost
+
+    for lost in ([3], [L - 1], [1, 17, 40], list(range(64, 80))):
+        for bad in (np.nan, np.inf, -np.inf):
+            a = qkv.copy()
+            a[0, lost, 5] = bad
+            check(a, np.array(lost))
+    a = qkv.copy()                                                   # key 70 scores +inf or -inf, by the sign of the query
+    a[0, 70, H + 5] = np.inf
+    check(a, np.flatnonzero(a[0, :, 5] > 0))
+
+
 def test_gemm_variant_word(lib):
     """Heights of the persistent kernel are kernel numbers of their own; what callers pass as start delays (bits 12..23) stays
     accepted and changes nothing; numbers beyond are refused."""
