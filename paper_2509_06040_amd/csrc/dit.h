@@ -107,7 +107,7 @@ br_status launch_block_rows(const br_model* m, const FwdBuffers& fb, const Sampl
 bool gemm_stream_supported(int mode, int K, size_t bytes_a, size_t bytes_w);
 br_status launch_gemm_bf16_stream(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
                                   const EpiArgs& ea, int height, int group_n, int row_block, hipStream_t st);
-bool gemm_ring_supported(int mode, int height);
+bool gemm_ring_supported(int mode, int height, int lda, int ldw);
 br_status launch_gemm_bf16_ring(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
                                 const EpiArgs& ea, int height, int group_n, hipStream_t st);
 br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH, int DH, int q_prescaled, hipStream_t st);

@@ -101,14 +101,14 @@ static br_status gemm_variant(const bf16* A, int lda, const bf16* W, int ldw, in
   int tile, group_n = 0, row_block = 0, height = 0;
   if (variant < 0) {
     tile = choose_tile(M, N, K, MODE == EPI_BIAS_GATE_RES ? ea.L : 0, gemm_stream_supported(MODE, K, (size_t)M * lda * 2, (size_t)N * ldw * 2),
-                       gemm_ring_supported(MODE, 2), &height);
+                       gemm_ring_supported(MODE, 12, lda, ldw), &height);
   } else {
     tile = variant & 15;
     group_n = (variant >> 4) & 255;
     height = 8;
     if (tile == TILE_RING) {
       height = (variant >> 24) & 127;
-      if (!gemm_ring_supported(MODE, height)) tile = TILE_128;  // (6 alone: 256x128 tiles in earlier versions)
+      if (!gemm_ring_supported(MODE, height, lda, ldw)) tile = TILE_128;  // (6 alone: 256x128 tiles in earlier versions)
     }
     if (tile > TILE_STREAM && tile <= TILE_STREAM + 4) {
       height = tile - TILE_STREAM + 3;

@@ -200,10 +200,10 @@ static br_status ring_height(const bf16* A, int lda, const bf16* W, int ldw, int
   return fail(BR_EINVAL, "gemm: unknown tile height");
 }
 
-// height: rows of a tile / 16
-bool gemm_ring_supported(int mode, int height) {
+// height: rows of a tile / 16.  A tile's rows are addressed with 32-bit byte offsets from its first one.
+bool gemm_ring_supported(int mode, int height, int lda, int ldw) {
   return (mode == EPI_BIAS || mode == EPI_BIAS_GELU || mode == EPI_BIAS_F32 || mode == EPI_BIAS_GATE_RES) &&
-         height >= 2 && height <= 12 && height % 2 == 0;
+         height >= 2 && height <= 12 && height % 2 == 0 && 16ull * height * lda * 2 < (1ull << 32) && (unsigned long long)BN * ldw * 2 < (1ull << 32);
 }
 
 br_status launch_gemm_bf16_ring(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K, const EpiArgs& ea,

@@ -612,6 +612,26 @@ def test_attention_bf16_queries_without_a_result(lib, dh, L, prescaled):
     check(a, np.flatnonzero(a[0, :, 5] > 0))
 
 
+def test_gemm_bf16_rows_far_apart(lib):
+    """192 rows of 576 values, 24 MB apart: the last rows of a tile are beyond 4 GiB from its first one.  Same bits as packed rows."""
+    import ctypes as C
+    M, N, K, lda = 192, 32768, 576, 12 << 20
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    A, W = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((M, K), (N, K)))
+    b = torch.randn(N, generator=g, device=DEV)
+    far = torch.empty((M, lda), dtype=torch.bfloat16, device=DEV)
+    far[:, :K] = A
+    ref, out = torch.empty((M, N), device=DEV), torch.empty((M, N), device=DEV)
+    br.op_gemm(br.BF16, 4, A, W, b, ref)
+    torch.cuda.synchronize()
+    i = C.c_int32
+    p = [C.c_void_p(t.data_ptr()) for t in (far, W, b, out)]
+    assert br.load().br_op_gemm(i(br.BF16), i(4), p[0], i(lda), p[1], i(K), i(M), i(N), i(K), p[2], p[3], i(N), None, i(0), i(0), None, i(1), i(-1), None) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)
+
+
 def test_gemm_variant_word(lib):
     """Heights of the persistent kernel are kernel numbers of their own; what callers pass as start delays (bits 12..23) stays
     accepted and changes nothing; numbers beyond are refused."""
