@@ -44,15 +44,23 @@ static int choose_tile(int M, int N, int K, int rps, bool stream_ok, bool ring_o
   // tiles, 300 x 1024 x 4096 10.4 instead of 23.  A long K makes the tile's operand traffic (twice that of 64x64 tiles
   // for the same outputs) the longer part sooner.
   // Beyond, the ring kernel, as long as its tiles are one round in some height: the lowest such, which spreads them over most units.
-  // Against what the rules below choose, over 235 shapes (M 300 to 8808, hidden sizes 512 to 3072 with their four projections): 6.9 %
-  // faster on average, 0.7 % slower than the best kernel of each (1101 x 3072 x 1024: 14.6 -> 11.0 us, 1101 x 2048 x 8192: 69 -> 46,
-  // 4404 x 1024 x 4096: 54 -> 39; worst 1101 x 2048 x 512, 7.6 -> 8.2).  From two rounds on its 128 columns cost operand traffic
-  // (4404 x 3072 x 1024: 28 us in the persistent kernel, 33).  Samples shorter than a wave's rows are left to the others.
+  // From two rounds on its 128 columns cost operand traffic (4404 x 3072 x 1024: 28 us in the persistent kernel, 33).  Samples
+  // shorter than a wave's rows are left to the others.
+  // A K below 768 hardly fills its stages and leaves its 5 us of launch, first stages and epilogue in sight, where smaller tiles come two
+  // to a unit (1638 x 2048 x 256: 5.8 us in 64x128 tiles, 7.2 in 128 rows of the ring; 1400 x 2304 x 576: 9.3, 10.2).  It wins there
+  // where those tiles are a little more than a round, so that some units have two and others one: 96 rows against 64x128 tiles (4404 x
+  // 512 x 512: 10.1 us, 8.9 in the ring), 160 and 192 against 128x128 and the persistent kernel (2202 x 2048 x 512: 12.4,
+  // 10.1; plain outputs with a K that the persistent kernel does not take stay with 128x128: 8831 x 640 x 192 9.8, 11.1).
+  // 64x64 tiles stay where they make one round and the ring needs 64 rows for it, half of its last columns being empty
+  // (4424 x 192 x 1536: 10.5 us, 11.1).
+  // 732 shapes (M 64 to 49 000, N 64 to 6144, K 64 to 4096): 5 % faster on average than the rules below alone, 2 % slower than the best
+  // kernel of each, at most 4 % slower than without the ring (1101 x 3072 x 1024: 14.6 -> 11.0 us, 1101 x 2048 x 8192: 69 -> 46).
   int ring = 0;
   for (int h = 2; ring_ok && h <= 12 && !ring; h += 2)
     if ((double)cdiv(M, 16 * h) * cdiv(N, 128) <= cu && (rps == 0 || rps >= 8 * h)) ring = h;
-  if (r32 <= (ring ? (K < 768 ? 4.0 : K <= 1024 ? 2.5 : 2.0) : (K < 1024 ? 4.0 : 3.0))) return TILE_32;
-  if (ring) {
+  if (K < 768 && !(N >= 128 && ((ring == 6 && K >= 384) || (ring >= 10 && (stream_ok || rps > 0))))) ring = 0;
+  if (r32 <= (ring && K >= 768 ? (K < 1024 ? 3.0 : K == 1024 ? 2.5 : 2.0) : (K < 1024 ? 4.0 : 3.0))) return TILE_32;
+  if (ring && !(ring >= 4 && r64 <= 1.0)) {
     *height = ring;
     return TILE_RING;
   }

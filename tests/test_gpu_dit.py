@@ -613,9 +613,9 @@ def test_attention_bf16_queries_without_a_result(lib, dh, L, prescaled):
 
 
 def test_gemm_bf16_rows_far_apart(lib):
-    """192 rows of 576 values, 24 MB apart: the last rows of a tile are beyond 4 GiB from its first one.  Same bits as packed rows."""
+    """192 rows of 832 values, 24 MB apart: the last rows of a tile are beyond 4 GiB from its first one.  Same bits as packed rows."""
     import ctypes as C
-    M, N, K, lda = 192, 32768, 576, 12 << 20
+    M, N, K, lda = 192, 32768, 832, 12 << 20
     g = torch.Generator(device=DEV)
     g.manual_seed(1)
     A, W = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((M, K), (N, K)))
@@ -630,6 +630,25 @@ def test_gemm_bf16_rows_far_apart(lib):
     assert br.load().br_op_gemm(i(br.BF16), i(4), p[0], i(lda), p[1], i(K), i(M), i(N), i(K), p[2], p[3], i(N), None, i(0), i(0), None, i(1), i(-1), None) == 0
     torch.cuda.synchronize()
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("M,N,K,kernel", [(1638, 2048, 256, 3), (1400, 2304, 576, 3), (4424, 192, 1536, 2), (32424, 96, 384, 3), (8831, 640, 192, 1),  # not the ring
+                                           (4404, 512, 512, 6), (2202, 2048, 512, 6), (1101, 3072, 1024, 6), (4404, 1024, 4096, 6)])
+def test_gemm_bf16_ring_where_it_is_the_faster_one(lib, M, N, K, kernel):
+    """The choice on 256 compute units: a short K stays with the tiles that come two to a unit unless they are a little more than a
+    round."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("sizes are for 256 compute units")
+    A, W = (torch.zeros(s, dtype=torch.bfloat16, device=DEV) for s in ((M, K), (N, K)))
+    out = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    br.profile_enable(True)
+    try:
+        br.op_gemm(br.BF16, 0, A, W, torch.zeros(N, device=DEV), out)
+        torch.cuda.synchronize()
+        ids = br.profile_read()
+    finally:
+        br.profile_enable(False)
+    assert list(ids) == [kernel]
 
 
 def test_gemm_variant_word(lib):
