@@ -62,8 +62,8 @@ __global__ __launch_bounds__(256) void root_noise_kernel(float* __restrict__ z, 
 constexpr int kSumShift = 11;
 constexpr double kSumScale = 4096.0;
 
-// s >= 0: the block's share; returns true (thread 0 only) when this block is the last of nblk,
-// with the complete sum in *total.
+// s >= 0: the block's share; called by one thread a word.  Returns true when this block is the last of nblk, with the
+// complete sum in *total.
 __device__ inline bool accumulate_share(unsigned long long* word, float s, int nblk, double* total) {
   const unsigned long long cap = ((1ull << 53) - 1) / (unsigned)nblk;  // a saturated total cannot wrap
   const double f = (double)s * kSumScale + 0.5;
@@ -83,11 +83,12 @@ __device__ inline bool accumulate_share(unsigned long long* word, float s, int n
 // index b*KC + k.
 //
 // What bounds it: HBM on plain steps (8 rows of 2.1 million elements: 32.5 us, 6.2 TB/s).  A split (4 rows into 8 children of
-// that size, 134 MB) took 30.5 us and takes 25.3, 5.3 TB/s: the noise of a quad costs about 1500 cycles of a SIMD, so
-//  - the next quads are fetched before the noise of the current ones is formed, and there is one branch-free body, in which
-//    the generator blocks of parent and children interleave (29.2 us);
-//  - the atomics of a block's children leave one wave together instead of one round trip after the other (25.3 us).
-// 1024 threads a block, two blocks a unit and two quads in flight are within 4 % or slower.
+// that size, 134 MB) took 30.5 us over the same buffers and takes 26: the noise of a quad costs about 1500 cycles of a SIMD, so
+// there is one branch-free body, in which the generator blocks of parent and children interleave, and the atomics of a block's
+// children leave one wave together instead of one round trip after the other.
+// Fetching the next quads in front of the noise of the current ones is no faster there (27 us) and slower where many rows stream
+// from HBM (64 rows of 262 144 into 128: 48 us, 55 with it; 32 plain rows of 2.1 million: 157, 164): a wave that
+// waits leaves the memory to others.  1024 threads a block, two blocks a unit and two quads in flight are within 4 % or slower.
 template <int KC, bool NOISE, int UNR, int NT>
 __global__ __launch_bounds__(NT) void sde_step_kernel(float* __restrict__ z, const float* __restrict__ v, int v_compact,
                                                        long long D, int n_nodes, int off_p, int off_c, int width_p,
@@ -104,26 +105,14 @@ __global__ __launch_bounds__(NT) void sde_step_kernel(float* __restrict__ z, con
   float acc[KC];
 #pragma unroll
   for (int k = 0; k < KC; ++k) acc[k] = 0.f;
-  const long long stride = (long long)gridDim.x * (NT * UNR);
-  long long q0 = (long long)blockIdx.x * (NT * UNR) + threadIdx.x;
-  float4 zn[UNR], vn[UNR];  // the next quads: in flight while the noise of the current ones is formed
-  auto fetch = [&](long long at) {
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const long long q = min(at + u * NT, nq - 1);
-      zn[u] = zp[q];
-      vn[u] = vp[q];
-    }
-  };
-  fetch(q0);
-  for (; q0 < nq; q0 += stride) {
+  for (long long q0 = (long long)blockIdx.x * (NT * UNR) + threadIdx.x; q0 < nq; q0 += (long long)gridDim.x * (NT * UNR)) {
     float4 zz[UNR], vv[UNR];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      zz[u] = zn[u];
-      vv[u] = vn[u];
+      const long long q = min(q0 + u * NT, nq - 1);
+      zz[u] = zp[q];
+      vv[u] = vp[q];
     }
-    fetch(q0 + stride);
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       const long long q = q0 + u * NT;
