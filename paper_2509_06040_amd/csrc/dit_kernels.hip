@@ -219,10 +219,11 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(const float* __restric
   }
 }
 
-// f(integral_constant R): the rows that a wavefront takes together, all of up to eight
+// f(integral_constant R): the rows that a wavefront takes together: all of up to eight, more in equal parts.  (A last part of fewer rows
+// costs as much as a whole one: a call of 9 conditions, hidden size 3072, one block, takes 436 us with 8 and 1, 376 with 5 and 4.)
 template <typename F>
 static void with_rows(int n, F&& f) {
-  switch (std::min(8, n)) {
+  switch (cdiv(n, cdiv(n, 8))) {
     case 1: f(std::integral_constant<int, 1>{}); break;
     case 2: f(std::integral_constant<int, 2>{}); break;
     case 3: f(std::integral_constant<int, 3>{}); break;
