@@ -97,7 +97,6 @@ enum { ROWS_HEAD = 0, ROWS_BODY = 1, ROWS_LAST = 2 };
 template <typename T, int RT, int SPS, int KIND>
 __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
   constexpr int ES = (int)sizeof(T), BMR = 16 * RT, LPR = NT / BMR, V = 64 / LPR;
-  constexpr bool BF = ES == 2;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   char* const xs = lds;                 // residual rows, 16-byte chunk c of row r in slot c ^ (r & xm)
   char* const act = lds + a.o_act;      // operand rows in stages of 128 bytes a row (gemm_frag.h)
@@ -168,7 +167,8 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
       *reinterpret_cast<T*>(hid + (byte >> 7) * (BMR * 128) + row * 128 + ((((byte >> 4) & 7) ^ ((row >> 1) & 7)) << 4) + (byte & 15)) =
           (T)a.z[(size_t)sample_row(a.sm, a.s0 + b) * a.D + idx];
     }
-    // zeros to the end of the last step, whose weights are the row's first ones once more
+    // zeros to the end of the last step, whose weights are the row's first ones once more.  (An infinite one among them makes a NaN where
+    // the product alone is infinite; the LayerNorm of the row makes that of either.)
     const int end = (a.pd * ES + SPS * 128 - 1) / (SPS * 128) * (SPS * 8);
     for (int row = tid; row < BMR; row += NT)
       for (int c = a.pd * ES / 16; c < end; ++c)
