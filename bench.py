@@ -91,6 +91,8 @@ HBM_KERNELS = {200: "sde_step", 201: "logp_eval", 300: "ln_modulate", 301: "adal
 def kernel_label(kid):
     if kid in HBM_KERNELS:
         return HBM_KERNELS[kid]
+    if kid >= 400:
+        return "block_rows[%s]" % ("head", "block", "last")[kid - 400]
     if kid < 100:
         return "gemm_bf16[%s,%s]" % (GEMM_NAMES[kid // 8], TILE_NAMES[kid % 8])
     return "attn_bf16[d%d]" % (kid - 100)
