@@ -50,16 +50,17 @@ ORDER = ("image", "video", "image_large")
 # same counter reads for a plain 1 GiB device copy; see profiles/hot_kernels_hbm_traffic.md.  Keyed
 # by (workload, kernel label); valid only for the kernel sources hashed beside the figures.
 TRAFFIC = {
-    'image_large|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=6952045158, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
-    'image_large|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=9131821466, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
-    'image_large|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=7260456594, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
-    'image_large|attn_bf16[d128]': dict(bytes_per_launch=2336352973, sources=('attn_bf16.hip',), sha1='deb7cb68be1bb871d37e9d8f4121d812368a0ff2'),
-    'image_large|ln_modulate': dict(bytes_per_launch=1213816320, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='4f9257b4d8c9ab0f648887a8347f2979685e772d'),
-    'image|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=546744704, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
-    'image|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=679507439, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
-    'image|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=508911121, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='e3383e1f33b39a56dd1a8c13f0442530082781d2'),
-    'image|attn_bf16[d64]': dict(bytes_per_launch=258962227, sources=('attn_bf16.hip',), sha1='deb7cb68be1bb871d37e9d8f4121d812368a0ff2'),
-    'image|ln_modulate': dict(bytes_per_launch=193815347, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='4f9257b4d8c9ab0f648887a8347f2979685e772d'),
+    'image_large|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=6993893413, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
+    'image_large|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=9137527402, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
+    'image_large|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=7248702204, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
+    'image_large|attn_bf16[d128]': dict(bytes_per_launch=2256482241, sources=('attn_bf16.hip',), sha1='f77bc27b4be26aaf5169e448ca679d11280a054f'),
+    'image_large|ln_modulate': dict(bytes_per_launch=1213816191, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='91f95ed4bce4d30b69d268204cb0d20bd10f3681'),
+    'image|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=663992245, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
+    'image|gemm_bf16[bias_gate_residual,32..192x128 ring]': dict(bytes_per_launch=102377259, sources=('gemm_bf16_ring.hip', 'gemm_frag.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='ec11ba58a4bbcec5759f2a0df21ddcecc50e0a8c'),
+    'image|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=674216228, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
+    'image|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=508174457, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
+    'image|attn_bf16[d64]': dict(bytes_per_launch=259208457, sources=('attn_bf16.hip',), sha1='f77bc27b4be26aaf5169e448ca679d11280a054f'),
+    'image|ln_modulate': dict(bytes_per_launch=193824571, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='91f95ed4bce4d30b69d268204cb0d20bd10f3681'),
 }
 
 

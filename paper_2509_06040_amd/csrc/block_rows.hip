@@ -315,7 +315,7 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
         for (int u = 0; u < SPS; ++u)
 #pragma unroll
           for (int i = 0; i < NF; ++i) w[u][i] = *reinterpret_cast<const frag*>(my_ring + slot + u * 2048 + (fo ^ (i * FLIP)));
-        if (p.steps > 1 || cb == wv) {  // (rows of one step stay in registers: what binds the loop is the LDS)
+        if (p.steps > 1 || cb == wv) {  // (rows of one step stay in registers)
 #pragma unroll
           for (int u = 0; u < SPS; ++u)
 #pragma unroll

@@ -64,11 +64,11 @@ static int choose_tile(int M, int N, int K, int rps, bool stream_ok, bool ring_o
     *height = ring;
     return TILE_RING;
   }
+  // What the ring kernel leaves: patch and unpatch products, gated residuals of short samples, short K.
   // Up to one round of 64x64 tiles: two waves each, four stages of 16 KB in flight.  1101 x 1024 x 4096: 23 us
-  // (34 in 128x128 tiles, 20.5 in the ring kernel).
+  // (34 in 128x128 tiles).
   if (r64 <= 1.2) return TILE_64;
-  // Up to one round of 128x128 tiles: half of them, so that the round is fuller (1101 x 3072 x 1024: 14.7 us,
-  // 20.8 in 256x128 tiles).
+  // Up to one round of 128x128 tiles: half of them, two to a unit (1710 x 2304 x 384: 7.9 us, 9.3 and 8.2 in 128x128 tiles of four and eight waves).
   if (r128 <= 1.0) return TILE_64_128;
   // Beyond: the persistent kernel, whose tiles are 128 to 256 rows high so that the last round of tiles is full
   // (9216 x 3072 x 12 288: 545 us in 432 tiles of 256 rows, 1.7 rounds, 490 in 504 of 224; 17 616 x 1024 x 1024: 67 us
