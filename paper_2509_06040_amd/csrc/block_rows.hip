@@ -423,12 +423,15 @@ RowsLds rows_lds(const br_model* m, int rt, bool head, int ntail) {
 // separate kernels -> fused:  bf16 hidden 64: 55 rows 105 -> 73, 2940 190 -> 117, 49 000 531 -> 400;  128: 279 rows 91 -> 68,
 // 13 500 300 -> 190, 55 700 550 -> 442;  192: 55 rows 122 -> 101;  256 (one tile only): 248 rows 169 -> 158, 3968 237 -> 172.
 // fp32 64: 24 rows 81 -> 64, 26 400 410 -> 358;  128 (one tile only): 762 rows 670 -> 655, 1905 177 -> 161.  Wider rows stream
-// more weights than the launches cost.
+// more weights than the launches cost.  fp32 96 in two tiles keeps the separate kernels where the last round of workgroups is less than a
+// quarter full (three blocks, velocity time fused / separate: 8280 rows 1.04, 9984 1.03, 24 984 1.01, 49 992 1.03; 12 000 0.86, 64 992
+// 0.98); narrower rows win there too (8280 rows: bf16 64 0.71, 128 0.77, fp32 32 0.78, 64 0.87).
 int rows_fused_tiles(const br_model* m, const FwdBuffers& fb, int M) {
   const bool bf = m->cfg.dtype == BR_BF16;
   const uintptr_t p = (uintptr_t)fb.x | (uintptr_t)fb.mods | (uintptr_t)fb.xn | (uintptr_t)fb.qkv | (uintptr_t)fb.cond_emb;
   if ((p & 15) != 0 || m->H * (bf ? 2 : 4) % 128 != 0 || m->H > (bf ? 256 : 128) || M > 65535) return 0;  // (FastDiv: M L < 2^32)
-  const int rt = cdiv(M, 16) <= device_cu_count() ? 1 : 2;
+  const int cu = device_cu_count(), rt = cdiv(M, 16) <= cu ? 1 : 2;
+  if (rt == 2 && m->H * (bf ? 2 : 4) > 256 && (cdiv(M, 32) - 1) % cu + 1 < cu / 4) return 0;
   for (int head = 0; head < 2; ++head)
     if (rows_lds(m, rt, head, std::max(3 * m->H, m->pd)).total > LDS_LIMIT) return 0;
   return rt;

@@ -517,7 +517,7 @@ def test_velocity_bits_where_the_normalisation_moves_into_the_gemm(lib, hidden, 
     (64, 1, (16, 1, 14, 18), 1, 6, synth.BF16, (1, 70, 950)), (128, 1, (16, 2, 14, 18), 2, 7, synth.BF16, (3, 200, 940)),
     (192, 3, (16, 1, 8, 6), 1, 3, synth.BF16, (1, 280)), (256, 2, (16, 1, 14, 18), 1, 6, synth.BF16, (2, 61)),
     (32, 2, (4, 1, 6, 10), 1, 2, synth.F32, (1, 300)), (64, 4, (4, 1, 8, 8), 1, 8, synth.F32, (1, 171, 2740)),
-    (96, 3, (4, 2, 10, 6), 2, 5, synth.F32, (5, 250)), (128, 2, (4, 1, 14, 18), 1, 6, synth.F32, (1, 61))])
+    (96, 3, (4, 2, 10, 6), 2, 5, synth.F32, (5, 250, 415)), (128, 2, (4, 1, 14, 18), 1, 6, synth.F32, (1, 61))])
 def test_velocity_of_narrow_networks_with_fused_rows(lib, hidden, heads, lat, pt, cond, dtype, Bs):
     """Narrow networks run the row-local part of a block in one launch, with one or two tiles of 16 rows a workgroup (the last one
     ragged, tiles across samples), in steps of 128 or 256 bytes, patch vectors shorter than a step; from the last batch size on
