@@ -24,7 +24,8 @@ extern "C" {
  * 64x64 / 64x128 / 256x256 / 128x128 tile per workgroup; 6 = one 16h x 128 tile per workgroup with a deep ring, h in bits
  * 24..30: 2, 4, 6, 8, 10 or 12, otherwise (or where 16h rows of A or 128 of W span 4 GiB) as 5; 7 = persistent streaming
  * kernel with tiles of 256 rows x 256 columns, 8 / 9 / 10 / 11 = the same with 128 / 160 / 192 / 224 rows, need
- * K % 128 == 0.  BR_F32 has 0, 3 and 5 and takes its own choice where another is asked for or does not apply.  bf16 only:
+ * K % 128 == 0.  BR_F32 has 0 and, where K % 32 == 0, 6 with h from 2 to 12 and 64 columns, 128 with bit 4, and takes its own
+ * choice where another is asked for or does not apply.  bf16 only:
  * bits 4..11 = column-group width of the tile walk, 0 = the kernel's own choice; for the persistent kernel bits 24..30 =
  * rows of a row block of the tile walk in units of 8 tile rows, 0 = the kernel's own choice; bits 12..23, start delays
  * of workgroups in earlier versions, are accepted and have no effect.  All of them give the same

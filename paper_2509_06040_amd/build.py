@@ -11,7 +11,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbranchrollout.so")
-SOURCES = ["tree.cpp", "sde_kernels.hip", "tree_kernels.hip", "dit_kernels.hip", "gemm_bf16.hip", "gemm_bf16_stream.hip", "gemm_bf16_ring.hip", "gemm_small.hip", "gemm_f32.hip", "block_rows.hip",
+SOURCES = ["tree.cpp", "sde_kernels.hip", "tree_kernels.hip", "dit_kernels.hip", "gemm_bf16.hip", "gemm_bf16_stream.hip", "gemm_bf16_ring.hip", "gemm_small.hip", "gemm_f32.hip", "gemm_f32_ring.hip", "block_rows.hip",
            "attn_bf16.hip", "attn_f32.hip",
            "forward.hip", "api.hip", "ops_api.hip", "prof.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -1,13 +1,9 @@
 // fp32 GEMM: C[m, n] = sum_k A[m, k] W[n, k] with the fused epilogues, on the matrix cores
 // (v_mfma_f32_32x32x2_f32 and 16x16x4, full fp32; 157 TFLOP/s nominal, twice the vector rate).  This file holds the
-// choice between the tile kernel (gemm_tile.h) and the kernel for small problems (gemm_small.hip), and a vector
+// choice between the ring kernel (gemm_f32_ring.hip) and the kernel for small problems (gemm_small.hip), and a vector
 // kernel for operands that cannot be fetched in 16-byte pieces.
-#include <algorithm>
-#include <cmath>
-
 #include "common.h"
 #include "dit.h"
-#include "gemm_tile.h"
 #include "prof.h"
 
 namespace br {
@@ -68,56 +64,23 @@ static br_status gemm_f32_any(const float* A, int lda, const float* W, int ldw, 
   return BR_OK;
 }
 
-template <int BM, int BN, int WGM, int WGN, int NST, int MODE>
-static br_status gemm_f32_tile(const float* A, int lda, const float* W, int ldw, int M, int N, int K, const EpiArgs& ea,
-                               hipStream_t st) {
-  Epilogue<MODE, float> epi{ea};
-  const int tiles_m = cdiv(M, BM), tiles_n = cdiv(N, BN);
-  hipLaunchKernelGGL((gemm_tile_kernel<float, BM, BN, WGM, WGN, NST, MODE, float>), dim3(tiles_m * tiles_n), dim3(WGM * WGN * 64), 0, st,
-                     A, lda, W, ldw, M, N, K, tiles_m, tiles_n, std::min(4, tiles_n), epi);
-  BR_LAUNCH_CHECK();
-  return BR_OK;
-}
-
-enum { F32_TILE_32 = 0, F32_TILE_64 = 3, F32_TILE_128 = 5 };  // variants
-
-// Share of the compute units' time that `tiles` equal tiles keep busy: they run in whole rounds.
-static double round_fill(long long tiles) {
-  const double r = (double)tiles / device_cu_count();
-  return r / std::ceil(r);
-}
-
-// Measured on MI355X (gated residual, M = 1101 / 4404 / 8808 rows, N and K 1024 to 4096), all three forms
-// run at a constant rate times the fill of their rounds: 133 TFLOP/s for 128x128 tiles, 132 for 64x128 and
-// 102 for 32x32, each within 7 %.  The smaller tile trades rate for fill: 4404 x 1024 x 1024 takes 130 / 98 / 100 us
-// (the vector kernel: 177), 4404 x 3072 x 1024 251 / 220 / 272 (401), 8808 x 4096 x 1024 558 / 570 / 728 (1011).  Far
-// below one round the 32x32 form wins by its four waves per tile: 24 x 64 x 256 takes 3.7 us instead of 12.
-static int f32_form(int M, int N, int K) {
-  if (K % 32 != 0) return F32_TILE_32;  // the tile kernel walks K in whole stages of 32
-  const double t128 = 133.0 * round_fill((long long)cdiv(M, 128) * cdiv(N, 128));
-  const double t64 = 132.0 * round_fill((long long)cdiv(M, 64) * cdiv(N, 128));
-  const double t32 = 102.0 * round_fill((long long)cdiv(M, 32) * cdiv(N, 32));
-  // padding of ragged edges is work done for nothing
-  const double used = (double)M * N;
-  const double e128 = t128 * used / ((double)cdiv(M, 128) * 128 * cdiv(N, 128) * 128);
-  const double e64 = t64 * used / ((double)cdiv(M, 64) * 64 * cdiv(N, 128) * 128);
-  const double e32 = t32 * used / ((double)cdiv(M, 32) * 32 * cdiv(N, 32) * 32);
-  if (e32 >= e64 && e32 >= e128) return F32_TILE_32;
-  return e64 >= e128 ? F32_TILE_64 : F32_TILE_128;
-}
+enum { F32_TILE_32 = 0, F32_RING = 6 };  // variants
 
 template <int MODE>
 static br_status gemm_f32_mode(const float* A, int lda, const float* W, int ldw, int M, int N, int K, const EpiArgs& ea,
                                int variant, hipStream_t st) {
   const bool chunks = K % 4 == 0 && lda % 4 == 0 && ldw % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
   if (!chunks) return gemm_f32_any<MODE>(A, lda, W, ldw, M, N, K, ea, st);
-  // patch embedding, condition embedding and unpatchify are a few per cent of a network: one form is enough
-  constexpr bool TILED = MODE == EPI_BIAS || MODE == EPI_BIAS_GELU || MODE == EPI_BIAS_GATE_RES;
-  const bool forced = variant == F32_TILE_64 || variant == F32_TILE_128 || variant == F32_TILE_32;
-  const int form = forced && K % 32 == 0 ? variant : f32_form(M, N, K);
-  if constexpr (TILED) {
-    if (form == F32_TILE_64) return gemm_f32_tile<64, 128, 2, 2, 2, MODE>(A, lda, W, ldw, M, N, K, ea, st);
-    if (form == F32_TILE_128) return gemm_f32_tile<128, 128, 2, 2, 2, MODE>(A, lda, W, ldw, M, N, K, ea, st);
+  // (patch embedding, condition embedding and unpatchify are a few per cent of a network: one form is enough)
+  if (variant != F32_TILE_32 && gemm_f32_ring_supported(MODE, K, lda, ldw)) {
+    int rb = variant < 0 ? 0 : variant >> 24 & 127, cb = variant >> 4 & 1 ? 2 : 1;
+    const bool forced = variant >= 0 && (variant & 15) == F32_RING && rb >= 2 && rb <= F32_RING_MAX_RB;
+    // Up to three 32x32 tiles a compute unit the four waves of each are faster (599 x 768 x 768 11.8 us, 13.9 in the best ring tile; 3833
+    // x 192 x 768 15.1, 16.0; 24 x 64 x 256 by far); beyond, the ring (1101 x 1024 x 4096 98 us, 91; 1624 x 768 x 3072 84, 70).
+    if (forced || (long long)cdiv(M, 32) * cdiv(N, 32) > 3LL * device_cu_count()) {
+      if (!forced) gemm_f32_ring_tile(M, N, K, MODE == EPI_BIAS_GATE_RES ? ea.L : 0, &rb, &cb);
+      return launch_gemm_f32_ring(MODE, A, lda, W, ldw, M, N, K, ea, rb, cb, st);
+    }
   }
   return launch_gemm_small(BR_F32, MODE, A, lda, W, ldw, M, N, K, ea, st);
 }

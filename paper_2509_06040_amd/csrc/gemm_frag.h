@@ -33,23 +33,6 @@ struct GemmFrag<__bf16> {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a, c, 0, 0, 0);
   }
 };
-template <>
-struct GemmFrag<float> {
-  typedef float type __attribute__((ext_vector_type(4)));
-  static constexpr int STEPS = 4;  // k = 2 e and 2 e + 1 of the pair's eight
-  static __device__ inline int offset(int row, int lh) { return row * 128 + (((row >> 1) & 7) << 4) + lh * 4; }
-  // (two reads of two words each, 3 % of a launch more than one of a chunk, which would interleave the chunks of a pair: 0 4 1 5
-  // 2 6 3 7; exchanging those between the halves of the wave costs 8 %, four reads of one word 5)
-  static __device__ inline type load(const char* p, int off) {
-    const float* c0 = reinterpret_cast<const float*>(p + off);
-    const float* c1 = reinterpret_cast<const float*>(p + (off ^ 16));
-    return type{c0[0], c0[2], c1[0], c1[2]};
-  }
-  static __device__ inline f32x16 mma(const type& w, const type& a, const f32x16& c, int e) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], a[e], c, 0, 0, 0);
-  }
-};
-
 // 16x16 instructions: fragment i of a stage for lane group g = lane / 16, at offset(row, g) ^ (i * FLIP), is chunk 4 i + g (bf16,
 // 32 k an instruction) or word g of chunk i (fp32, 4 k).
 template <typename T>

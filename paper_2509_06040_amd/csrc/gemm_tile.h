@@ -1,4 +1,4 @@
-// GEMM with one output tile per workgroup on the gfx950 matrix cores, bf16 or fp32 operands:
+// GEMM with one output tile per workgroup on the gfx950 matrix cores (T: bf16):
 // C[m, n] = sum_k A[m, k] W[n, k], fp32 accumulate, fused epilogue.
 #pragma once
 #include <type_traits>

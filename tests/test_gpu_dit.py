@@ -778,3 +778,22 @@ def test_gemm_bf16_ring_tiles(lib, height, M, N, K, L):
             outs.append(out)
         assert torch.equal(outs[0], outs[1]), mode
         assert torch.equal(outs[1][M], x0[M].to(outs[1].dtype))
+
+
+# fp32 tiles of 16 h rows x 64 or 128 columns: one stage of 32 k, two (both slots), an odd and an even number more; one row, ragged rows and
+# columns, samples shorter and longer than a tile.  Same bits as the 32x32 tiles, nothing past the end.
+@pytest.mark.parametrize("height", range(2, 13))
+@pytest.mark.parametrize("M,N,K,L", [(1, 4, 32, 1), (160, 128, 64, 160), (203, 132, 160, 7), (390, 260, 96, 195), (577, 384, 1056, 577)])
+def test_gemm_fp32_ring_tiles(lib, height, M, N, K, L):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K)
+    A, W, b, mods, x0 = (torch.randn(s, generator=g, device=DEV) for s in ((M, K), (N, K), (N,), (3, N), (M + 1, N)))
+    cond = torch.arange(M // L, device=DEV, dtype=torch.int32) % 3
+    for mode in (0, 1, 2):
+        outs = []
+        for variant in (0, 6 | (height << 24), 6 | (height << 24) | 16):
+            out = x0.clone()
+            br.op_gemm(br.F32, mode, A, W, b, out[:M], mods=mods if mode == 2 else None, cond=cond if mode == 2 else None, L=L, variant=variant)
+            outs.append(out)
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), mode
+        assert torch.equal(outs[0][M], x0[M])
