@@ -797,3 +797,24 @@ def test_gemm_fp32_ring_tiles(lib, height, M, N, K, L):
             outs.append(out)
         assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), mode
         assert torch.equal(outs[0][M], x0[M])
+
+
+# Head dim 64 has two kernels, chosen by the number of workgroups: one tile of keys, two, three (each buffer refilled), an odd and an even number
+# more; last tiles of 1, 32, 33 and 64 keys; a reference that moves mid-sequence in some queries; waves without queries.  The same bits.
+@pytest.mark.parametrize("prescaled", [0, 1])
+@pytest.mark.parametrize("L", [1, 33, 64, 65, 128, 161, 192, 257, 300, 417])
+def test_attention_bf16_head_dim_64_does_not_depend_on_the_kernel(lib, L, prescaled):
+    nh, n = 2, 9 * 256 // (2 * ((L + 127) // 128)) + 1     # nine workgroups a compute unit
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    qkv = torch.randn((3, L, 3 * nh * 64), generator=g, device=DEV)
+    qkv[1, L // 2:, nh * 64:2 * nh * 64] *= 12.0           # later keys score far above the first tiles'
+    qkv = qkv.bfloat16()
+    few, many = torch.empty((3, L, nh * 64), device=DEV).bfloat16(), torch.empty((n, L, nh * 64), device=DEV).bfloat16()
+    br.op_attention(br.BF16, qkv, few, nh, prescaled)
+    br.op_attention(br.BF16, qkv[torch.arange(n, device=DEV) % 3].contiguous(), many, nh, prescaled)
+    assert torch.equal(many, few[torch.arange(n, device=DEV) % 3])
+    q, k, v = (t.float().reshape(3, L, nh, 64).transpose(1, 2).double().cpu() for t in qkv.split(nh * 64, dim=2))
+    s = (q @ k.transpose(2, 3).contiguous()) * (0.6931471805599453 if prescaled else 0.125)
+    ref = (torch.softmax(s, dim=3) @ v).transpose(1, 2).reshape(3, L, nh * 64)
+    assert rel_l2(host(few.float()), ref.numpy()) < 8e-3   # probabilities and outputs rounded to bf16, 2^-9 each
