@@ -15,6 +15,7 @@
 // group of 16 lanes, lane 4 r + q supplies the address of 8 bytes (4 values of row r) and
 // lane j receives element j of rows 0..3, so each lane ends up with four consecutive keys
 // of its own channel.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -40,6 +41,7 @@ template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(std::make_integer_sequence<int, N>{}, f); }
 
 constexpr int KV_TILE = 64;
+constexpr long long WARM_BYTES_PER_TILE = 2 << 20;  // what 256 idle compute units read while a workgroup takes a key tile
 
 // (a uniform address; saying so keeps it in scalar registers)
 static __device__ inline const char* uniform_ptr(const char* p) {
@@ -52,6 +54,27 @@ static __device__ inline const char* uniform_ptr(const char* p) {
 static __device__ inline u32x4 sample_rows(const bf16* p, unsigned bytes) {
   const unsigned long long v = reinterpret_cast<unsigned long long>(p);
   return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((unsigned)v), (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(v >> 32)) & 0xffffu, bytes, 0x00020000u};
+}
+
+// What the workgroups in front of a launch that leaves compute units idle do: they read the weights of the products behind the attention
+// once, in whole rows, so that these find them in the memory-side cache (256 MB) instead of pulling them from HBM in columns of 128 bytes,
+// 8 KB apart at K = 4096 (1101 x 1024 x 4096 with weights from HBM 25 us, from that cache 19.3).  One sample of the image network, 112 of 256
+// units idle: the two gated projections of a block 37 -> 29 us, the attention itself 14.3 -> 15.3; with plain stores of the activations, which
+// leave those in the caches as well, 1128 -> 1025 us a call (plain stores alone 1117, the weights alone 1117).
+static __device__ inline void warm_rows(const WarmRows& w) {
+  const unsigned stride = w.blocks * 256;
+#pragma unroll
+  for (int r = 0; r < WarmRows::RANGES; ++r) {
+    const u32x4* p = reinterpret_cast<const u32x4*>(w.p[r]);
+    const unsigned n = w.n16[r];
+    for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < n; i += 8 * stride) {
+      u32x4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[min(i + u * stride, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) asm volatile("" ::"v"(v[u]));  // (read for its own sake)
+    }
+  }
 }
 
 // Slot permutations of the K and V tiles: 16-byte chunk c of row r sits in slot c ^ swz(r).
@@ -75,7 +98,7 @@ __device__ inline int v_swz(int r) { return DH == 128 ? ((r & 3) << 2) : (((r >>
 // QKV projection writes it; otherwise the exponent is scaled here, one multiplication per score.
 template <int DH, bool PRE>
 __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out, int L,
-                                                           int H, int NH, int n_pairs, int grouped, float scale_log2) {
+                                                           int H, int NH, int n_pairs, int grouped, float scale_log2, WarmRows warm) {
   constexpr int CH = DH / 8;    // 16-byte chunks per K row
   constexpr int KS = DH / 16;   // MFMA k-steps of the score product
   constexpr int DB = DH / 32;   // 32-row blocks of O^T
@@ -98,13 +121,18 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
   // (With few pairs that would leave XCDs idle: then tiles are simply dealt out in order.)
   const int nq = (L + 127) / 128;
   int pair, qt;
+  if ((int)blockIdx.x < warm.blocks) {
+    warm_rows(warm);
+    return;
+  }
+  const int block = blockIdx.x - warm.blocks;  // (a multiple of 8)
   if (grouped) {
-    const int x = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int x = block & 7, slot = block >> 3;
     pair = (slot / nq) * 8 + x;
     qt = slot - (slot / nq) * nq;
   } else {
-    pair = blockIdx.x / nq;
-    qt = blockIdx.x - pair * nq;
+    pair = block / nq;
+    qt = block - pair * nq;
   }
   if (pair >= n_pairs) return;
   const int b = pair / NH, h = pair - b * NH;
@@ -435,7 +463,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
 // of LDS instead of four.  (At head dim 128 it does not fit 256 registers: 1068 TFLOP/s at 4608 tokens, 1168 above.)
 template <int DH, bool PRE>
 __global__ __launch_bounds__(256, 2) void attn_bf16_pipe_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out, int L,
-                                                           int H, int NH, int n_pairs, int grouped, float scale_log2) {
+                                                           int H, int NH, int n_pairs, int grouped, float scale_log2, WarmRows warm) {
   constexpr int CH = DH / 8;    // 16-byte chunks per K row
   constexpr int KS = DH / 16;   // MFMA k-steps of the score product
   constexpr int DB = DH / 32;   // 32-row blocks of O^T
@@ -455,13 +483,18 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_pipe_kernel(const bf16* __re
   // (With few pairs that would leave XCDs idle: then tiles are simply dealt out in order.)
   const int nq = (L + 127) / 128;
   int pair, qt;
+  if ((int)blockIdx.x < warm.blocks) {
+    warm_rows(warm);
+    return;
+  }
+  const int block = blockIdx.x - warm.blocks;  // (a multiple of 8)
   if (grouped) {
-    const int x = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int x = block & 7, slot = block >> 3;
     pair = (slot / nq) * 8 + x;
     qt = slot - (slot / nq) * nq;
   } else {
-    pair = blockIdx.x / nq;
-    qt = blockIdx.x - pair * nq;
+    pair = block / nq;
+    qt = block - pair * nq;
   }
   if (pair >= n_pairs) return;
   const int b = pair / NH, h = pair - b * NH;
@@ -789,7 +822,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_pipe_kernel(const bf16* __re
 }
 
 
-br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH, int DH, int q_prescaled, hipStream_t st) {
+br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH, int DH, int q_prescaled, const WarmRows& next, hipStream_t st) {
   BR_REQUIRE(L >= 1, BR_EINVAL, "attention: empty sequence");
   // the ragged last tile addresses its rows with 32-bit byte offsets from the sample's first row
   BR_REQUIRE((unsigned long long)L * 3ull * NH * DH * 2ull < (1ull << 32), BR_ESHAPE,
@@ -798,12 +831,23 @@ br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH
   const int grouped = n_pairs >= 32 ? 1 : 0;
   const long long n_blocks = (grouped ? (n_pairs + 7) / 8 * 8 : n_pairs) * cdiv(L, 128);
   BR_REQUIRE(n_blocks <= 0x7FFFFFFFLL, BR_ESHAPE, "attention: too many workgroups for one launch");
-  dim3 g((unsigned)n_blocks), blk(256);
+  // Where the launch leaves compute units idle: as much of the list as they read meanwhile (see warm_rows).
+  WarmRows warm = next;
+  const int idle = device_cu_count() - (int)std::min<long long>(n_blocks, device_cu_count());
+  warm.blocks = idle / 8 * 8;
+  if (warm.blocks < 32) warm = WarmRows{};
+  unsigned budget = (unsigned)(WARM_BYTES_PER_TILE / 16 * (cdiv(L, KV_TILE) + 4) / 256 * warm.blocks);
+  for (unsigned& n : warm.n16) {
+    n = std::min(n, budget);
+    budget -= n;
+  }
+  if (warm.n16[0] == 0) warm.blocks = 0;
+  dim3 g((unsigned)n_blocks + warm.blocks), blk(256);
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)DH));
   const int H = NH * DH;
   ProfScope ps(st, PROF_ATTN + DH, 4.0 * B * (double)L * L * H);
 #define BR_ATTN_GO_K(KERNEL, DHc, PREc) \
-  hipLaunchKernelGGL((KERNEL<DHc, PREc>), g, blk, 0, st, qkv, out, L, H, NH, (int)n_pairs, grouped, scale_log2)
+  hipLaunchKernelGGL((KERNEL<DHc, PREc>), g, blk, 0, st, qkv, out, L, H, NH, (int)n_pairs, grouped, scale_log2, warm)
 #define BR_ATTN_GO(DHc, PREc) BR_ATTN_GO_K(attn_bf16_kernel, DHc, PREc)
   // up to six workgroups a compute unit the pipelined loop is the faster one (figures there), bit for bit the same
   const bool pipe = DH == 64 && n_blocks <= 6LL * device_cu_count();

@@ -81,7 +81,14 @@ br_status embed_cond(const br_model* m, const FwdBuffers& fb, const void* cond_t
 br_status launch_gemm(int dtype, int mode, const void* A, int lda, const void* W, int ldw, int M, int N, int K,
                       const EpiArgs& ea, hipStream_t st);
 // q_prescaled: the q third already carries the factor log2(e) / sqrt(DH) (bf16 only)
-br_status launch_attention(int dtype, const void* qkv, void* out, int B, int L, int NH, int DH, int q_prescaled,
+// next: memory that the launches behind this one read
+struct WarmRows {
+  static constexpr int RANGES = 4;
+  const void* p[RANGES] = {};
+  unsigned n16[RANGES] = {};  // 16-byte pieces
+  int blocks = 0;
+};
+br_status launch_attention(int dtype, const void* qkv, void* out, int B, int L, int NH, int DH, int q_prescaled, const WarmRows& next,
                            hipStream_t st);
 br_status launch_gemm_bf16(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
                            const EpiArgs& ea, int variant, hipStream_t st);
@@ -115,7 +122,7 @@ br_status launch_gemm_bf16_stream(int mode, const bf16* A, int lda, const bf16* 
 bool gemm_ring_supported(int mode, int height, int lda, int ldw);
 br_status launch_gemm_bf16_ring(int mode, const bf16* A, int lda, const bf16* W, int ldw, int M, int N, int K,
                                 const EpiArgs& ea, int height, int group_n, hipStream_t st);
-br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH, int DH, int q_prescaled, hipStream_t st);
+br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH, int DH, int q_prescaled, const WarmRows& next, hipStream_t st);
 br_status launch_attention_f32(const float* qkv, float* out, int B, int L, int NH, int DH, hipStream_t st);
 br_status launch_ln_modulate(int dtype, const float* x, void* out, int n_rows, int rows_per_sample, int L_in, int H,
                              const float* mods, int A, int shift_off, int scale_off, const int* condmap,
@@ -224,7 +231,7 @@ struct Epilogue {
       store4<T>(reinterpret_cast<T*>(a.out) + (long long)m * a.ldo + n, gelu_tanh_f(v0), gelu_tanh_f(v1),
                 gelu_tanh_f(v2), gelu_tanh_f(v3));
     } else if (MODE == EPI_BIAS_GATE_RES) {
-      store4_stream(reinterpret_cast<float*>(a.out) + (long long)m * a.ldo + n, fmaf(sc.gate.x, v0, add.x),
+      store4<float>(reinterpret_cast<float*>(a.out) + (long long)m * a.ldo + n, fmaf(sc.gate.x, v0, add.x),
                     fmaf(sc.gate.y, v1, add.y), fmaf(sc.gate.z, v2, add.z), fmaf(sc.gate.w, v3, add.w));
     } else if (MODE == EPI_PATCH_EMBED) {
       store4<float>(reinterpret_cast<float*>(a.out) + sc.o + (long long)tok * a.ldo + n, v0 + add.x, v1 + add.y,

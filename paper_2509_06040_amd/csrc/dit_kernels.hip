@@ -323,7 +323,7 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
     for (int i = 0; i < VPL; ++i) {
       const int c4 = lane + 64 * i;
       const float4 a = sh[c4], g = sc[c4];
-      store4_stream(orow + 4 * c4, fmaf((v[i].x - mean) * rstd, 1.f + g.x, a.x), fmaf((v[i].y - mean) * rstd, 1.f + g.y, a.y),
+      store4<T>(orow + 4 * c4, fmaf((v[i].x - mean) * rstd, 1.f + g.x, a.x), fmaf((v[i].y - mean) * rstd, 1.f + g.y, a.y),
                 fmaf((v[i].z - mean) * rstd, 1.f + g.z, a.z), fmaf((v[i].w - mean) * rstd, 1.f + g.w, a.w));
     }
   } else {
@@ -376,10 +376,10 @@ br_status launch_gemm(int dtype, int mode, const void* A, int lda, const void* W
   return launch_gemm_f32(mode, (const float*)A, lda, (const float*)W, ldw, M, N, K, ea, -1, st);
 }
 
-br_status launch_attention(int dtype, const void* qkv, void* out, int B, int L, int NH, int DH, int q_prescaled,
+br_status launch_attention(int dtype, const void* qkv, void* out, int B, int L, int NH, int DH, int q_prescaled, const WarmRows& next,
                            hipStream_t st) {
   if (B == 0) return BR_OK;
-  if (dtype == BR_BF16) return launch_attention_bf16((const bf16*)qkv, (bf16*)out, B, L, NH, DH, q_prescaled, st);
+  if (dtype == BR_BF16) return launch_attention_bf16((const bf16*)qkv, (bf16*)out, B, L, NH, DH, q_prescaled, next, st);
   BR_REQUIRE(!q_prescaled, BR_EINVAL, "attention: prescaled queries are a bf16 layout");
   return launch_attention_f32((const float*)qkv, (float*)out, B, L, NH, DH, st);
 }

@@ -63,7 +63,7 @@ br_status forward(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, 
   if (const int rt = rows_fused_tiles(m, fb, B * L)) {
     ProfChain chain(dt == BR_BF16);
     for (int k = -1; k < m->NB; ++k) {
-      if (k >= 0) BR_TRY(launch_attention(dt, fb.qkv, fb.xn, B, L, m->NH, m->DH, dt == BR_BF16 ? 1 : 0, st));
+      if (k >= 0) BR_TRY(launch_attention(dt, fb.qkv, fb.xn, B, L, m->NH, m->DH, dt == BR_BF16 ? 1 : 0, WarmRows{}, st));
       BR_TRY(launch_block_rows(m, fb, sm, b0, B, v_rows_mode, z_base, v_out, k, rt, st));
     }
     return BR_OK;
@@ -90,6 +90,8 @@ br_status forward(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, 
     const br_status e = launch_ln_modulate(dt, fb.x, fb.xn, rows, rows_per_sample, L, H, fb.mods, m->A, shift, shift + H, fb.modmap, st);
     return e != BR_OK ? e : launch_gemm(dt, mode, fb.xn, H, W, H, rows, N, H, ea, st);
   };
+  // Networks whose matrices (of the blocks and the modulation) do not stay in the memory-side cache from one evaluation to the next.
+  const bool cold_weights = dt == BR_BF16 && ((4.0 + 2.0 * m->R) * m->NB * H * H + (double)m->A * H) * es > 192e6;
   // the bf16 block stack launches only instrumented kernels, back to back
   ProfChain chain(dt == BR_BF16);
   for (int k = 0; k < m->NB; ++k) {
@@ -109,7 +111,18 @@ br_status forward(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, 
       }
       BR_TRY(ln_gemm(EPI_BIAS, L, mo, qkv_w, 3 * H, ea));
     }
-    BR_TRY(launch_attention(dt, fb.qkv, fb.xn, B, L, m->NH, m->DH, dt == BR_BF16 ? 1 : 0, st));  // xn is free again: attention output
+    WarmRows next;  // the weights that the block's other products and the next block's first one are about to stream
+    if (cold_weights) {
+      auto range = [&](int i, const char* p, size_t bytes) {
+        next.p[i] = p;
+        next.n16[i] = (unsigned)std::min<size_t>(bytes / 16, 1u << 24);
+      };
+      range(0, proj_w, (size_t)H * H * es);
+      range(1, fc1_w, (size_t)m->R * H * H * es);
+      range(2, fc2_w, (size_t)m->R * H * H * es);
+      if (k + 1 < m->NB) range(3, qkv_w + (size_t)3 * H * H * es, (size_t)3 * H * H * es);
+    }
+    BR_TRY(launch_attention(dt, fb.qkv, fb.xn, B, L, m->NH, m->DH, dt == BR_BF16 ? 1 : 0, next, st));  // xn is free again: attention output
     {
       EpiArgs ea{};
       ea.bias = (const float*)m->w[BR_W_PROJ_B] + (size_t)k * H;

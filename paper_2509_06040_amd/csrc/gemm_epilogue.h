@@ -5,6 +5,7 @@
 // the row-wise reads) and stores whole row segments of its 64 columns:
 //   - bf16 outputs of a full tile: bias / GELU in the accumulator layout, rounded, 32 rows per pass;
 //   - everything else: fp32 through LDS, 16 rows per pass, then bias / gate / addend per row.
+// Stores are plain: the outputs of these kernels are small enough to be in the caches when the next launch reads them.
 //
 // A wave's loads and stores retire through one in-order counter, so a load issued behind a
 // store waits for that store's write acknowledgement.  The pass loops therefore contain no
@@ -190,7 +191,7 @@ __device__ inline void wave_epilogue_bf16_full(const f32x16_e (&acc)[TN][TM], ch
     for (int q = 0; q < 4; ++q) {
       const int r = rrow + 8 * q;
       const u32x4_e v = *reinterpret_cast<const u32x4_e*>(ebuf + r * 128 + ((rc ^ ((r >> 1) & 7)) << 4));
-      __builtin_nontemporal_store(v, reinterpret_cast<u32x4_e*>(obase + (long long)(j * 32 + 8 * q) * epi.a.ldo));
+      *reinterpret_cast<u32x4_e*>(obase + (long long)(j * 32 + 8 * q) * epi.a.ldo) = v;
     }
   }
 }
@@ -257,7 +258,7 @@ __device__ inline void wave_epilogue16_bf16_full(const f32x4_e (&acc)[4][RB], ch
     for (int q = 0; q < (2 * p + 1 < RB ? 4 : 2); ++q) {
       const int r = rrow + 8 * q;
       const u32x4_e v = *reinterpret_cast<const u32x4_e*>(ebuf + r * 128 + ((rc ^ ((r >> 1) & 7)) << 4));
-      __builtin_nontemporal_store(v, reinterpret_cast<u32x4_e*>(obase + (long long)(p * 32 + 8 * q) * epi.a.ldo));
+      *reinterpret_cast<u32x4_e*>(obase + (long long)(p * 32 + 8 * q) * epi.a.ldo) = v;
     }
   }
 }

@@ -41,7 +41,7 @@ extern "C" br_status br_op_attention(int32_t dtype, const void* qkv, void* out, 
   BR_REQUIRE(B >= 1 && L >= 1 && NH >= 1, BR_EINVAL, "br_op_attention: bad sizes");
   BR_REQUIRE(q_prescaled == 0 || (q_prescaled == 1 && dtype == BR_BF16), BR_EINVAL,
              "br_op_attention: q_prescaled is 0, or 1 with BR_BF16");
-  return launch_attention(dtype, qkv, out, B, L, NH, DH, q_prescaled, (hipStream_t)stream);
+  return launch_attention(dtype, qkv, out, B, L, NH, DH, q_prescaled, WarmRows{}, (hipStream_t)stream);
 }
 
 extern "C" br_status br_op_ln_modulate(int32_t dtype, const float* x, void* out, int32_t n_rows,

@@ -818,3 +818,20 @@ def test_attention_bf16_head_dim_64_does_not_depend_on_the_kernel(lib, L, presca
     s = (q @ k.transpose(2, 3).contiguous()) * (0.6931471805599453 if prescaled else 0.125)
     ref = (torch.softmax(s, dim=3) @ v).transpose(1, 2).reshape(3, L, nh * 64)
     assert rel_l2(host(few.float()), ref.numpy()) < 8e-3   # probabilities and outputs rounded to bf16, 2^-9 each
+
+
+def test_velocity_where_attention_leaves_units_to_the_weights(lib):
+    """Networks too large for the memory-side cache read the next weights in front of an attention that leaves compute units idle (one
+    sample), and not where it does not (eighteen): the same bits, right against the oracle."""
+    cfg = synth.model_cfg(3, 2048, 32, (16, 1, 14, 18), (1, 2, 2), 9, synth.BF16)
+    W = synth.make_weights(cfg, 3, 0.03)
+    model = make_model(cfg, W)
+    D = synth.model_sizes(cfg)["D"]
+    z, tok = synth.random_latents(1, D, 4), synth.cond_tokens(cfg, 1, 5)
+    out = []
+    for n in (1, 18):
+        v = torch.empty((n, D), device=DEV)
+        br.velocity(model, dev(z).repeat(n, 1), 0.4, cond_dev(cfg, tok), np.zeros(n, np.int32), v, bytes_buffer(br.workspace_bytes(None, model, n)))
+        out.append(v)
+    assert torch.equal(out[1], out[0].expand(18, -1))
+    assert_velocity(cfg, host(out[0])[0], dit.forward(cfg, W, z, 0.4, tok, np.zeros(1, np.int32))[0], 2e-2)
