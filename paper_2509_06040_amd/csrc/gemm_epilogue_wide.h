@@ -107,7 +107,8 @@ __device__ __forceinline__ void wide_epilogue_pair(const f32x4_e (&acc)[8][RB], 
 
 // bf16 outputs of a wave tile wholly inside the matrix: bias and activation in the accumulator layout, rounded before
 // the trip through LDS, 32 rows of 256 bytes per pass (16-byte chunk c of row r in slot c ^ (r & 15)).
-template <int RB, int MODE>
+// KEEP: plain stores, which leave the rows in the caches for the launch that reads them; else past the caches (see the kernel).
+template <int RB, int MODE, bool KEEP>
 __device__ __forceinline__ void wide_epilogue_bf16(const f32x4_e (&acc)[8][RB], char* ebuf, int m_base, int n_base,
                                                    const Epilogue<MODE, bf16>& epi, int lane) {
   typedef __bf16 bf16x4_e __attribute__((ext_vector_type(4)));
@@ -146,13 +147,15 @@ __device__ __forceinline__ void wide_epilogue_bf16(const f32x4_e (&acc)[8][RB], 
     for (int q = 0; q < (2 * p + 1 < RB ? 8 : 4); ++q) {
       const int r = lq + 4 * q;
       const u32x4_e v = *reinterpret_cast<const u32x4_e*>(ebuf + r * 256 + ((l16 ^ (r & 15)) << 4));
-      __builtin_nontemporal_store(v, reinterpret_cast<u32x4_e*>(obase + (long long)(p * 32 + 4 * q) * epi.a.ldo));
+      u32x4_e* const dst = reinterpret_cast<u32x4_e*>(obase + (long long)(p * 32 + 4 * q) * epi.a.ldo);
+      if constexpr (KEEP) *dst = v;
+      else __builtin_nontemporal_store(v, dst);
     }
   }
 }
 
 // Returns a lower bound on the number of store instructions the wave has issued (0 on the guarded paths).
-template <int RB, int MODE, typename TOUT>
+template <int RB, int MODE, typename TOUT, bool KEEP>
 __device__ __forceinline__ int wide_epilogue(const f32x4_e (&acc)[8][RB], char* ebuf, int m_base, int n_base, int M, int N,
                                              const Epilogue<MODE, TOUT>& epi, int lane) {
   const int rps = epi.rows_per_sample();
@@ -160,7 +163,7 @@ __device__ __forceinline__ int wide_epilogue(const f32x4_e (&acc)[8][RB], char* 
     wide_epilogue_rows<RB, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
   } else if (m_base + 16 * RB <= M && n_base + 128 <= N) {
     if constexpr (std::is_same<TOUT, bf16>::value) {
-      wide_epilogue_bf16<RB, MODE>(acc, ebuf, m_base, n_base, epi, lane);
+      wide_epilogue_bf16<RB, MODE, KEEP>(acc, ebuf, m_base, n_base, epi, lane);
       return 4 * RB;
     } else {
       wide_epilogue_pair<true, RB, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);

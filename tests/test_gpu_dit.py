@@ -820,6 +820,23 @@ def test_attention_bf16_head_dim_64_does_not_depend_on_the_kernel(lib, L, presca
     assert rel_l2(host(few.float()), ref.numpy()) < 8e-3   # probabilities and outputs rounded to bf16, 2^-9 each
 
 
+# Outputs of 32 to 160 MB are stored plainly by the persistent kernel, smaller and larger ones past the caches: below, at and above either line, full
+# and ragged tiles, against the 128x128 kernel, bit for bit.
+@pytest.mark.parametrize("M,N", [(8191, 2048), (8192, 2048), (8200, 2060), (40960, 2048), (40961, 2048)])
+def test_gemm_persistent_outputs_that_stay_in_the_caches(lib, M, N):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M)
+    A, W = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((M, 128), (N, 128)))
+    b = torch.randn(N, generator=g, device=DEV)
+    for mode in (0, 1):
+        outs = []
+        for variant in (STREAM[7], 5):
+            out = torch.full((M + 1, N), -9.0, device=DEV).bfloat16()
+            br.op_gemm(br.BF16, mode, A, W, b, out[:M], variant=variant)
+            outs.append(out)
+        assert torch.equal(outs[0], outs[1]), mode
+
+
 def test_velocity_where_attention_leaves_units_to_the_weights(lib):
     """Networks too large for the memory-side cache read the next weights in front of an attention that leaves compute units idle (one
     sample), and not where it does not (eighteen): the same bits, right against the oracle."""

@@ -95,3 +95,22 @@ def test_wait_states_around_the_inline_matrix_instructions(tmp_path):
             assert count >= 4 * 8 * 4 * 2 and not bad, (name, count, bad[:5])
             kernels += 1
     assert kernels == 20
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="llvm-objdump is missing")
+def test_wait_states_where_outputs_stay_in_the_caches(tmp_path):
+    """The same of the kernels that store bf16 outputs plainly (five tile heights, with and without GELU)."""
+    kernels = 0
+    for i, obj in enumerate(code_objects(br.LIB_PATH)):
+        if b"gemm_bf16_stream_keep_kernel" not in obj:
+            continue
+        f = tmp_path / ("%d.co" % i)
+        f.write_bytes(obj)
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(f)], capture_output=True, text=True, check=True).stdout
+        for part in re.split(r"\n(?=[0-9a-f]+ <)", text):
+            name, _, body = part.partition("\n")
+            if "gemm_bf16_stream_keep_kernel" in name:
+                count, bad = hazards(body.split("\n"))
+                assert count >= 4 * 8 * 4 * 2 and not bad, (name, count, bad[:5])
+                kernels += 1
+    assert kernels == 10
