@@ -71,27 +71,6 @@ struct RowsArgs {
   int o_act, o_hid, o_mods, o_bias, o_ring;
 };
 
-// Sum over groups of N consecutive lanes, at distances N / 2 ... 1 in turn (the order of __shfl_xor, without its trips to the LDS
-// unit).  Rotations by 8, 4 of 16 lanes reach the lane that the exclusive-or reaches, or one that holds the same sum.
-template <int N>
-__device__ __forceinline__ float lanes_sum(float x) {
-  static_assert(N >= 16, "whole rows of 16 lanes");
-  if constexpr (N == 64) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
-    x = __builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]);
-  }
-  if constexpr (N >= 32) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
-    x = __builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]);
-  }
-  auto add = [&](auto CTRL) { x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(CTRL)::value, 0xf, 0xf, true)); };
-  add(std::integral_constant<int, 0x128>{});  // row_ror:8
-  add(std::integral_constant<int, 0x124>{});  // row_ror:4
-  add(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
-  add(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
-  return x;
-}
-
 enum { ROWS_HEAD = 0, ROWS_BODY = 1, ROWS_LAST = 2 };
 
 template <typename T, int RT, int SPS, int KIND>

@@ -1,5 +1,7 @@
 // Velocity-network internals: model handle, workspace plan, epilogues, launchers.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 typedef __bf16 bf16;
@@ -132,6 +134,27 @@ br_status launch_ln_modulate(int dtype, const float* x, void* out, int n_rows, i
 __device__ inline float sum_sq4(const float4& v, float mean) {
   const float a = v.x - mean, b = v.y - mean, c = v.z - mean, d = v.w - mean;
   return fmaf(a, a, b * b) + fmaf(c, c, d * d);
+}
+
+// Sum over groups of N consecutive lanes, at distances N / 2 ... 1 in turn (the order of __shfl_xor, without its trips to the LDS
+// unit).  Rotations by 8, 4 of 16 lanes reach the lane that the exclusive-or reaches, or one that holds the same sum.
+template <int N>
+__device__ __forceinline__ float lanes_sum(float x) {
+  static_assert(N >= 16, "whole rows of 16 lanes");
+  if constexpr (N == 64) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    x = __builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]);
+  }
+  if constexpr (N >= 32) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    x = __builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]);
+  }
+  auto add = [&](auto CTRL) { x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(CTRL)::value, 0xf, 0xf, true)); };
+  add(std::integral_constant<int, 0x128>{});  // row_ror:8
+  add(std::integral_constant<int, 0x124>{});  // row_ror:4
+  add(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+  add(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+  return x;
 }
 
 // ---- epilogue device code, shared by the fp32 and the MFMA GEMM

@@ -276,34 +276,62 @@ br_status conditioning(const br_model* m, const FwdBuffers& fb, const void* cond
 // out[r, :] = LN(x[src(r), :]) (1 + scale) + shift; one wavefront per row, the row held in
 // registers (VPL float4 per lane; VPL = 0: any H, the row is re-read from cache instead).
 // r = b * rows_per_sample + tok, src = b * L_in + tok; LN without affine, eps 1e-6.
-template <typename T, int VPL>
+//
+// What bounds it: a small launch, the chain of one row (row, group of its sample, modulation vectors, two sums of 64 lanes), a large one the
+// memory.  The row's number is scalar, so the group comes by a scalar load beside the row's own; up to VPL = 4 the modulation vectors are
+// under way with the row too (beyond, the compiler decides); the sums are exchanged without the LDS unit.  Large fp32 launches fetch the
+// vectors last (LATE): they lose by more registers or more loads in front of the row.  STREAM: rows that the caches cannot
+// hold until the next launch reads them are stored past them.  us before -> now, bf16:  8808 x 1024 12.6 -> 11.4, 17 616 x 1024 21.6 -> 19.6,
+// 26 424 x 1024 30.4 -> 27.8, 70 464 x 1024 74.3 -> 74.4, 36 864 x 3072 123.9 -> 116.8, 33 272 x 1536 the same 53.7; fp32: 8808 x 1024 15.8 -> 14.7,
+// 17 616 x 1024 27.2 -> 25.1, 26 424 to 70 464 x 1024 1 % slower.  (Plain stores throughout: bf16 70 464 x 1024 77.0, 33 272 x 1536 54.7.)
+constexpr double LN_STREAM_FROM = 192e6;  // bytes of rows read and written
+template <bool STREAM, typename T>
+__device__ __forceinline__ void store4_row(T* p, float a, float b, float c, float d) {
+  typedef T t4 __attribute__((ext_vector_type(4)));
+  const t4 v = {(T)a, (T)b, (T)c, (T)d};
+  if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<t4*>(p));
+  else *reinterpret_cast<t4*>(p) = v;
+}
+template <typename T, int VPL, bool STREAM>
 __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restrict__ x, T* __restrict__ out, int n_rows,
                                                           int rows_per_sample, int L_in, int H,
                                                           const float* __restrict__ mods, int A, int shift_off,
                                                           int scale_off, const int* __restrict__ condmap) {
+  constexpr int NV = VPL > 0 ? VPL : 1;
+  constexpr bool LATE = std::is_same<T, float>::value && (STREAM || VPL > 4), EARLY = !LATE && VPL > 0 && VPL <= 4;
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (r >= n_rows) return;
   const int b = r / rows_per_sample, tok = r - b * rows_per_sample;
   const float4* xr = reinterpret_cast<const float4*>(x + ((size_t)b * L_in + tok) * H);
   const int H4 = H >> 2;
-  float4 v[VPL > 0 ? VPL : 1];
+  float4 v[NV], a[NV], g[NV];
+  if (VPL > 0) {
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) v[i] = xr[lane + 64 * i];
+  }
+  const float* mrow = mods + (size_t)condmap[b] * A;
+  const float4* sh = reinterpret_cast<const float4*>(mrow + shift_off);
+  const float4* sc = reinterpret_cast<const float4*>(mrow + scale_off);
+  if (EARLY) {
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+      a[i] = sh[lane + 64 * i];
+      g[i] = sc[lane + 64 * i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
   float s = 0.f;
   if (VPL > 0) {
 #pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-      v[i] = xr[lane + 64 * i];
-      s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-    }
+    for (int i = 0; i < VPL; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
   } else {
     for (int i = lane; i < H4; i += 64) {
       const float4 u = xr[i];
       s += (u.x + u.y) + (u.z + u.w);
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  const float mean = s / (float)H;
+  const float mean = lanes_sum<64>(s) / (float)H;
   float q = 0.f;
   if (VPL > 0) {
 #pragma unroll
@@ -311,34 +339,33 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
   } else {
     for (int i = lane; i < H4; i += 64) q += sum_sq4(xr[i], mean);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
-  const float rstd = 1.0f / __builtin_sqrtf(q / (float)H + 1e-6f);
-  const float* mrow = mods + (size_t)condmap[b] * A;
-  const float4* sh = reinterpret_cast<const float4*>(mrow + shift_off);
-  const float4* sc = reinterpret_cast<const float4*>(mrow + scale_off);
+  const float rstd = 1.0f / __builtin_sqrtf(lanes_sum<64>(q) / (float)H + 1e-6f);
   T* orow = out + (size_t)r * H;
+  if (LATE) asm volatile("" ::: "memory");
   if (VPL > 0) {
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
       const int c4 = lane + 64 * i;
-      const float4 a = sh[c4], g = sc[c4];
-      store4<T>(orow + 4 * c4, fmaf((v[i].x - mean) * rstd, 1.f + g.x, a.x), fmaf((v[i].y - mean) * rstd, 1.f + g.y, a.y),
-                fmaf((v[i].z - mean) * rstd, 1.f + g.z, a.z), fmaf((v[i].w - mean) * rstd, 1.f + g.w, a.w));
+      if (!EARLY) {
+        a[i] = sh[c4];
+        g[i] = sc[c4];
+      }
+      store4_row<STREAM, T>(orow + 4 * c4, fmaf((v[i].x - mean) * rstd, 1.f + g[i].x, a[i].x), fmaf((v[i].y - mean) * rstd, 1.f + g[i].y, a[i].y),
+                fmaf((v[i].z - mean) * rstd, 1.f + g[i].z, a[i].z), fmaf((v[i].w - mean) * rstd, 1.f + g[i].w, a[i].w));
     }
   } else {
     for (int i = lane; i < H4; i += 64) {
-      const float4 u = xr[i], a = sh[i], g = sc[i];
-      store4<T>(orow + 4 * i, fmaf((u.x - mean) * rstd, 1.f + g.x, a.x), fmaf((u.y - mean) * rstd, 1.f + g.y, a.y),
-                fmaf((u.z - mean) * rstd, 1.f + g.z, a.z), fmaf((u.w - mean) * rstd, 1.f + g.w, a.w));
+      const float4 u = xr[i], m = sh[i], k = sc[i];
+      store4_row<STREAM, T>(orow + 4 * i, fmaf((u.x - mean) * rstd, 1.f + k.x, m.x), fmaf((u.y - mean) * rstd, 1.f + k.y, m.y),
+                fmaf((u.z - mean) * rstd, 1.f + k.z, m.z), fmaf((u.w - mean) * rstd, 1.f + k.w, m.w));
     }
   }
 }
 
-template <typename T>
+template <typename T, bool STREAM>
 static void ln_launch(dim3 g, dim3 b, hipStream_t st, const float* x, T* out, int n_rows, int rows_per_sample, int L_in,
                       int H, const float* mods, int A, int shift_off, int scale_off, const int* condmap) {
-#define BR_LN(V) hipLaunchKernelGGL((ln_modulate_kernel<T, V>), g, b, 0, st, x, out, n_rows, rows_per_sample, L_in, H, \
+#define BR_LN(V) hipLaunchKernelGGL((ln_modulate_kernel<T, V, STREAM>), g, b, 0, st, x, out, n_rows, rows_per_sample, L_in, H, \
                                     mods, A, shift_off, scale_off, condmap)
   switch (H % 256 == 0 ? H / 256 : 0) {
     case 1: BR_LN(1); break;
@@ -359,10 +386,14 @@ br_status launch_ln_modulate(int dtype, const float* x, void* out, int n_rows, i
   if (n_rows == 0) return BR_OK;
   dim3 g(cdiv(n_rows, 4)), b(256);
   ProfScope ps(st, PROF_LN_MOD, (double)n_rows * H * (4.0 + (dtype == BR_BF16 ? 2.0 : 4.0)));
-  if (dtype == BR_BF16)
-    ln_launch<bf16>(g, b, st, x, (bf16*)out, n_rows, rows_per_sample, L_in, H, mods, A, shift_off, scale_off, condmap);
-  else
-    ln_launch<float>(g, b, st, x, (float*)out, n_rows, rows_per_sample, L_in, H, mods, A, shift_off, scale_off, condmap);
+  auto go = [&](auto Tc, auto Sc) {
+    using T = decltype(Tc);
+    ln_launch<T, decltype(Sc)::value>(g, b, st, x, (T*)out, n_rows, rows_per_sample, L_in, H, mods, A, shift_off, scale_off, condmap);
+  };
+  const bool stream = (double)n_rows * H * (dtype == BR_BF16 ? 6.0 : 8.0) > LN_STREAM_FROM;
+  auto type = [&](auto Tc) { stream ? go(Tc, std::true_type{}) : go(Tc, std::false_type{}); };
+  if (dtype == BR_BF16) type(bf16{});
+  else type(float{});
   BR_LAUNCH_CHECK();
   return BR_OK;
 }

@@ -242,6 +242,27 @@ def test_ln_modulate(lib, dt):
         assert rel_l2(host(out).reshape(B, rows, H), ref) < tol
 
 
+@pytest.mark.parametrize("dt", [br.F32, br.BF16])
+@pytest.mark.parametrize("B,L,H", [(1, 1, 256), (3, 5, 512), (2, 3, 768), (5, 7, 1024), (2, 9, 1536), (1, 3, 2048), (2, 2, 3072), (3, 11, 260),
+                                   (1, 9765, 3072), (4, 7813, 1024)])
+def test_ln_modulate_row_lengths(lib, dt, B, L, H):
+    """Each way a row is held, with samples that share a workgroup, and launches on both sides of the size from which rows are stored past
+    the caches (192 MB read and written).  The bound: one rounding to bf16 (2^-9), fp32 sums elsewhere."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(H + L)
+    x = torch.randn((B * L, H), generator=g, device=DEV) * 2 + 0.5
+    mods = torch.randn((B, 2 * H + 8), generator=g, device=DEV) * 0.3
+    cond = torch.arange(B - 1, -1, -1, dtype=torch.int32, device=DEV)
+    out = torch.empty((B * L, H), dtype=torch.bfloat16 if dt == br.BF16 else torch.float32, device=DEV)
+    br.op_ln_modulate(dt, x, out, L, L, mods, 0, H + 8, cond)
+    for b in range(B):
+        m, xs = mods[B - 1 - b].double(), x[b * L:(b + 1) * L].double()
+        xs = xs - xs.mean(1, keepdim=True)
+        ref = xs / (xs.square().mean(1, keepdim=True) + 1e-6).sqrt() * (1 + m[H + 8:2 * H + 8]) + m[:H]
+        err = (out[b * L:(b + 1) * L].double() - ref).norm(dim=1) / ref.norm(dim=1)
+        assert float(err.max()) < (2.0 ** -9 if dt == br.BF16 else 2e-6), b
+
+
 def _velocity_case(cfg, n_cond, B, t, seed, std=0.02):
     W = synth.make_weights(cfg, seed, std)
     D = synth.model_sizes(cfg)["D"]
