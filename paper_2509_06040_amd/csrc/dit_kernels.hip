@@ -200,21 +200,56 @@ __global__ __launch_bounds__(256) void cond_vector_kernel(const float* __restric
   }
 }
 
-// out[g, n] = sum_k in[g, k] W[n, k] + bias[n]: one wavefront per column, which keeps to its weight row for all groups (the second
-// eight find it in cache: 448 000 columns of 3072 for 64 groups stream 2.7 GB once).
-template <typename TW, int R>
+// out[g, n] = sum_k in[g, k] W[n, k] + bias[n]: a wavefront takes NC columns, and keeps to their weight rows for all groups (the second
+// eight find them in cache: 448 000 columns of 3072 for 64 groups stream 2.7 GB once).
+// What bounds it: the weights from memory with few groups, the input rows from the compute unit's cache with many.  Four columns a wave keep
+// four pieces of the weights in flight instead of one and read the inputs a quarter as often:  444 000 columns of 3072 for two groups
+// 736 -> 469 us (5.8 TB/s), 76 000 of 1024 for one 32.9 -> 27.9, for 80 751 -> 462.  Fewer than 64 columns a compute unit stay one to a
+// wave: four would leave units idle.
+template <typename TW, int R, int NC>
 __global__ __launch_bounds__(256) void skinny_gemm_kernel(const float* __restrict__ in, int G, const TW* __restrict__ W, int K, int N,
                                                           const float* __restrict__ bias, float* __restrict__ out) {
   const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= N) return;
+  const int n0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * NC;
+  if (n0 >= N) return;
+  const TW* wr[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) wr[c] = W + (size_t)min(n0 + c, N - 1) * K;
   for (int g0 = 0; g0 < G; g0 += R) {
-    float acc[R];
-    skinny_dot<TW, R>([&](int r) { return in + (size_t)min(g0 + r, G - 1) * K; }, W + (size_t)n * K, K, lane, acc);
-    if (lane == 0) {
+    const float* row[R];
+    float acc[NC][R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      row[r] = in + (size_t)min(g0 + r, G - 1) * K;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c][r] = 0.f;
+    }
+    for (int k = lane * 8; k < K; k += 512) {
+      float w[NC][8];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) WChunk<TW>::load(wr[c] + k, w[c]);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float4 a0 = *reinterpret_cast<const float4*>(row[r] + k);
+        const float4 a1 = *reinterpret_cast<const float4*>(row[r] + k + 4);
+        const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[c][r] = fmaf(a[e], w[c][e], acc[c][r]);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        if (g0 + r < G) out[(size_t)(g0 + r) * N + n] = acc[r] + bias[n];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc[c][r] += __shfl_down(acc[c][r], o, 64);
+      if (lane == 0 && n0 + c < N) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if (g0 + r < G) out[(size_t)(g0 + r) * N + n0 + c] = acc[c][r] + bias[n0 + c];
+      }
     }
   }
 }
@@ -259,8 +294,12 @@ static br_status conditioning_t(const br_model* m, const FwdBuffers& fb, const T
   ProfScope ps(st, PROF_ADALN, (double)m->A * H * sizeof(T));
   with_rows(G, [&](auto Rc) {
     constexpr int R = decltype(Rc)::value;
-    hipLaunchKernelGGL((skinny_gemm_kernel<T, R>), dim3(cdiv(m->A, 4)), dim3(256), 0, st, fb.cvec, G, w(BR_W_ADA_W), H, m->A, b(BR_W_ADA_B),
-                       fb.mods);
+    if (m->A >= 64 * device_cu_count())
+      hipLaunchKernelGGL((skinny_gemm_kernel<T, R, 4>), dim3(cdiv(m->A, 16)), dim3(256), 0, st, fb.cvec, G, w(BR_W_ADA_W), H, m->A, b(BR_W_ADA_B),
+                         fb.mods);
+    else
+      hipLaunchKernelGGL((skinny_gemm_kernel<T, R, 1>), dim3(cdiv(m->A, 4)), dim3(256), 0, st, fb.cvec, G, w(BR_W_ADA_W), H, m->A, b(BR_W_ADA_B),
+                         fb.mods);
   });
   BR_LAUNCH_CHECK();
   return BR_OK;

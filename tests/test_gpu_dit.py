@@ -313,6 +313,15 @@ def test_velocity_normalisation_inside_the_gemm(lib, hidden, heads, dtype, B):
         assert_velocity(cfg, got[b], ref[b], 1e-4 if dtype == synth.F32 else 2e-2, "hidden %d b=%d" % (hidden, b))
 
 
+@pytest.mark.parametrize("dtype,B", [(synth.F32, 1), (synth.BF16, 3), (synth.F32, 9)])
+def test_velocity_modulation_vectors_four_columns_a_wave(lib, dtype, B):
+    """6 x 6 x 512 + 2 x 512 modulation columns, above 64 a compute unit; one group, a few, and more than the eight that a wave takes together."""
+    cfg = synth.model_cfg(6, 512, 4, (16, 1, 4, 6), (1, 2, 2), 5, dtype)
+    got, ref, _ = _velocity_case(cfg, B, B, 0.4, 6, 0.05)
+    for b in range(B):
+        assert_velocity(cfg, got[b], ref[b], 1e-4 if dtype == synth.F32 else 2e-2, "modulation b=%d" % b)
+
+
 def test_velocity_chunked_batches_agree(lib):
     cfg = synth.WORKLOADS["tiny"]["model"]
     got, ref, (model, W, z, cond, cidx) = _velocity_case(cfg, 2, 5, 0.5, 4)
