@@ -9,6 +9,7 @@
 #include <cmath>
 
 #include "common.h"
+#include "dispatch.h"
 #include "dit.h"
 #include "gemm_tile.h"
 #include "prof.h"
@@ -22,8 +23,12 @@ static br_status gemm_tile_launch(const bf16* A, int lda, const bf16* W, int ldw
   const int tiles_m = cdiv(M, BM), tiles_n = cdiv(N, BN);
   // Columns in even groups of at most 8: the tiles a compute die works on at once then share both operands.
   if (group_n <= 0 || group_n > tiles_n) group_n = cdiv(tiles_n, cdiv(tiles_n, 8));
-  hipLaunchKernelGGL((gemm_tile_kernel<bf16, BM, BN, WGM, WGN, NST, MODE, TOUT>), dim3(tiles_m * tiles_n), dim3(WGM * WGN * 64),
-                     0, st, A, lda, W, ldw, M, N, K, tiles_m, tiles_n, group_n, epi);
+  constexpr bool LARGE = BM >= 128 && std::is_same<TOUT, bf16>::value;  // (smaller tiles are not chosen for outputs of that size)
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(WGM * WGN * 64), 0, st, A, lda, W, ldw, M, N, K, tiles_m, tiles_n, group_n, epi);
+  };
+  if (LARGE && rule::tile_output_streams((size_t)M * N * sizeof(TOUT))) go(gemm_tile_kernel<bf16, BM, BN, WGM, WGN, NST, MODE, TOUT, LARGE>);
+  else go(gemm_tile_kernel<bf16, BM, BN, WGM, WGN, NST, MODE, TOUT, false>);
   BR_LAUNCH_CHECK();
   return BR_OK;
 }

@@ -5,7 +5,8 @@
 // the row-wise reads) and stores whole row segments of its 64 columns:
 //   - bf16 outputs of a full tile: bias / GELU in the accumulator layout, rounded, 32 rows per pass;
 //   - everything else: fp32 through LDS, 16 rows per pass, then bias / gate / addend per row.
-// Stores are plain: the outputs of these kernels are small enough to be in the caches when the next launch reads them.
+// STREAM: bf16 rows of full tiles go past the caches (tile_output_streams); else stores are plain and leave the rows there for the launch
+// that reads them.
 //
 // A wave's loads and stores retire through one in-order counter, so a load issued behind a
 // store waits for that store's write acknowledgement.  The pass loops therefore contain no
@@ -146,7 +147,7 @@ __device__ inline void wave_epilogue_pair(const ACC& acc, char* ebuf, int m_base
 // LDS, which halves the LDS traffic and lets a pass cover 32 rows: per pass 8 x ds_write_b64 by
 // every lane, 4 x ds_read_b128, 4 stores of 16 bytes per lane (8 rows x 128 bytes each).  A buffer
 // row is 128 bytes = eight 16-byte chunks, chunk c of row r sits in slot c ^ ((r >> 1) & 7).
-template <int TM, int TN, int MODE>
+template <int TM, int TN, int MODE, bool STREAM>
 __device__ inline void wave_epilogue_bf16_full(const f32x16_e (&acc)[TN][TM], char* ebuf, int m_base, int n_base,
                                                const Epilogue<MODE, bf16>& epi, int lane) {
   static_assert(MODE == EPI_BIAS || MODE == EPI_BIAS_GELU, "plain bf16 outputs only");
@@ -191,12 +192,14 @@ __device__ inline void wave_epilogue_bf16_full(const f32x16_e (&acc)[TN][TM], ch
     for (int q = 0; q < 4; ++q) {
       const int r = rrow + 8 * q;
       const u32x4_e v = *reinterpret_cast<const u32x4_e*>(ebuf + r * 128 + ((rc ^ ((r >> 1) & 7)) << 4));
-      *reinterpret_cast<u32x4_e*>(obase + (long long)(j * 32 + 8 * q) * epi.a.ldo) = v;
+      u32x4_e* const dst = reinterpret_cast<u32x4_e*>(obase + (long long)(j * 32 + 8 * q) * epi.a.ldo);
+      if constexpr (STREAM) __builtin_nontemporal_store(v, dst);
+      else *dst = v;
     }
   }
 }
 
-template <int TM, int TN, int MODE, typename TOUT>
+template <int TM, int TN, int MODE, typename TOUT, bool STREAM>
 __device__ inline void wave_epilogue(const f32x16_e (&acc)[TN][TM], char* ebuf, int m_base, int n_base, int M, int N,
                                     const Epilogue<MODE, TOUT>& epi, int lane) {
   static_assert(TN == 2, "waves own 64 output columns");
@@ -205,7 +208,7 @@ __device__ inline void wave_epilogue(const f32x16_e (&acc)[TN][TM], char* ebuf, 
     wave_epilogue_rows<2 * TM, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
   } else if (m_base + TM * 32 <= M && n_base + TN * 32 <= N) {
     if constexpr ((MODE == EPI_BIAS || MODE == EPI_BIAS_GELU) && std::is_same<TOUT, bf16>::value) {
-      wave_epilogue_bf16_full<TM, TN, MODE>(acc, ebuf, m_base, n_base, epi, lane);
+      wave_epilogue_bf16_full<TM, TN, MODE, STREAM>(acc, ebuf, m_base, n_base, epi, lane);
     } else {
       wave_epilogue_pair<true, 2 * TM, MODE, TOUT>(acc, ebuf, m_base, n_base, M, N, epi, lane);
     }

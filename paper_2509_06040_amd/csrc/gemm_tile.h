@@ -27,7 +27,7 @@ namespace br {
 template <int BYTES, int S>
 __shared__ __attribute__((aligned(1024))) char g_stage[BYTES];
 
-template <typename T, int BM, int BN, int WGM, int WGN, int NST, int MODE, typename TOUT>
+template <typename T, int BM, int BN, int WGM, int WGN, int NST, int MODE, typename TOUT, bool STREAM>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_kernel(const T* __restrict__ A, int lda,
                                                                   const T* __restrict__ W, int ldw, int M, int N,
                                                                   int K, int tiles_m, int tiles_n, int group_n,
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_kernel(const T* __res
     constexpr int WPS = STAGE / 4096;  // waves whose 4 KB fit in one stage
     static_assert(2 * WPS >= NW && WTN == 64, "epilogue staging needs 4 KB per wave");
     char* ebuf = (wv < WPS ? g_stage<STAGE, 0> + wv * 4096 : g_stage<STAGE, 1> + (wv - WPS) * 4096);
-    wave_epilogue<TM, TN, MODE, TOUT>(acc, ebuf, m0 + wm0, n0 + wn0, M, N, epi, lane);
+    wave_epilogue<TM, TN, MODE, TOUT, STREAM>(acc, ebuf, m0 + wm0, n0 + wn0, M, N, epi, lane);
   }
 }
 

@@ -1,0 +1,32 @@
+"""The rules that choose between forms of a kernel (csrc/dispatch.h), compiled for the host and asked at the sizes on either side of their lines."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_06040_amd", "csrc")
+SOURCE = """
+#include "dispatch.h"
+using namespace br;
+extern "C" {
+int tile_output_streams(unsigned long long bytes) { return rule::tile_output_streams(bytes); }
+}
+"""
+CU = 256
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "rules.so"), str(d / "rules.cpp")], check=True)
+    return C.CDLL(str(d / "rules.so"))
+
+
+def test_large_outputs_of_the_tile_kernels_go_past_the_caches(rule):
+    """hidden 960 and 2880, whose products the persistent kernel does not take: first MLP layer of 8 and of 64 samples of 1101 rows, QKV of 64."""
+    stream = lambda M, N: bool(rule.tile_output_streams(C.c_ulonglong(M * N * 2)))
+    assert not stream(8 * 1101, 4 * 960) and not stream(4 * 1101, 4 * 2880)
+    assert stream(64 * 1101, 4 * 960) and stream(64 * 1101, 3 * 2880)
+    assert not stream(40960, 2048) and stream(40961, 2048)

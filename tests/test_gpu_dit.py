@@ -867,6 +867,24 @@ def test_gemm_persistent_outputs_that_stay_in_the_caches(lib, M, N):
         assert torch.equal(outs[0], outs[1]), mode
 
 
+# Outputs above 160 MB go past the caches in the kernels of 128x128 and 256x256 tiles: at and above the line, full and ragged tiles, against the
+# 64x64 kernel, whose stores are always plain, bit for bit; and nothing past the end.
+@pytest.mark.parametrize("variant", [1, 4, 5])
+@pytest.mark.parametrize("M,N", [(40960, 2048), (40961, 2048), (40963, 2060)])
+def test_gemm_tile_outputs_past_the_caches(lib, variant, M, N):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + N)
+    A, W = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((M, 64), (N, 64)))
+    b = torch.randn(N, generator=g, device=DEV)
+    for mode in (0, 1):
+        outs = []
+        for v in (variant, 2):
+            out = torch.full((M + 1, N), -9.0, device=DEV).bfloat16()
+            br.op_gemm(br.BF16, mode, A, W, b, out[:M], variant=v)
+            outs.append(out)
+        assert torch.equal(outs[0], outs[1]), mode
+
+
 def test_velocity_where_attention_leaves_units_to_the_weights(lib):
     """Networks too large for the memory-side cache read the next weights in front of an attention that leaves compute units idle (one
     sample), and not where it does not (eighteen): the same bits, right against the oracle."""
