@@ -23,6 +23,7 @@
 #include <utility>
 
 #include "common.h"
+#include "dispatch.h"
 #include "dit.h"
 #include "gemm_epilogue_wide.h"
 #include "gemm_frag.h"
@@ -36,7 +37,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 namespace {
 constexpr int BN = 256, NW = 4;
 constexpr int BK = 64;            // k-depth of a stage: 128-byte row segments (64-byte ones pull a third less through the L2)
-constexpr int KEEP_FROM = 32 << 20, KEEP_TO = 160 << 20;  // bytes of an output that stays in the memory-side cache
 constexpr int IW = BN / 8 / NW;   // LDS-direct loads of W per wave and stage (8 rows each)
 }  // namespace
 
@@ -312,13 +312,8 @@ static br_status stream_launch(const bf16* A, int lda, const bf16* W, int ldw, i
   const int n_cu = device_cu_count();
   const int nt = tiles_m * tiles_n;
   const int grid = nt < n_cu ? nt : n_cu;
-  // Where bf16 outputs go.  Small enough for the memory-side cache (256 MB, with the operands) and too large for the L2 caches, they are
-  // stored plainly, and the launch that reads them finds them there; elsewhere past the caches, which leaves those to the operands.
-  // Velocity calls of the image network (1101 rows a sample; outputs of 18, 27, 36, 72, 144, 288 and 577 MB of the MLP's first layer),
-  // plain against streaming: 1.018, 1.014, 0.985, 0.978, 0.967, 1.015, 1.023; large images, 113 and 226 MB: 0.994, 0.999.
-  const size_t out_bytes = (size_t)M * N * 2;
   if constexpr (std::is_same<TOUT, bf16>::value) {
-    if (out_bytes >= (size_t)KEEP_FROM && out_bytes <= (size_t)KEEP_TO) {
+    if (rule::persistent_output_stays((size_t)M * N * sizeof(TOUT), K)) {
       hipLaunchKernelGGL((gemm_bf16_stream_keep_kernel<RB, MODE, TOUT>), dim3(grid), dim3(256), 0, st, A, lda, W, ldw, M, N, K,
                          tiles_m, tiles_n, group_n, row_block, epi);
       BR_LAUNCH_CHECK();
