@@ -77,6 +77,38 @@ static __device__ inline void warm_rows(const WarmRows& w) {
   }
 }
 
+// Launches without such workgroups carry neither their code nor their list.  With both, head dim 128: 4 heads of 2561 tokens 58.6 -> 59.2 us, 8 of 3492
+// 75.7 -> 76.5, 4 of 8 4.05 -> 4.10; 0.2 us of the host's.
+struct NoWarm {};
+template <bool WARM>
+using Warm = std::conditional_t<WARM, WarmRows, NoWarm>;
+
+// The (sample, head) pair and the query tile of a workgroup; false: none (a workgroup that reads weights, or one past the last pair).
+// Workgroups are dispatched round-robin over the 8 XCDs.  All query tiles of one
+// (sample, head) read the same keys and values, so they are given to one XCD and run
+// back to back there: K/V then come out of that XCD's L2 instead of being fetched 8 times.
+// (With few pairs that would leave XCDs idle: then tiles are simply dealt out in order.)
+template <typename W>
+static __device__ __forceinline__ bool attn_tile(const W& warm, int nq, int n_pairs, int grouped, int* pair, int* qt) {
+  unsigned block = blockIdx.x;
+  if constexpr (std::is_same<W, WarmRows>::value) {
+    if (block < (unsigned)warm.blocks) {
+      warm_rows(warm);
+      return false;
+    }
+    block -= warm.blocks;  // (a multiple of 8)
+  }
+  if (grouped) {
+    const int x = block & 7, slot = block >> 3;
+    *pair = (slot / nq) * 8 + x;
+    *qt = slot - (slot / nq) * nq;
+  } else {
+    *pair = block / nq;
+    *qt = block - *pair * nq;
+  }
+  return *pair < n_pairs;
+}
+
 // Slot permutations of the K and V tiles: 16-byte chunk c of row r sits in slot c ^ swz(r).
 // The LDS has 64 banks of 4 bytes; a 16-byte read is served 16 lanes at a time and an 8-byte
 // read 32 lanes at a time, conflict-free when those lanes cover all 256 bytes of a bank row.
@@ -96,9 +128,9 @@ __device__ inline int v_swz(int r) { return DH == 128 ? ((r & 3) << 2) : (((r >>
 // tile loop then spills nothing; a fourth wave bought no time).
 // PRE: the q third of the buffer already carries the factor log2(e) / sqrt(DH), as the network's
 // QKV projection writes it; otherwise the exponent is scaled here, one multiplication per score.
-template <int DH, bool PRE>
+template <int DH, bool PRE, bool WARM>
 __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out, int L,
-                                                           int H, int NH, int n_pairs, int grouped, float scale_log2, WarmRows warm) {
+                                                           int H, int NH, int n_pairs, int grouped, float scale_log2, Warm<WARM> warm) {
   constexpr int CH = DH / 8;    // 16-byte chunks per K row
   constexpr int KS = DH / 16;   // MFMA k-steps of the score product
   constexpr int DB = DH / 32;   // 32-row blocks of O^T
@@ -115,26 +147,8 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
   __shared__ __attribute__((aligned(1024))) char sK[2][TILE_B];
   __shared__ __attribute__((aligned(1024))) char sV[2][TILE_B];
 
-  // Workgroups are dispatched round-robin over the 8 XCDs.  All query tiles of one
-  // (sample, head) read the same keys and values, so they are given to one XCD and run
-  // back to back there: K/V then come out of that XCD's L2 instead of being fetched 8 times.
-  // (With few pairs that would leave XCDs idle: then tiles are simply dealt out in order.)
-  const int nq = (L + 127) / 128;
   int pair, qt;
-  if ((int)blockIdx.x < warm.blocks) {
-    warm_rows(warm);
-    return;
-  }
-  const int block = blockIdx.x - warm.blocks;  // (a multiple of 8)
-  if (grouped) {
-    const int x = block & 7, slot = block >> 3;
-    pair = (slot / nq) * 8 + x;
-    qt = slot - (slot / nq) * nq;
-  } else {
-    pair = block / nq;
-    qt = block - pair * nq;
-  }
-  if (pair >= n_pairs) return;
+  if (!attn_tile(warm, (L + 127) / 128, n_pairs, grouped, &pair, &qt)) return;
   const int b = pair / NH, h = pair - b * NH;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -461,9 +475,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
 // here: 144 workgroups of 1101 tokens 15.7 -> 13.1 us, 288 21.3 -> 19.3, 272 of 2100 34.7 -> 32.2, 376 of 6000 91.7 -> 85.0, 1152 of 1101 50.1
 // -> 49.0, 2304 89.6 -> 90.3.  Inside a network, where the rows come from the product before, the 144 take 18.3 -> 14 us, 17 with two buffers
 // of LDS instead of four.  (At head dim 128 it does not fit 256 registers: 1068 TFLOP/s at 4608 tokens, 1168 above.)
-template <int DH, bool PRE>
+template <int DH, bool PRE, bool WARM>
 __global__ __launch_bounds__(256, 2) void attn_bf16_pipe_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out, int L,
-                                                           int H, int NH, int n_pairs, int grouped, float scale_log2, WarmRows warm) {
+                                                           int H, int NH, int n_pairs, int grouped, float scale_log2, Warm<WARM> warm) {
   constexpr int CH = DH / 8;    // 16-byte chunks per K row
   constexpr int KS = DH / 16;   // MFMA k-steps of the score product
   constexpr int DB = DH / 32;   // 32-row blocks of O^T
@@ -477,26 +491,8 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_pipe_kernel(const bf16* __re
   __shared__ __attribute__((aligned(1024))) char sK[NB][TILE_B];
   __shared__ __attribute__((aligned(1024))) char sV[NB][TILE_B];
 
-  // Workgroups are dispatched round-robin over the 8 XCDs.  All query tiles of one
-  // (sample, head) read the same keys and values, so they are given to one XCD and run
-  // back to back there: K/V then come out of that XCD's L2 instead of being fetched 8 times.
-  // (With few pairs that would leave XCDs idle: then tiles are simply dealt out in order.)
-  const int nq = (L + 127) / 128;
   int pair, qt;
-  if ((int)blockIdx.x < warm.blocks) {
-    warm_rows(warm);
-    return;
-  }
-  const int block = blockIdx.x - warm.blocks;  // (a multiple of 8)
-  if (grouped) {
-    const int x = block & 7, slot = block >> 3;
-    pair = (slot / nq) * 8 + x;
-    qt = slot - (slot / nq) * nq;
-  } else {
-    pair = block / nq;
-    qt = block - pair * nq;
-  }
-  if (pair >= n_pairs) return;
+  if (!attn_tile(warm, (L + 127) / 128, n_pairs, grouped, &pair, &qt)) return;
   const int b = pair / NH, h = pair - b * NH;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -832,33 +828,30 @@ br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH
   const long long n_blocks = (grouped ? (n_pairs + 7) / 8 * 8 : n_pairs) * cdiv(L, 128);
   BR_REQUIRE(n_blocks <= 0x7FFFFFFFLL, BR_ESHAPE, "attention: too many workgroups for one launch");
   // Where the launch leaves compute units idle: as much of the list as they read meanwhile (see warm_rows).
+  const int n_cu = device_cu_count();
   WarmRows warm = next;
-  const int idle = device_cu_count() - (int)std::min<long long>(n_blocks, device_cu_count());
-  warm.blocks = idle / 8 * 8;
-  if (warm.blocks < 32) warm = WarmRows{};
+  warm.blocks = next.n16[0] > 0 && q_prescaled ? (n_cu - (int)std::min<long long>(n_blocks, n_cu)) / 8 * 8 : 0;
+  if (warm.blocks < 32) warm.blocks = 0;
   unsigned budget = (unsigned)(WARM_BYTES_PER_TILE / 16 * (cdiv(L, KV_TILE) + 4) / 256 * warm.blocks);
   for (unsigned& n : warm.n16) {
     n = std::min(n, budget);
     budget -= n;
   }
-  if (warm.n16[0] == 0) warm.blocks = 0;
   dim3 g((unsigned)n_blocks + warm.blocks), blk(256);
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)DH));
   const int H = NH * DH;
   ProfScope ps(st, PROF_ATTN + DH, 4.0 * B * (double)L * L * H);
-#define BR_ATTN_GO_K(KERNEL, DHc, PREc) \
-  hipLaunchKernelGGL((KERNEL<DHc, PREc>), g, blk, 0, st, qkv, out, L, H, NH, (int)n_pairs, grouped, scale_log2, warm)
-#define BR_ATTN_GO(DHc, PREc) BR_ATTN_GO_K(attn_bf16_kernel, DHc, PREc)
+  auto go = [&](auto kernel, const auto& w) { hipLaunchKernelGGL(kernel, g, blk, 0, st, qkv, out, L, H, NH, (int)n_pairs, grouped, scale_log2, w); };
+#define BR_ATTN_GO(KERNEL, DHc)                                   \
+  if (warm.blocks > 0) go(KERNEL<DHc, true, true>, warm);         \
+  else if (q_prescaled) go(KERNEL<DHc, true, false>, NoWarm{});   \
+  else go(KERNEL<DHc, false, false>, NoWarm{})
   // up to six workgroups a compute unit the pipelined loop is the faster one (figures there), bit for bit the same
-  const bool pipe = DH == 64 && n_blocks <= 6LL * device_cu_count();
-  if (pipe && q_prescaled) BR_ATTN_GO_K(attn_bf16_pipe_kernel, 64, true);
-  else if (pipe) BR_ATTN_GO_K(attn_bf16_pipe_kernel, 64, false);
-  else if (DH == 64 && q_prescaled) BR_ATTN_GO(64, true);
-  else if (DH == 64) BR_ATTN_GO(64, false);
-  else if (DH == 128 && q_prescaled) BR_ATTN_GO(128, true);
-  else if (DH == 128) BR_ATTN_GO(128, false);
+  const bool pipe = DH == 64 && n_blocks <= 6LL * n_cu;
+  if (pipe) { BR_ATTN_GO(attn_bf16_pipe_kernel, 64); }
+  else if (DH == 64) { BR_ATTN_GO(attn_bf16_kernel, 64); }
+  else if (DH == 128) { BR_ATTN_GO(attn_bf16_kernel, 128); }
 #undef BR_ATTN_GO
-#undef BR_ATTN_GO_K
   else return fail(BR_ESHAPE, "bf16 attention: head dim must be 64 or 128");
   BR_LAUNCH_CHECK();
   return BR_OK;

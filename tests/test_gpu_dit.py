@@ -885,10 +885,12 @@ def test_gemm_tile_outputs_past_the_caches(lib, variant, M, N):
         assert torch.equal(outs[0], outs[1]), mode
 
 
-def test_velocity_where_attention_leaves_units_to_the_weights(lib):
+@pytest.mark.parametrize("heads", [32, 16])
+def test_velocity_where_attention_leaves_units_to_the_weights(lib, heads):
     """Networks too large for the memory-side cache read the next weights in front of an attention that leaves compute units idle (one
-    sample), and not where it does not (eighteen): the same bits, right against the oracle."""
-    cfg = synth.model_cfg(3, 2048, 32, (16, 1, 14, 18), (1, 2, 2), 9, synth.BF16)
+    sample, 32 workgroups), and not where it does not (eighteen, 576): the same bits, right against the oracle.  32 heads of 64: the
+    pipelined loop, tiles grouped by die; 16 of 128: the other loop, two query tiles a head, dealt out in order."""
+    cfg = synth.model_cfg(3, 2048, heads, (16, 1, 14, 18) if heads == 32 else (16, 1, 20, 26), (1, 2, 2), 9, synth.BF16)
     W = synth.make_weights(cfg, 3, 0.03)
     model = make_model(cfg, W)
     D = synth.model_sizes(cfg)["D"]
