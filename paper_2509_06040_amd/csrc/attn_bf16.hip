@@ -20,6 +20,7 @@
 #include <utility>
 
 #include "common.h"
+#include "dispatch.h"
 #include "dit.h"
 #include "prof.h"
 
@@ -472,8 +473,8 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bf16_kernel(const 
 // 16 cycles each, 16 conversions), 700 and more of LDS reads shared by four waves.  A wave alone on its SIMD takes 560 for the first half of
 // an iteration and 430 for the second; in the order of the kernel above, with tile loads that branch for the ragged tile, 1800.  At full
 // load it is the power limit that binds, and the second score tile leaves room for two waves per SIMD only.  Head dim 64, above ->
-// here: 144 workgroups of 1101 tokens 15.7 -> 13.1 us, 288 21.3 -> 19.3, 272 of 2100 34.7 -> 32.2, 376 of 6000 91.7 -> 85.0, 1152 of 1101 50.1
-// -> 49.0, 2304 89.6 -> 90.3.  Inside a network, where the rows come from the product before, the 144 take 18.3 -> 14 us, 17 with two buffers
+// here: 144 workgroups of 1101 tokens 15.7 -> 13.1 us, 288 21.3 -> 19.3, 272 of 2100 34.7 -> 32.2, 376 of 6000 91.7 -> 85.0; where the
+// first is the faster one: attention_pipelined.  Inside a network, where the rows come from the product before, the 144 take 18.3 -> 14 us, 17 with two buffers
 // of LDS instead of four.  (At head dim 128 it does not fit 256 registers: 1068 TFLOP/s at 4608 tokens, 1168 above.)
 template <int DH, bool PRE, bool WARM>
 __global__ __launch_bounds__(256, 2) void attn_bf16_pipe_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out, int L,
@@ -831,7 +832,7 @@ br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH
   const int n_cu = device_cu_count();
   WarmRows warm = next;
   warm.blocks = next.n16[0] > 0 && q_prescaled ? (n_cu - (int)std::min<long long>(n_blocks, n_cu)) / 8 * 8 : 0;
-  if (warm.blocks < 32) warm.blocks = 0;
+  if (warm.blocks < 32) warm.blocks = 0;  // (at head dim 64 fewer workgroups than units: the pipelined loop)
   unsigned budget = (unsigned)(WARM_BYTES_PER_TILE / 16 * (cdiv(L, KV_TILE) + 4) / 256 * warm.blocks);
   for (unsigned& n : warm.n16) {
     n = std::min(n, budget);
@@ -842,16 +843,15 @@ br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH
   const int H = NH * DH;
   ProfScope ps(st, PROF_ATTN + DH, 4.0 * B * (double)L * L * H);
   auto go = [&](auto kernel, const auto& w) { hipLaunchKernelGGL(kernel, g, blk, 0, st, qkv, out, L, H, NH, (int)n_pairs, grouped, scale_log2, w); };
-#define BR_ATTN_GO(KERNEL, DHc)                                   \
-  if (warm.blocks > 0) go(KERNEL<DHc, true, true>, warm);         \
-  else if (q_prescaled) go(KERNEL<DHc, true, false>, NoWarm{});   \
-  else go(KERNEL<DHc, false, false>, NoWarm{})
-  // up to six workgroups a compute unit the pipelined loop is the faster one (figures there), bit for bit the same
-  const bool pipe = DH == 64 && n_blocks <= 6LL * n_cu;
-  if (pipe) { BR_ATTN_GO(attn_bf16_pipe_kernel, 64); }
-  else if (DH == 64) { BR_ATTN_GO(attn_bf16_kernel, 64); }
-  else if (DH == 128) { BR_ATTN_GO(attn_bf16_kernel, 128); }
-#undef BR_ATTN_GO
+  const bool pipe = rule::attention_pipelined(DH, L, n_blocks, n_cu);  // bit for bit the same either way
+  if (warm.blocks > 0 && pipe) go(attn_bf16_pipe_kernel<64, true, true>, warm);
+  else if (warm.blocks > 0 && DH == 128) go(attn_bf16_kernel<128, true, true>, warm);
+  else if (pipe && q_prescaled) go(attn_bf16_pipe_kernel<64, true, false>, NoWarm{});
+  else if (pipe) go(attn_bf16_pipe_kernel<64, false, false>, NoWarm{});
+  else if (DH == 64 && q_prescaled) go(attn_bf16_kernel<64, true, false>, NoWarm{});
+  else if (DH == 64) go(attn_bf16_kernel<64, false, false>, NoWarm{});
+  else if (DH == 128 && q_prescaled) go(attn_bf16_kernel<128, true, false>, NoWarm{});
+  else if (DH == 128) go(attn_bf16_kernel<128, false, false>, NoWarm{});
   else return fail(BR_ESHAPE, "bf16 attention: head dim must be 64 or 128");
   BR_LAUNCH_CHECK();
   return BR_OK;

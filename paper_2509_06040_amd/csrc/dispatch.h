@@ -24,5 +24,16 @@ inline bool persistent_output_stays(size_t bytes, int K) {
   return bytes >= (size_t)32 << 20 && bytes <= to;
 }
 
+// bf16 attention of head dim 64: the loop pipelined by a key tile, two workgroups a compute unit (64 KB of LDS), or the plain one, three.  The first is
+// faster tile by tile (one workgroup a unit: 3000 tokens 0.85, 1101 0.90, 512 0.94, 32 0.97 of the other's time), the second starts more at once.
+// So the line follows the rounds both need: up to one workgroup a unit any length, up to two from 385 tokens (1101 to 6000 tokens 0.85 to 0.96,
+// 512 0.98 to 1.00; 256 1.00 to 1.03, 32 1.03 to 1.06), and where the plain loop needs a second round for a fourth (1101 to 9000 tokens 0.96 to 1.00;
+// 512 1.01 to 1.03).  Three a unit: 1.02 to 1.08 from 1101 tokens, up to 1.37 at 32; beyond four 1.00 to 1.10, 1.30 at 32.
+inline bool attention_pipelined(int head_dim, int tokens, long long workgroups, int units) {
+  if (head_dim != 64) return false;
+  const long long rounds = (workgroups + units - 1) / units;
+  return rounds <= 1 || (rounds == 2 && tokens > 384) || (rounds == 4 && tokens >= 1024);
+}
+
 }  // namespace rule
 }  // namespace br

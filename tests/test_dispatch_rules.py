@@ -12,6 +12,7 @@ using namespace br;
 extern "C" {
 int tile_output_streams(unsigned long long bytes) { return rule::tile_output_streams(bytes); }
 int persistent_output_stays(unsigned long long bytes, int K) { return rule::persistent_output_stays(bytes, K); }
+int attention_pipelined(int dh, int tokens, long long workgroups, int units) { return rule::attention_pipelined(dh, tokens, workgroups, units); }
 }
 """
 CU = 256
@@ -42,3 +43,15 @@ def test_outputs_of_the_persistent_kernel_that_stay_in_the_caches(rule):
     for H, rows in ((256, 441 * 93), (512, 126 * 93), (512, 221 * 93), (768, 63 * 93), (1024, 8 * 1101), (1024, 47 * 93), (1536, 105 * 93), (2048, 8 * 1101), (3072, 3 * 1101)):
         assert stays(rows, H), (H, rows)
     assert not stays(2047, 1024 * 2) and stays(2048, 1024 * 2) and not stays(11 * 93, 3072)
+
+
+def test_attention_is_pipelined_where_its_two_workgroups_a_unit_suffice(rule):
+    pipe = lambda dh, L, w: bool(rule.attention_pipelined(dh, L, C.c_longlong(w), CU))
+    for L in (1, 64, 385, 1101, 6000):
+        assert pipe(64, L, 1) and pipe(64, L, CU)
+        assert not pipe(64, L, 2 * CU + 1) and not pipe(64, L, 3 * CU) and not pipe(64, L, 4 * CU + 1) and not pipe(64, L, 9 * CU)
+        assert not pipe(128, L, 1)
+    assert not pipe(64, 384, CU + 1) and pipe(64, 385, CU + 1) and pipe(64, 1101, 2 * CU)
+    assert not pipe(64, 1023, 3 * CU + 1) and pipe(64, 1024, 3 * CU + 1) and pipe(64, 6000, 4 * CU)
+    # what the plain loop is 13 to 30 % faster on: many short samples, and 608 workgroups of 210 tokens
+    assert not pipe(64, 28, 1528) and not pipe(64, 69, 576) and not pipe(64, 86, 1032) and not pipe(64, 210, 608)
