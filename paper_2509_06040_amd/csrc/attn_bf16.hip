@@ -832,8 +832,10 @@ br_status launch_attention_bf16(const bf16* qkv, bf16* out, int B, int L, int NH
   const int n_cu = device_cu_count();
   WarmRows warm = next;
   warm.blocks = next.n16[0] > 0 && q_prescaled ? (n_cu - (int)std::min<long long>(n_blocks, n_cu)) / 8 * 8 : 0;
-  if (warm.blocks < 32) warm.blocks = 0;  // (at head dim 64 fewer workgroups than units: the pipelined loop)
   unsigned budget = (unsigned)(WARM_BYTES_PER_TILE / 16 * (cdiv(L, KV_TILE) + 4) / 256 * warm.blocks);
+  size_t bytes = 0;
+  for (const unsigned n : next.n16) bytes += (size_t)n * 16;
+  if (warm.blocks < 32 || !rule::read_ahead((size_t)budget * 16, bytes)) warm.blocks = 0;  // (at head dim 64 fewer workgroups than units: the pipelined loop)
   for (unsigned& n : warm.n16) {
     n = std::min(n, budget);
     budget -= n;

@@ -13,6 +13,7 @@ extern "C" {
 int tile_output_streams(unsigned long long bytes) { return rule::tile_output_streams(bytes); }
 int persistent_output_stays(unsigned long long bytes, int K) { return rule::persistent_output_stays(bytes, K); }
 int attention_pipelined(int dh, int tokens, long long workgroups, int units) { return rule::attention_pipelined(dh, tokens, workgroups, units); }
+int read_ahead(unsigned long long room, unsigned long long bytes) { return rule::read_ahead(room, bytes); }
 }
 """
 CU = 256
@@ -55,3 +56,15 @@ def test_attention_is_pipelined_where_its_two_workgroups_a_unit_suffice(rule):
     assert not pipe(64, 1023, 3 * CU + 1) and pipe(64, 1024, 3 * CU + 1) and pipe(64, 6000, 4 * CU)
     # what the plain loop is 13 to 30 % faster on: many short samples, and 608 workgroups of 210 tokens
     assert not pipe(64, 28, 1528) and not pipe(64, 69, 576) and not pipe(64, 86, 1032) and not pipe(64, 210, 608)
+
+
+def test_weights_are_read_ahead_where_a_good_part_of_them_fits(rule):
+    """A block's four matrices (2 x 12 H^2 bytes) against what the idle units read during an attention of L tokens: 2 MB a tile of 64 keys, and four
+    tiles' time around them, of 256 units."""
+    def ahead(H, head_dim, L, B):
+        idle = (CU - B * (H // head_dim) * -(-L // 128)) // 8 * 8
+        return idle >= 32 and bool(rule.read_ahead(C.c_ulonglong(2 ** 21 * (-(-L // 64) + 4) // 256 * idle), C.c_ulonglong(24 * H * H)))
+    for case in ((1024, 64, 1101, 1), (1024, 128, 333, 2), (1024, 64, 100, 1), (1536, 128, 1101, 1), (2048, 64, 200, 2), (2560, 128, 613, 1)):
+        assert ahead(*case), case
+    for case in ((3072, 128, 333, 1), (3072, 128, 80, 1), (3072, 128, 1101, 1), (2880, 64, 200, 1), (2560, 64, 333, 1), (2560, 128, 613, 2), (1024, 64, 1101, 2)):
+        assert not ahead(*case), case
