@@ -1,5 +1,6 @@
 // Rules that choose between forms of a kernel, as plain functions of sizes: no runtime, no device, so that they can be checked anywhere.
 #pragma once
+#include <cmath>
 #include <cstddef>
 
 namespace br {
@@ -40,6 +41,32 @@ inline bool attention_pipelined(int head_dim, int tokens, long long workgroups, 
 // against without: hidden 2560 to 3072, 333 to 1101 tokens, 3 to 7 % of the list 1.001 to 1.008; hidden 2048, 200 tokens, 8 and 13 % 0.978 and 0.982;
 // 2560, 10 and 11 % 0.978 and 0.982; 1536 and 2048, head dim 128, 20 to 45 % 0.967 to 0.996; 1024, head dims 64 and 128, 44 to 100 % 0.91 to 0.98.
 inline bool read_ahead(size_t room, size_t bytes) { return room * 13 >= bytes; }
+
+// fp32 products: the 32x32 tiles up to three a compute unit, whose four waves are faster there (599 x 768 x 768 11.8 us, 13.9 in the best tile of the ring
+// kernel; 3833 x 192 x 768 15.1, 16.0; 24 x 64 x 256 by far); beyond, the ring kernel (1101 x 1024 x 4096 98 us, 91; 1624 x 768 x 3072 84, 70).
+inline bool f32_small(int M, int N, int units) { return ((long long)M + 31) / 32 * ((N + 31) / 32) <= 3LL * units; }
+
+// The cheapest tile of the ring kernel, 16 rb rows x 64 cb columns: whole rounds of tiles, each its products (a 16 x 64 block of them is K / 300 us
+// of a compute unit) and half a block's time that they do not hide, and half a microsecond a tile for first stage and epilogue.  Fitted to 90 shapes
+// (M 100 to 40 000, hidden sizes 64 to 1024) in all 22 tiles: 1.6 % slower on average than the best of each shape.  Where a sample
+// (rps rows, 0: nothing is looked up per sample) is shorter than the tile, every row would look its gate up by itself.
+// (The units come from the caller: asked of the runtime for every tile they cost a microsecond and more of each call.)
+constexpr int F32_RING_MAX_RB = 12;
+inline void f32_ring_tile(int M, int N, int K, int rps, int units, int* rb, int* cb) {
+  double best = 0.0;
+  *rb = 0;
+  for (int c = 1; c <= 2; ++c)
+    for (int r = 2; r <= F32_RING_MAX_RB; ++r) {
+      if (r > 2 && rps > 0 && rps < 16 * r) break;
+      const double n = (double)((M + 16LL * r - 1) / (16 * r)) * ((N + 64LL * c - 1) / (64 * c)) / units;
+      const double cost = std::ceil(n) * (r * c + 0.47) * K / 300.0 + 0.5 * n;
+      if (*rb == 0 || cost < best) {
+        best = cost;
+        *rb = r;
+        *cb = c;
+      }
+    }
+}
 
 }  // namespace rule
 }  // namespace br

@@ -98,9 +98,8 @@ br_status launch_gemm_small(int dtype, int mode, const void* A, int lda, const v
                              const EpiArgs& ea, hipStream_t st);
 br_status launch_gemm_f32(int mode, const float* A, int lda, const float* W, int ldw, int M, int N, int K,
                           const EpiArgs& ea, int variant, hipStream_t st);
-constexpr int F32_RING_MAX_RB = 12;  // tiles of 2 .. 12 times 16 rows x 64 (cb 1) or 128 (cb 2) columns
-void gemm_f32_ring_tile(int M, int N, int K, int rps, int* rb, int* cb);
 bool gemm_f32_ring_supported(int mode, int K, int lda, int ldw);
+// tiles of 16 rb rows (rb 2 .. 12) x 64 cb columns (cb 1, 2)
 br_status launch_gemm_f32_ring(int mode, const float* A, int lda, const float* W, int ldw, int M, int N, int K, const EpiArgs& ea, int rb,
                                int cb, hipStream_t st);
 // GEMM whose A operand is LayerNorm(x[src(r), :]) (1 + scale) + shift (rows as in launch_ln_modulate), for small problems.

@@ -3,6 +3,7 @@
 // choice between the ring kernel (gemm_f32_ring.hip) and the kernel for small problems (gemm_small.hip), and a vector
 // kernel for operands that cannot be fetched in 16-byte pieces.
 #include "common.h"
+#include "dispatch.h"
 #include "dit.h"
 #include "prof.h"
 
@@ -74,11 +75,10 @@ static br_status gemm_f32_mode(const float* A, int lda, const float* W, int ldw,
   // (patch embedding, condition embedding and unpatchify are a few per cent of a network: one form is enough)
   if (variant != F32_TILE_32 && gemm_f32_ring_supported(MODE, K, lda, ldw)) {
     int rb = variant < 0 ? 0 : variant >> 24 & 127, cb = variant >> 4 & 1 ? 2 : 1;
-    const bool forced = variant >= 0 && (variant & 15) == F32_RING && rb >= 2 && rb <= F32_RING_MAX_RB;
-    // Up to three 32x32 tiles a compute unit the four waves of each are faster (599 x 768 x 768 11.8 us, 13.9 in the best ring tile; 3833
-    // x 192 x 768 15.1, 16.0; 24 x 64 x 256 by far); beyond, the ring (1101 x 1024 x 4096 98 us, 91; 1624 x 768 x 3072 84, 70).
-    if (forced || (long long)cdiv(M, 32) * cdiv(N, 32) > 3LL * device_cu_count()) {
-      if (!forced) gemm_f32_ring_tile(M, N, K, MODE == EPI_BIAS_GATE_RES ? ea.L : 0, &rb, &cb);
+    const bool forced = variant >= 0 && (variant & 15) == F32_RING && rb >= 2 && rb <= rule::F32_RING_MAX_RB;
+    const int units = device_cu_count();
+    if (forced || !rule::f32_small(M, N, units)) {
+      if (!forced) rule::f32_ring_tile(M, N, K, MODE == EPI_BIAS_GATE_RES ? ea.L : 0, units, &rb, &cb);
       return launch_gemm_f32_ring(MODE, A, lda, W, ldw, M, N, K, ea, rb, cb, st);
     }
   }

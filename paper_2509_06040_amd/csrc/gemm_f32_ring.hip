@@ -13,6 +13,7 @@
 #include <utility>
 
 #include "common.h"
+#include "dispatch.h"
 #include "dit.h"
 #include "gemm_frag.h"
 
@@ -227,30 +228,10 @@ static br_status f32_ring_height(const float* A, int lda, const float* W, int ld
   return fail(BR_EINVAL, "gemm: unknown tile height");
 }
 
-// The cheapest tile: whole rounds of tiles, each its products (a 16 x 64 block of them is K / 300 us of a compute unit) and half a block's
-// time that they do not hide, and half a microsecond a tile for first stage and epilogue.  Fitted to 90 shapes (M 100 to 40 000, hidden
-// sizes 64 to 1024) in all 22 tiles: 1.6 % slower on average than the best of each shape.  Where a sample is shorter than the tile, every
-// row would look its gate up by itself.
-void gemm_f32_ring_tile(int M, int N, int K, int rps, int* rb, int* cb) {
-  double best = 0.0;
-  *rb = 0;
-  for (int c = 1; c <= 2; ++c)
-    for (int r = 2; r <= F32_RING_MAX_RB; ++r) {
-      if (r > 2 && rps > 0 && rps < 16 * r) break;
-      const double n = (double)cdiv(M, 16 * r) * cdiv(N, 64 * c) / device_cu_count();
-      const double cost = std::ceil(n) * (r * c + 0.47) * K / 300.0 + 0.5 * n;
-      if (*rb == 0 || cost < best) {
-        best = cost;
-        *rb = r;
-        *cb = c;
-      }
-    }
-}
-
 // Whole stages; a tile's rows are addressed with 32-bit byte offsets from its first one.
 bool gemm_f32_ring_supported(int mode, int K, int lda, int ldw) {
   return (mode == EPI_BIAS || mode == EPI_BIAS_GELU || mode == EPI_BIAS_GATE_RES) && K % 32 == 0 &&
-         16ull * F32_RING_MAX_RB * lda * 4 < (1ull << 32) && 128ull * ldw * 4 < (1ull << 32);
+         16ull * rule::F32_RING_MAX_RB * lda * 4 < (1ull << 32) && 128ull * ldw * 4 < (1ull << 32);
 }
 
 br_status launch_gemm_f32_ring(int mode, const float* A, int lda, const float* W, int ldw, int M, int N, int K, const EpiArgs& ea, int rb,

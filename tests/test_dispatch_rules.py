@@ -14,6 +14,8 @@ int tile_output_streams(unsigned long long bytes) { return rule::tile_output_str
 int persistent_output_stays(unsigned long long bytes, int K) { return rule::persistent_output_stays(bytes, K); }
 int attention_pipelined(int dh, int tokens, long long workgroups, int units) { return rule::attention_pipelined(dh, tokens, workgroups, units); }
 int read_ahead(unsigned long long room, unsigned long long bytes) { return rule::read_ahead(room, bytes); }
+int f32_small(int M, int N, int units) { return rule::f32_small(M, N, units); }
+void f32_ring_tile(int M, int N, int K, int rps, int units, int* rb, int* cb) { rule::f32_ring_tile(M, N, K, rps, units, rb, cb); }
 }
 """
 CU = 256
@@ -68,3 +70,25 @@ def test_weights_are_read_ahead_where_a_good_part_of_them_fits(rule):
         assert ahead(*case), case
     for case in ((3072, 128, 333, 1), (3072, 128, 80, 1), (3072, 128, 1101, 1), (2880, 64, 200, 1), (2560, 64, 333, 1), (2560, 128, 613, 2), (1024, 64, 1101, 2)):
         assert not ahead(*case), case
+
+
+def test_fp32_products_small_tiles_or_which_ring_tile(rule):
+    """The rule is a function of sizes and the number of units alone (a caller that asked the runtime for them once a tile paid 1.3 us a call)."""
+    def tile(M, N, K, rps=0):
+        rb, cb = C.c_int(), C.c_int()
+        rule.f32_ring_tile(M, N, K, rps, CU, C.byref(rb), C.byref(cb))
+        return rb.value, cb.value
+    small = lambda M, N: bool(rule.f32_small(M, N, CU))
+    assert small(599, 768) and small(24 * 32, 32 * 32) and not small(24 * 32 + 1, 32 * 32) and not small(1101, 1024) and not small(1624, 768)
+    assert not small(2 ** 31 - 1, 1024)
+    # one round of 144 x 128 tiles (0.97 full) for 4404 x 1024; two of 128 x 128 for 32 of the same rows
+    assert tile(4404, 1024, 4096) == (9, 2)
+    for M, N, K in ((1101, 1024, 4096), (1624, 768, 3072), (2000, 1536, 512), (32768, 4096, 4096)):
+        rb, cb = tile(M, N, K)
+        rounds = lambda r, c: -(-(-(-M // (16 * r)) * -(-N // (64 * c))) // CU)
+        # no other tile needs less of the matrix pipes by a quarter
+        assert all(rounds(rb, cb) * rb * cb <= 1.25 * rounds(r, c) * r * c for r in range(2, 13) for c in (1, 2)), (M, N, K)
+    # gated residual: no taller than a sample, unless that is shorter than the lowest tile
+    for rps in (7, 31, 32, 50, 100, 191, 192):
+        rb, cb = tile(rps * 300, 1024, 1024, rps)
+        assert rb == 2 or 16 * rb <= rps, rps
