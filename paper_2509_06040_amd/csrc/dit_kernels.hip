@@ -320,11 +320,15 @@ br_status conditioning(const br_model* m, const FwdBuffers& fb, const void* cond
 //
 // What bounds it: a small launch, the chain of one row (row, group of its sample, modulation vectors, two sums of 64 lanes), a large one the
 // memory.  The row's number is scalar, so the group comes by a scalar load beside the row's own; up to VPL = 4 the modulation vectors are
-// under way with the row too (beyond, the compiler decides); the sums are exchanged without the LDS unit.  Large fp32 launches fetch the
-// vectors last (LATE): they lose by more registers or more loads in front of the row.  STREAM: rows that the caches cannot
-// hold until the next launch reads them are stored past them.  us before -> now, bf16:  8808 x 1024 12.6 -> 11.4, 17 616 x 1024 21.6 -> 19.6,
-// 26 424 x 1024 30.4 -> 27.8, 70 464 x 1024 74.3 -> 74.4, 36 864 x 3072 123.9 -> 116.8, 33 272 x 1536 the same 53.7; fp32: 8808 x 1024 15.8 -> 14.7,
-// 17 616 x 1024 27.2 -> 25.1, 26 424 to 70 464 x 1024 1 % slower.  (Plain stores throughout: bf16 70 464 x 1024 77.0, 33 272 x 1536 54.7.)
+// under way with the row too (beyond, the compiler decides); the sums are exchanged without the LDS unit.  fp32 rows of more than 1024
+// columns, and of large launches, fetch the vectors last (LATE): they lose by more registers or more loads in front of the row.  STREAM: rows that the caches cannot
+// hold until the next launch reads them are stored past them.  Long rows of such launches keep the sums in the LDS unit (bf16 from 1536 columns: 22 020 x 2048
+// 49.9 us without it, 49.1 with, 147 456 x 3072 462, 458), in fp32 from 1024 also the row number in a vector register and the vectors
+// behind the sums (LONG: 9216 x 3072 45.0 us in the other form, 42.4; 147 456 x 3072 662, 647; 70 464 x 1024 96.8, 95.7; but 33 272 x 1536 71.2, 71.8).
+// us before -> now (a graph over buffers in turn), bf16:  8808 x 1024 12.3 -> 11.1, 17 616 x 1024 21.2 -> 19.4, 26 424 x 1024 29.9 -> 27.5, 70 464 x 1024
+// 74.1 -> 74.4, 38 336 x 512 22.9 -> 19.9, 36 864 x 3072 123.6 -> 117.0, 33 272 x 1536 53.8 -> 53.6; fp32: 8808 x 1024 15.2 -> 14.4, 17 616 x 1024
+// 27.2 -> 24.8, 76 800 x 256 31.3 -> 28.1.  Plain stores below the line cost an isolated launch that writes the same rows again up to a
+// tenth (4000 x 1536 7.8 -> 8.8), in a network they are worth 0 to 2 % of the call.
 constexpr double LN_STREAM_FROM = 192e6;  // bytes of rows read and written
 template <bool STREAM, typename T>
 __device__ __forceinline__ void store4_row(T* p, float a, float b, float c, float d) {
@@ -339,9 +343,10 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
                                                           const float* __restrict__ mods, int A, int shift_off,
                                                           int scale_off, const int* __restrict__ condmap) {
   constexpr int NV = VPL > 0 ? VPL : 1;
-  constexpr bool LATE = std::is_same<T, float>::value && (STREAM || VPL > 4), EARLY = !LATE && VPL > 0 && VPL <= 4;
+  constexpr bool F32 = std::is_same<T, float>::value, LONG = F32 && STREAM && VPL >= 4 && VPL != 6;
+  constexpr bool LATE = F32 && !LONG && (STREAM || VPL > 4), EARLY = !LATE && !LONG && VPL > 0 && VPL <= 4;
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = threadIdx.x >> 6, r = blockIdx.x * 4 + (LONG ? wave : __builtin_amdgcn_readfirstlane(wave));
   if (r >= n_rows) return;
   const int b = r / rows_per_sample, tok = r - b * rows_per_sample;
   const float4* xr = reinterpret_cast<const float4*>(x + ((size_t)b * L_in + tok) * H);
@@ -351,9 +356,13 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
 #pragma unroll
     for (int i = 0; i < VPL; ++i) v[i] = xr[lane + 64 * i];
   }
-  const float* mrow = mods + (size_t)condmap[b] * A;
-  const float4* sh = reinterpret_cast<const float4*>(mrow + shift_off);
-  const float4* sc = reinterpret_cast<const float4*>(mrow + scale_off);
+  const float4 *sh, *sc;
+  auto vectors = [&] {
+    const float* mrow = mods + (size_t)condmap[b] * A;
+    sh = reinterpret_cast<const float4*>(mrow + shift_off);
+    sc = reinterpret_cast<const float4*>(mrow + scale_off);
+  };
+  if (!LONG) vectors();
   if (EARLY) {
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
@@ -362,6 +371,12 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
     }
     __builtin_amdgcn_sched_barrier(0);
   }
+  auto sum = [](float u) {
+    if (!STREAM || !(F32 ? LONG : VPL >= 6)) return lanes_sum<64>(u);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) u += __shfl_xor(u, o, 64);
+    return u;
+  };
   float s = 0.f;
   if (VPL > 0) {
 #pragma unroll
@@ -372,7 +387,7 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
       s += (u.x + u.y) + (u.z + u.w);
     }
   }
-  const float mean = lanes_sum<64>(s) / (float)H;
+  const float mean = sum(s) / (float)H;
   float q = 0.f;
   if (VPL > 0) {
 #pragma unroll
@@ -380,7 +395,8 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
   } else {
     for (int i = lane; i < H4; i += 64) q += sum_sq4(xr[i], mean);
   }
-  const float rstd = 1.0f / __builtin_sqrtf(lanes_sum<64>(q) / (float)H + 1e-6f);
+  const float rstd = 1.0f / __builtin_sqrtf(sum(q) / (float)H + 1e-6f);
+  if (LONG) vectors();
   T* orow = out + (size_t)r * H;
   if (LATE) asm volatile("" ::: "memory");
   if (VPL > 0) {

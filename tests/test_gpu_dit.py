@@ -263,6 +263,22 @@ def test_ln_modulate_row_lengths(lib, dt, B, L, H):
         assert float(err.max()) < (2.0 ** -9 if dt == br.BF16 else 2e-6), b
 
 
+@pytest.mark.parametrize("dt", [br.F32, br.BF16])
+@pytest.mark.parametrize("rows,H", [(125004, 256), (62505, 512), (41700, 768), (31270, 1024), (20900, 1536), (15700, 2048), (10500, 3072), (33000, 992)])
+def test_ln_modulate_bits_do_not_depend_on_the_launch(lib, dt, rows, H):
+    """A launch whose rows are stored past the caches (long ones summed through the LDS unit) and the same rows in small launches: the same bits."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(H)
+    x, mods = torch.randn((rows, H), generator=g, device=DEV) * 2 + 0.5, torch.randn((1, 2 * H), generator=g, device=DEV)
+    cond, tdt = torch.zeros(1, dtype=torch.int32, device=DEV), torch.bfloat16 if dt == br.BF16 else torch.float32
+    out = torch.empty((rows, H), dtype=tdt, device=DEV)
+    br.op_ln_modulate(dt, x, out, rows, rows, mods, 0, H, cond)
+    for lo in range(0, rows, 2500):
+        part = torch.empty((min(2500, rows - lo), H), dtype=tdt, device=DEV)
+        br.op_ln_modulate(dt, x[lo:lo + 2500], part, len(part), len(part), mods, 0, H, cond)
+        assert torch.equal(out[lo:lo + 2500], part), lo
+
+
 def _velocity_case(cfg, n_cond, B, t, seed, std=0.02):
     W = synth.make_weights(cfg, seed, std)
     D = synth.model_sizes(cfg)["D"]
