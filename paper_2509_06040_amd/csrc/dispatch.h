@@ -16,12 +16,19 @@ inline bool tile_output_streams(size_t bytes) { return bytes > (size_t)160 << 20
 // bf16 outputs of the persistent kernel: stored plainly, the launch that reads them finds them in the memory-side cache (256 MB, with the
 // operands and the residual stream); else past the caches, which leaves those to the operands.  Below 32 MB the L2 caches of the dies count.  Above,
 // a product of small K stores so fast that plain stores of more than the cache takes stall it, and the line lies where that begins.
-// Velocity calls (samples of 93, 1101 and 4608 rows), plain against past the caches, by the bytes of the MLP's first layer:
-//   hidden 256 to 640:   up to 100 MB 0.944 to 1.010, mean 0.982; 100 to 130 MB 1.002 to 1.072, 1.030; 130 to 170 MB 0.988 to 1.023, 1.006
-//   hidden 768 to 1024:  up to 75 MB 0.944 to 1.011, mean 0.990; 75 to 100 MB 0.984 to 1.018, 1.003; 100 to 170 MB 0.987 to 1.034, 1.009
-//   hidden 1280 to 3072: up to 75 MB 0.938 to 1.021, mean 1.000; 75 to 130 MB 0.981 to 1.017, 0.999; 130 to 170 MB 0.982 to 1.002, 0.994
-inline bool persistent_output_stays(size_t bytes, int K) {
-  const size_t to = K <= 640 ? 100000000 : K <= 1024 ? 75000000 : (size_t)160 << 20;
+// Velocity calls (samples of 93, 1101 and 4608 rows), plain against past the caches, mean (least to greatest):
+//   hidden           256 to 640                768 to 1024               1280 to 3072
+//   MLP's first layer (with GELU)
+//     up to  75 MB   0.982 (0.949 to 1.010)    0.990 (0.944 to 1.011)    1.000 (0.938 to 1.021)   [with the QKV rows in front]
+//      75 to 100     0.989 (0.953 to 1.011)    1.009 (0.981 to 1.025)    1.000 (0.989 to 1.015)
+//     100 to 130     1.035 (1.001 to 1.104)    1.013 (0.993 to 1.037)    0.997 (0.981 to 1.003)
+//     130 to 170     1.009 (0.990 to 1.048)    1.008 (0.989 to 1.033)    0.995 (0.987 to 1.002)
+//   QKV rows
+//      60 to  85     0.993 (0.979 to 1.002)    0.996 (0.985 to 1.004)    1.002 (0.994 to 1.014)
+//      85 to 112     0.994 (0.979 to 1.007)    0.998 (0.981 to 1.023)    0.998 (0.992 to 1.004)
+//     112 to 130     1.002 (0.988 to 1.015)    1.003 (0.992 to 1.015)    1.000 (0.997 to 1.007)
+inline bool persistent_output_stays(size_t bytes, int K, bool gelu) {
+  const size_t to = K > 1024 ? (size_t)160 << 20 : !gelu ? 112000000 : K <= 640 ? 100000000 : 75000000;
   return bytes >= (size_t)32 << 20 && bytes <= to;
 }
 

@@ -313,7 +313,7 @@ static br_status stream_launch(const bf16* A, int lda, const bf16* W, int ldw, i
   const int nt = tiles_m * tiles_n;
   const int grid = nt < n_cu ? nt : n_cu;
   if constexpr (std::is_same<TOUT, bf16>::value) {
-    if (rule::persistent_output_stays((size_t)M * N * sizeof(TOUT), K)) {
+    if (rule::persistent_output_stays((size_t)M * N * sizeof(TOUT), K, MODE == EPI_BIAS_GELU)) {
       hipLaunchKernelGGL((gemm_bf16_stream_keep_kernel<RB, MODE, TOUT>), dim3(grid), dim3(256), 0, st, A, lda, W, ldw, M, N, K,
                          tiles_m, tiles_n, group_n, row_block, epi);
       BR_LAUNCH_CHECK();
