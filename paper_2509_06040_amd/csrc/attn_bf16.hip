@@ -17,12 +17,12 @@
 // of its own channel.
 #include <algorithm>
 #include <type_traits>
-#include <utility>
 
 #include "common.h"
 #include "dispatch.h"
 #include "dit.h"
 #include "prof.h"
+#include "static_for.h"
 
 namespace br {
 
@@ -36,11 +36,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #define BR_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
-template <int... I, class F>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) { static_for_impl(std::make_integer_sequence<int, N>{}, f); }
-
 constexpr int KV_TILE = 64;
 constexpr long long WARM_BYTES_PER_TILE = 2 << 20;  // what 256 idle compute units read while a workgroup takes a key tile
 

@@ -27,8 +27,8 @@ static br_status gemm_tile_launch(const bf16* A, int lda, const bf16* W, int ldw
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(WGM * WGN * 64), 0, st, A, lda, W, ldw, M, N, K, tiles_m, tiles_n, group_n, epi);
   };
-  if (LARGE && rule::tile_output_streams((size_t)M * N * sizeof(TOUT))) go(gemm_tile_kernel<bf16, BM, BN, WGM, WGN, NST, MODE, TOUT, LARGE>);
-  else go(gemm_tile_kernel<bf16, BM, BN, WGM, WGN, NST, MODE, TOUT, false>);
+  if (LARGE && rule::tile_output_streams((size_t)M * N * sizeof(TOUT))) go(gemm_tile_kernel<BM, BN, WGM, WGN, NST, MODE, TOUT, LARGE>);
+  else go(gemm_tile_kernel<BM, BN, WGM, WGN, NST, MODE, TOUT, false>);
   BR_LAUNCH_CHECK();
   return BR_OK;
 }

@@ -20,13 +20,13 @@
 // Requirements: K % 128 == 0 (every tile starts on ring slot 0), K >= 128, operands below 4 GiB.
 #include <cmath>
 #include <type_traits>
-#include <utility>
 
 #include "common.h"
 #include "dispatch.h"
 #include "dit.h"
 #include "gemm_epilogue_wide.h"
 #include "gemm_frag.h"
+#include "static_for.h"
 
 namespace br {
 
@@ -43,16 +43,6 @@ constexpr int IW = BN / 8 / NW;   // LDS-direct loads of W per wave and stage (8
 template <int BYTES, int S>
 __shared__ __attribute__((aligned(1024))) char g_ring[BYTES];
 __shared__ __attribute__((aligned(1024))) char g_epi[NW * WIDE_EPI_BYTES];
-
-// f(integral_constant 0) ... f(integral_constant N - 1)
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 // Matrix instructions on accumulators that stay in the accumulation registers.  (From the builtin the compiler keeps
 // some of the 64 blocks in vector registers and moves them back and forth.)  The first of a tile starts from zero.

@@ -10,41 +10,31 @@
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
-#include <utility>
 
 #include "common.h"
 #include "dispatch.h"
 #include "dit.h"
 #include "gemm_frag.h"
+#include "static_for.h"
 
 namespace br {
 
 #define BR_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
 namespace {
-constexpr int NW = 4;
-}
-
-// f(integral_constant 0) ... f(integral_constant N - 1)
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
+constexpr int NW = 4, NST = 2;  // waves; stages in LDS
 }
 
 extern __shared__ __attribute__((aligned(1024))) char g_f32_ring[];
 
-template <int RB, int CB, int NST, int MODE>
+template <int RB, int CB, int MODE>
 __global__ __launch_bounds__(256, 2) void gemm_f32_ring_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
                                                                int M, int N, int K, int tiles_m, int tiles_n, int group_n,
                                                                Epilogue<MODE, float> epi) {
   typedef GemmFrag16<float> F;
   constexpr int BM = 16 * RB, BN = 64 * CB, STAGE = (BM + BN) * 128;
   constexpr int GA = BM / 8, GT = GA + BN / 8, LPW = (GT + NW - 1) / NW;  // groups of 8 rows; loads of a wave and stage
-  static_assert(NST * STAGE <= 160 * 1024 && NST >= 2 && NST <= 4 && (NST - 1) * LPW < 64, "ring");
+  static_assert(NST * STAGE <= 160 * 1024 && LPW < 64, "ring");
   int wg = blockIdx.x;
   {
     const int nwg = tiles_m * tiles_n, per = nwg / 8, rem = nwg % 8, x = wg % 8, i = wg / 8;
@@ -77,9 +67,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_ring_kernel(const float* __re
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(ring0 + slot * STAGE + g * 1024), "v"(off[j]), "s"(src) : "memory", "m0");
   };
   auto wait = [&](int younger) __attribute__((always_inline)) {
-    if (NST > 2 && younger >= 2)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST > 2 ? 2 : 0) * LPW) : "memory");
-    else if (younger >= 1)
+    if (younger >= 1)
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW) : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -129,18 +117,18 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_ring_kernel(const float* __re
   int slot = 0;
   auto stage = [&](int kt, auto LOADS) __attribute__((always_inline)) {
     constexpr bool loads = decltype(LOADS)::value;
-    const int next = slot + 1 == NST ? 0 : slot + 1, prev = slot == 0 ? NST - 1 : slot - 1;
+    const int other = slot ^ 1;
     static_for<7>([&](auto S) __attribute__((always_inline)) {
       constexpr int s = decltype(S)::value, first = std::min(s * LQ, LPW), count = loads ? std::min(LPW, (s + 1) * LQ) - first : 0;
-      step(S, slot, std::integral_constant<int, s + 1>{}, std::integral_constant<int, first>{}, std::integral_constant<int, count>{}, kt - 1 + NST, prev);
+      step(S, slot, std::integral_constant<int, s + 1>{}, std::integral_constant<int, first>{}, std::integral_constant<int, count>{}, kt - 1 + NST, other);
     });
     // Stage kt + 1 has landed and the fragments of stage kt are in registers; behind the barrier for every wave.  (Behind the last stage an
     // old one is read once more, which nobody uses.)
-    wait(min(nk - 2 - kt, NST - 2));
+    wait(0);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    step(std::integral_constant<int, 7>{}, next, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, 0, 0);
-    slot = next;
+    step(std::integral_constant<int, 7>{}, other, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, 0, 0);
+    slot = other;
   };
   stage(0, std::false_type{});
   int kt = 1;
@@ -204,12 +192,12 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_ring_kernel(const float* __re
 
 template <int RB, int CB, int MODE>
 static br_status f32_ring_launch(const float* A, int lda, const float* W, int ldw, int M, int N, int K, const EpiArgs& ea, hipStream_t st) {
-  constexpr int BM = 16 * RB, BN = 64 * CB, NST = 2;
+  constexpr int BM = 16 * RB, BN = 64 * CB;
   Epilogue<MODE, float> epi{ea};
   const int tiles_m = cdiv(M, BM), tiles_n = cdiv(N, BN);
   const int want = std::max(1, (int)std::lround(std::sqrt(tiles_m * tiles_n / 8.0 * BM / BN)));
   const int group_n = std::min(tiles_n, cdiv(tiles_n, cdiv(tiles_n, std::min(want, 8))));
-  hipLaunchKernelGGL((gemm_f32_ring_kernel<RB, CB, NST, MODE>), dim3(tiles_m * tiles_n), dim3(NW * 64), NST * (BM + BN) * 128, st, A, lda, W, ldw,
+  hipLaunchKernelGGL((gemm_f32_ring_kernel<RB, CB, MODE>), dim3(tiles_m * tiles_n), dim3(NW * 64), NST * (BM + BN) * 128, st, A, lda, W, ldw,
                      M, N, K, tiles_m, tiles_n, group_n, epi);
   BR_LAUNCH_CHECK();
   return BR_OK;

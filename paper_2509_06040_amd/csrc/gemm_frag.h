@@ -19,20 +19,17 @@ __device__ inline const char* scalar_ptr(const char* p) {
   return reinterpret_cast<const char*>(((unsigned long long)hi << 32) | lo);
 }
 
-// 32x32 instructions: lanes 0..31 hold the first half of an instruction's k, lanes 32..63 the second.  The fragments of chunk
+// 32x32 instructions (bf16, one a chunk pair): lanes 0..31 hold the first half of an instruction's k, lanes 32..63 the second.  The fragments of chunk
 // pair p (chunks 2p and 2p + 1) are at offset(row, lane / 32) ^ (p << 5).
-template <typename T>
-struct GemmFrag;
-template <>
-struct GemmFrag<__bf16> {
+struct GemmFrag32 {
   typedef __bf16 type __attribute__((ext_vector_type(8)));
-  static constexpr int STEPS = 1;  // matrix instructions per chunk pair
   static __device__ inline int offset(int row, int lh) { return row * 128 + ((lh ^ ((row >> 1) & 7)) << 4); }
   static __device__ inline type load(const char* p, int off) { return *reinterpret_cast<const type*>(p + off); }
-  static __device__ inline f32x16 mma(const type& w, const type& a, const f32x16& c, int) {
+  static __device__ inline f32x16 mma(const type& w, const type& a, const f32x16& c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a, c, 0, 0, 0);
   }
 };
+
 // 16x16 instructions: fragment i of a stage for lane group g = lane / 16, at offset(row, g) ^ (i * FLIP), is chunk 4 i + g (bf16,
 // 32 k an instruction) or word g of chunk i (fp32, 4 k).
 template <typename T>

@@ -1,4 +1,4 @@
-// GEMM with one output tile per workgroup on the gfx950 matrix cores (T: bf16):
+// GEMM with one output tile per workgroup on the gfx950 matrix cores (bf16 operands):
 // C[m, n] = sum_k A[m, k] W[n, k], fp32 accumulate, fused epilogue.
 #pragma once
 #include <type_traits>
@@ -27,13 +27,13 @@ namespace br {
 template <int BYTES, int S>
 __shared__ __attribute__((aligned(1024))) char g_stage[BYTES];
 
-template <typename T, int BM, int BN, int WGM, int WGN, int NST, int MODE, typename TOUT, bool STREAM>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_kernel(const T* __restrict__ A, int lda,
-                                                                  const T* __restrict__ W, int ldw, int M, int N,
+template <int BM, int BN, int WGM, int WGN, int NST, int MODE, typename TOUT, bool STREAM>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_kernel(const bf16* __restrict__ A, int lda,
+                                                                  const bf16* __restrict__ W, int ldw, int M, int N,
                                                                   int K, int tiles_m, int tiles_n, int group_n,
                                                                   Epilogue<MODE, TOUT> epi) {
-  constexpr int CE = 16 / (int)sizeof(T), KD = 8 * CE;  // elements of a 16-byte chunk; k-depth of a stage
-  typedef typename GemmFrag<T>::type frag;
+  constexpr int KD = 64;  // k-depth of a stage
+  typedef GemmFrag32::type frag;
   constexpr int NW = WGM * WGN;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -69,18 +69,18 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_kernel(const T* __res
 #pragma unroll
   for (int j = 0; j < IA; ++j) {
     const int row = (wv * IA + j) * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
-    off_a[j] = (unsigned)min(row, M - 1 - m0) * (unsigned)lda * (unsigned)sizeof(T) + c * 16;
+    off_a[j] = (unsigned)min(row, M - 1 - m0) * (unsigned)lda * 2u + c * 16;
   }
 #pragma unroll
   for (int j = 0; j < IW; ++j) {
     const int row = (wv * IW + j) * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
-    off_w[j] = (unsigned)min(row, N - 1 - n0) * (unsigned)ldw * (unsigned)sizeof(T) + c * 16;
+    off_w[j] = (unsigned)min(row, N - 1 - n0) * (unsigned)ldw * 2u + c * 16;
   }
   const char* a_tile = reinterpret_cast<const char*>(A + (size_t)m0 * lda);
   const char* w_tile = reinterpret_cast<const char*>(W + (size_t)n0 * ldw);
   // byte offsets of this lane's first operand fragments inside a stage for chunk pair 0; pair p is the same ^ (p << 5), the
   // fragments of the other 32-row blocks are 4 KB apart
-  const int fa_off = GemmFrag<T>::offset(wm0 + l32, lh), fw_off = SA + GemmFrag<T>::offset(wn0 + l32, lh);
+  const int fa_off = GemmFrag32::offset(wm0 + l32, lh), fw_off = SA + GemmFrag32::offset(wn0 + l32, lh);
 
   f32x16 acc[TN][TM];
 #pragma unroll
@@ -127,17 +127,15 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_kernel(const T* __res
   frag fa[2][TM], fw[2][TN];
   auto read_pair = [&](const char* stage, int p, int set) {
 #pragma unroll
-    for (int j = 0; j < TM; ++j) fa[set][j] = GemmFrag<T>::load(stage + j * 4096, fa_off ^ (p << 5));
+    for (int j = 0; j < TM; ++j) fa[set][j] = GemmFrag32::load(stage + j * 4096, fa_off ^ (p << 5));
 #pragma unroll
-    for (int i = 0; i < TN; ++i) fw[set][i] = GemmFrag<T>::load(stage + i * 4096, fw_off ^ (p << 5));
+    for (int i = 0; i < TN; ++i) fw[set][i] = GemmFrag32::load(stage + i * 4096, fw_off ^ (p << 5));
   };
   auto mma_pair = [&](int set) {
 #pragma unroll
-    for (int e = 0; e < GemmFrag<T>::STEPS; ++e)
+    for (int i = 0; i < TN; ++i)
 #pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j) acc[i][j] = GemmFrag<T>::mma(fw[set][i], fa[set][j], acc[i][j], e);
+      for (int j = 0; j < TM; ++j) acc[i][j] = GemmFrag32::mma(fw[set][i], fa[set][j], acc[i][j]);
   };
   auto step = [&](auto S, int kt) {
     constexpr int CUR = decltype(S)::value, NXT = (CUR + 1) % NST;
