@@ -350,12 +350,12 @@ def test_velocity_chunked_batches_agree(lib):
     assert e.value.code == -4
 
 
-# every form of the fp32 GEMM (128x128, 64x128 and 32x32 tiles) at tile
-# edges, with K of less than one stage, one to 32 whole stages of 32 (the tile kernels' ring has two slots; where K is not
+# every form of the fp32 GEMM (32x32 tiles, the ring kernel in 64 and 128 columns; its choice, which the last shape gives to the ring) at tile
+# edges, with K of less than one stage, one to 32 whole stages of 32 (the ring has two slots; where K is not
 # a multiple of 32 the 32x32 tiles take over) and a stage that ends inside a 16-byte chunk pair
-@pytest.mark.parametrize("variant", [-1, 0, 3, 5])
+@pytest.mark.parametrize("variant", [-1, 0, 6 | (3 << 24), 6 | (8 << 24) | 16])
 @pytest.mark.parametrize("M,N,K", [(1, 4, 4), (31, 36, 12), (33, 132, 16), (64, 128, 20), (65, 124, 32), (129, 260, 144),
-                                   (257, 128, 1040), (1000, 516, 96), (129, 132, 64), (65, 260, 128), (257, 124, 160), (130, 388, 1024)])
+                                   (257, 128, 1040), (1000, 516, 96), (129, 132, 64), (65, 260, 128), (257, 124, 160), (130, 388, 1024), (1005, 1028, 96)])
 def test_gemm_fp32_every_form(lib, variant, M, N, K):
     rng = np.random.default_rng(M * 7 + K)
     A, W, b = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (N, K), (N,)))
@@ -470,7 +470,9 @@ def test_gemm_bits_do_not_depend_on_the_kernel(lib, dt, M, N, K):
         br.op_gemm(dt, mode, A, W, b, out, variant=variant)
         return out
     ref = run(A, 0)
-    variants = [-1, 1, 2, 3, 4, 5, 6] + ([7] if K % 128 == 0 else []) if dt == br.BF16 else [-1, 3, 5]
+    variants = [-1, 1, 2, 3, 4, 5, 6] + ([7] if K % 128 == 0 else [])
+    if dt == br.F32:  # (3 and 5, kernels of earlier versions, are the library's choice; so is the ring where it does not apply)
+        variants = [-1, 3, 5] + [6 | (h << 24) | cols for h in (2, 5, 9, 12) for cols in (0, 16)]
     for v in variants:
         assert torch.equal(run(A, v), ref), v
     # the automatic choice for a few rows alone, and for the same rows at the end of a large problem
@@ -754,20 +756,23 @@ def test_gemm_variant_word(lib):
         assert e.value.code == -1
 
 
-@pytest.mark.parametrize("M,N,K,form", [(4404, 1024, 1024, 3), (1101, 3072, 1024, 5), (1101, 1024, 1024, 0)])
-def test_gemm_fp32_automatic_choice_of_every_form(lib, M, N, K, form):
-    """Shapes that the size rule gives to 64x128, 128x128 and 32x32 tiles: as the form by itself, and right against fp64."""
+@pytest.mark.parametrize("M,N,K,mode", [(4404, 1024, 1024, 1), (1101, 3072, 1024, 0), (1101, 1024, 4096, 2), (6144, 768, 192, 1), (599, 768, 768, 1)])
+def test_gemm_fp32_automatic_choice_of_every_form(lib, M, N, K, mode):
+    """Shapes that the size rule gives to the ring kernel (the last one: to 32x32 tiles), against the other kernel (32x32 tiles, or a ring tile) bit for bit,
+    and right against fp64."""
     rng = np.random.default_rng(N + M)
-    A, W, b = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (N, K), (N,)))
+    A, W, b, x0 = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (N, K), (N,), (M, N)))
+    mods, cond = rng.standard_normal((1, N)).astype(np.float32), np.zeros(1, np.int32)
     outs = []
-    for variant in (-1, form):
-        out = torch.empty((M, N), device=DEV)
-        br.op_gemm(br.F32, 1, dev(A), dev(W), dev(b), out, variant=variant)
+    for variant in (-1, 0, 6 | (5 << 24) | 16):
+        out = dev(x0.copy())
+        br.op_gemm(br.F32, mode, dev(A), dev(W), dev(b), out, mods=dev(mods) if mode == 2 else None, cond=dev(cond) if mode == 2 else None, L=M, variant=variant)
         outs.append(out)
-    assert torch.equal(outs[0], outs[1])
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
     rows = np.r_[0:3, 63:66, 127:130, M - 130:M - 126, M - 3:M]
+    ref = A[rows].astype(np.float64) @ W.astype(np.float64).T + b
     # fp32 sums of K products: about sqrt(K) 2^-24 of the norm
-    assert rel_l2(host(outs[0])[rows], dit.gelu_tanh(A[rows].astype(np.float64) @ W.astype(np.float64).T + b)) < 3e-6
+    assert rel_l2(host(outs[0])[rows], dit.gelu_tanh(ref) if mode == 1 else x0[rows] + mods * ref if mode == 2 else ref) < 3e-6
 
 
 @pytest.mark.parametrize("height", [4, 5, 6, 7, 8])
@@ -845,10 +850,11 @@ def test_gemm_fp32_ring_tiles(lib, height, M, N, K, L):
         assert torch.equal(outs[0][M], x0[M])
 
 
-# Head dim 64 has two kernels, chosen by the number of workgroups: one tile of keys, two, three (each buffer refilled), an odd and an even number
-# more; last tiles of 1, 32, 33 and 64 keys; a reference that moves mid-sequence in some queries; waves without queries.  The same bits.
+# Head dim 64 has two kernels, chosen by the number of workgroups.  One to seven tiles of keys (four fill the buffers of keys and of values, from the
+# fifth on they are refilled; the last tile ends in either parity of the two score registers), last tiles of 1, 32, 33 and 64 keys; a
+# reference that moves mid-sequence in some queries; waves without queries.  The same bits.
 @pytest.mark.parametrize("prescaled", [0, 1])
-@pytest.mark.parametrize("L", [1, 33, 64, 65, 128, 161, 192, 257, 300, 417])
+@pytest.mark.parametrize("L", [1, 32, 33, 64, 65, 96, 128, 161, 192, 224, 256, 257, 300, 352, 384, 417])
 def test_attention_bf16_head_dim_64_does_not_depend_on_the_kernel(lib, L, prescaled):
     nh, n = 2, 9 * 256 // (2 * ((L + 127) // 128)) + 1     # nine workgroups a compute unit
     g = torch.Generator(device=DEV)
