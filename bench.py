@@ -50,17 +50,17 @@ ORDER = ("image", "video", "image_large")
 # same counter reads for a plain 1 GiB device copy; see profiles/hot_kernels_hbm_traffic.md.  Keyed
 # by (workload, kernel label); valid only for the kernel sources hashed beside the figures.
 TRAFFIC = {
-    'image_large|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=6993893413, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
-    'image_large|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=9137527402, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
-    'image_large|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=7248702204, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
-    'image_large|attn_bf16[d128]': dict(bytes_per_launch=2256482241, sources=('attn_bf16.hip',), sha1='f77bc27b4be26aaf5169e448ca679d11280a054f'),
-    'image_large|ln_modulate': dict(bytes_per_launch=1213816191, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='91f95ed4bce4d30b69d268204cb0d20bd10f3681'),
-    'image|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=663992245, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
-    'image|gemm_bf16[bias_gate_residual,32..192x128 ring]': dict(bytes_per_launch=102377259, sources=('gemm_bf16_ring.hip', 'gemm_frag.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='ec11ba58a4bbcec5759f2a0df21ddcecc50e0a8c'),
-    'image|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=674216228, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
-    'image|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=508174457, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='95147c199932a6dc5d45b44c250280be5122ede5'),
-    'image|attn_bf16[d64]': dict(bytes_per_launch=259208457, sources=('attn_bf16.hip',), sha1='f77bc27b4be26aaf5169e448ca679d11280a054f'),
-    'image|ln_modulate': dict(bytes_per_launch=193824571, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='91f95ed4bce4d30b69d268204cb0d20bd10f3681'),
+    'image_large|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=7050439300, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='daa64ac31a70e39715021109f31621881366c9bd'),
+    'image_large|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=9111797361, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='daa64ac31a70e39715021109f31621881366c9bd'),
+    'image_large|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=7227106720, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='daa64ac31a70e39715021109f31621881366c9bd'),
+    'image_large|attn_bf16[d128]': dict(bytes_per_launch=2257252781, sources=('attn_bf16.hip', 'static_for.h', 'dispatch.h'), sha1='aa8d4a299dce6c98b2ba51fef1921f8eec2f5fd8'),
+    'image_large|ln_modulate': dict(bytes_per_launch=1213805184, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='998091bd5364fdca1920d9d73be429ce9a55ff4e'),
+    'image|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=661646036, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='daa64ac31a70e39715021109f31621881366c9bd'),
+    'image|gemm_bf16[bias_gate_residual,32..192x128 ring]': dict(bytes_per_launch=102374017, sources=('gemm_bf16_ring.hip', 'gemm_frag.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='d35ff4421ba1ed85897eedd28d23aad6d75b5326'),
+    'image|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=682170794, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='daa64ac31a70e39715021109f31621881366c9bd'),
+    'image|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=509274418, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='daa64ac31a70e39715021109f31621881366c9bd'),
+    'image|attn_bf16[d64]': dict(bytes_per_launch=259195965, sources=('attn_bf16.hip', 'static_for.h', 'dispatch.h'), sha1='aa8d4a299dce6c98b2ba51fef1921f8eec2f5fd8'),
+    'image|ln_modulate': dict(bytes_per_launch=193835641, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='998091bd5364fdca1920d9d73be429ce9a55ff4e'),
 }
 
 
