@@ -43,6 +43,11 @@ inline bool attention_pipelined(int head_dim, int tokens, long long workgroups, 
   return rounds <= 1 || (rounds == 2 && tokens > 384) || (rounds == 4 && tokens >= 1024);
 }
 
+// Whether a network's matrices (of the blocks and the modulation) stay in the memory-side cache (256 MB) from one evaluation to the next: then there is
+// nothing to read ahead.  One sample, hidden 512 to 2048, 333 and 1101 tokens, read ahead against not: 58 to 236 MB 1.003 to 1.025; 264 to 278 MB 0.948
+// to 1.011 (once 1.064), mean 0.987; 319 to 350 MB 0.909 to 0.995, mean 0.945.
+inline bool weights_stay(double bytes) { return bytes <= 256e6; }
+
 // Whether an attention that leaves compute units idle has them read the next products' weights: `room` bytes of a list of `bytes`.  Below a
 // thirteenth what is read ahead does not pay for the memory that the attention shares meanwhile.  Velocity calls of one and two samples, with
 // against without: hidden 2560 to 3072, 333 to 1101 tokens, 3 to 7 % of the list 1.001 to 1.008; hidden 2048, 200 tokens, 8 and 13 % 0.978 and 0.982;

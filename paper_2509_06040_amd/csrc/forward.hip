@@ -3,6 +3,7 @@
 #include <new>
 
 #include "common.h"
+#include "dispatch.h"
 #include "dit.h"
 #include "kernels.h"
 #include "prof.h"
@@ -90,8 +91,7 @@ br_status forward(const br_model* m, const FwdBuffers& fb, const SampleMap& sm, 
     const br_status e = launch_ln_modulate(dt, fb.x, fb.xn, rows, rows_per_sample, L, H, fb.mods, m->A, shift, shift + H, fb.modmap, st);
     return e != BR_OK ? e : launch_gemm(dt, mode, fb.xn, H, W, H, rows, N, H, ea, st);
   };
-  // Networks whose matrices (of the blocks and the modulation) do not stay in the memory-side cache from one evaluation to the next.
-  const bool cold_weights = dt == BR_BF16 && ((4.0 + 2.0 * m->R) * m->NB * H * H + (double)m->A * H) * es > 192e6;
+  const bool cold_weights = dt == BR_BF16 && !rule::weights_stay(((4.0 + 2.0 * m->R) * m->NB * H * H + (double)m->A * H) * es);
   // the bf16 block stack launches only instrumented kernels, back to back
   ProfChain chain(dt == BR_BF16);
   for (int k = 0; k < m->NB; ++k) {

@@ -13,6 +13,7 @@ extern "C" {
 int tile_output_streams(unsigned long long bytes) { return rule::tile_output_streams(bytes); }
 int persistent_output_stays(unsigned long long bytes, int K, int gelu) { return rule::persistent_output_stays(bytes, K, gelu); }
 int attention_pipelined(int dh, int tokens, long long workgroups, int units) { return rule::attention_pipelined(dh, tokens, workgroups, units); }
+int weights_stay(double bytes) { return rule::weights_stay(bytes); }
 int read_ahead(unsigned long long room, unsigned long long bytes) { return rule::read_ahead(room, bytes); }
 int f32_small(int M, int N, int units) { return rule::f32_small(M, N, units); }
 void f32_ring_tile(int M, int N, int K, int rps, int units, int* rb, int* cb) { rule::f32_ring_tile(M, N, K, rps, units, rb, cb); }
@@ -72,6 +73,13 @@ def test_weights_are_read_ahead_where_a_good_part_of_them_fits(rule):
         assert ahead(*case), case
     for case in ((3072, 128, 333, 1), (3072, 128, 80, 1), (3072, 128, 1101, 1), (2880, 64, 200, 1), (2560, 64, 333, 1), (2560, 128, 613, 2), (1024, 64, 1101, 2)):
         assert not ahead(*case), case
+
+
+def test_weights_that_stay_in_the_cache_are_not_read_ahead(rule):
+    """12 matrices of H^2 a block, 6 of modulation and 2 at the end: networks that lost 2 % by it, and ones that gain 3 to 9 %."""
+    stay = lambda H, blocks: bool(rule.weights_stay(C.c_double((18.0 * blocks + 2) * H * H * 2)))
+    assert stay(768, 9) and stay(768, 11) and stay(1024, 5) and stay(1024, 6) and stay(512, 24)
+    assert not stay(768, 13) and not stay(1024, 7) and not stay(1024, 12) and not stay(512, 37) and not stay(1536, 3) and not stay(3072, 24)
 
 
 def test_fp32_products_small_tiles_or_which_ring_tile(rule):
