@@ -107,7 +107,7 @@ __device__ __forceinline__ void wide_epilogue_pair(const f32x4_e (&acc)[8][RB], 
 
 // bf16 outputs of a wave tile wholly inside the matrix: bias and activation in the accumulator layout, rounded before
 // the trip through LDS, 32 rows of 256 bytes per pass (16-byte chunk c of row r in slot c ^ (r & 15)).
-// KEEP: plain stores, which leave the rows in the caches for the launch that reads them; else past the caches (see the kernel).
+// KEEP: plain stores, which leave the rows in the caches for the launch that reads them; else past the caches (persistent_output_stays).
 template <int RB, int MODE, bool KEEP>
 __device__ __forceinline__ void wide_epilogue_bf16(const f32x4_e (&acc)[8][RB], char* ebuf, int m_base, int n_base,
                                                    const Epilogue<MODE, bf16>& epi, int lane) {
