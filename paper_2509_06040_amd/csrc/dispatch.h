@@ -32,15 +32,26 @@ inline bool persistent_output_stays(size_t bytes, int K, bool gelu) {
   return bytes >= (size_t)32 << 20 && bytes <= to;
 }
 
-// bf16 attention of head dim 64: the loop pipelined by a key tile, two workgroups a compute unit (64 KB of LDS), or the plain one, three.  The first is
-// faster tile by tile (one workgroup a unit: 3000 tokens 0.85, 1101 0.90, 512 0.94, 32 0.97 of the other's time), the second starts more at once.
-// So the line follows the rounds both need: up to one workgroup a unit any length, up to two from 385 tokens (1101 to 6000 tokens 0.85 to 0.96,
-// 512 0.98 to 1.00; 256 1.00 to 1.03, 32 1.03 to 1.06), and where the plain loop needs a second round for a fourth (1101 to 9000 tokens 0.96 to 1.00;
-// 512 1.01 to 1.03).  Three a unit: 1.02 to 1.08 from 1101 tokens, up to 1.37 at 32; beyond four 1.00 to 1.10, 1.30 at 32.
+// bf16 attention of head dim 64 had two loops: one pipelined by a key tile with two workgroups a compute unit, where its rounds were no more than those of the
+// plain one with three.  The woven loop that replaces both is level with or faster than either on both sides of this line, and no launch asks for it any more.
 inline bool attention_pipelined(int head_dim, int tokens, long long workgroups, int units) {
   if (head_dim != 64) return false;
   const long long rounds = (workgroups + units - 1) / units;
   return rounds <= 1 || (rounds == 2 && tokens > 384) || (rounds == 4 && tokens >= 1024);
+}
+
+// Parts, with 16 queries a wave instead of 32, that a bf16 attention cuts the last `left` tiles into, behind `whole` tiles in full rounds of the units (of
+// one compute die where its pairs are grouped so).  A part takes about 0.6 of its tile's time at twice the workgroups.
+// Head dim 128 (256 queries and one workgroup a unit), by the share of the units that the last round takes, us whole / in two / in four parts: 9 % (12 heads
+// of 33 272 tokens) 5520 / 5230 / 5025; 16 % (8 of 1101) 28.6 / 19.5 / 15.0; 25 % behind a round (64 of 1101) 60.1 / 51.2 / 47.2; 38 % behind three (48 of
+// 4608) 427 / 404 / 424; 42 % (54 of 458) 17.5 / 12.1 / 17.0; 50 % behind thirteen (192 of 4608) 1593 / 1587 / 1607; 69 % behind one (24 of 4608) 212 / 246 / 248.
+// Head dim 64 (128 queries, three a unit, which share it: parts only help where units would stay empty or have one workgroup more than others), whole
+// / in two: workgroups a unit 0.56 (16 heads of 1101) 14.4 / 12.9, 1.13 19.4 / 18.0; 0.74 9.0 / 9.1, 0.96 24.7 / 27.1, 1.5 13.5 / 16.5, 2.25 28.2 / 29.8,
+// behind two rounds 950 / 975.
+inline int attention_parts(int head_dim, bool brief, long long left, long long whole, int units) {
+  if (brief) return left * 2 <= units ? 2 : 1;  // (up to 128 or 192 tokens: level within the launch's own time)
+  if (head_dim == 128) return left * 4 <= units ? 4 : left * 2 <= units ? 2 : 1;
+  return whole == 0 && (left * 5 <= units * 3LL || (left > units && left * 8 <= units * 9LL)) ? 2 : 1;
 }
 
 // Whether a network's matrices (of the blocks and the modulation) stay in the memory-side cache (256 MB) from one evaluation to the next: then there is

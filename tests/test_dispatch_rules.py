@@ -12,6 +12,7 @@ using namespace br;
 extern "C" {
 int tile_output_streams(unsigned long long bytes) { return rule::tile_output_streams(bytes); }
 int persistent_output_stays(unsigned long long bytes, int K, int gelu) { return rule::persistent_output_stays(bytes, K, gelu); }
+int attention_parts(int dh, int brief, long long left, long long whole, int units) { return rule::attention_parts(dh, brief, left, whole, units); }
 int attention_pipelined(int dh, int tokens, long long workgroups, int units) { return rule::attention_pipelined(dh, tokens, workgroups, units); }
 int weights_stay(double bytes) { return rule::weights_stay(bytes); }
 int read_ahead(unsigned long long room, unsigned long long bytes) { return rule::read_ahead(room, bytes); }
@@ -61,6 +62,17 @@ def test_attention_is_pipelined_where_its_two_workgroups_a_unit_suffice(rule):
     assert not pipe(64, 1023, 3 * CU + 1) and pipe(64, 1024, 3 * CU + 1) and pipe(64, 6000, 4 * CU)
     # what the plain loop is 13 to 30 % faster on: many short samples, and 608 workgroups of 210 tokens
     assert not pipe(64, 28, 1528) and not pipe(64, 69, 576) and not pipe(64, 86, 1032) and not pipe(64, 210, 608)
+
+
+def test_attention_cuts_the_tiles_of_a_last_round_that_leaves_units_idle(rule):
+    """Never into more workgroups than units at head dim 128 (but for those that are whole); all units or those of one compute die."""
+    parts = lambda dh, left, whole, units=CU, brief=0: rule.attention_parts(dh, brief, C.c_longlong(left), C.c_longlong(whole), units)
+    for units in (CU, CU // 8):
+        for left in range(units + 1):
+            p = parts(128, left, 7 * units, units)
+            assert p in (1, 2, 4) and (p == 1 or left * p <= units) and (p > 1) == (2 * left <= units) and p == parts(128, left, 0, units)
+            assert parts(64, left, 3 * units, units) == 1 and parts(64, left, 0, units) == (2 if 5 * left <= 3 * units else 1)
+    assert parts(64, CU + 32, 0) == 2 and parts(64, CU + 33, 0) == 1 and parts(64, 380, 0) == 1
 
 
 def test_weights_are_read_ahead_where_a_good_part_of_them_fits(rule):

@@ -872,6 +872,34 @@ def test_attention_bf16_head_dim_64_does_not_depend_on_the_kernel(lib, L, presca
     assert rel_l2(host(few.float()), ref.numpy()) < 8e-3   # probabilities and outputs rounded to bf16, 2^-9 each
 
 
+# Tiles whole, in two and in four parts, and the kernel of short sequences, which is left at 193 tokens (128) and 129 (64): tiles of keys up to the fifth,
+# where the four or three buffers have been refilled; last tiles of 1, 31, 32, 33 and 64 keys; parts without queries; a reference that moves mid-sequence.
+@pytest.mark.parametrize("prescaled", [0, 1])
+@pytest.mark.parametrize("dh,L", [(128, L) for L in (1, 31, 64, 65, 128, 129, 191, 192, 193, 224, 225, 255, 256, 257, 320, 321, 449, 577)] + [(64, 129), (64, 160), (64, 193)])
+def test_attention_bf16_does_not_depend_on_the_parts(lib, dh, L, prescaled):
+    nh, rows = 2, 128 if dh == 64 or L <= 192 else 256
+    tiles = nh * ((L + rows - 1) // rows)                   # of a sample
+    # a part of a round (in four parts at head dim 128), a third (in two), and full rounds behind which few are left
+    counts = [3, -(-90 // tiles), -(-(3 * 256 + 8) // tiles)]
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    qkv = torch.randn((3, L, 3 * nh * dh), generator=g, device=DEV)
+    qkv[1, L // 2:, nh * dh:2 * nh * dh] *= 12.0            # later keys score far above the first tiles'
+    qkv = qkv.bfloat16()
+    outs = []
+    for n in counts:
+        out = torch.full((n + 1, L, nh * dh), 3.0, device=DEV).bfloat16()
+        br.op_attention(br.BF16, qkv[torch.arange(n, device=DEV) % 3].contiguous(), out[:n], nh, prescaled)
+        assert bool((out[n] == 3.0).all())
+        outs.append(out[:n])
+    for n, out in zip(counts, outs):
+        assert torch.equal(out, outs[0][torch.arange(n, device=DEV) % 3]), n
+    q, k, v = (t.float().reshape(3, L, nh, dh).transpose(1, 2).double().cpu() for t in qkv.split(nh * dh, dim=2))
+    s = (q @ k.transpose(2, 3).contiguous()) * (0.6931471805599453 if prescaled else dh ** -0.5)
+    ref = (torch.softmax(s, dim=3) @ v).transpose(1, 2).reshape(3, L, nh * dh)
+    assert rel_l2(host(outs[0].float()), ref.numpy()) < 8e-3   # probabilities and outputs rounded to bf16, 2^-9 each
+
+
 # Outputs of 32 to 112 MB, with GELU 100, are stored plainly by the persistent kernel at this K, smaller and larger ones past the caches: below, at and
 # above the lines, full and ragged tiles, against the 128x128 kernel, bit for bit (which stores plainly up to 160 MB).
 @pytest.mark.parametrize("M,N", [(8191, 2048), (8192, 2048), (8200, 2060), (24414, 2048), (24415, 2048), (27343, 2048), (27344, 2048), (40960, 2048), (40961, 2048)])
