@@ -589,6 +589,33 @@ def test_velocity_of_narrow_networks_with_fused_rows(lib, hidden, heads, lat, pt
         assert torch.equal(v, first[torch.arange(len(v), device=DEV) % 5])
 
 
+# The fused rows have a form for each hidden size (MLP ratio 4, patch vectors of up to 256 bytes and 128 elements) and one for anything else: patch vectors that are
+# not whole column blocks, or a step and a half of weights; just beyond the form's limits; another ratio; samples so short that their modulation vectors
+# need the room.
+@pytest.mark.parametrize("hidden,heads,lat,patch,cond,dtype,ratio", [
+    (64, 4, (3, 1, 6, 10), (1, 2, 2), 5, synth.F32, 4), (64, 4, (5, 1, 6, 10), (1, 2, 2), 5, synth.F32, 4), (32, 2, (16, 1, 6, 10), (1, 2, 2), 5, synth.F32, 4),
+    (96, 3, (12, 1, 6, 10), (1, 2, 2), 5, synth.F32, 4), (64, 4, (17, 1, 6, 10), (1, 2, 2), 5, synth.F32, 4), (128, 2, (16, 1, 6, 10), (1, 2, 2), 5, synth.F32, 2),
+    (64, 1, (32, 1, 6, 10), (1, 2, 2), 5, synth.BF16, 4), (128, 1, (16, 1, 6, 10), (1, 2, 2), 5, synth.BF16, 3), (64, 1, (48, 1, 6, 10), (1, 2, 2), 5, synth.BF16, 4),
+    (128, 2, (16, 1, 2, 2), (1, 2, 2), 1, synth.BF16, 4), (64, 4, (4, 1, 2, 4), (1, 2, 2), 1, synth.F32, 4), (256, 4, (16, 1, 6, 10), (1, 2, 2), 1, synth.BF16, 4)])
+def test_velocity_of_fused_rows_in_either_form(lib, hidden, heads, lat, patch, cond, dtype, ratio):
+    cfg = synth.model_cfg(2, hidden, heads, lat, patch, cond, dtype, ratio)
+    W = synth.make_weights(cfg, 3, 0.05)
+    model = make_model(cfg, W)
+    D = synth.model_sizes(cfg)["D"]
+    n = 4200 // synth.model_sizes(cfg)["L"] + 3             # rows in two tiles a workgroup
+    z, tok = synth.random_latents(5, D, 4), synth.cond_tokens(cfg, 2, 5)
+    zd, c = dev(z)[torch.arange(n, device=DEV) % 5], cond_dev(cfg, tok)
+    outs = []
+    for B in (5, n):
+        v = torch.full((B + 1, D), 7.0, device=DEV)
+        br.velocity(model, zd[:B].contiguous(), 0.4, c, np.arange(B) % 5 % 2, v[:B], bytes_buffer(br.workspace_bytes(None, model, B)))
+        assert bool((v[B] == 7.0).all())
+        outs.append(v[:B])
+    for b in range(5):
+        assert_velocity(cfg, host(outs[0])[b], dit.forward(cfg, W, z[b:b + 1], 0.4, tok, np.array([b % 2], np.int32))[0], 2e-2 if dtype == synth.BF16 else 1e-4)
+    assert torch.equal(outs[1], outs[0][torch.arange(n, device=DEV) % 5])
+
+
 @pytest.mark.parametrize("n_cond", [1, 8, 11])
 def test_velocity_conditions_passed_with_the_launch_or_transferred(lib, n_cond):
     """Up to 64 samples carry their conditions in the launch, more in a buffer; up to eight conditions share a pass over the
