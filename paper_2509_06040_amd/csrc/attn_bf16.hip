@@ -487,40 +487,41 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
 template <int DH>
 struct AttnForm {
   static constexpr int NW = DH == 128 ? 8 : 4, NB = DH == 128 ? 4 : 3, WPE = DH == 128 ? 2 : 3, SHORT_NW = 4;
-  static constexpr int WARM_NB = 4;  // (launches of at most one whole tile a unit: 1038 -> 1033 us a call of one image sample)
+  static constexpr int WARM_NW = 8, WARM_NB = 4;
   static constexpr int BM = 32 * NW, SHORT_BM = 32 * SHORT_NW, TILES = 2 * KV_TILE * DH * 2;  // TILES: bytes of a buffer of either
 };
 
 extern __shared__ __attribute__((aligned(1024))) char g_tiles[];
 
-// At least NB key tiles; WARM: any number, all tiles in two parts (head dim 64 also whole).
+// At least NB key tiles; WARM: any number, tiles of 128 queries by eight waves of 16, as two waves a SIMD issue what one alone takes twice as long for: one image
+// sample (144 tiles of 16 heads of 64) 1044 us a call with
+// four waves of 32, 1038 with twice the workgroups of four waves of 16, 1026 so.
 template <int DH, bool PRE, bool WARM>
-__global__ __launch_bounds__(AttnForm<DH>::NW * 64, WARM ? 2 : AttnForm<DH>::WPE) void attn_bf16_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out,
-                                                                                             int L, int H, int NH, int n_pairs, int plan,
-                                                                                             float scale_log2, Warm<WARM> warm) {
+__global__ __launch_bounds__((WARM ? AttnForm<DH>::WARM_NW : AttnForm<DH>::NW) * 64, WARM ? 2 : AttnForm<DH>::WPE) void attn_bf16_kernel(
+    const bf16* __restrict__ qkv, bf16* __restrict__ out, int L, int H, int NH, int n_pairs, int plan, float scale_log2, Warm<WARM> warm) {
   using F = AttnForm<DH>;
+  constexpr int NW = WARM ? F::WARM_NW : F::NW, NB = WARM ? F::WARM_NB : F::NB, BM = WARM ? 16 * NW : F::BM;
   unsigned block = blockIdx.x;
   if constexpr (WARM) {
     if (block < (unsigned)warm.blocks) {
-      warm_rows<F::NW * 64>(warm);
+      warm_rows<NW * 64>(warm);
       return;
     }
     block -= warm.blocks;  // (a multiple of 8)
   }
   int pair, q_first, parts;
-  if (!attn_tile(block, (L + F::BM - 1) / F::BM, n_pairs, plan, F::BM, &pair, &q_first, &parts) || q_first >= L) return;
+  if (!attn_tile(block, (L + BM - 1) / BM, n_pairs, plan, BM, &pair, &q_first, &parts) || q_first >= L) return;
   auto run = [&](auto QBc, auto SHORTc, int waves) __attribute__((always_inline)) {
-    attn_queries<DH, F::NW, WARM ? F::WARM_NB : F::NB, decltype(QBc)::value, decltype(SHORTc)::value, PRE>(g_tiles, qkv, out, L, H, NH, pair, q_first, waves, scale_log2);
+    attn_queries<DH, NW, NB, decltype(QBc)::value, decltype(SHORTc)::value, PRE>(g_tiles, qkv, out, L, H, NH, pair, q_first, waves, scale_log2);
   };
   using Q1 = std::integral_constant<int, 1>;
   using Q2 = std::integral_constant<int, 2>;
   if constexpr (WARM) {
-    if (L <= (F::WARM_NB - 1) * KV_TILE) run(Q1{}, std::true_type{}, F::NW);
-    else if (DH == 64 && parts == 1) run(Q2{}, std::false_type{}, F::NW);
-    else run(Q1{}, std::false_type{}, F::NW);
+    if (L <= (NB - 1) * KV_TILE) run(Q1{}, std::true_type{}, NW);
+    else run(Q1{}, std::false_type{}, NW);
   } else {
-    if (parts == 1) run(Q2{}, std::false_type{}, F::NW);
-    else run(Q1{}, std::false_type{}, 2 * F::NW / parts);
+    if (parts == 1) run(Q2{}, std::false_type{}, NW);
+    else run(Q1{}, std::false_type{}, 2 * NW / parts);
   }
 }
 
@@ -561,9 +562,8 @@ static br_status attn_launch(const bf16* qkv, bf16* out, int B, int L, int NH, b
       n = std::min(n, budget);
       budget -= n;
     }
-    const int split = DH == 128 || L <= (F::WARM_NB - 1) * KV_TILE ? 2 : rule::attention_parts(DH, false, tiles(F::BM), 0, n_cu / dies);
-    hipLaunchKernelGGL((attn_bf16_kernel<DH, true, true>), dim3((unsigned)(tiles(F::BM) * split * dies + warm.blocks)), dim3(F::NW * 64), lds(F::WARM_NB), st, qkv, out,
-                       L, H, NH, (int)n_pairs, grouped | split << 1, scale_log2, warm);
+    hipLaunchKernelGGL((attn_bf16_kernel<DH, true, true>), dim3((unsigned)(n_blocks + warm.blocks)), dim3(F::WARM_NW * 64), lds(F::WARM_NB), st, qkv, out, L, H,
+                       NH, (int)n_pairs, grouped | 1 << 1, scale_log2, warm);
     BR_LAUNCH_CHECK();
     return BR_OK;
   }
