@@ -302,40 +302,41 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
-    frag w[SPS][NF], o[SPS][RT][NF];
+    frag w[2][SPS][NF], o[2][SPS][RT][NF];
     f32x4 acc[RT];
-    auto landed = [&](auto Sc, auto Yc) __attribute__((always_inline)) {  // waits for a step; Y: stores that are certainly younger than it
+    auto landed = [&](auto Sc) __attribute__((always_inline)) {  // waits for a step
       constexpr int at = decltype(Sc)::value, young = at + PD - 1 < S - 1 ? PD - 1 : S - 1 - at;
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS * young + decltype(Yc)::value) : "memory");
-    };
-    auto read_w = [&](auto Sc) __attribute__((always_inline)) {
-      constexpr int slot = decltype(Sc)::value % PD * STEP_B;
-#pragma unroll
-      for (int u = 0; u < SPS; ++u)
-#pragma unroll
-        for (int i = 0; i < NF; ++i) w[u][i] = *reinterpret_cast<const frag*>(my_ring + (fo ^ (i * FLIP)) + (slot + u * 2048));
-    };
-    auto read_o = [&](const char* op, auto Kc) __attribute__((always_inline)) {
-#pragma unroll
-      for (int u = 0; u < SPS; ++u)
-#pragma unroll
-        for (int r = 0; r < RT; ++r)
-#pragma unroll
-          for (int i = 0; i < NF; ++i)
-            o[u][r][i] = *reinterpret_cast<const frag*>(op + (fo ^ (i * FLIP)) + (decltype(Kc)::value * SPS * BMR * 128 + (u * RT + r) * 2048));
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS * young) : "memory");
     };
     const int n0 = wv * 16 + lq * 4;  // this lane's columns of the wave's first block
-    // A phase: NBp blocks of KSp steps from step FIRST on, operand rows at `op`, N columns; epi(i) takes the sums of block i.  The next step's fragments
-    // are read behind a step's products, and a step's slot is refilled as soon as its own are in registers.
-    auto run = [&](auto FIRSTc, auto NBc, auto KSc, const char* op, int n_cols, auto Yc, auto&& epi) __attribute__((always_inline)) {
-      constexpr int FIRST = decltype(FIRSTc)::value, NBp = decltype(NBc)::value, KSp = decltype(KSc)::value;
+    // A phase: NBp blocks of KSp steps from step FIRST on, operand rows at `op`, N columns; epi(i) takes the sums of block i.  A step's slot is refilled
+    // as soon as its fragments are in registers; the next step's are read behind its products, in fp32 between them (BETWEEN): those are sixteen that
+    // wait for one another (hidden 128, 762 rows: 300 -> 285 us a call; bf16, with four: 281 -> 286).
+    auto run = [&](auto FIRSTc, auto NBc, auto KSc, const char* op, int n_cols, auto&& epi) __attribute__((always_inline)) {
+      constexpr int FIRST = decltype(FIRSTc)::value, NBp = decltype(NBc)::value, KSp = decltype(KSc)::value, NMMA = SPS * NF;
+      constexpr bool BETWEEN = ES == 4;
+      // fragment f of step j of the phase (rows of one step are read once, to set 0)
+      auto read_w = [&](auto Jc, int u, int i) __attribute__((always_inline)) {
+        constexpr int j = decltype(Jc)::value, slot = (FIRST + j) % PD * STEP_B;
+        w[j & 1][u][i] = *reinterpret_cast<const frag*>(my_ring + (fo ^ (i * FLIP)) + (slot + u * 2048));
+      };
+      auto read_o = [&](auto Jc, int u, int i) __attribute__((always_inline)) {
+        constexpr int j = decltype(Jc)::value, k = j % KSp;
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+          o[KSp == 1 ? 0 : j & 1][u][r][i] = *reinterpret_cast<const frag*>(op + (fo ^ (i * FLIP)) + (k * SPS * BMR * 128 + (u * RT + r) * 2048));
+      };
       if (wv * 16 < n_cols) {
-        landed(FIRSTc, Yc);
-        read_w(FIRSTc);
-        read_o(op, std::integral_constant<int, 0>{});
+        landed(FIRSTc);
+        static_for<NMMA>([&](auto Fc) __attribute__((always_inline)) {
+          constexpr int f = decltype(Fc)::value;
+          read_w(std::integral_constant<int, 0>{}, f / NF, f % NF);
+          read_o(std::integral_constant<int, 0>{}, f / NF, f % NF);
+        });
       }
       static_for<NBp * KSp>([&](auto Jc) __attribute__((always_inline)) {
         constexpr int j = decltype(Jc)::value, i = j / KSp, k = j % KSp, at = FIRST + j;
+        constexpr bool more = j + 1 < NBp * KSp;
         const bool here = (wv + NW * i) * 16 < n_cols;  // (uniform; false in the last round alone)
         if (here) {
           if constexpr (k == 0) {
@@ -345,19 +346,31 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
           __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
           asm volatile("" ::: "memory");
           __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int u = 0; u < SPS; ++u)
-#pragma unroll
-            for (int f = 0; f < NF; ++f)
-#pragma unroll
-              for (int r = 0; r < RT; ++r) acc[r] = GemmFrag16<T>::mma(w[u][f], o[u][r][f], acc[r]);
         }
         fetch(std::integral_constant<int, at + PD>{});
-        if constexpr (j + 1 < NBp * KSp) {
-          if ((wv + NW * ((j + 1) / KSp)) * 16 < n_cols) {
-            landed(std::integral_constant<int, at + 1>{}, std::integral_constant<int, 0>{});
-            read_w(std::integral_constant<int, at + 1>{});
-            if constexpr (KSp > 1) read_o(op, std::integral_constant<int, (j + 1) % KSp>{});
+        if (here) {
+          if constexpr (more && BETWEEN) landed(std::integral_constant<int, at + 1>{});
+          static_for<NMMA>([&](auto Fc) __attribute__((always_inline)) {
+            constexpr int f = decltype(Fc)::value, u = f / NF, n = f % NF;
+            static_for<RT>([&](auto Rc) __attribute__((always_inline)) {
+              constexpr int r = decltype(Rc)::value;
+              acc[r] = GemmFrag16<T>::mma(w[j & 1][u][n], o[KSp == 1 ? 0 : j & 1][u][r][n], acc[r]);
+            });
+            if constexpr (more && BETWEEN) {  // (of a block that the wave does not have: something from the ring, for nobody)
+              read_w(std::integral_constant<int, j + 1>{}, u, n);
+              if constexpr (KSp > 1) read_o(std::integral_constant<int, j + 1>{}, u, n);
+            }
+            if constexpr (BETWEEN) __builtin_amdgcn_sched_barrier(0);
+          });
+          if constexpr (more && !BETWEEN) {
+            if ((wv + NW * ((j + 1) / KSp)) * 16 < n_cols) {
+              landed(std::integral_constant<int, at + 1>{});
+              static_for<NMMA>([&](auto Fc) __attribute__((always_inline)) {
+                constexpr int f = decltype(Fc)::value;
+                read_w(std::integral_constant<int, j + 1>{}, f / NF, f % NF);
+                if constexpr (KSp > 1) read_o(std::integral_constant<int, j + 1>{}, f / NF, f % NF);
+              });
+            }
           }
         }
         if constexpr (k == KSp - 1) {
@@ -398,14 +411,13 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
         }
       }
     };
-    using Y0 = std::integral_constant<int, 0>;
-    run(std::integral_constant<int, 0>{}, std::integral_constant<int, NB0>{}, std::integral_constant<int, KS0>{}, HEAD ? hid : act, HC, Y0{},
+    run(std::integral_constant<int, 0>{}, std::integral_constant<int, NB0>{}, std::integral_constant<int, KS0>{}, HEAD ? hid : act, HC,
         [&](auto Ic) __attribute__((always_inline)) { residual(Ic, 0, 0); });
     __syncthreads();
     layer_norm(HEAD ? 0 : HC, HEAD);
     __syncthreads();
     if constexpr (!HEAD) {
-      run(std::integral_constant<int, S1>{}, std::integral_constant<int, NB1>{}, std::integral_constant<int, KS>{}, act, 4 * HC, Y0{},
+      run(std::integral_constant<int, S1>{}, std::integral_constant<int, NB1>{}, std::integral_constant<int, KS>{}, act, 4 * HC,
           [&](auto Ic) __attribute__((always_inline)) {
             constexpr int i = decltype(Ic)::value;
             const float4 bb = bias_of(HC + i * 128);
@@ -415,13 +427,13 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
                         gelu_tanh_f(acc[r][2] + bb.z), gelu_tanh_f(acc[r][3] + bb.w));
           });
       __syncthreads();
-      run(std::integral_constant<int, S2>{}, std::integral_constant<int, NB2>{}, std::integral_constant<int, KS2>{}, hid, HC, Y0{},
+      run(std::integral_constant<int, S2>{}, std::integral_constant<int, NB2>{}, std::integral_constant<int, KS2>{}, hid, HC,
           [&](auto Ic) __attribute__((always_inline)) { residual(Ic, 5 * HC, 3 * HC); });
       __syncthreads();
       layer_norm(4 * HC, !LAST);
       __syncthreads();
     }
-    run(std::integral_constant<int, S3>{}, std::integral_constant<int, NB3>{}, std::integral_constant<int, KS>{}, act, ntail, Y0{},
+    run(std::integral_constant<int, S3>{}, std::integral_constant<int, NB3>{}, std::integral_constant<int, KS>{}, act, ntail,
         [&](auto Ic) __attribute__((always_inline)) {
           constexpr int n = decltype(Ic)::value * 128;
           const float4 bb = bias_of((HEAD ? HC : 6 * HC) + n);
