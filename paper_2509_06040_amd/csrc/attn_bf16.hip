@@ -294,15 +294,22 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
   // maximum nearly every tile of a sequence rescales, and maximum, scale-and-subtract and rescale were half of the kernel's vector
   // instructions.  Each query moves for itself: its result does not depend on which queries share its wave.  (A query that is not
   // finite, or that some key scores +inf, has a NaN among its own sums and no other query's.)
+  // A query's first reference (m_first) is its maximum over the first half tile with a key that scores above -inf.  Where that is not the very first one, for
+  // some query of the wave, the halves behind are looked through once, with keys straight from memory, before the loop (which then meets
+  // nothing but zeros until that half).  Without any such key there is no result: zero by zero.
+  auto top = [&](auto Pc, int qb) __attribute__((always_inline)) {
+    constexpr int P = decltype(Pc)::value;
+    const f32x4 v = __builtin_elementwise_maximum(s[P][0][qb], s[P][1][qb]);
+    float mx = __builtin_elementwise_maximum(__builtin_elementwise_maximum(v[0], v[1]), __builtin_elementwise_maximum(v[2], v[3]));
+    mx = __builtin_elementwise_maximum(mx, __shfl_xor(mx, 16, 64));
+    return __builtin_elementwise_maximum(mx, __shfl_xor(mx, 32, 64));
+  };
+  float m_first[QB];
   auto settle = [&](auto Pc, bool first, bool next) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
     static_for<QB>([&](auto Qc) __attribute__((always_inline)) {
       constexpr int qb = decltype(Qc)::value;
-      const f32x4 v0 = s[P][0][qb], v1 = s[P][1][qb];
-      const f32x4 v = __builtin_elementwise_maximum(v0, v1);
-      float mx = __builtin_elementwise_maximum(__builtin_elementwise_maximum(v[0], v[1]), __builtin_elementwise_maximum(v[2], v[3]));
-      mx = __builtin_elementwise_maximum(mx, __shfl_xor(mx, 16, 64));
-      mx = __builtin_elementwise_maximum(mx, __shfl_xor(mx, 32, 64));
+      const float mx = first ? m_first[qb] : top(Pc, qb);
       const float m_new = first || !(lt[qb][0] <= REF_LIMIT) ? (float)(bf16)(m_run[qb] + (first ? mx : fmaxf(mx, 0.f))) : m_run[qb];
       const float delta = m_new - m_run[qb];
       if (!first) {
@@ -408,6 +415,36 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
 
   scores(P0{}, 0);
   if (L < 32) mask(0, P0{});
+  auto unset = [&]() __attribute__((always_inline)) {
+    bool none = false;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) none = none || m_first[qb] == -INFINITY;
+    return __builtin_amdgcn_ballot_w64(none) != 0;
+  };
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) m_first[qb] = top(P0{}, qb);
+  if (__builtin_expect(unset(), 0)) {
+#pragma unroll 1
+    for (int j = 1; j * 32 < L; ++j) {
+      static_for<DB>([&](auto Ic) __attribute__((always_inline)) {
+        constexpr int ks = decltype(Ic)::value >> 1, kb = decltype(Ic)::value & 1;
+        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(base + (size_t)min(j * 32 + kb * 16 + l16, L - 1) * ld + H + ks * 32 + lq * 8);
+        static_for<QB>([&](auto Qc) __attribute__((always_inline)) {
+          constexpr int qb = decltype(Qc)::value;
+          s[1][kb][qb] = mma(kf, qf[qb][ks], ks == 0 ? zero : s[1][kb][qb]);
+        });
+      });
+      mask(j, P1{});
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        const float mx = top(P1{}, qb);
+        m_first[qb] = m_first[qb] == -INFINITY ? mx : m_first[qb];
+      }
+      if (!unset()) break;
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) m_first[qb] = m_first[qb] == -INFINITY ? 0.f : m_first[qb];
+  }
   settle(P0{}, true, false);
   int bl = 0;  // buffer of the last tile
   if (nkv > 1) {

@@ -724,6 +724,45 @@ def test_attention_bf16_queries_without_a_result(lib, dh, L, prescaled):
     check(a, np.flatnonzero(a[0, :, 5] > 0))
 
 
+# A query's reference comes from the first half tile of keys in which one scores above -inf: the first, one of the next, the last; in the kernel of short
+# sequences, the one with a loop, whole tiles and parts.  The other keys score about -210, which a reference of zero would lose, in some heads and samples.
+@pytest.mark.parametrize("prescaled", [0, 1])
+@pytest.mark.parametrize("dh,L,leading", [(dh, L, n) for dh in (64, 128) for L, n in ((20, 7), (34, 32), (34, 33), (65, 64), (100, 31), (100, 32), (100, 33), (100, 63),
+                                                                                      (190, 65), (300, 32), (300, 64), (300, 65), (333, 320), (470, 200))])
+def test_attention_bf16_leading_keys_that_score_minus_infinity(lib, dh, L, leading, prescaled):
+    rng = np.random.default_rng(dh + L + leading)
+    H, c = 2 * dh, np.log2(np.e) / np.sqrt(dh)
+    qkv = rng.standard_normal((3, L, 3 * H)).astype(np.float32)
+    qkv[..., 5:H:dh] = np.abs(qkv[..., 5:H:dh]) + 0.1        # by element 5 of every key of `leading`, whatever the query
+    qkv[1, ..., 5:dh:dh] *= np.where(np.arange(L) % 3 == 0, -1, 1)[:, None]   # (sample 1, head 0: +inf for every third query)
+    qkv[..., 6:H:dh], qkv[1:, :, H + 6:2 * H:dh] = 4.0, -52.5 * np.sqrt(dh)
+    if prescaled:
+        qkv[..., :H] *= c
+    qkv = _bf(qkv)
+    x = qkv.astype(np.float64)
+    if prescaled:
+        x[..., :H] /= c
+    q, k, v = x.reshape(3, L, 3, 2, dh).transpose(2, 0, 3, 1, 4)
+    s = q @ k.transpose(0, 1, 3, 2) / np.sqrt(dh)
+    s[..., :leading] = -np.inf
+    p = np.exp(s - s.max(axis=3, keepdims=True))
+    ref = (p / p.sum(axis=3, keepdims=True) @ v).transpose(0, 2, 1, 3)
+    lost = np.zeros((3, L, 2), bool)
+    lost[1, ::3, 0] = True
+    a = dev(qkv, torch.bfloat16)
+    a[:, :leading, H + 5:2 * H:dh] = -np.inf
+    n = -(-(2 * 256 * 256 + 1) // (2 * L))                   # samples of at least two rounds of whole tiles
+    outs = []
+    for rows in (torch.arange(3, device=DEV), torch.arange(n, device=DEV) % 3):
+        out = torch.full((len(rows), L, H), 3.0, dtype=torch.bfloat16, device=DEV)
+        br.op_attention(br.BF16, a[rows].contiguous(), out, 2, prescaled)
+        outs.append(out)
+    got = host(outs[0].float()).reshape(3, L, 2, dh)
+    assert np.isnan(got[lost]).all() and np.isfinite(got[~lost]).all()
+    assert rel_l2(got[~lost], ref[~lost]) < 8e-3             # probabilities and outputs rounded to bf16, 2^-9 each
+    assert torch.equal(torch.nan_to_num(outs[1], nan=7.0), torch.nan_to_num(outs[0], nan=7.0)[torch.arange(n, device=DEV) % 3])
+
+
 def test_gemm_bf16_rows_far_apart(lib):
     """192 rows of 832 values, 24 MB apart: the last rows of a tile are beyond 4 GiB from its first one.  Same bits as packed rows."""
     import ctypes as C
