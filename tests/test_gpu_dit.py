@@ -1001,12 +1001,13 @@ def test_gemm_tile_outputs_past_the_caches(lib, variant, M, N):
         assert torch.equal(outs[0], outs[1]), mode
 
 
-@pytest.mark.parametrize("heads", [32, 16])
-def test_velocity_where_attention_leaves_units_to_the_weights(lib, heads):
+# Up to 192 tokens an attention that reads weights ahead has all its keys under way at once, beyond it has a loop over four buffers: 72, 139, 193, 257, 321 and 389
+# tokens; last tiles of keys of 1 and 5, which come into each of the buffers; waves of 16 queries without any; heads of 64 (grouped by die) and 128 (dealt out in order).
+@pytest.mark.parametrize("heads,lat_h,lat_w", [(32, 14, 18), (16, 20, 26)] + [(h, *hw) for h in (32, 16) for hw in ((16, 46), (16, 62), (24, 52), (38, 40))])
+def test_velocity_where_attention_leaves_units_to_the_weights(lib, heads, lat_h, lat_w):
     """Networks too large for the memory-side cache read the next weights in front of an attention that leaves compute units idle (one
-    sample, 32 workgroups), and not where it does not (eighteen, 576): the same bits, right against the oracle.  32 heads of 64: the
-    pipelined loop, tiles grouped by die; 16 of 128: the other loop, two query tiles a head, dealt out in order."""
-    cfg = synth.model_cfg(3, 2048, heads, (16, 1, 14, 18) if heads == 32 else (16, 1, 20, 26), (1, 2, 2), 9, synth.BF16)
+    sample: 16 to 128 workgroups), and not where it does not (eighteen): the same bits, right against the oracle."""
+    cfg = synth.model_cfg(3, 2048, heads, (16, 1, lat_h, lat_w), (1, 2, 2), 9, synth.BF16)
     W = synth.make_weights(cfg, 3, 0.03)
     model = make_model(cfg, W)
     D = synth.model_sizes(cfg)["D"]
