@@ -1,5 +1,5 @@
-// bf16 flash attention on the gfx950 matrix cores: softmax(Q K^T / sqrt(d)) V over all L tokens of a sample.  A workgroup takes 256
-// (head dim 128) or 128 (head dim 64) queries of a (sample, head) pair, 32 a wave, over key/value tiles of 64 keys in LDS.
+// bf16 flash attention on the gfx950 matrix cores: softmax(Q K^T / sqrt(d)) V over all L tokens of a sample.  A workgroup takes 128 or (head dim 128) 256
+// queries of a (sample, head) pair, 32 a wave, over key/value tiles of 64 keys in LDS.
 //
 // Scores are computed transposed, S^T = K Q^T, in 16x16x32 matrix instructions: a lane then holds four keys of ONE query per block
 // of 16 keys (the others sit in the lanes 16, 32 and 48 further), so the reference / sum / rescale of the online softmax are per-lane
@@ -136,7 +136,7 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
   constexpr int TILE_B = KV_TILE * ROW_B;
   constexpr int FR = QB == 1 ? 8 : 4, RA = FR - 1;  // ring of operand fragments; read ahead
   constexpr int NS = 2 * DB;                // slots of a step (2 KS score blocks, DB value blocks)
-  static_assert(2 * KS == DB && NS % FR == 0 && LPW >= 1 && 2 * LPW <= NS && NB >= 3, "");
+  static_assert(2 * KS == DB && NS % FR == 0 && LPW >= 1 && 2 * LPW <= NS && NB >= 2, "");
 
   const int b = pair / NH, h = pair - b * NH;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
@@ -230,9 +230,10 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
   __syncthreads();
   // The one barrier of a tile, in the middle of tile t: the keys of t + 2 and the values of t + 1 have landed, every wave is done with the keys of t
   // and the values of t - 1, whose buffers take those of t + NB and t + NB - 1 behind it.  What the first slots of the next step read
-  // was there one barrier earlier, so that those reads need not wait for this one.
+  // was there one barrier earlier, so that those reads need not wait for this one.  (Two buffers: the keys of t + 1 and the values of t have landed, and those
+  // reads come behind it; one more barrier in front of the last tile, for its values.)
   auto turn = [&]() __attribute__((always_inline)) {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * (NB - 3) * LPW) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NB == 2 ? 0 : 2 * (NB - 3) * LPW) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
@@ -245,6 +246,7 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
         fetch_k(b0);
         b0 = b0 == (NB - 1) * TILE_B ? 0 : b0 + TILE_B;
       }
+      if constexpr (NB == 2) turn();
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     return;
@@ -382,12 +384,12 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
   };
   auto step = [&](auto Pc, int koffs, int voffs, int kn, int vn, auto LOADc, int lk, int lv) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
-    constexpr bool LOAD = decltype(LOADc)::value;
+    constexpr bool LOAD = decltype(LOADc)::value, AHEAD = SHORT || NB > 2 || P == 1;
     constexpr int EN = DH == 128 && QB == 2 ? NS - 4 : NS - 2;  // the probabilities are taken in the first EN slots
     static_for<NS>([&](auto Nc) __attribute__((always_inline)) {
       constexpr int n = decltype(Nc)::value, i = n / 2, NE = 8 * QB;
       if constexpr (n + RA < NS) fr[(n + RA) % FR] = frag_of(std::integral_constant<int, n + RA>{}, koffs, voffs);
-      else fr[(n + RA) % FR] = frag_of(std::integral_constant<int, n + RA - NS>{}, kn, vn);
+      else if constexpr (AHEAD) fr[(n + RA) % FR] = frag_of(std::integral_constant<int, n + RA - NS>{}, kn, vn);
       __builtin_amdgcn_sched_barrier(0);
       static_for<QB>([&](auto Qc) __attribute__((always_inline)) {
         constexpr int qb = decltype(Qc)::value;
@@ -457,6 +459,7 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
       constexpr int B = decltype(Bc)::value, BP = (B + NB - 1) % NB, BN = (B + 1) % NB;
       step(P0{}, B * TILE_B + HALF, BP * TILE_B + HALF, BN * TILE_B, B * TILE_B, NO{}, 0, 0);
       turn();
+      if constexpr (NB == 2) static_for<RA>([&](auto Nc) __attribute__((always_inline)) { fr[decltype(Nc)::value] = frag_of(Nc, BN * TILE_B, B * TILE_B); });
       step(P1{}, BN * TILE_B, B * TILE_B, BN * TILE_B + HALF, B * TILE_B + HALF, YES{}, B * TILE_B, BP * TILE_B);
     };
     if constexpr (!SHORT) {
@@ -476,6 +479,7 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
         });
       }
       bl = (nkv - 1) % NB;
+      if constexpr (NB == 2) turn();
     } else {  // (fewer tiles than buffers: tile t in buffer t, nothing to wait for)
       static_for<RA>([&](auto Nc) __attribute__((always_inline)) { fr[decltype(Nc)::value] = frag_of(Nc, TILE_B, 0); });
       step(P1{}, TILE_B, 0, TILE_B + HALF, HALF, NO{}, 0, 0);
@@ -519,27 +523,34 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
   }
 }
 
-// Head dim 128: eight waves, two a SIMD (228 registers), four buffers of 32 KB, one workgroup a compute unit.  Head dim 64: four waves, three workgroups
-// a unit (168 registers, 48 KB).  (Two with four or eight buffers: 5 to 40 % slower from three workgroups a unit on, no faster below.)
-template <int DH>
+// Forms of the loop.  WIDE: head dim 128, eight waves, two a SIMD (228 registers), four buffers of 32 KB, one workgroup a compute unit; head dim 64, four
+// waves, three workgroups a unit (168 registers, 48 KB; two with four or eight buffers: 5 to 40 % slower from three workgroups a unit on, no faster below).
+// PAIR: head dim 128, four waves and two buffers, two workgroups a unit: one's first fetch, last tile and stores run beside the other's loop, and tiles are
+// finer (rule::attention_pair; 64 samples of 24 heads, 192 tokens 109 -> 74 us, 257 172 -> 118, 1024 859 -> 770).  AHEAD: beside workgroups that read weights.
+constexpr int ATTN_WIDE = 0, ATTN_PAIR = 1, ATTN_AHEAD = 2;  // (an unnamed enumeration in a kernel's type has another name on the host than on the device)
+template <int DH, int KIND>
 struct AttnForm {
-  static constexpr int NW = DH == 128 ? 8 : 4, NB = DH == 128 ? 4 : 3, WPE = DH == 128 ? 2 : 3, SHORT_NW = 4;
-  static constexpr int WARM_NW = 8, WARM_NB = 4;
-  static constexpr int BM = 32 * NW, SHORT_BM = 32 * SHORT_NW, TILES = 2 * KV_TILE * DH * 2;  // TILES: bytes of a buffer of either
+  static constexpr int NW = KIND == ATTN_AHEAD || (KIND == ATTN_WIDE && DH == 128) ? 8 : 4, NB = KIND == ATTN_PAIR ? 2 : KIND == ATTN_AHEAD || DH == 128 ? 4 : 3;
+  static constexpr int WPE = KIND == ATTN_AHEAD || DH == 128 ? 2 : 3, QB = KIND == ATTN_AHEAD ? 1 : 2, BM = 16 * QB * NW;
 };
+constexpr int SHORT_NW = 4, SHORT_BM = 32 * SHORT_NW;
+template <int DH>
+constexpr int SHORT_TILES = DH == 128 ? 3 : 2;  // key tiles that the kernel of short sequences takes
+template <int DH>
+constexpr int TILES_B = 2 * KV_TILE * DH * 2;   // bytes of a buffer of keys and one of values
 
 extern __shared__ __attribute__((aligned(1024))) char g_tiles[];
 
-// At least NB key tiles; WARM: any number, tiles of 128 queries by eight waves of 16, as two waves a SIMD issue what one alone takes twice as long for: one image
+// At least NB key tiles; AHEAD: any number, tiles of 128 queries by eight waves of 16, as two waves a SIMD issue what one alone takes twice as long for: one image
 // sample (144 tiles of 16 heads of 64) 1044 us a call with
 // four waves of 32, 1038 with twice the workgroups of four waves of 16, 1026 so.
-template <int DH, bool PRE, bool WARM>
-__global__ __launch_bounds__((WARM ? AttnForm<DH>::WARM_NW : AttnForm<DH>::NW) * 64, WARM ? 2 : AttnForm<DH>::WPE) void attn_bf16_kernel(
-    const bf16* __restrict__ qkv, bf16* __restrict__ out, int L, int H, int NH, int n_pairs, int plan, float scale_log2, Warm<WARM> warm) {
-  using F = AttnForm<DH>;
-  constexpr int NW = WARM ? F::WARM_NW : F::NW, NB = WARM ? F::WARM_NB : F::NB, BM = WARM ? 16 * NW : F::BM;
+template <int DH, bool PRE, int KIND>
+__global__ __launch_bounds__((AttnForm<DH, KIND>::NW) * 64, (AttnForm<DH, KIND>::WPE)) void attn_bf16_kernel(
+    const bf16* __restrict__ qkv, bf16* __restrict__ out, int L, int H, int NH, int n_pairs, int plan, float scale_log2, Warm<KIND == ATTN_AHEAD> warm) {
+  using F = AttnForm<DH, KIND>;
+  constexpr int NW = F::NW, NB = F::NB, BM = F::BM;
   unsigned block = blockIdx.x;
-  if constexpr (WARM) {
+  if constexpr (KIND == ATTN_AHEAD) {
     if (block < (unsigned)warm.blocks) {
       warm_rows<NW * 64>(warm);
       return;
@@ -553,11 +564,11 @@ __global__ __launch_bounds__((WARM ? AttnForm<DH>::WARM_NW : AttnForm<DH>::NW) *
   };
   using Q1 = std::integral_constant<int, 1>;
   using Q2 = std::integral_constant<int, 2>;
-  if constexpr (WARM) {
+  if constexpr (KIND == ATTN_AHEAD) {
     if (L <= (NB - 1) * KV_TILE) run(Q1{}, std::true_type{}, NW);
     else run(Q1{}, std::false_type{}, NW);
   } else {
-    if (parts == 1) run(Q2{}, std::false_type{}, NW);
+    if (KIND == ATTN_PAIR || parts == 1) run(Q2{}, std::false_type{}, NW);
     else run(Q1{}, std::false_type{}, 2 * NW / parts);
   }
 }
@@ -565,24 +576,20 @@ __global__ __launch_bounds__((WARM ? AttnForm<DH>::WARM_NW : AttnForm<DH>::NW) *
 // Fewer key tiles than NB: without the loop's code and with LDS for these tiles alone, so that more workgroups share a unit.  (Queries scaled ahead:
 // scale_log2 = 1.)
 template <int DH>
-__global__ __launch_bounds__(AttnForm<DH>::SHORT_NW * 64, AttnForm<DH>::WPE) void attn_bf16_short_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out,
-                                                                                                         int L, int H, int NH, int n_pairs, int plan,
-                                                                                                         float scale_log2) {
-  using F = AttnForm<DH>;
+__global__ __launch_bounds__(SHORT_NW * 64, DH == 128 ? 2 : 3) void attn_bf16_short_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out, int L, int H,
+                                                                                             int NH, int n_pairs, int plan, float scale_log2) {
+  constexpr int NB = SHORT_TILES<DH> + 1;
   int pair, q_first, parts;
-  if (!attn_tile(blockIdx.x, (L + F::SHORT_BM - 1) / F::SHORT_BM, n_pairs, plan, F::SHORT_BM, &pair, &q_first, &parts) || q_first >= L) return;
-  if (parts == 1) attn_queries<DH, F::SHORT_NW, F::NB, 2, true, false>(g_tiles, qkv, out, L, H, NH, pair, q_first, F::SHORT_NW, scale_log2);
-  else attn_queries<DH, F::SHORT_NW, F::NB, 1, true, false>(g_tiles, qkv, out, L, H, NH, pair, q_first, F::SHORT_NW, scale_log2);
+  if (!attn_tile(blockIdx.x, (L + SHORT_BM - 1) / SHORT_BM, n_pairs, plan, SHORT_BM, &pair, &q_first, &parts) || q_first >= L) return;
+  if (parts == 1) attn_queries<DH, SHORT_NW, NB, 2, true, false>(g_tiles, qkv, out, L, H, NH, pair, q_first, SHORT_NW, scale_log2);
+  else attn_queries<DH, SHORT_NW, NB, 1, true, false>(g_tiles, qkv, out, L, H, NH, pair, q_first, SHORT_NW, scale_log2);
 }
 
 template <int DH>
 static br_status attn_launch(const bf16* qkv, bf16* out, int B, int L, int NH, bool prescaled, const WarmRows& next, hipStream_t st) {
-  using F = AttnForm<DH>;
   const long long n_pairs = (long long)B * NH;
-  const int grouped = n_pairs >= 32 ? 1 : 0, n_cu = device_cu_count(), H = NH * DH;
-  const bool brief = L <= (F::NB - 1) * KV_TILE;
+  const int grouped = n_pairs >= 32 ? 1 : 0, n_cu = device_cu_count(), H = NH * DH, nkv = cdiv(L, KV_TILE);
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)DH));
-  auto lds = [&](int buffers) { return std::min(cdiv(L, KV_TILE), buffers) * F::TILES; };
   // tiles of BM queries: of a die if grouped, else of all
   auto tiles = [&](int rows) { return (grouped ? (n_pairs + 7) / 8 : n_pairs) * cdiv(L, rows); };
   const int dies = grouped ? 8 : 1;
@@ -591,30 +598,42 @@ static br_status attn_launch(const bf16* qkv, bf16* out, int B, int L, int NH, b
   WarmRows warm = next;
   const long long n_blocks = tiles(128) * dies;
   warm.blocks = next.n16[0] > 0 && prescaled ? (n_cu - (int)std::min<long long>(n_blocks, n_cu)) / 8 * 8 : 0;
-  unsigned budget = (unsigned)(WARM_BYTES_PER_TILE / 16 * (cdiv(L, KV_TILE) + 4) / 256 * warm.blocks);
+  unsigned budget = (unsigned)(WARM_BYTES_PER_TILE / 16 * (nkv + 4) / 256 * warm.blocks);
   size_t bytes = 0;
   for (const unsigned n : next.n16) bytes += (size_t)n * 16;
   if (warm.blocks >= 32 && rule::read_ahead((size_t)budget * 16, bytes)) {
+    using F = AttnForm<DH, ATTN_AHEAD>;
     for (unsigned& n : warm.n16) {
       n = std::min(n, budget);
       budget -= n;
     }
-    hipLaunchKernelGGL((attn_bf16_kernel<DH, true, true>), dim3((unsigned)(n_blocks + warm.blocks)), dim3(F::WARM_NW * 64), lds(F::WARM_NB), st, qkv, out, L, H,
-                       NH, (int)n_pairs, grouped | 1 << 1, scale_log2, warm);
+    hipLaunchKernelGGL((attn_bf16_kernel<DH, true, ATTN_AHEAD>), dim3((unsigned)(n_blocks + warm.blocks)), dim3(F::NW * 64), std::min(nkv, F::NB) * TILES_B<DH>, st,
+                       qkv, out, L, H, NH, (int)n_pairs, grouped | 1 << 1, scale_log2, warm);
     BR_LAUNCH_CHECK();
     return BR_OK;
   }
-  const long long n = tiles(brief ? F::SHORT_BM : F::BM), slots = (long long)n_cu / dies * (DH == 64 ? 3 : 1);
+  const bool pair = DH == 128 && rule::attention_pair(L, tiles(128), tiles(256), n_cu / dies), brief = !pair && nkv <= SHORT_TILES<DH>;
+  const long long n = tiles(pair || brief ? 128 : AttnForm<DH, ATTN_WIDE>::BM), slots = (long long)n_cu / dies * (DH == 64 ? 3 : 1);
   const long long whole = brief ? 0 : n / slots * slots;
-  const int split = n < (1 << 26) ? rule::attention_parts(DH, brief, n - whole, whole, n_cu / dies) : 1;
+  const int split = !pair && n < (1 << 26) ? rule::attention_parts(DH, brief, n - whole, whole, n_cu / dies) : 1;
   const int plan = grouped | split << 1 | (split > 1 ? (int)whole << 4 : 0);
   const dim3 g((unsigned)((split > 1 ? whole + (n - whole) * split : n) * dies));
-  if (brief)
-    hipLaunchKernelGGL((attn_bf16_short_kernel<DH>), g, dim3(F::SHORT_NW * 64), lds(F::NB), st, qkv, out, L, H, NH, (int)n_pairs, plan, prescaled ? 1.f : scale_log2);
-  else if (prescaled)
-    hipLaunchKernelGGL((attn_bf16_kernel<DH, true, false>), g, dim3(F::NW * 64), lds(F::NB), st, qkv, out, L, H, NH, (int)n_pairs, plan, scale_log2, NoWarm{});
-  else
-    hipLaunchKernelGGL((attn_bf16_kernel<DH, false, false>), g, dim3(F::NW * 64), lds(F::NB), st, qkv, out, L, H, NH, (int)n_pairs, plan, scale_log2, NoWarm{});
+  auto loop = [&](auto KINDc) {
+    constexpr int KIND = decltype(KINDc)::value;
+    using F = AttnForm<DH, KIND>;
+    const dim3 b(F::NW * 64);
+    if (prescaled)
+      hipLaunchKernelGGL((attn_bf16_kernel<DH, true, KIND>), g, b, F::NB * TILES_B<DH>, st, qkv, out, L, H, NH, (int)n_pairs, plan, scale_log2, NoWarm{});
+    else hipLaunchKernelGGL((attn_bf16_kernel<DH, false, KIND>), g, b, F::NB * TILES_B<DH>, st, qkv, out, L, H, NH, (int)n_pairs, plan, scale_log2, NoWarm{});
+  };
+  if (pair) {
+    if constexpr (DH == 128) loop(std::integral_constant<int, ATTN_PAIR>{});
+  } else if (brief) {
+    hipLaunchKernelGGL((attn_bf16_short_kernel<DH>), g, dim3(SHORT_NW * 64), nkv * TILES_B<DH>, st, qkv, out, L, H, NH, (int)n_pairs, plan,
+                       prescaled ? 1.f : scale_log2);
+  } else {
+    loop(std::integral_constant<int, ATTN_WIDE>{});
+  }
   BR_LAUNCH_CHECK();
   return BR_OK;
 }

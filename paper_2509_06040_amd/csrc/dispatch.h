@@ -54,6 +54,20 @@ inline int attention_parts(int head_dim, bool brief, long long left, long long w
   return whole == 0 && (left * 5 <= units * 3LL || (left > units && left * 8 <= units * 9LL)) ? 2 : 1;
 }
 
+// bf16 attention of head dim 128: whether tiles of 128 queries, two workgroups a unit, take the place of 256 in one workgroup (up to 192 tokens: of 128 in the
+// kernel that fetches all keys at once, one workgroup a unit from 129 on).  `tiles128` and `tiles256`, of all units or of one compute die and its.  27 sequences
+// of 65 to 8192 tokens, 6 to 1536 pairs, us with 256 / 128, by the number of tiles of 128 a unit:
+//   up to a half: 256, in parts (1101 tokens, 6 pairs 15.0 / 18.6).  Up to one: 128, in one round (513 tokens, 48 pairs 18.8 / 12.9; 4608, 6 pairs 67 / 61).
+//   More, but one round of 256: 256 (2048 tokens, 24 pairs 51.0 / 53.7; 193, 192 pairs 12.9 / 13.9; not 129 to 192, 144 pairs 14.9 / 11.7).
+//   Beyond: 128, whose workgroups hide one another's ends, up to 4096 tokens (192 tokens, 1536 pairs 109 / 74; 320, 768 pairs 92.8 / 57.8; 1101, 768 515 / 458; 3000,
+//   384 1441 / 1392; but 1400, 48 pairs 54.7 / 57.5); longer loops have the bytes into LDS of 256 (4608, 24 pairs 208 / 224, 144 1191 / 1189; 8192, 48 1165 / 1204).
+// Up to 128 tokens the short kernel has two workgroups a unit itself (128 tokens, 288 pairs 10.8 / 12.3).
+inline bool attention_pair(int tokens, long long tiles128, long long tiles256, int units) {
+  if (tokens <= 128 || tiles128 * 2 <= units) return false;
+  if (tiles128 <= units || tokens <= 192) return true;
+  return tiles256 > units && tokens <= 4096;
+}
+
 // Whether a network's matrices (of the blocks and the modulation) stay in the memory-side cache (256 MB) from one evaluation to the next: then there is
 // nothing to read ahead.  One sample, hidden 512 to 2048, 333 and 1101 tokens, read ahead against not: 58 to 236 MB 1.003 to 1.025; 264 to 278 MB 0.948
 // to 1.011 (once 1.064), mean 0.987; 319 to 350 MB 0.909 to 0.995, mean 0.945.

@@ -13,6 +13,7 @@ extern "C" {
 int tile_output_streams(unsigned long long bytes) { return rule::tile_output_streams(bytes); }
 int persistent_output_stays(unsigned long long bytes, int K, int gelu) { return rule::persistent_output_stays(bytes, K, gelu); }
 int attention_parts(int dh, int brief, long long left, long long whole, int units) { return rule::attention_parts(dh, brief, left, whole, units); }
+int attention_pair(int tokens, long long tiles128, long long tiles256, int units) { return rule::attention_pair(tokens, tiles128, tiles256, units); }
 int attention_pipelined(int dh, int tokens, long long workgroups, int units) { return rule::attention_pipelined(dh, tokens, workgroups, units); }
 int weights_stay(double bytes) { return rule::weights_stay(bytes); }
 int read_ahead(unsigned long long room, unsigned long long bytes) { return rule::read_ahead(room, bytes); }
@@ -73,6 +74,20 @@ def test_attention_cuts_the_tiles_of_a_last_round_that_leaves_units_idle(rule):
             assert p in (1, 2, 4) and (p == 1 or left * p <= units) and (p > 1) == (2 * left <= units) and p == parts(128, left, 0, units)
             assert parts(64, left, 3 * units, units) == 1 and parts(64, left, 0, units) == (2 if 5 * left <= 3 * units else 1)
     assert parts(64, CU + 32, 0) == 2 and parts(64, CU + 33, 0) == 1 and parts(64, 380, 0) == 1
+
+
+def test_attention_in_two_workgroups_a_unit(rule):
+    """Sizes that one workgroup of 256 queries a unit cost 7 to 60 %, and ones that two of 128 cost 3 to 30 %; pairs are dealt out by die from 32 on."""
+    def pair(L, pairs):
+        dies = 8 if pairs >= 32 else 1
+        tiles = lambda rows: C.c_longlong((-(-pairs // 8) if dies == 8 else pairs) * -(-L // rows))
+        return bool(rule.attention_pair(L, tiles(128), tiles(256), CU // dies))
+    for L, pairs in ((129, 144), (192, 96), (192, 1536), (193, 288), (257, 144), (257, 768), (320, 48), (513, 48), (640, 96), (800, 144), (1024, 192), (1101, 192), (2048, 384),
+                     (3000, 96), (4608, 6)):
+        assert pair(L, pairs), (L, pairs)
+    for L, pairs in ((1, 1536), (65, 288), (128, 384), (128, 1536), (129, 64), (192, 48), (193, 144), (193, 192), (257, 40), (385, 24), (513, 24), (800, 40), (1101, 6), (1101, 40), (2048, 24),
+                     (4608, 24), (8192, 6), (8192, 48), (33272, 12)):
+        assert not pair(L, pairs), (L, pairs)
 
 
 def test_weights_are_read_ahead_where_a_good_part_of_them_fits(rule):

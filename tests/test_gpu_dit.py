@@ -966,6 +966,34 @@ def test_attention_bf16_does_not_depend_on_the_parts(lib, dh, L, prescaled):
     assert rel_l2(host(outs[0].float()), ref.numpy()) < 8e-3   # probabilities and outputs rounded to bf16, 2^-9 each
 
 
+# Head dim 128 has tiles of 128 queries, two workgroups a compute unit with two buffers of keys and of values, beside those of 256: few samples (in parts), three quarters
+# of a workgroup a unit (128), just under a round of 256, just above one and three (128; 256 and a cut last round beyond 4096 tokens).  Two to five tiles of keys and
+# long loops, which end in either buffer; last tiles of 1, 31, 32, 33 and 64 keys; waves without queries; a reference that moves mid-sequence.  The same bits.
+@pytest.mark.parametrize("prescaled", [0, 1])
+@pytest.mark.parametrize("L", [129, 160, 161, 192, 193, 223, 224, 225, 256, 257, 320, 449, 577, 1101, 4095, 4097])
+def test_attention_bf16_head_dim_128_does_not_depend_on_the_form(lib, L, prescaled):
+    nh, dh = 2, 128
+    t128, t256 = nh * ((L + 127) // 128), nh * ((L + 255) // 256)           # tiles of a sample
+    counts = [3] + [max(3, n) for n in (192 // t128, 256 // t256, 256 // t256 + 9, 3 * 256 // t256 + 9)]
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    qkv = torch.randn((3, L, 3 * nh * dh), generator=g, device=DEV)
+    qkv[1, L // 2:, nh * dh:2 * nh * dh] *= 12.0            # later keys score far above the first tiles'
+    qkv = qkv.bfloat16()
+    first = None
+    for n in counts:
+        which = torch.arange(n, device=DEV) % 3
+        out = torch.full((n + 1, L, nh * dh), 3.0, device=DEV).bfloat16()
+        br.op_attention(br.BF16, qkv[which].contiguous(), out[:n], nh, prescaled)
+        assert bool((out[n] == 3.0).all()), n
+        first = out[:3] if first is None else first
+        assert torch.equal(out[:n], first[which]), n
+    q, k, v = (t.float().reshape(3, L, nh, dh).transpose(1, 2) for t in qkv.split(nh * dh, dim=2))
+    s = torch.matmul(q, k.transpose(2, 3).contiguous()) * (0.6931471805599453 if prescaled else dh ** -0.5)   # (fp32: 1e-6 of the sum)
+    ref = torch.matmul(torch.softmax(s, dim=3), v).transpose(1, 2).reshape(3, L, nh * dh)
+    assert rel_l2(host(first.float()), host(ref)) < 8e-3   # probabilities and outputs rounded to bf16, 2^-9 each
+
+
 # Outputs of 32 to 112 MB, with GELU 100, are stored plainly by the persistent kernel at this K, smaller and larger ones past the caches: below, at and
 # above the lines, full and ragged tiles, against the 128x128 kernel, bit for bit (which stores plainly up to 160 MB).
 @pytest.mark.parametrize("M,N", [(8191, 2048), (8192, 2048), (8200, 2060), (24414, 2048), (24415, 2048), (27343, 2048), (27344, 2048), (40960, 2048), (40961, 2048)])
