@@ -30,10 +30,10 @@ def kernel_metadata(tmp_path, part):
 
 @pytest.mark.skipif(not os.path.exists(READELF), reason="llvm-readelf is missing")
 def test_attention_that_reads_no_weights_ahead_carries_no_list_of_them(tmp_path):
-    """Head dim 64 in two loops and 128, queries scaled ahead or not: no list of ranges (five numbers, two pointers and a factor); and scaled
-    ahead with one, in the loops that launches with idle units have."""
+    """Short sequences, the loop at head dim 64 and in both forms of 128, queries scaled ahead or not: no list of ranges (five numbers, two
+    pointers and a factor); and scaled ahead with one, in the loops that launches with idle units have."""
     sizes = sorted(int(re.search(r"\.kernarg_segment_size:\s+(\d+)", e)[1]) for e in kernel_metadata(tmp_path, "attn_bf16").values())
-    assert len(sizes) == 8 and sizes[5] <= 48 and sizes[6] > 64
+    assert len(sizes) == 2 + 2 + 4 + 2 and sizes[7] <= 48 and sizes[8] > 64
 
 
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="llvm-objdump is missing")
