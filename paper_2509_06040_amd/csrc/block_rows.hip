@@ -163,7 +163,7 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
     for (int p = wv; p * 64 < mq; p += NW)
       if (p * 64 + lane < mq) fill(dst + p * 1024, src + (p * 64 + lane) * 4);
   }
-  if (KIND == ROWS_LAST && wv == 0) {  // where the samples of these rows go
+  if (HC && KIND == ROWS_LAST && wv == 0) {  // where the samples of these rows go
     const unsigned d = (unsigned)(uintptr_t)BR_LPTR(svrow);
     const int* const src = a.fin.a.vrows + min(b_first + lane, b_last);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(d), "v"(src) : "memory", "m0");
@@ -515,6 +515,16 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
       f_block();
     }
   };
+  long long vo[RT];  // last: where the sample of this lane's rows starts in v
+  int vtok[RT];
+  if constexpr (KIND == ROWS_LAST) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const int m = m0 + r * 16 + l16, b = a.by_L.div(min(m, M - 1));
+      vtok[r] = m < M ? m - b * L : a.n_img;
+      vo[r] = (long long)a.fin.a.vrows[b] * a.D;
+    }
+  }
   f_block();
 #pragma unroll 1
   for (int i = 0; i < PD; ++i) fetch();
@@ -579,8 +589,7 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
             const int m = m0 + r * 16 + l16;
             const float v0 = acc[r][0] + bb.x, v1 = acc[r][1] + bb.y, v2 = acc[r][2] + bb.z, v3 = acc[r][3] + bb.w;
             if constexpr (KIND == ROWS_LAST) {
-              const int b = a.by_L.div(min(m, M - 1)), tok = m < M ? m - b * L : a.n_img;
-              if (tok < a.n_img) a.fin.scatter_unpatch({(long long)svrow[b - b_first] * a.D, nullptr, tok}, n, v0, v1, v2, v3);
+              if (vtok[r] < a.n_img) a.fin.scatter_unpatch({vo[r], nullptr, vtok[r]}, n, v0, v1, v2, v3);
             } else {
               if (m < M) store4<T>(reinterpret_cast<T*>(a.qkv) + (size_t)m * NTAIL + n, v0 * cs, v1 * cs, v2 * cs, v3 * cs);
             }
@@ -629,7 +638,8 @@ namespace {
 struct RowsLds {
   int act, hid, mods, bias, vrow, ring, total;
 };
-// KIND's vectors of a sample: 2 H floats (head) or 6 H; samples that 16 rt rows can touch: at most (16 rt - 2) / L + 2
+// KIND's vectors of a sample: 2 H floats (head) or 6 H; samples that 16 rt rows can touch: at most (16 rt - 2) / L + 2.  ring: bytes of a wave's
+// weights in flight in a form for a hidden size, which also keeps the samples' places in v; 0: the form for any sizes
 RowsLds rows_lds(const br_model* m, int rt, bool head, int ntail, int ring) {
   const int es = m->cfg.dtype == BR_BF16 ? 2 : 4, rows = 16 * rt, samples = std::min(rows, (rows - 2) / m->L + 2);
   const size_t op = (size_t)rows * align_up((size_t)m->H * es, 128);
@@ -643,8 +653,8 @@ RowsLds rows_lds(const br_model* m, int rt, bool head, int ntail, int ring) {
   l.mods = (int)(o += hid);
   l.bias = (int)(o += mods);
   l.vrow = (int)(o += bias);
-  l.ring = (int)(o += 256);
-  l.total = (int)std::min<size_t>(o + (size_t)NW * ring, 1 << 30);
+  l.ring = (int)(o += ring ? 256 : 0);
+  l.total = (int)std::min<size_t>(o + (size_t)NW * (ring ? ring : RING_B), 1 << 30);
   return l;
 }
 }  // namespace
@@ -664,7 +674,7 @@ int rows_fused_tiles(const br_model* m, const FwdBuffers& fb, int M) {
   const int cu = device_cu_count(), rt = cdiv(M, 16) <= cu ? 1 : 2;
   if (rt == 2 && m->H * (bf ? 2 : 4) > 256 && (cdiv(M, 32) - 1) % cu + 1 < cu / 4) return 0;
   for (int head = 0; head < 2; ++head)
-    if (rows_lds(m, rt, head, std::max(3 * m->H, m->pd), RING_B).total > LDS_LIMIT) return 0;
+    if (rows_lds(m, rt, head, std::max(3 * m->H, m->pd), 0).total > LDS_LIMIT) return 0;
   return rt;
 }
 
@@ -724,7 +734,7 @@ br_status launch_block_rows(const br_model* m, const FwdBuffers& fb, const Sampl
   auto go = [&](auto Tc, auto RTc, auto SPSc, auto HCc) {
     constexpr int R_ = decltype(RTc)::value, S_ = decltype(SPSc)::value, H_ = decltype(HCc)::value;
     using T = decltype(Tc);
-    const RowsLds l = rows_lds(m, rt, head, a.NTAIL, H_ ? rows_ring(sizeof(T), H_, R_) : RING_B);
+    const RowsLds l = rows_lds(m, rt, head, a.NTAIL, H_ ? rows_ring(sizeof(T), H_, R_) : 0);
     a.o_act = l.act; a.o_hid = l.hid; a.o_mods = l.mods; a.o_bias = l.bias; a.o_vrow = l.vrow; a.o_ring = l.ring;
     const dim3 g(cdiv(a.M, 16 * R_)), b(NT);
     if (head) hipLaunchKernelGGL((block_rows_kernel<T, R_, S_, ROWS_HEAD, H_>), g, b, l.total, st, a);

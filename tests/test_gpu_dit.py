@@ -616,6 +616,27 @@ def test_velocity_of_fused_rows_in_either_form(lib, hidden, heads, lat, patch, c
     assert torch.equal(outs[1], outs[0][torch.arange(n, device=DEV) % 5])
 
 
+# Rows, modulation vectors, biases and weights in flight of 160 KB to the byte: the form for any sizes, one row tile and two.
+@pytest.mark.parametrize("hidden,heads,lat,ratio,n", [(128, 2, (16, 1, 6, 6), 16, 30), (192, 3, (16, 1, 6, 10), 3, 230)])
+def test_velocity_of_rows_that_fill_the_lds_stays_fused(lib, hidden, heads, lat, ratio, n):
+    cfg = synth.model_cfg(2, hidden, heads, lat, (1, 2, 2), 5, synth.BF16, ratio)
+    W = synth.make_weights(cfg, 3, 0.05)
+    model = make_model(cfg, W)
+    D = synth.model_sizes(cfg)["D"]
+    z, tok = synth.random_latents(3, D, 4), synth.cond_tokens(cfg, 2, 5)
+    v = torch.empty((n, D), device=DEV)
+    br.profile_enable(True)
+    br.profile_read()
+    try:
+        br.velocity(model, dev(z)[torch.arange(n, device=DEV) % 3], 0.4, cond_dev(cfg, tok), np.arange(n) % 3 % 2, v, bytes_buffer(br.workspace_bytes(None, model, n)))
+        assert {400, 401, 402} <= set(br.profile_read())     # head, block, last block
+    finally:
+        br.profile_enable(False)
+    for b in range(3):
+        assert_velocity(cfg, host(v)[b], dit.forward(cfg, W, z[b:b + 1], 0.4, tok, np.array([b % 2], np.int32))[0], 2e-2)
+    assert torch.equal(v, v[torch.arange(n, device=DEV) % 3])
+
+
 @pytest.mark.parametrize("n_cond", [1, 8, 11])
 def test_velocity_conditions_passed_with_the_launch_or_transferred(lib, n_cond):
     """Up to 64 samples carry their conditions in the launch, more in a buffer; up to eight conditions share a pass over the
