@@ -59,7 +59,7 @@ struct RowsArgs {
   int H, RH, NTAIL;                 // hidden size, MLP width, columns of the tail (3 H or the patch vector)
   float* x;                         // [M, H] residual stream
   const float* mods;                // modulation vectors: per group, consecutive from mods_off (see the kernel)
-  int A, mods_off, mods_n;          // row length; offset and number of floats taken
+  int A, mods_off;                  // row length; offset of the floats taken
   const int* modmap;                // [samples] group (body)
   const void* attn;                 // [M, H] (body)
   const void *w0, *fc1_w, *fc2_w, *tail_w;  // w0: output projection, or patch embedding (head)
@@ -118,13 +118,13 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
   // behind the last block only image rows have an output
   if (KIND == ROWS_LAST && m0 - b_first * L >= a.n_img && a.by_L.div(min(m0 + BMR, M) - 1) == b_first) return;
 
-  // modulation group of a sample (a uniform index: scalar loads, which wait for none of the others)
+  // modulation group of a sample (forms for a hidden size; a uniform index: scalar loads, which wait for none of the others)
   auto group_of = [&](int b) __attribute__((always_inline)) {
     return KIND != ROWS_HEAD ? scalar_load(a.modmap, b)
            : a.sm.group      ? scalar_load(a.sm.group, a.s0 + b)
                              : a.sm.group0 + (a.sm.cond ? scalar_load(a.sm.cond, a.s0 + b) : sample_cond(a.sm, a.s0 + b));
   };
-  const int g_first = group_of(b_first);
+  const int g_first = HC ? group_of(b_first) : 0;
   // ---- rows, modulation vectors and biases to LDS (global -> LDS directly, 1 KB per wave and instruction)
   auto fill = [&](char* dst, const void* src) __attribute__((always_inline)) {
     const unsigned d = (unsigned)(uintptr_t)BR_LPTR(dst);
@@ -146,6 +146,15 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
     }
     fill(xs + p * 1024, src + c * 4);
   }
+  const int b_last = a.by_L.div(min(m0 + BMR, M) - 1), mq = mods_n >> 2;
+  if constexpr (HC == 0) {  // (a lane looks up its own sample's: one wait for all, in front of what waits for nothing)
+    const int n_mods = (b_last - b_first + 1) * mq;
+    for (int p = wv; p * 64 < n_mods; p += NW) {
+      const int i = min(p * 64 + lane, n_mods - 1), s = a.by_mq.div(i), b = b_first + s;
+      const int g = KIND != ROWS_HEAD ? a.modmap[b] : a.sm.group ? a.sm.group[a.s0 + b] : a.sm.group0 + sample_cond(a.sm, a.s0 + b);
+      fill(reinterpret_cast<char*>(smods) + p * 1024, a.mods + (size_t)g * a.A + a.mods_off + (i - s * mq) * 4);
+    }
+  }
   // biases: first product | FC1 | FC2 | tail
   const float *const b_0 = a.b0, *const b_1 = a.fc1_b, *const b_2 = a.fc2_b, *const b_3 = a.tail_b;
   const int nb1 = H4, nb2 = KIND == ROWS_HEAD ? nb1 : nb1 + (RH >> 2), nb3 = KIND == ROWS_HEAD ? nb2 : nb2 + H4,
@@ -155,13 +164,14 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
     const float* src = i < nb1 ? b_0 + i * 4 : i < nb2 ? b_1 + (i - nb1) * 4 : i < nb3 ? b_2 + (i - nb2) * 4 : b_3 + (i - nb3) * 4;
     fill(reinterpret_cast<char*>(sbias) + p * 1024, src);
   }
-  const int b_last = a.by_L.div(min(m0 + BMR, M) - 1), mq = mods_n >> 2;
-  for (int b = b_first; b <= b_last; ++b) {
-    const int g = b == b_first ? g_first : group_of(b);
-    const float* src = a.mods + (size_t)g * a.A + a.mods_off;
-    char* const dst = reinterpret_cast<char*>(smods) + (b - b_first) * mods_n * 4;
-    for (int p = wv; p * 64 < mq; p += NW)
-      if (p * 64 + lane < mq) fill(dst + p * 1024, src + (p * 64 + lane) * 4);
+  if constexpr (HC != 0) {
+    for (int b = b_first; b <= b_last; ++b) {
+      const int g = b == b_first ? g_first : group_of(b);
+      const float* src = a.mods + (size_t)g * a.A + a.mods_off;
+      char* const dst = reinterpret_cast<char*>(smods) + (b - b_first) * mods_n * 4;
+      for (int p = wv; p * 64 < mq; p += NW)
+        if (p * 64 + lane < mq) fill(dst + p * 1024, src + (p * 64 + lane) * 4);
+    }
   }
   if (HC && KIND == ROWS_LAST && wv == 0) {  // where the samples of these rows go
     const unsigned d = (unsigned)(uintptr_t)BR_LPTR(svrow);
@@ -452,6 +462,7 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
         });
     return;
   } else {
+  gather();
   // ---- phases: 0 the first product, 1 FC1, 2 FC2, 3 the tail (head: 0 and 3).  One has N columns, 16 a block, dealt out to the
   // waves; a row of its weights is kb bytes, in steps of SPS times 128.
   constexpr int STEP_B = SPS * 2048, PD = RING_B / STEP_B;
@@ -460,22 +471,11 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
     const char* w;
     int N, kb, steps;
   };
-  const char *const w_0 = reinterpret_cast<const char*>(a.w0), *const w_1 = reinterpret_cast<const char*>(a.fc1_w),
-             *const w_2 = reinterpret_cast<const char*>(a.fc2_w), *const w_3 = reinterpret_cast<const char*>(a.tail_w);
-  auto phase = [&](int ph) __attribute__((always_inline)) {
-    // (copies: choosing among captured variables themselves, the compiler chooses among their addresses and keeps all of them in memory)
-    const char *c0 = w_0, *c1 = w_1, *c2 = w_2, *c3 = w_3;
-    const int h = H, rh = RH, nt = NTAIL, pd = a.pd;
+  auto phase = [&](int ph) {  // (from the kernel's arguments: copies in scalar registers cost 11 to 36 spilled ones, bf16 hidden 64, 28 200 rows 280 -> 296 us)
     Phase p;
-    p.w = c2;
-    p.w = ph == 0 ? c0 : p.w;
-    p.w = ph == 1 ? c1 : p.w;
-    p.w = ph == 3 ? c3 : p.w;
-    p.N = ph == 1 ? rh : h;
-    p.N = ph == 3 ? nt : p.N;
-    p.kb = ph == 2 ? rh : h;
-    if (KIND == ROWS_HEAD) p.kb = ph == 0 ? pd : p.kb;
-    p.kb *= ES;
+    p.w = reinterpret_cast<const char*>(ph == 0 ? a.w0 : ph == 1 ? a.fc1_w : ph == 2 ? a.fc2_w : a.tail_w);
+    p.N = ph == 1 ? a.RH : ph == 3 ? a.NTAIL : H;
+    p.kb = (ph == 2 ? a.RH : KIND == ROWS_HEAD && ph == 0 ? a.pd : H) * ES;
     p.steps = (p.kb + SPS * 128 - 1) / (SPS * 128);
     return p;
   };
@@ -528,7 +528,6 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
   f_block();
 #pragma unroll 1
   for (int i = 0; i < PD; ++i) fetch();
-  gather();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
@@ -694,8 +693,7 @@ br_status launch_block_rows(const br_model* m, const FwdBuffers& fb, const Sampl
   a.x = fb.x;
   a.mods = fb.mods; a.A = m->A;
   a.mods_off = head ? 0 : k * 6 * H + 2 * H;
-  a.mods_n = head ? 2 * H : 6 * H;
-  a.by_mq = FastDiv(a.mods_n / 4);
+  a.by_mq = FastDiv((head ? 2 * H : 6 * H) / 4);
   a.modmap = fb.modmap;
   a.attn = fb.xn;
   a.D = m->D;
