@@ -177,8 +177,9 @@ static __device__ __forceinline__ void attn_queries(char* lds, const bf16* __res
 #pragma unroll
   for (int t = 0; t < LPW; ++t) {
     const int row = (wv * LPW + t) * RPI + lrow;
-    koff[t] = row * ldb + (H + (slot ^ k_swz<DH>(row)) * 8) * 2;
-    voff[t] = row * ldb + (2 * H + (slot ^ v_swz<DH>(row)) * 8) * 2;
+    // (a row that does not exist: its product need not fit 32 bits)
+    koff[t] = row < L ? row * ldb + (H + (slot ^ k_swz<DH>(row)) * 8) * 2 : 0xFFFFFFFFu;
+    voff[t] = row < L ? row * ldb + (2 * H + (slot ^ v_swz<DH>(row)) * 8) * 2 : 0xFFFFFFFFu;
   }
   const u32x4 rows = sample_rows(base, (unsigned)(L - 1) * ldb + (2 * H + DH) * 2);
   const int nkv = (L + KV_TILE - 1) / KV_TILE;

@@ -784,6 +784,23 @@ def test_attention_bf16_leading_keys_that_score_minus_infinity(lib, dh, L, leadi
     assert torch.equal(torch.nan_to_num(outs[1], nan=7.0), torch.nan_to_num(outs[0], nan=7.0)[torch.arange(n, device=DEV) % 3])
 
 
+def test_attention_bf16_rows_far_apart(lib):
+    """One token of 190 000 heads of 128: rows 29 to 31 of the first half of its tile of keys would lie 4 GiB and more from row 0 (modulo that, the values of
+    row 29 are the query of the head 132 784 further).  The softmax of one key is 1, so the outputs are the values; queries that are not numbers
+    reach their own heads alone."""
+    nh, dh = 190000, 128
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    qkv = torch.randn((1, 1, 3 * nh * dh), generator=g, device=DEV).bfloat16()
+    qkv[0, 0].view(3, nh, dh)[0, ::7] = float("nan")
+    out = torch.full((1, 1, nh * dh), 3.0, dtype=torch.bfloat16, device=DEV)
+    br.op_attention(br.BF16, qkv, out, nh)
+    got, v = out.view(nh, dh), qkv[0, 0].view(3, nh, dh)[2]
+    lost = torch.zeros(nh, dtype=torch.bool, device=DEV)
+    lost[::7] = True
+    assert bool(got[lost].isnan().all()) and torch.equal(got[~lost], v[~lost])
+
+
 def test_gemm_bf16_rows_far_apart(lib):
     """192 rows of 832 values, 24 MB apart: the last rows of a tile are beyond 4 GiB from its first one.  Same bits as packed rows."""
     import ctypes as C
