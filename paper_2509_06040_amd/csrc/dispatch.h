@@ -45,13 +45,14 @@ inline bool attention_pipelined(int head_dim, int tokens, long long workgroups, 
 // Head dim 128 (256 queries and one workgroup a unit), by the share of the units that the last round takes, us whole / in two / in four parts: 9 % (12 heads
 // of 33 272 tokens) 5520 / 5230 / 5025; 16 % (8 of 1101) 28.6 / 19.5 / 15.0; 25 % behind a round (64 of 1101) 60.1 / 51.2 / 47.2; 38 % behind three (48 of
 // 4608) 427 / 404 / 424; 42 % (54 of 458) 17.5 / 12.1 / 17.0; 50 % behind thirteen (192 of 4608) 1593 / 1587 / 1607; 69 % behind one (24 of 4608) 212 / 246 / 248.
-// Head dim 64 (128 queries, three a unit, which share it: parts only help where units would stay empty or have one workgroup more than others), whole
-// / in two: workgroups a unit 0.56 (16 heads of 1101) 14.4 / 12.9, 1.13 19.4 / 18.0; 0.74 9.0 / 9.1, 0.96 24.7 / 27.1, 1.5 13.5 / 16.5, 2.25 28.2 / 29.8,
-// behind two rounds 950 / 975.
+// Head dim 64 (128 queries, three a unit, which share it): where units would stay empty, or have one workgroup or two, as long as the parts still start all at
+// once.  140 to 4096 tokens, 4 and 16 heads, 128 launches, two parts against whole by tiles a unit: up to 0.5 0.85 to 1.01; 0.5 to 0.6 0.92 to 1.02 (16 heads of
+// 1101 14.3 / 13.1 us); 0.6 to 0.9 0.98 to 1.05; 0.9 to 1 0.99 to 1.09; 1 to 1.13 0.91 to 0.99 (32 of 1101 19.7 / 18.3); 1.13 to 1.5 0.91 to 0.99 (36 of
+// 1101 20.2 / 19.0); 1.5 to 2 1.16 to 1.24 (48 of 1101 21.2 / 25.1); 2 to 2.5 1.04 to 1.17; behind two rounds 950 / 975 us.
 inline int attention_parts(int head_dim, bool brief, long long left, long long whole, int units) {
   if (brief) return left * 2 <= units ? 2 : 1;  // (up to 128 or 192 tokens: level within the launch's own time)
   if (head_dim == 128) return left * 4 <= units ? 4 : left * 2 <= units ? 2 : 1;
-  return whole == 0 && (left * 5 <= units * 3LL || (left > units && left * 8 <= units * 9LL)) ? 2 : 1;
+  return whole == 0 && (left * 5 <= units * 3LL || (left > units && left * 2 <= units * 3LL)) ? 2 : 1;
 }
 
 // bf16 attention of head dim 128: whether tiles of 128 queries, two workgroups a unit, take the place of 256 in one workgroup (up to 192 tokens: of 128 in the
