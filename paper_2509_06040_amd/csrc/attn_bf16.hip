@@ -37,17 +37,9 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 #define BR_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
 constexpr int KV_TILE = 64;
 constexpr float REF_LIMIT = 2048.f;  // a query's reference moves when its probabilities of a half tile add up to more
 constexpr long long WARM_BYTES_PER_TILE = 2 << 20;  // what 256 idle compute units read while a workgroup takes a key tile
-
-// (a uniform address; saying so keeps it in scalar registers)
-static __device__ inline const char* uniform_ptr(const char* p) {
-  const unsigned long long v = reinterpret_cast<unsigned long long>(p);
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-  return reinterpret_cast<const char*>(((unsigned long long)hi << 32) | lo);
-}
 
 // A buffer of `bytes` bytes from p (uniform over the wave) on.
 static __device__ inline u32x4 sample_rows(const bf16* p, unsigned bytes) {

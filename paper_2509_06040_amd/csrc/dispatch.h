@@ -32,14 +32,6 @@ inline bool persistent_output_stays(size_t bytes, int K, bool gelu) {
   return bytes >= (size_t)32 << 20 && bytes <= to;
 }
 
-// bf16 attention of head dim 64 had two loops: one pipelined by a key tile with two workgroups a compute unit, where its rounds were no more than those of the
-// plain one with three.  The woven loop that replaces both is level with or faster than either on both sides of this line, and no launch asks for it any more.
-inline bool attention_pipelined(int head_dim, int tokens, long long workgroups, int units) {
-  if (head_dim != 64) return false;
-  const long long rounds = (workgroups + units - 1) / units;
-  return rounds <= 1 || (rounds == 2 && tokens > 384) || (rounds == 4 && tokens >= 1024);
-}
-
 // Parts, with 16 queries a wave instead of 32, that a bf16 attention cuts the last `left` tiles into, behind `whole` tiles in full rounds of the units (of
 // one compute die where its pairs are grouped so).  A part takes about 0.6 of its tile's time at twice the workgroups.
 // Head dim 128 (256 queries and one workgroup a unit), by the share of the units that the last round takes, us whole / in two / in four parts: 9 % (12 heads

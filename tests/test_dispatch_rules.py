@@ -14,7 +14,6 @@ int tile_output_streams(unsigned long long bytes) { return rule::tile_output_str
 int persistent_output_stays(unsigned long long bytes, int K, int gelu) { return rule::persistent_output_stays(bytes, K, gelu); }
 int attention_parts(int dh, int brief, long long left, long long whole, int units) { return rule::attention_parts(dh, brief, left, whole, units); }
 int attention_pair(int tokens, long long tiles128, long long tiles256, int units) { return rule::attention_pair(tokens, tiles128, tiles256, units); }
-int attention_pipelined(int dh, int tokens, long long workgroups, int units) { return rule::attention_pipelined(dh, tokens, workgroups, units); }
 int weights_stay(double bytes) { return rule::weights_stay(bytes); }
 int read_ahead(unsigned long long room, unsigned long long bytes) { return rule::read_ahead(room, bytes); }
 int f32_small(int M, int N, int units) { return rule::f32_small(M, N, units); }
@@ -51,18 +50,6 @@ def test_outputs_of_the_persistent_kernel_that_stay_in_the_caches(rule):
         assert fc1(rows, H), (H, rows)
     assert qkv(16 * 1101, 1024) and not qkv(19 * 1101, 1024) and not qkv(441 * 93, 1024) and qkv(16 * 1101, 1536) and not qkv(22 * 1101, 2304)
     assert not fc1(2047, 1024 * 2) and fc1(2048, 1024 * 2) and not qkv(11 * 93, 3072)
-
-
-def test_attention_is_pipelined_where_its_two_workgroups_a_unit_suffice(rule):
-    pipe = lambda dh, L, w: bool(rule.attention_pipelined(dh, L, C.c_longlong(w), CU))
-    for L in (1, 64, 385, 1101, 6000):
-        assert pipe(64, L, 1) and pipe(64, L, CU)
-        assert not pipe(64, L, 2 * CU + 1) and not pipe(64, L, 3 * CU) and not pipe(64, L, 4 * CU + 1) and not pipe(64, L, 9 * CU)
-        assert not pipe(128, L, 1)
-    assert not pipe(64, 384, CU + 1) and pipe(64, 385, CU + 1) and pipe(64, 1101, 2 * CU)
-    assert not pipe(64, 1023, 3 * CU + 1) and pipe(64, 1024, 3 * CU + 1) and pipe(64, 6000, 4 * CU)
-    # what the plain loop is 13 to 30 % faster on: many short samples, and 608 workgroups of 210 tokens
-    assert not pipe(64, 28, 1528) and not pipe(64, 69, 576) and not pipe(64, 86, 1032) and not pipe(64, 210, 608)
 
 
 def test_attention_cuts_the_tiles_of_a_last_round_that_leaves_units_idle(rule):

@@ -954,8 +954,8 @@ def test_gemm_fp32_ring_tiles(lib, height, M, N, K, L):
         assert torch.equal(outs[0][M], x0[M])
 
 
-# Head dim 64 has two kernels, chosen by the number of workgroups.  One to seven tiles of keys (four fill the buffers of keys and of values, from the
-# fifth on they are refilled; the last tile ends in either parity of the two score registers), last tiles of 1, 32, 33 and 64 keys; a
+# Head dim 64: three samples, whose tiles are cut in two, and nine workgroups a compute unit, whole.  One to seven tiles of keys (up to two in the kernel of short
+# sequences; three fill the buffers of keys and of values, from the fourth on they are refilled), last tiles of 1, 32, 33 and 64 keys; a
 # reference that moves mid-sequence in some queries; waves without queries.  The same bits.
 @pytest.mark.parametrize("prescaled", [0, 1])
 @pytest.mark.parametrize("L", [1, 32, 33, 64, 65, 96, 128, 161, 192, 224, 256, 257, 300, 352, 384, 417])
