@@ -70,10 +70,11 @@ def test_attention_in_two_workgroups_a_unit(rule):
         dies = 8 if pairs >= 32 else 1
         tiles = lambda rows: C.c_longlong((-(-pairs // 8) if dies == 8 else pairs) * -(-L // rows))
         return bool(rule.attention_pair(L, tiles(128), tiles(256), CU // dies))
-    for L, pairs in ((129, 144), (192, 96), (192, 1536), (193, 288), (257, 144), (257, 768), (320, 48), (513, 48), (640, 96), (800, 144), (1024, 192), (1101, 192), (2048, 384),
-                     (3000, 96), (4608, 6)):
+    for L, pairs in ((129, 144), (192, 96), (192, 1536), (193, 288), (257, 144), (257, 768), (320, 48), (513, 48), (640, 96), (800, 144), (1024, 72), (1024, 192), (1101, 56), (1101, 72), (1101, 192),
+                     (1500, 56), (2048, 48), (2048, 384), (4608, 6)):
         assert pair(L, pairs), (L, pairs)
-    for L, pairs in ((1, 1536), (65, 288), (128, 384), (128, 1536), (129, 64), (192, 48), (193, 144), (193, 192), (257, 40), (385, 24), (513, 24), (800, 40), (1101, 6), (1101, 40), (2048, 24),
+    for L, pairs in ((1, 1536), (65, 288), (128, 384), (128, 1536), (129, 64), (192, 48), (193, 144), (193, 192), (257, 40), (385, 24), (513, 24), (800, 40), (1101, 6), (1101, 40), (1101, 64), (1500, 48), (2048, 24), (2048, 40),
+                     (2049, 384), (2300, 48), (3000, 96),
                      (4608, 24), (8192, 6), (8192, 48), (33272, 12)):
         assert not pair(L, pairs), (L, pairs)
 

@@ -1005,7 +1005,7 @@ def test_attention_bf16_does_not_depend_on_the_parts(lib, dh, L, prescaled):
 
 
 # Head dim 128 has tiles of 128 queries, two workgroups a compute unit with two buffers of keys and of values, beside those of 256: few samples (in parts), three quarters
-# of a workgroup a unit (128), just under a round of 256, just above one and three (128; 256 and a cut last round beyond 4096 tokens).  Two to five tiles of keys and
+# of a workgroup a unit (128), just under a round of 256, just above one and three (128; 256 and a cut last round beyond 2048 tokens).  Two to five tiles of keys and
 # long loops, which end in either buffer; last tiles of 1, 31, 32, 33 and 64 keys; waves without queries; a reference that moves mid-sequence.  The same bits.
 @pytest.mark.parametrize("prescaled", [0, 1])
 @pytest.mark.parametrize("L", [129, 160, 161, 192, 193, 223, 224, 225, 256, 257, 320, 449, 577, 1101, 4095, 4097])
