@@ -13,7 +13,7 @@
 // (Fetched straight into registers, in the layout of the matrix instruction, four lanes of a load touch four lines: 14
 // bytes a clock of a compute unit, a quarter of this.)  The hidden sizes that networks have (MLP ratio 4) get a form laid out at compile time; one loop
 // serves all phases of any other: whole velocity calls of bf16 hidden 64, 90 rows 121 -> 93 us, 31 590 rows 593 -> 473; 128, 90 rows 369 -> 281,
-// 24 732 rows 894 -> 694; 256, 1778 rows 198 -> 162; fp32 64, 200 rows 103 -> 92; 96, 122 rows 272 -> 234; 128, 762 rows 335 -> 300.
+// 24 732 rows 894 -> 694; 256, 1778 rows 198 -> 162; fp32 64, 200 rows 103 -> 92; 96, 122 rows 272 -> 234; 128, 762 rows 335 -> 285.
 //
 // Every output is one chain over k in ascending order (gemm_frag.h), every rounding and every LayerNorm sum is where
 // the separate kernels have it: the results are theirs bit for bit, whatever the number of rows selects.
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(NT) void block_rows_kernel(RowsArgs a) {
     // ... of each, KS steps a block, are one list of steps, and everything a step needs is an immediate.  What bounded the form for any sizes was the
     // issue of instructions: a wave takes one about every six cycles, and the products were a tenth of them beside the cursor, loops
     // and branches.  Cycles of a workgroup, any sizes -> this: bf16 hidden 64 20 800 -> 9800, 128 24 600 -> 15 100, 256 54 400 -> 45 200; fp32 64 27 800 ->
-    // 18 600, 128 59 000 -> 45 800.  (In the form for any sizes neither more weights in flight nor fragments read a step ahead gained anything.)
+    // 18 600 (before its reads moved between the products).  (In the form for any sizes neither more weights in flight nor fragments read a step ahead gained anything.)
     // Left at 64 in bf16: 3600 until rows and modulation vectors are there, 950 a LayerNorm, 100 to 450 a barrier, 700 to 1000 a phase.
     // A wave without a column block in a round fetches the last one all the same: what it waits for is a number of loads.
     constexpr int STEP_B = SPS * 2048, RING = rows_ring(ES, HC, RT), PD = RING / STEP_B, LPS = 2 * SPS;  // LPS: loads of a step

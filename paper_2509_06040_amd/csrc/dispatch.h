@@ -52,7 +52,7 @@ inline int attention_parts(int head_dim, bool brief, long long left, long long w
 // of 65 to 8192 tokens, 6 to 1536 pairs, us with 256 / 128, by the number of tiles of 128 a unit:
 //   up to a half: 256, in parts (1101 tokens, 6 pairs 15.0 / 18.6).  Up to one: 128, in one round (513 tokens, 48 pairs 18.8 / 12.9; 4608, 6 pairs 67 / 61).
 //   More, but one round of 256: 256 (2048 tokens, 24 pairs 51.0 / 53.7; 193, 192 pairs 12.9 / 13.9; not 129 to 192, 144 pairs 14.9 / 11.7).
-//   Beyond: 128, whose workgroups hide one another's ends, up to 2048 tokens (192 tokens, 1536 pairs 109 / 74; 320, 768 pairs 92.8 / 57.8; 1101, 768 515 / 458; 250
+//   Beyond: 128, whose workgroups hide one another's ends, up to 2048 tokens (192 tokens, 1536 pairs 109 / 74; 320, 768 pairs 92.8 / 57.8; 1101, 768 515 / 458; 210
 //   launches of 193 to 2048 tokens, 40 to 1320 pairs 0.65 to 1.02 of the time, mean 0.91), but not where 256 have a last round of at most a quarter, which
 //   is cut in four, and 128 begin a second of theirs, from 1025 tokens on (1101, 64 pairs 49.1 / 50.6; 1500, 48 62.5 / 64.6; 2048, 40 84.4 / 86.9).  Longer
 //   loops have the bytes into LDS of 256 (2300, 48 pairs 121 / 126; 3000, 56 233 / 239; 4000, 32 to 80 1.03 to 1.06; 4608, 24 208 / 224; 8192, 48 1165 / 1204).
