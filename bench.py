@@ -50,17 +50,17 @@ ORDER = ("image", "video", "image_large")
 # same counter reads for a plain 1 GiB device copy; see profiles/hot_kernels_hbm_traffic.md.  Keyed
 # by (workload, kernel label); valid only for the kernel sources hashed beside the figures.
 TRAFFIC = {
-    'image_large|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=7050439300, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='116c3470982935d70fab19c3ad94d962428e10ed'),
-    'image_large|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=9111797361, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='116c3470982935d70fab19c3ad94d962428e10ed'),
-    'image_large|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=7227106720, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='116c3470982935d70fab19c3ad94d962428e10ed'),
-    'image_large|attn_bf16[d128]': dict(bytes_per_launch=2257252781, sources=('attn_bf16.hip', 'static_for.h', 'dispatch.h'), sha1='393ad2e0eb4ae60d121ef95b9bdc7cd8d78109f8'),
-    'image_large|ln_modulate': dict(bytes_per_launch=1213805184, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='998091bd5364fdca1920d9d73be429ce9a55ff4e'),
-    'image|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=661646036, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='116c3470982935d70fab19c3ad94d962428e10ed'),
-    'image|gemm_bf16[bias_gate_residual,32..192x128 ring]': dict(bytes_per_launch=102374017, sources=('gemm_bf16_ring.hip', 'gemm_frag.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='d35ff4421ba1ed85897eedd28d23aad6d75b5326'),
-    'image|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=682170794, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='116c3470982935d70fab19c3ad94d962428e10ed'),
-    'image|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=509274418, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='116c3470982935d70fab19c3ad94d962428e10ed'),
-    'image|attn_bf16[d64]': dict(bytes_per_launch=259195965, sources=('attn_bf16.hip', 'static_for.h', 'dispatch.h'), sha1='393ad2e0eb4ae60d121ef95b9bdc7cd8d78109f8'),
-    'image|ln_modulate': dict(bytes_per_launch=193835641, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='998091bd5364fdca1920d9d73be429ce9a55ff4e'),
+    'image_large|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=6992107567, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='cf3a79d489df3d142b0306e4875b3a85674ebf5c'),
+    'image_large|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=9155711826, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='cf3a79d489df3d142b0306e4875b3a85674ebf5c'),
+    'image_large|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=7282528235, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='cf3a79d489df3d142b0306e4875b3a85674ebf5c'),
+    'image_large|attn_bf16[d128]': dict(bytes_per_launch=2026877005, sources=('attn_bf16.hip', 'static_for.h', 'dispatch.h'), sha1='4dc0ae7f34359a8756fefd63604c57551036df8d'),
+    'image_large|ln_modulate': dict(bytes_per_launch=1213805134, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='998091bd5364fdca1920d9d73be429ce9a55ff4e'),
+    'image|gemm_bf16[bias_gate_residual,128..256x256 persistent stream]': dict(bytes_per_launch=662176096, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='cf3a79d489df3d142b0306e4875b3a85674ebf5c'),
+    'image|gemm_bf16[bias_gate_residual,32..192x128 ring]': dict(bytes_per_launch=102374145, sources=('gemm_bf16_ring.hip', 'gemm_frag.h', 'gemm_epilogue.h', 'dit.h', 'common.h'), sha1='d35ff4421ba1ed85897eedd28d23aad6d75b5326'),
+    'image|gemm_bf16[bias_gelu,128..256x256 persistent stream]': dict(bytes_per_launch=681780861, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='cf3a79d489df3d142b0306e4875b3a85674ebf5c'),
+    'image|gemm_bf16[bias,128..256x256 persistent stream]': dict(bytes_per_launch=509143027, sources=('gemm_bf16_stream.hip', 'gemm_epilogue_wide.h', 'gemm_epilogue.h', 'dit.h', 'common.h', 'gemm_frag.h', 'static_for.h', 'dispatch.h'), sha1='cf3a79d489df3d142b0306e4875b3a85674ebf5c'),
+    'image|attn_bf16[d64]': dict(bytes_per_launch=258808846, sources=('attn_bf16.hip', 'static_for.h', 'dispatch.h'), sha1='4dc0ae7f34359a8756fefd63604c57551036df8d'),
+    'image|ln_modulate': dict(bytes_per_launch=193835727, sources=('dit_kernels.hip', 'dit.h', 'common.h'), sha1='998091bd5364fdca1920d9d73be429ce9a55ff4e'),
 }
 
 
