@@ -746,10 +746,11 @@ def test_attention_bf16_queries_without_a_result(lib, dh, L, prescaled):
 
 
 # A query's reference comes from the first half tile of keys in which one scores above -inf: the first, one of the next, the last; in the kernel of short
-# sequences, the one with a loop, whole tiles and parts.  The other keys score about -210, which a reference of zero would lose, in some heads and samples.
+# sequences, the one with a loop, whole tiles (of 256 queries at head dim 128 beyond 2048 tokens, else two workgroups a unit) and parts.
+# The other keys score about -210, which a reference of zero would lose, in some heads and samples.
 @pytest.mark.parametrize("prescaled", [0, 1])
 @pytest.mark.parametrize("dh,L,leading", [(dh, L, n) for dh in (64, 128) for L, n in ((20, 7), (34, 32), (34, 33), (65, 64), (100, 31), (100, 32), (100, 33), (100, 63),
-                                                                                      (190, 65), (300, 32), (300, 64), (300, 65), (333, 320), (470, 200))])
+                                                                                      (190, 65), (300, 32), (300, 64), (300, 65), (333, 320), (470, 200), (2100, 70))])
 def test_attention_bf16_leading_keys_that_score_minus_infinity(lib, dh, L, leading, prescaled):
     rng = np.random.default_rng(dh + L + leading)
     H, c = 2 * dh, np.log2(np.e) / np.sqrt(dh)
@@ -976,14 +977,15 @@ def test_attention_bf16_head_dim_64_does_not_depend_on_the_kernel(lib, L, presca
     assert rel_l2(host(few.float()), ref.numpy()) < 8e-3   # probabilities and outputs rounded to bf16, 2^-9 each
 
 
-# Tiles whole, in two and in four parts, and the kernel of short sequences, which is left at 193 tokens (128) and 129 (64): tiles of keys up to the fifth,
-# where the four or three buffers have been refilled; last tiles of 1, 31, 32, 33 and 64 keys; parts without queries; a reference that moves mid-sequence.
+# Tiles whole, in two and in four parts, and the kernel of short sequences, which is left at 193 tokens (128; with more tiles, at 129) and 129 (64): tiles of keys up to
+# the fifth, where the four or three buffers have been refilled; whole rounds of 256 queries in front of parts, which head dim 128 has beyond 2048 tokens;
+# last tiles of 1, 31, 32, 33 and 64 keys; parts without queries; a reference that moves mid-sequence.
 @pytest.mark.parametrize("prescaled", [0, 1])
-@pytest.mark.parametrize("dh,L", [(128, L) for L in (1, 31, 64, 65, 128, 129, 191, 192, 193, 224, 225, 255, 256, 257, 320, 321, 449, 577)] + [(64, 129), (64, 160), (64, 193)])
+@pytest.mark.parametrize("dh,L", [(128, L) for L in (1, 31, 64, 65, 128, 129, 191, 192, 193, 224, 225, 255, 256, 257, 320, 321, 449, 577, 2081, 2304)] + [(64, 129), (64, 160), (64, 193)])
 def test_attention_bf16_does_not_depend_on_the_parts(lib, dh, L, prescaled):
     nh, rows = 2, 128 if dh == 64 or L <= 192 else 256
     tiles = nh * ((L + rows - 1) // rows)                   # of a sample
-    # a part of a round (in four parts at head dim 128), a third (in two), and full rounds behind which few are left
+    # a part of a round (in four parts at head dim 128), a third (in two; 128: two workgroups a unit), and full rounds behind which few are left
     counts = [3, -(-90 // tiles), -(-(3 * 256 + 8) // tiles)]
     g = torch.Generator(device=DEV)
     g.manual_seed(L)
